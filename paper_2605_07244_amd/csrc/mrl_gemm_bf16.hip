@@ -79,7 +79,7 @@ struct Params {
   int K;
   const int32_t* row_index;   // already offset to the chunk start
   const int64_t* n_scored; int64_t chunk_start; int chunk_rows;
-  int sup_m, sup_n;           // super-tile shape of the workgroup -> tile mapping
+  int sup_m, sup_n;           // DW: super-tile shape of the workgroup -> tile mapping
   // FWD
   const float* zt; float* part_sum; float* part_ez; int64_t part_stride; uint16_t* estash; int64_t lde; int V;
   // DH
@@ -93,15 +93,44 @@ struct Params {
   int tail_first[NXCD + 1];   // items tail_first[x] .. tail_first[x + 1] - 1 run on XCD x
 };
 
-// Workgroup -> tile mapping.  Workgroups are dealt round-robin to the 8 XCDs, each with its own
-// L2 and 32 compute units; sup_m x sup_n consecutive workgroups of one XCD form a super-tile so
-// that they share operand panels in that L2 (each A panel is used by sup_n tiles, each B panel by
-// sup_m), and super-tiles are numbered N-fastest so that the XCDs walk the same A rows at the same
-// time.  The shape is picked per launch from what measurement favours: 8 x 4 when the N extent is
-// a multiple of 4 tiles, else 8 x 2.  Two things matter more than the panel-sharing count: the N
-// extent must fill whole super-tile columns (6 tiles at d = 1536 and 14 at d = 3584 leave 8 x 4
-// with a half-empty last column: dH / dW 11-30 % slower than 8 x 2), and the super-tile size
-// must divide the 32 compute units of an XCD, so that the workgroups running on it at any time
+// Workgroup -> tile mapping of the forward and dH launches.  Workgroups are dealt round-robin to the
+// 8 XCDs, each with its own L2 and 32 compute units; 32 consecutive workgroups of one XCD take 32
+// consecutive tiles, numbered down the columns of bands of 8 tile rows (8 x 4 tiles when the N extent
+// allows), so that they share operand panels in that L2 and all XCDs walk the same A rows at the same
+// time.  The numbering runs over the VALID tiles (the scored rows are counted on the device) without
+// holes: numbering super-tiles over the launch's upper bound gave each XCD fixed tile columns, and
+// with 20 of 32 tile columns valid three XCDs had nothing to do (scoring 5120 of 8192 slots,
+// V = 128256, d = 2048: 3233 us a call against 2088 us now).  The tiles of the last, incomplete round
+// of 256 are dealt evenly.
+constexpr int kBand = 8;
+constexpr int kXcdCus = 32;
+constexpr int kRound = NXCD * kXcdCus;
+__device__ inline bool dealt_tile(int bid, int Mt, int Nt, int& tm, int& tn) {
+  const int tiles = Mt * Nt, whole = tiles / kRound * kRound;
+  const int xcd = bid % NXCD, local = bid / NXCD;
+  int t;
+  if (bid < whole) {
+    t = (local / kXcdCus * NXCD + xcd) * kXcdCus + local % kXcdCus;
+  } else {
+    const int per = (tiles - whole + NXCD - 1) / NXCD, k = local - whole / NXCD;
+    t = whole + xcd * per + k;
+    if (k >= per || t >= tiles) return false;
+  }
+  const int band = t / (kBand * Nt), in_band = t - band * kBand * Nt;
+  const int rows = Mt - band * kBand < kBand ? Mt - band * kBand : kBand;
+  tn = in_band / rows;
+  tm = band * kBand + in_band - tn * rows;
+  return true;
+}
+
+// Workgroup -> tile mapping of the dW launch (its tile counts do not depend on the scored rows):
+// sup_m x sup_n consecutive workgroups of one XCD form a super-tile (each A panel is used by sup_n
+// tiles, each B panel by sup_m), and super-tiles are numbered N-fastest so that the XCDs walk the
+// same A rows at the same time.  The shape is picked per launch from what measurement favours: 8 x 4
+// when the N extent is a multiple of 4 tiles, else 8 x 2.  Two things matter more than the
+// panel-sharing count: the N extent must fill whole super-tile columns (6 tiles at d = 1536 and 14 at
+// d = 3584 leave 8 x 4 with a half-empty last column: 11-30 % slower than 8 x 2), and the super-tile
+// size must divide the 32 compute units of an XCD, so that the workgroups running on it at any time
 // are whole super-tiles (shapes of 24, 28 or 30 tiles lose 5-20 %).
 struct SuperTile { int m, n; };
 inline SuperTile pick_super_tile(int Nt) {
@@ -180,11 +209,16 @@ __global__ __launch_bounds__(NTHREADS) void gemm_nt_bf16(Params p) {
   if (MODE == MODE_DH && nvalid == 0) return;
   if (MODE == MODE_DW && nvalid == 0 && !p.overwrite) return;
 
-  const int Mt = (p.M + BM - 1) / BM, Nt = (p.N + BN - 1) / BN;
-  int tm, tn, sm, sn;
+  const int Mt = (M + BM - 1) / BM, Nt = (N + BN - 1) / BN;
+  int tm, tn;
+  int sm, sn, sup_m, sup_n;        // position of the tile among those that share its panels
   int k_first = 0;                 // first K panel of this workgroup (DW tail slices start later)
   float* tail_out = nullptr;       // DW tail slice: where the accumulators go instead of dW
-  if (MODE == MODE_DW && p.tail_split > 0) {
+  if (MODE != MODE_DW) {
+    if (!dealt_tile(blockIdx.x, Mt, Nt, tm, tn)) return;
+    sm = tm % kBand; sn = tn % 4; sup_m = kBand; sup_n = 4;
+  } else if (p.tail_split > 0) {
+    sup_m = p.sup_m; sup_n = p.sup_n;
     if ((int)blockIdx.x < p.main_blocks) {
       if (!tile_coords(blockIdx.x, p.tail_m0, Nt, p.sup_m, p.sup_n, tm, tn, sm, sn)) return;
     } else {
@@ -206,9 +240,11 @@ __global__ __launch_bounds__(NTHREADS) void gemm_nt_bf16(Params p) {
       K = k_end > k_first ? (k_end - k_first) * BK : 0;
       tail_out = p.tail_part + (int64_t)item * (BM * BN);
     }
-  } else if (!tile_coords(blockIdx.x, Mt, Nt, p.sup_m, p.sup_n, tm, tn, sm, sn)) return;
+  } else {
+    sup_m = p.sup_m; sup_n = p.sup_n;
+    if (!tile_coords(blockIdx.x, Mt, Nt, sup_m, sup_n, tm, tn, sm, sn)) return;
+  }
   const int m0 = tm * BM, n0 = tn * BN;
-  if (m0 >= M || n0 >= N) return;
 
   // ---- global -> LDS: one direct load moves 1 KB, contiguous in LDS.
   // Row-major operands ([row][k], k contiguous): 8 rows x 128 B per load.  Wave w owns row
@@ -236,7 +272,7 @@ __global__ __launch_bounds__(NTHREADS) void gemm_nt_bf16(Params p) {
   uint32_t lds_a[8], lds_b[8];                        // LDS offset of load i within the wave's 8 KB
   const float* zt_ptr = nullptr;                      // forward: this lane's entry of the tile's target logits
   {
-    const int rot_a = (sn * 8 / p.sup_n) & 7, rot_b = (sm * 8 / p.sup_m) & 7;
+    const int rot_a = (sn * 8 / sup_n) & 7, rot_b = (sm * 8 / sup_m) & 7;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       const int ia = (i + rot_a) & 7, ib = (i + rot_b) & 7;
@@ -716,7 +752,7 @@ void launch(Params& p, hipStream_t stream) {
   const int Mt = (p.M + BM - 1) / BM, Nt = (p.N + BN - 1) / BN;
   const SuperTile st = pick_super_tile(Nt);
   p.sup_m = st.m; p.sup_n = st.n;
-  int blocks = num_blocks(Mt, Nt, st.m, st.n);
+  int blocks = MODE == MODE_DW ? num_blocks(Mt, Nt, st.m, st.n) : (Mt * Nt + NXCD - 1) / NXCD * NXCD;
   DwTailPlan tail = {0, 0, 0, {}};
   if (MODE == MODE_DW && p.tail_part != nullptr) tail = dw_tail_plan(Mt, Nt, st.m, st.n);
   if (tail.split > 0) {
