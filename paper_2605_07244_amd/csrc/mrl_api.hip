@@ -103,13 +103,14 @@ void* static_scratch_ptr() {
 struct Layout {
   size_t total = 0;
   size_t counters, row_index, block_counts, zt, part_max, part_sum, part_ez;
-  size_t seq_len, seq_coef, seq_expo, group_count, lse_c, g_c, row_scale, loss_partials, Z, Pt, Ht, Wt;
-  size_t dw_tail = 0;          // bf16: partial tiles of the dW launch's K-split tail
+  size_t seq_len, seq_coef, seq_expo, group_count, lse_c, g_c, row_scale, loss_partials, Z, Pt, Ht, Wt = 0;
+  size_t tail = 0;             // bf16: partial tiles of the dH and dW launches' K-split tails
+  int tail_items = 0;          // ... how many
   size_t Hc = 0, Wp = 0;       // bf16: the pass's token rows, gathered and zero-padded to dp columns; W padded likewise (only if dp != d)
   int dp = 0;                  // bf16: d rounded up to the 128-wide panel pairs of the GEMM kernels
   int64_t ldh = 0;             // row stride of Hc and Wp
   int chunk_rows = 0, n_partials = 0;
-  int64_t n_chunks = 0, Vp = 0, ldz = 0, ldr = 0;   // ldz: row stride of the stash (Z) and Wt, ldr: of Ht (and the fp32 path's Pt)
+  int64_t n_chunks = 0, Vp = 0, ldz = 0, ldr = 0;   // ldz: row stride of the stash (Z; and of the fp32 path's Wt), ldr: of Ht (and the fp32 path's Pt)
   int64_t epi_blocks_total = 0;
 };
 
@@ -161,8 +162,16 @@ Layout make_layout(int64_t N, int64_t B, int d, int V, int dtype, int chunk_rows
     L.Z = take(off, (size_t)chunk_rows * L.ldz * es);
     L.Pt = bf16 ? 0 : take(off, (size_t)L.Vp * L.ldr * es);   // fp32 path only: the bf16 dW GEMM reads P itself
     L.Ht = take(off, (size_t)dk * L.ldr * es);
-    L.Wt = take(off, (size_t)dk * L.ldz * es);
-    if (bf16) L.dw_tail = take(off, gemm_dw_tail_bytes());
+    if (bf16) {
+      // 256 partial tiles for the dW launch; the dH launch's last round of up to 255 tiles can use up
+      // to four per compute unit; a quarter of the size of the head, which has the longer tiles the larger it
+      // is, bounds the extra ones
+      const size_t extra = (size_t)dk * L.ldz * es / 4 / gemm_tail_tile_bytes();
+      L.tail_items = gemm_dw_tail_items() + (int)(extra < 768 ? extra : 768);
+      L.tail = take(off, L.tail_items * gemm_tail_tile_bytes());
+    } else {
+      L.Wt = take(off, (size_t)dk * L.ldz * es);         // fp32 path only: the bf16 dH GEMM reads W itself
+    }
   } else if (!bf16) {
     L.Z = take(off, (size_t)chunk_rows * L.ldz * es);
   }
@@ -488,13 +497,9 @@ int mrl_grpo_loss_fwd_bwd(const void* hidden, const void* lm_head_w, const int32
     if (counters[1] != 0) return MRL_ERR_TARGET_RANGE;
     if (counters[2] != 0) return MRL_ERR_GROUP_RANGE;
   }
-  if (out_dH) {
+  if (out_dH && !bf16) {
     Scope sc(MRL_PROF_CONVERT, s);
-    if (bf16)
-      launch_transpose(L.Wp != 0 ? at<void>(ws, L.Wp) : lm_head_w, L.Wp != 0 ? L.ldh : d, nullptr, nullptr,
-                       at<void>(ws, L.Wt), L.ldz, V, nullptr, 0, 0, L.dp, L.Vp, es, s);
-    else
-      launch_transpose(lm_head_w, d, nullptr, nullptr, at<void>(ws, L.Wt), L.ldz, V, nullptr, 0, 0, d, L.Vp, es, s);
+    launch_transpose(lm_head_w, d, nullptr, nullptr, at<void>(ws, L.Wt), L.ldz, V, nullptr, 0, 0, d, L.Vp, es, s);
   }
   int64_t n_passes = L.n_chunks;
   if (cfg->scored_rows_hint > 0) {
@@ -564,9 +569,9 @@ int mrl_grpo_loss_fwd_bwd(const void* hidden, const void* lm_head_w, const int32
     if (out_dH) {
       Scope sc(MRL_PROF_GEMM_DH, s);
       if (bf16) {
-        launch_gemm_dh_bf16(at<void>(ws, L.Z), L.ldz, at<void>(ws, L.Wt), L.ldz, row_index,
-                            at<float>(ws, L.row_scale), n_scored, c0, L.chunk_rows, (int)L.Vp, d, out_dH,
-                            cfg->dh_dtype == MRL_F32, s);
+        launch_gemm_dh_bf16(at<void>(ws, L.Z), L.ldz, lm_head_w, d, V, row_index, at<float>(ws, L.row_scale),
+                            n_scored, c0, L.chunk_rows, d, out_dH, cfg->dh_dtype == MRL_F32,
+                            at<float>(ws, L.tail), L.tail_items, s);
       } else {
         GemmF32Args g = {};
         g.A = at<float>(ws, L.Z); g.lda = L.ldz; g.a_rows = nullptr;
@@ -583,7 +588,7 @@ int mrl_grpo_loss_fwd_bwd(const void* hidden, const void* lm_head_w, const int32
       const int overwrite = (c == 0 && !cfg->accumulate_dw) ? 1 : 0;
       if (bf16) {
         launch_gemm_dw_bf16(at<void>(ws, L.Z), L.ldz, at<void>(ws, L.Ht), L.ldr, n_scored, c0,
-                            L.chunk_rows, V, d, out_dW, overwrite, at<float>(ws, L.dw_tail), s);
+                            L.chunk_rows, V, d, out_dW, overwrite, at<float>(ws, L.tail), s);
       } else {
         GemmF32Args g = {};
         g.A = at<float>(ws, L.Pt); g.lda = L.ldr; g.a_rows = nullptr;

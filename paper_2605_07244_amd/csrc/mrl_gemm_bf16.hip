@@ -25,8 +25,9 @@
 //        permuted so that a lane's accumulators are 8 consecutive vocabulary ids
 //        and the stash of exponentials e = exp(z - row offset) is stored as bf16
 //        straight from registers.
-//   DH : A = stash rows (tokens), B = W^T; each output row is multiplied by its
-//        row scale (-g / S) and scattered to its slot.
+//   DH : A = stash rows (tokens), B = W^T, read from the rows of W themselves (K-major
+//        panel, transposing LDS reads); each output row is multiplied by its row scale
+//        (-g / S) and scattered to its slot.
 //   DW : A = stash^T, read from the stash rows themselves (K-major panel, transposing
 //        LDS reads), B = (row-scaled H)^T; fp32 read-modify-write of dW.
 #include "../../include/mrl.h"
@@ -83,7 +84,7 @@ struct Params {
   // FWD
   const float* zt; float* part_sum; float* part_ez; int64_t part_stride; uint16_t* estash; int64_t lde; int V;
   // DH
-  const float* row_scale; void* dH; int dh_f32; int d;
+  const float* row_scale; void* dH; int dh_f32; int d; int max_items;   // max_items: partial tiles tail_part holds
   // DW
   float* dW; int overwrite;
   // DW, K-split tail (see dw_tail_plan): workgroups from main_blocks on take the tiles of the
@@ -105,6 +106,12 @@ struct Params {
 constexpr int kBand = 8;
 constexpr int kXcdCus = 32;
 constexpr int kRound = NXCD * kXcdCus;
+__device__ inline void tile_at(int t, int Mt, int Nt, int& tm, int& tn) {
+  const int band = t / (kBand * Nt), in_band = t - band * kBand * Nt;
+  const int rows = Mt - band * kBand < kBand ? Mt - band * kBand : kBand;
+  tn = in_band / rows;
+  tm = band * kBand + in_band - tn * rows;
+}
 __device__ inline bool dealt_tile(int bid, int Mt, int Nt, int& tm, int& tn) {
   const int tiles = Mt * Nt, whole = tiles / kRound * kRound;
   const int xcd = bid % NXCD, local = bid / NXCD;
@@ -116,12 +123,33 @@ __device__ inline bool dealt_tile(int bid, int Mt, int Nt, int& tm, int& tn) {
     t = whole + xcd * per + k;
     if (k >= per || t >= tiles) return false;
   }
-  const int band = t / (kBand * Nt), in_band = t - band * kBand * Nt;
-  const int rows = Mt - band * kBand < kBand ? Mt - band * kBand : kBand;
-  tn = in_band / rows;
-  tm = band * kBand + in_band - tn * rows;
+  tile_at(t, Mt, Nt, tm, tn);
   return true;
 }
+
+// dH: the tiles of the last, incomplete round of 256 (all of them, when a pass has few rows) are cut
+// into slices of the contraction over the vocabulary, one work item each, which store their
+// accumulators to a scratch area; dh_tail_reduce adds them in slice order.  A dH tile is long (2374
+// panels at V = 151936, about 2.4 ms), so an idle compute unit in that round costs more than
+// writing and adding the partial tiles (256 KB per item): 327 rows at d = 4096 are 32 tiles.
+// The slice count is the one whose rounds of items end earliest, kItemCost covering an item's
+// prologue, partial store and share of the reduce.  Measured (launch and reduce, V = 151936; before:
+// whole tiles and a transposed copy of W in front): 327 rows, d = 4096, 32 tiles: 3480 -> 527 us;
+// 5120 rows, d = 1536, 120 tiles: 3251 -> 1720 us; 47360 rows, d = 3584, 2590 tiles: 39.1 -> 35.9 ms.
+constexpr int kMinSlicePanels = 16;
+__host__ __device__ inline int dh_split(int tail_tiles, int panels, int max_items) {
+  constexpr float kItemCost = 0.02f;
+  int best = 1;
+  float best_end = 1.f;
+  for (int s = 2; s <= 64 && s * kMinSlicePanels <= panels && s * tail_tiles <= max_items; ++s) {
+    const int rounds = (tail_tiles * s + kRound - 1) / kRound;
+    const float end = rounds * (1.f / s + kItemCost);
+    if (end < best_end) { best_end = end; best = s; }
+  }
+  return best;
+}
+// panels per slice: an even number (the K loop's body is two panels)
+__host__ __device__ inline int slice_panels(int panels, int split) { return ((panels + split - 1) / split + 1) & ~1; }
 
 // Workgroup -> tile mapping of the dW launch (its tile counts do not depend on the scored rows):
 // sup_m x sup_n consecutive workgroups of one XCD form a super-tile (each A panel is used by sup_n
@@ -157,6 +185,7 @@ __device__ inline bool tile_coords(int bid, int Mt, int Nt, int sup_m, int sup_n
 // swizzle of the K-major A panel: rows k, k+1, k+2, k+3 and k+8 (or k+16) get distinct values
 __device__ inline int kswz(int k) { return (k & 3) | ((((k >> 3) ^ (k >> 4)) & 1) << 2); }
 
+__device__ inline int min_int(int a, int b) { return a < b ? a : b; }
 __device__ inline float exp2_fast(float x) { return __builtin_amdgcn_exp2f(x); }
 
 // The MFMA is issued through inline assembly with the accumulator tied in place in an
@@ -212,10 +241,29 @@ __global__ __launch_bounds__(NTHREADS) void gemm_nt_bf16(Params p) {
   const int Mt = (M + BM - 1) / BM, Nt = (N + BN - 1) / BN;
   int tm, tn;
   int sm, sn, sup_m, sup_n;        // position of the tile among those that share its panels
-  int k_first = 0;                 // first K panel of this workgroup (DW tail slices start later)
-  float* tail_out = nullptr;       // DW tail slice: where the accumulators go instead of dW
+  int k_first = 0;                 // first K panel of this workgroup (tail slices start later)
+  float* tail_out = nullptr;       // DH / DW tail slice: where the accumulators go instead
   if (MODE != MODE_DW) {
-    if (!dealt_tile(blockIdx.x, Mt, Nt, tm, tn)) return;
+    int bid = blockIdx.x, split = 1, slice = 0;
+    const int tiles = Mt * Nt, whole = tiles / kRound * kRound;
+    if (MODE == MODE_DH && bid >= whole) {
+      const int rest = tiles - whole;
+      split = dh_split(rest, K / BK, p.max_items);
+      if (split > 1) {
+        // an XCD takes consecutive items, i.e. mostly tiles of one slice
+        const int items = rest * split, per = (items + NXCD - 1) / NXCD;
+        const int e = bid - whole, item = e % NXCD * per + e / NXCD;
+        if (e / NXCD >= per || item >= items) return;
+        slice = item / rest;
+        tile_at(whole + item - slice * rest, Mt, Nt, tm, tn);
+        const int nk_all = K / BK, per_slice = slice_panels(nk_all, split);
+        k_first = slice * per_slice;
+        const int k_end = k_first + per_slice < nk_all ? k_first + per_slice : nk_all;
+        K = k_end > k_first ? (k_end - k_first) * BK : 0;
+        tail_out = p.tail_part + (int64_t)item * (BM * BN);
+      }
+    }
+    if (split == 1 && !dealt_tile(bid, Mt, Nt, tm, tn)) return;
     sm = tm % kBand; sn = tn % 4; sup_m = kBand; sup_n = 4;
   } else if (p.tail_split > 0) {
     sup_m = p.sup_m; sup_n = p.sup_n;
@@ -250,11 +298,12 @@ __global__ __launch_bounds__(NTHREADS) void gemm_nt_bf16(Params p) {
   // Row-major operands ([row][k], k contiguous): 8 rows x 128 B per load.  Wave w owns row
   // blocks 8w .. 8w+7 of each operand panel; lane l fills LDS chunk (row l/8, slot l%8) and
   // therefore fetches logical chunk slot ^ ((row >> 1) & 7).
-  // K-major A operand (DW: A[m][k] = dz[k][m], stored as token rows with the vocabulary
-  // contiguous): the panel is 64 k rows x 512 B and a load moves 2 of them; lane l fills chunk
+  // K-major operands (DW: A[m][k] = dz[k][m], stored as token rows with the vocabulary contiguous;
+  // DH: B[n][k] = W[k][n], the rows of W): the panel is 64 k rows x 512 B and a load moves 2 of them; lane l fills chunk
   // slot l%32 of row l/32 and fetches logical chunk slot ^ (h(k) << 1), the swizzle that makes
   // the transposing fragment reads below conflict-free.
   constexpr bool A_KMAJOR = (MODE == MODE_DW);
+  constexpr bool B_KMAJOR = (MODE == MODE_DH);
   // FWD: the 16 rows of A fragment i are not 16 consecutive panel rows but
   //   rho(i, r) = 32*(i/2) + 8*(r/4) + 4*(i%2) + r%4      (within the wave's 128 rows),
   // so that a lane's accumulators (i = 2t, 2t+1; e = 0..3) are 8 consecutive vocabulary ids
@@ -266,6 +315,7 @@ __global__ __launch_bounds__(NTHREADS) void gemm_nt_bf16(Params p) {
   const int lrow = lane >> 3;
   const uint16_t* a_ptr[8];
   const uint16_t* b_ptr[8];
+  uint32_t b_voff[8];                                 // DH: byte offset of the lane's chunk from the wave's 16 rows of W
   // Workgroups that share a panel (same sm for A, same sn for B) walk its row blocks in a
   // different cyclic order (rot_a, rot_b), so that they do not all ask the L2 for the same lines
   // at the same moment (1-2 % on the forward and dH launches).
@@ -289,9 +339,12 @@ __global__ __launch_bounds__(NTHREADS) void gemm_nt_bf16(Params p) {
         const int k = 2 * (wave * 8 + ia) + (lane >> 5);  // k row within the panel
         a_ptr[i] = p.A + ((int64_t)k_first * BK + k) * p.lda + m0 + (((lane & 31) ^ (kswz(k) << 1)) << 3);
       } else {
-        a_ptr[i] = p.A + rowa * p.lda + lchunk_a * 8;
+        a_ptr[i] = p.A + rowa * p.lda + lchunk_a * 8 + (MODE == MODE_DH ? k_first * BK : 0);
       }
-      b_ptr[i] = p.B + rowb * p.ldb + lchunk * 8 + (MODE == MODE_DW ? k_first * BK : 0);
+      if (B_KMAJOR) {
+        const int k = 2 * ib + (lane >> 5);
+        b_voff[i] = (uint32_t)k * (uint32_t)(p.ldb * 2) + (((lane & 31) ^ (kswz(wave * 16 + k) << 1)) << 4);
+      } else b_ptr[i] = p.B + rowb * p.ldb + lchunk * 8 + (MODE == MODE_DW ? k_first * BK : 0);
     }
     if (MODE == MODE_FWD) {
       int n = n0 + wave * 64 + lane; n = n < N ? n : N - 1;
@@ -305,21 +358,6 @@ __global__ __launch_bounds__(NTHREADS) void gemm_nt_bf16(Params p) {
   // explicitly below with s_waitcnt vmcnt(0) before the barrier that publishes a panel.
   const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
   const uint32_t wave_lds = __builtin_amdgcn_readfirstlane(lds_base + wave * 8192);
-
-  auto load_lds16 = [](const uint16_t* g, uint32_t lds_addr) {
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
-                 :: "v"(g), "s"(lds_addr) : "memory");
-  };
-  // loads i0 .. i0+n-1 (of 8) of both operand panels of K panel kt into ring slot `slot`
-  auto issue_loads = [&](int kt, int slot, int i0, int n) {
-    const uint32_t st = slot * STAGE_BYTES + wave_lds;
-    const int koff = kt * BK;
-#pragma unroll
-    for (int i = i0; i < i0 + n; ++i) {
-      load_lds16(a_ptr[i] + kt * a_kstep, st + lds_a[i]);
-      load_lds16(b_ptr[i] + koff, st + TILE_BYTES + lds_b[i]);
-    }
-  };
 
   // forward: the tile's 256 target logits travel to LDS with the tile's first panel (4 bytes per
   // lane, one direct load per wave) and are published by the same barrier, so that the epilogue
@@ -348,26 +386,28 @@ __global__ __launch_bounds__(NTHREADS) void gemm_nt_bf16(Params p) {
     b_off[ks] = TILE_BYTES + (wn * 128 + frow) * 128 + (chunk << 4);
   }
 
-  // K-major A panel: the transposing LDS read hands lane (g = lane / 16, s = lane % 16) the four
+  // K-major panel: the transposing LDS read hands lane (g = lane / 16, s = lane % 16) the four
   // k values kb .. kb+3 of column m = mb + s when lane s points at row kb + s/4, columns
   // mb + 4*(s%4) .. +3.  Two of them (kb = 8g and 8g + 4 within the K step) make the lane's
   // 8-element fragment.  A 64-bit read is served 32 lanes per cycle: 8 rows x 32 bytes, and the
   // swizzle h(k) moves the 32-byte column groups of those rows to distinct bank windows.
-  int a_tr_base = 0;
-  if (A_KMAJOR) {
+  int a_tr_base = 0, b_tr_base = 0;
+  {
     const int k = 8 * fq + (frow >> 2);
-    a_tr_base = k * 512 + wm * 256 + (kswz(k) << 5) + ((frow & 2) << 3) + ((frow & 1) << 3);
+    const int base = k * 512 + (kswz(k) << 5) + ((frow & 2) << 3) + ((frow & 1) << 3);
+    if (A_KMAJOR) a_tr_base = base + wm * 256;
+    if (B_KMAJOR) b_tr_base = base + wn * 256;
   }
+  auto read_kmajor = [&](int off) -> bf16x8 {
+    typedef short v4i16 __attribute__((ext_vector_type(4)));
+    typedef __attribute__((address_space(3))) v4i16* lds_v4i16;
+    unsigned char* q = smem + off;
+    const v4i16 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16)q);
+    const v4i16 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16)(q + 2048));
+    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+  };
   auto read_a = [&](int st, int ks, int ib) -> bf16x8 {
-    if (A_KMAJOR) {
-      typedef short v4i16 __attribute__((ext_vector_type(4)));
-      typedef short v8i16 __attribute__((ext_vector_type(8)));
-      typedef __attribute__((address_space(3))) v4i16* lds_v4i16;
-      unsigned char* q = smem + st + (a_tr_base ^ (ib << 5)) + ks * 16384;
-      const v4i16 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16)q);
-      const v4i16 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16)(q + 2048));
-      return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-    }
+    if (A_KMAJOR) return read_kmajor(st + (a_tr_base ^ (ib << 5)) + ks * 16384);
     return *reinterpret_cast<const bf16x8*>(smem + st + a_off[ks] +
                                             (A_PERM ? (ib >> 1) * 4096 + (ib & 1) * 512 : ib * 2048));
   };
@@ -388,6 +428,7 @@ __global__ __launch_bounds__(NTHREADS) void gemm_nt_bf16(Params p) {
   bf16x8 fbx[2][2][8];   // [set][K step][16-column block]
   bf16x8 fax[4][2];      // [ring slot][K step]
   auto read_b = [&](int st, int ks, int j) -> bf16x8 {
+    if (B_KMAJOR) return read_kmajor(st + TILE_BYTES + (b_tr_base ^ (j << 5)) + ks * 16384);
     return *reinterpret_cast<const bf16x8*>(smem + st + b_off[ks] + j * 2048);
   };
   // One load of the K loop: three instructions, what one MFMA leaves room for.  The address
@@ -398,11 +439,36 @@ __global__ __launch_bounds__(NTHREADS) void gemm_nt_bf16(Params p) {
     asm volatile("s_mov_b32 m0, %3\n\tv_lshl_add_u64 %0, %1, 0, %2\n\tglobal_load_lds_dwordx4 %0, off"
                  : "=&v"(addr) : "v"(base), "s"(byte_off), "s"(lds_addr) : "memory");
   };
+  // DH: the wave's 16 rows of W in the panel being loaded, as a buffer descriptor that ends with row
+  // V - 1: the contraction runs over the vocabulary rounded up to whole panel pairs, and loads
+  // beyond the descriptor's end return zeros (the stash columns there are zeros as well).  b_advance
+  // moves it on by a panel.
+  uint64_t w_addr = 0;
+  int w_left = 0;                                     // rows of W from the wave's first one on
+  u32x4 w_desc = {0, 0, 0, 0x00020000u};
+  auto w_set = [&]() {
+    const int rows = min_int(w_left, 16);             // (below 2^25 bytes: ldb is at most 2^20)
+    const int bytes = rows * (int)(p.ldb * 2) - n0 * 2;
+    w_desc[0] = (uint32_t)w_addr; w_desc[1] = (uint32_t)(w_addr >> 32);
+    w_desc[2] = (uint32_t)(bytes > 0 ? bytes : 0);
+  };
+  auto w_advance = [&]() { w_addr += (uint64_t)p.ldb * (BK * 2); w_left -= BK; w_set(); };
+  if (B_KMAJOR) {
+    const int64_t first = (int64_t)k_first * BK + wave_u * 16;
+    w_addr = (uint64_t)(p.B + first * p.ldb + n0);
+    w_left = p.V - (int)first;
+    w_set();
+  }
+  auto load_lds16_w = [](uint32_t voff, const u32x4& desc, uint32_t lds_addr) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds"
+                 :: "v"(voff), "s"(desc), "s"(lds_addr) : "memory");
+  };
   auto issue_range = [&](int kt, int slot, int j0, int j1) {
 #pragma unroll
     for (int j = j0; j < j1; ++j) {
       const uint32_t st = slot * STAGE_BYTES + wave_lds;
-      if (j & 1) load_lds16_at(b_ptr[j >> 1], (int64_t)kt * (BK * 2), st + TILE_BYTES + lds_b[j >> 1]);
+      if (B_KMAJOR && (j & 1)) load_lds16_w(b_voff[j >> 1], w_desc, st + TILE_BYTES + lds_b[j >> 1]);
+      else if (j & 1) load_lds16_at(b_ptr[j >> 1], (int64_t)kt * (BK * 2), st + TILE_BYTES + lds_b[j >> 1]);
       else load_lds16_at(a_ptr[j >> 1], (int64_t)kt * a_kstep * 2, st + lds_a[j >> 1]);
     }
   };
@@ -434,6 +500,7 @@ __global__ __launch_bounds__(NTHREADS) void gemm_nt_bf16(Params p) {
       if (m < 2) fax[3][m] = read_a(st_cur, m, 3);
     } else if (g <= 4) {
       if (m < 2) fax[(g - 1) & 3][m] = read_a(st_cur, m, g + 3);
+      if (B_KMAJOR && g == 4 && m == 6) w_advance();
     } else {
       const int q = g - 5;                          // 0, 1, 2
       if (g == 5 && m == 0) {
@@ -482,7 +549,8 @@ __global__ __launch_bounds__(NTHREADS) void gemm_nt_bf16(Params p) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) acc[i][j][e] = 0.f;
   if (nk > 0) {
-    issue_loads(0, 0, 0, 8);
+    issue_range(0, 0, 0, 16);
+    if (B_KMAJOR) w_advance();
     if (MODE == MODE_FWD) issue_zt();
     __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
     __syncthreads();
@@ -503,8 +571,6 @@ __global__ __launch_bounds__(NTHREADS) void gemm_nt_bf16(Params p) {
   //   row m = m0 + wm*128 + i*16 + 4*(lane>>4) + e      (FWD: the permuted row, see vrow below)
   //   col n = n0 + wn*128 + j*16 + (lane & 15)
   if (MODE == MODE_DH) __syncthreads();   // its staged epilogue reuses the panels' LDS
-  const int mrow_base = m0 + wm * 128 + 4 * fq;
-  const int ncol_base = n0 + wn * 128 + frow;
 
   if (MODE == MODE_FWD) {
     const int lane = lane_now(), wave = wave_u;
@@ -584,9 +650,27 @@ __global__ __launch_bounds__(NTHREADS) void gemm_nt_bf16(Params p) {
       if (p.part_ez != nullptr) body(Flag<false>{}, Flag<true>{}); else body(Flag<false>{}, Flag<false>{});
     }
   } else if (MODE == MODE_DH) {
+    const int lane = lane_now(), wave = wave_u, tid = wave * 64 + lane;
+    const int wm = wave >> 1, wn = wave & 1, frow = lane & 15, fq = lane >> 4;
+    const int mrow_base = m0 + wm * 128 + 4 * fq;
+    const int ncol_base = n0 + wn * 128 + frow;
     // rows = token rows of the chunk (scattered to their slots), cols = hidden index; a row
     // of the stash times W is the row's dz W up to its scale -g / S, applied here
-    if (p.dh_f32) {
+    if (tail_out != nullptr) {
+      // a slice of the contraction: the accumulators as they are, [256][256] fp32
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          float* row = tail_out + (wm * 128 + i * 16 + 4 * fq + e) * BN + wn * 128 + frow;
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            float x;                                  // (read where it is used, as in the forward epilogue)
+            asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(x) : "a"(acc[i][j][e]));
+            row[j * 16] = x;
+          }
+        }
+    } else if (p.dh_f32) {
 #pragma unroll
       for (int i = 0; i < 8; ++i)
 #pragma unroll
@@ -627,6 +711,10 @@ __global__ __launch_bounds__(NTHREADS) void gemm_nt_bf16(Params p) {
       }
     }
   } else {
+    const int lane = lane_now(), wave = wave_u;
+    const int wm = wave >> 1, wn = wave & 1, frow = lane & 15, fq = lane >> 4;
+    const int mrow_base = m0 + wm * 128 + 4 * fq;
+    const int ncol_base = n0 + wn * 128 + frow;
     // rows = vocabulary ids, cols = hidden index; fp32 accumulate into dW.  The old values of
     // one 16-row band are fetched as a batch before any store, so their latencies overlap.
     // A K slice of a tail tile stores its partial tile as it is, [256][256] fp32, to the scratch
@@ -745,6 +833,44 @@ __global__ __launch_bounds__(256) void dw_tail_reduce(const float* __restrict__ 
   *out = overwrite ? s : *out + s;
 }
 
+// Adds the slices of the dH launch's tail tiles (slice 0 first), applies the row scale and scatters
+// the rows to their slots: 8 columns per thread.  Blocks beyond the tiles that the device finds cut
+// return at once.
+__global__ __launch_bounds__(256) void dh_tail_reduce(Params p) {
+  int64_t nv64 = *p.n_scored - p.chunk_start;
+  const int M = nv64 < 0 ? 0 : (nv64 > p.chunk_rows ? p.chunk_rows : (int)nv64);
+  const int Mt = (M + BM - 1) / BM, Nt = (p.N + BN - 1) / BN;
+  const int tiles = Mt * Nt, whole = tiles / kRound * kRound, rest = tiles - whole;
+  const int t = blockIdx.x / (BM * BN / 2048);
+  if (t >= rest) return;
+  const int split = dh_split(rest, p.K / BK, p.max_items);
+  if (split == 1) return;
+  int tm, tn;
+  tile_at(whole + t, Mt, Nt, tm, tn);
+  const int within = (blockIdx.x % (BM * BN / 2048)) * 2048 + threadIdx.x * 8;
+  const int m = tm * BM + within / BN, n = tn * BN + within % BN;
+  if (m >= M || n >= p.d) return;
+  f32x4 lo = {0.f, 0.f, 0.f, 0.f}, hi = lo;
+#pragma unroll 4
+  for (int s = 0; s < split; ++s) {
+    const f32x4* q = reinterpret_cast<const f32x4*>(p.tail_part + ((int64_t)s * rest + t) * (BM * BN) + within);
+    lo += q[0];
+    hi += q[1];
+  }
+  const float sc = p.row_scale[m];
+  const int64_t at = (int64_t)p.row_index[m] * p.d + n;
+  if (p.dh_f32) {
+    float* out = static_cast<float*>(p.dH) + at;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) { out[e] = sc * lo[e]; out[4 + e] = sc * hi[e]; }
+  } else {
+    bf16x8 h;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) { h[e] = (__bf16)(sc * lo[e]); h[4 + e] = (__bf16)(sc * hi[e]); }
+    *reinterpret_cast<bf16x8*>(static_cast<uint16_t*>(p.dH) + at) = h;
+  }
+}
+
 template <int MODE>
 void launch(Params& p, hipStream_t stream) {
   static LdsLimit lds_limit;
@@ -766,11 +892,16 @@ void launch(Params& p, hipStream_t stream) {
     p.tail_first[NXCD] = tail.first[NXCD];
     blocks = p.main_blocks + most * NXCD;
   }
+  if (MODE == MODE_DH) blocks = (Mt * Nt) / kRound * kRound + (p.max_items + NXCD - 1) / NXCD * NXCD;
   hipLaunchKernelGGL(gemm_nt_bf16<MODE>, dim3(blocks), dim3(NTHREADS), lds_bytes<MODE>(), stream, p);
   if (tail.split > 0) {
     const int tiles = tail.rows * Nt;
     hipLaunchKernelGGL(dw_tail_reduce, dim3(tiles * (BM * BN / 256)), dim3(256), 0, stream, p.tail_part, tiles,
                        tail.split, Nt, tail.m0, p.V, p.d, p.dW, p.overwrite, p.n_scored, p.chunk_start);
+  }
+  if (MODE == MODE_DH) {
+    const int most = Mt * Nt < kRound ? Mt * Nt : kRound - 1;
+    hipLaunchKernelGGL(dh_tail_reduce, dim3(most * (BM * BN / 2048)), dim3(256), 0, stream, p);
   }
 }
 
@@ -791,22 +922,24 @@ void launch_gemm_fwd_bf16(const void* W, int64_t ldw, const void* Hc, int64_t ld
   launch<MODE_FWD>(p, stream);
 }
 
-void launch_gemm_dh_bf16(const void* E, int64_t lde, const void* Wt, int64_t ldwt,
+void launch_gemm_dh_bf16(const void* E, int64_t lde, const void* W, int64_t ldw, int V,
                          const int32_t* row_index, const float* row_scale, const int64_t* n_scored,
-                         int64_t chunk_start, int chunk_rows, int Vp, int d, void* dH, int dh_f32,
-                         hipStream_t stream) {
+                         int64_t chunk_start, int chunk_rows, int d, void* dH, int dh_f32,
+                         float* tail_part, int tail_items, hipStream_t stream) {
   Params p = {};
   p.A = static_cast<const uint16_t*>(E); p.lda = lde; p.M = chunk_rows;
   p.row_scale = row_scale + chunk_start;
-  p.B = static_cast<const uint16_t*>(Wt); p.ldb = ldwt; p.N = d;
-  p.K = Vp;
+  p.B = static_cast<const uint16_t*>(W); p.ldb = ldw; p.N = d;
+  p.K = (int)round_up(V, 2 * BK);
   p.row_index = row_index + chunk_start;
   p.n_scored = n_scored; p.chunk_start = chunk_start; p.chunk_rows = chunk_rows;
-  p.dH = dH; p.dh_f32 = dh_f32; p.d = d; p.V = Vp;
+  p.dH = dH; p.dh_f32 = dh_f32; p.d = d; p.V = V;
+  p.tail_part = tail_part; p.max_items = tail_items;
   launch<MODE_DH>(p, stream);
 }
 
-size_t gemm_dw_tail_bytes() { return (size_t)kDwTailMaxItems * BM * BN * sizeof(float); }
+size_t gemm_tail_tile_bytes() { return (size_t)BM * BN * sizeof(float); }
+int gemm_dw_tail_items() { return kDwTailMaxItems; }
 
 void launch_gemm_dw_bf16(const void* E, int64_t lde, const void* Ht, int64_t ldht,
                          const int64_t* n_scored, int64_t chunk_start, int chunk_rows,

@@ -62,21 +62,24 @@ void launch_gemm_fwd_bf16(const void* W, int64_t ldw, const void* Hc, int64_t ld
                           int V, int d, float* part_sum, float* part_ez,
                           int64_t part_stride, void* estash, int64_t lde, hipStream_t stream);
 
-// dH: A = E [chunk_rows, Vp] (the patched bf16 stash), B = Wt [d, Vp]; row m, multiplied by
-// row_scale[chunk_start + m], goes to dH[row_index[chunk_start + m], :] as bf16 (dh_f32 = 0) or
-// float (dh_f32 = 1).
-void launch_gemm_dh_bf16(const void* E, int64_t lde, const void* Wt, int64_t ldwt,
+// dH: A = E [chunk_rows, Vp] (the patched bf16 stash), B = W^T read in place from W [V, d] (row
+// stride ldw); row m, multiplied by row_scale[chunk_start + m], goes to
+// dH[row_index[chunk_start + m], :] as bf16 (dh_f32 = 0) or float (dh_f32 = 1).
+// tail_part: scratch of tail_items * gemm_tail_tile_bytes() bytes for the K slices of the last
+// round's tiles.
+void launch_gemm_dh_bf16(const void* E, int64_t lde, const void* W, int64_t ldw, int V,
                          const int32_t* row_index, const float* row_scale, const int64_t* n_scored,
-                         int64_t chunk_start, int chunk_rows, int Vp, int d, void* dH, int dh_f32,
-                         hipStream_t stream);
+                         int64_t chunk_start, int chunk_rows, int d, void* dH, int dh_f32,
+                         float* tail_part, int tail_items, hipStream_t stream);
 
 // dW: A = E^T read in place from E [chunk_rows, Vp] (rows >= valid rows rounded up to 128 and
 // columns >= V must be zero), B = Ht [d, chunk_rows] (the pass's hidden rows, each already
 // multiplied by its row scale); dW[v, :] = (or +=) sum over the chunk's valid rows.
 // overwrite = 1 stores, 0 adds into the existing values.
-// tail_part: scratch of gemm_dw_tail_bytes() bytes for the K-split tail tiles (nullptr: the
+// tail_part: scratch of gemm_dw_tail_items() * gemm_tail_tile_bytes() bytes for the K-split tail tiles (nullptr: the
 // ragged last rows of tiles run as whole tiles).
-size_t gemm_dw_tail_bytes();
+size_t gemm_tail_tile_bytes();
+int gemm_dw_tail_items();
 void launch_gemm_dw_bf16(const void* P, int64_t ldp, const void* Ht, int64_t ldht,
                          const int64_t* n_scored, int64_t chunk_start, int chunk_rows,
                          int V, int d, float* dW, int overwrite, float* tail_part, hipStream_t stream);
@@ -182,7 +185,7 @@ void launch_gather_rows_b16(const void* in, int64_t ld_in, const int32_t* rows, 
 
 // Out[c][r] = scale[r] * In[rows[r]][c] (rows == nullptr: identity; scale == nullptr: 1, 2-byte
 // elements only) for r < n_rows_valid, zero beyond, r in [0, out_cols_pad), c in [0, n_cols).
-// Used for Wt (static) and Ht (gathered, dynamic, scaled).
+// Used for Ht (gathered, dynamic, scaled) and the fp32 path's Wt (static).
 void launch_transpose(const void* in, int64_t ld_in, const int32_t* rows, const float* scale, void* out, int64_t ld_out,
                       int64_t n_rows_static, const int64_t* n_scored, int64_t chunk_start,
                       int chunk_rows, int n_cols, int64_t out_cols_pad, int elem_bytes,

@@ -44,3 +44,47 @@ def test_forward_tiles_cover_scored_rows(mrl, N, scored, d, V):
     assert np.max(np.abs(logp[rows].cpu().numpy() - want)) <= 1e-4
     assert np.max(np.abs(lse[rows].cpu().numpy() - want_lse)) <= 1e-4
     assert torch.all(logp[mask == 0] == 0) and torch.all(lse[mask == 0] == 0)
+
+
+def _step(mrl, H, W, y, mask, dh_dtype, seed, chunk_rows=0):
+    """One loss step of a single sequence (its tokens' advantages and traces random) and the same in float64."""
+    g = torch.Generator("cuda").manual_seed(seed)
+    N, d = H.shape
+    V = W.shape[0]
+    rows = torch.nonzero(mask)[:, 0]
+    z = H[rows].double() @ W.double().t()
+    lse = torch.logsumexp(z, 1)
+    at = torch.arange(rows.numel(), device="cuda")
+    lp = z[at, y[rows].long()] - lse
+    behav = torch.zeros(N, device="cuda")
+    behav[rows] = (lp + 0.05 * torch.randn(rows.numel(), device="cuda", generator=g)).float()
+    cfg = mrl.LossConfig(kl_beta=0.0, dh_dtype=dh_dtype, chunk_rows=chunk_rows)
+    one = lambda v, t: torch.tensor([v], dtype=t, device="cuda")
+    out = mrl.grpo_loss_fwd_bwd(H, W, y, mask, behav, None, one(0.7, torch.float32), one(0, torch.int32), None, 1, N, 1, cfg)
+    torch.cuda.synchronize()
+    w = torch.exp(lp - behav[rows].double())
+    gr = torch.where(w <= 1.2, -0.7 * w, 0.0) / rows.numel()          # A > 0: clipped above 1.2
+    dz = -gr[:, None] * torch.exp(z - lse[:, None])
+    dz[at, y[rows].long()] += gr
+    dH = torch.zeros((N, d), dtype=torch.float64, device="cuda")
+    dH[rows] = dz @ W.double()
+    return out, dH.cpu().numpy(), (dz.t() @ H[rows].double()).cpu().numpy()
+
+
+@pytest.mark.parametrize("scored,d,V,dh_f32", [
+    (1, 256, 70, 0),              # one tile, a vocabulary shorter than a panel pair
+    (300, 136, 1000, 1),          # two tiles of a padded width, too few panels to slice
+    (255, 512, 9001, 0),          # two tiles, eight slices and more
+    (700, 1000, 16500, 1),        # twelve tiles, 21 slices, float output, a width that ends inside a tile
+    (2500, 4096, 4200, 0),        # 160 tiles: more than half a round, slices run in several rounds
+    (4200, 4096, 5003, 0),        # 272 tiles: a whole round and 16 sliced tiles
+])
+def test_dh_tiles_and_slices(mrl, scored, d, V, dh_f32):
+    H, W, y, mask = _head(scored + 37, d, V, scored, scored)
+    out, dH, dW = _step(mrl, H, W, y, mask, mrl.F32 if dh_f32 else mrl.BF16, scored)
+    # bf16 operands (e, the scaled hidden rows, the output): 2^-9 each, the bar of the parity tests
+    util.check_gradient("dH", util.to_f64(out["dH"]), dH)
+    util.check_gradient("dW", util.to_f64(out["dW"]), dW)
+    assert torch.all(out["dH"][mask == 0] == 0)
+    again, _, _ = _step(mrl, H, W, y, mask, mrl.F32 if dh_f32 else mrl.BF16, scored)
+    assert torch.equal(out["dH"], again["dH"])
