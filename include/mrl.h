@@ -232,8 +232,9 @@ typedef struct {
                                 magnitudes of App. E.3's sequence-ratio table are those of a mean)
                             Levels 1 and 2 need loss_agg = 0; the KL term stays per token; the
                             ratio statistics then count each token with its response's ratio.
-                            They run the forward contraction twice (the response sums must be
-                            complete before any token's gradient weight is known).           */
+                            They run the forward contraction of every pass but the first twice (the
+                            response sums must be complete before any token's gradient weight is
+                            known).                                                          */
   int32_t debug_sync;    /* 0 = fully asynchronous (default): target and group ids are range-checked on
                             the device only, offenders are skipped and counted (n_bad_targets; a bad
                             group id gives its row weight 0).
