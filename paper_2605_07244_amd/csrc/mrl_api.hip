@@ -231,16 +231,24 @@ int last_error() {
   return e == hipSuccess ? MRL_OK : MRL_ERR_DEVICE;
 }
 
+// preparation of a pass: target logits, and on the bf16 path the gathered rows.  `more`: what the first
+// pass of a loss call carries along (zero dH rows, sequence weights)
+void prepare_chunk(const void* H, const void* W, const int32_t* targets, int d, bool bf16, const Layout& L, void* ws,
+                   int64_t c0, RowPrepArgs more, hipStream_t s) {
+  Scope sc(MRL_PROF_CONVERT, s);
+  more.H = H; more.W = W; more.targets = targets; more.row_index = at<int32_t>(ws, L.row_index);
+  more.n_scored = at<int64_t>(ws, L.counters); more.chunk_start = c0; more.chunk_rows = L.chunk_rows; more.d = d;
+  if (bf16) { more.Hc = at<void>(ws, L.Hc); more.ldh = L.ldh; more.dp = L.dp; }
+  more.zt = at<float>(ws, L.zt);
+  launch_row_prep(more, bf16, s);
+}
+
 // forward of one chunk: logits tile GEMM with fused (or, in fp32, separate) log-sum-exp
 void forward_chunk(const void* H, const void* W, int d, int V, bool bf16, const Layout& L, void* ws,
                    int64_t c0, bool stash, hipStream_t s, bool entropy = false) {
   const int32_t* row_index = at<int32_t>(ws, L.row_index);
   const int64_t* n_scored = at<int64_t>(ws, L.counters);
   if (bf16) {
-    {
-      Scope sc(MRL_PROF_CONVERT, s);
-      launch_gather_rows_b16(H, d, row_index + c0, at<void>(ws, L.Hc), L.ldh, 0, n_scored, c0, L.chunk_rows, d, L.dp, s);
-    }
     const void* Wk = L.dp != d ? at<void>(ws, L.Wp) : W;
     const int64_t ldw = L.dp != d ? L.ldh : d;
     for (int sub = 0; sub < L.chunk_rows; sub += kFwdSubChunk) {
@@ -354,15 +362,14 @@ int mrl_token_scores(const void* hidden, const void* lm_head_w, const int32_t* t
   int64_t* n_scored = at<int64_t>(ws, L.counters);
   {
     Scope sc(MRL_PROF_PREP, s);
-    PrepOut po = {row_index, n_scored, n_scored + 1, at<int32_t>(ws, L.block_counts)};
+    const PrepOut po = {row_index, n_scored, n_scored + 1, at<int32_t>(ws, L.block_counts),
+                        {out_logp, out_lse, out_entropy}, 0, 0, nullptr};
     launch_prep(token_mask, target_ids, N, V, po, s);
-    launch_zero_unscored(token_mask, target_ids, N, V, d, out_logp, out_lse, nullptr, 0, s);
-    if (entropy) launch_zero_unscored(token_mask, target_ids, N, V, d, out_entropy, nullptr, nullptr, 0, s);
-    launch_target_logit(hidden, lm_head_w, target_ids, row_index, n_scored, N, d, bf16, at<float>(ws, L.zt), s);
-    if (L.Wp != 0) launch_gather_rows_b16(lm_head_w, d, nullptr, at<void>(ws, L.Wp), L.ldh, V, nullptr, 0, 0, d, L.dp, s);
+    if (L.Wp != 0) launch_pad_rows_b16(lm_head_w, d, at<void>(ws, L.Wp), L.ldh, V, d, L.dp, s);
   }
   for (int64_t c = 0; c < L.n_chunks; ++c) {
     const int64_t c0 = c * L.chunk_rows;
+    prepare_chunk(hidden, lm_head_w, target_ids, d, bf16, L, ws, c0, RowPrepArgs{}, s);
     forward_chunk(hidden, lm_head_w, d, V, bf16, L, ws, c0, false, s, entropy);
     Scope sc(MRL_PROF_ROW_EPI, s);
     RowEpiArgs e = {};
@@ -467,7 +474,6 @@ int mrl_grpo_loss_fwd_bwd(const void* hidden, const void* lm_head_w, const int32
   hipStream_t s = static_cast<hipStream_t>(stream);
   const bool bf16 = dtype == MRL_BF16;
   const bool bwd = out_dH != nullptr || out_dW != nullptr;
-  const int es = bf16 ? 2 : 4;
   void* ws = workspace;
   int32_t* row_index = at<int32_t>(ws, L.row_index);
   int64_t* n_scored = at<int64_t>(ws, L.counters);
@@ -475,16 +481,25 @@ int mrl_grpo_loss_fwd_bwd(const void* hidden, const void* lm_head_w, const int32
 
   {
     Scope sc(MRL_PROF_PREP, s);
-    PrepOut po = {row_index, n_scored, n_scored + 1, at<int32_t>(ws, L.block_counts)};
+    const PrepOut po = {row_index, n_scored, n_scored + 1, at<int32_t>(ws, L.block_counts),
+                        {out_logp, nullptr, nullptr}, B, T, at<int32_t>(ws, L.seq_len)};
     launch_prep(token_mask, target_ids, N, V, po, s);
-    launch_seq_weights(token_mask, target_ids, group_id, seq_kind, B, T, G, V, cfg->loss_agg,
-                       at<int32_t>(ws, L.seq_len), at<float>(ws, L.seq_coef), at<int32_t>(ws, L.group_count),
-                       n_scored + 2, s);
-    launch_zero_unscored(token_mask, target_ids, N, V, d, out_logp, nullptr, out_dH,
-                         cfg->dh_dtype == MRL_BF16 ? 2 : 4, s);
-    launch_target_logit(hidden, lm_head_w, target_ids, row_index, n_scored, N, d, bf16, at<float>(ws, L.zt), s);
-    if (L.Wp != 0) launch_gather_rows_b16(lm_head_w, d, nullptr, at<void>(ws, L.Wp), L.ldh, V, nullptr, 0, 0, d, L.dp, s);
+    if (L.Wp != 0) launch_pad_rows_b16(lm_head_w, d, at<void>(ws, L.Wp), L.ldh, V, d, L.dp, s);
   }
+  int64_t n_passes = L.n_chunks;
+  if (cfg->scored_rows_hint > 0) {
+    const int64_t by_hint = (cfg->scored_rows_hint + L.chunk_rows - 1) / L.chunk_rows;
+    n_passes = by_hint < n_passes ? by_hint : n_passes;
+  }
+  // the first pass that is prepared carries the sequence weights and the zero dH rows along
+  RowPrepArgs once = {};
+  once.mask = token_mask; once.N = N; once.V = V;
+  once.dH = out_dH; once.dh_row_bytes = (int64_t)d * (cfg->dh_dtype == MRL_BF16 ? 2 : 4);
+  once.seq_len = at<int32_t>(ws, L.seq_len); once.group_id = group_id; once.seq_kind = seq_kind;
+  once.B = B; once.G = G; once.loss_agg = cfg->loss_agg; once.group_count = at<int32_t>(ws, L.group_count);
+  once.seq_coef = at<float>(ws, L.seq_coef); once.n_bad_groups = n_scored + 2;
+  const int64_t c_first = cfg->ratio_level != 0 ? n_passes - 1 : 0;
+  prepare_chunk(hidden, lm_head_w, target_ids, d, bf16, L, ws, c_first * L.chunk_rows, once, s);
   if (cfg->debug_sync) {
     // debugging aid: wait for the preparation kernels and turn the device-side range counters
     // into error codes before any further work is enqueued
@@ -499,12 +514,7 @@ int mrl_grpo_loss_fwd_bwd(const void* hidden, const void* lm_head_w, const int32
   }
   if (out_dH && !bf16) {
     Scope sc(MRL_PROF_CONVERT, s);
-    launch_transpose(lm_head_w, d, nullptr, nullptr, at<void>(ws, L.Wt), L.ldz, V, nullptr, 0, 0, d, L.Vp, es, s);
-  }
-  int64_t n_passes = L.n_chunks;
-  if (cfg->scored_rows_hint > 0) {
-    const int64_t by_hint = (cfg->scored_rows_hint + L.chunk_rows - 1) / L.chunk_rows;
-    n_passes = by_hint < n_passes ? by_hint : n_passes;
+    launch_transpose_f32(lm_head_w, d, nullptr, at<void>(ws, L.Wt), L.ldz, V, nullptr, 0, 0, d, L.Vp, s);
   }
   if (cfg->ratio_level != 0) {
     // Response-level ratio: a response may span several passes, so the log-probs of all rows are
@@ -514,6 +524,7 @@ int mrl_grpo_loss_fwd_bwd(const void* hidden, const void* lm_head_w, const int32
     // forward contraction once (28672 rows, V = 128256, d = 2048: 42.8 -> 31.9 ms a step).
     for (int64_t c = n_passes - 1; c >= 0; --c) {
       const int64_t c0 = c * L.chunk_rows;
+      if (c != c_first) prepare_chunk(hidden, lm_head_w, target_ids, d, bf16, L, ws, c0, RowPrepArgs{}, s);
       forward_chunk(hidden, lm_head_w, d, V, bf16, L, ws, c0, bwd && c == 0, s);
       Scope sc(MRL_PROF_ROW_EPI, s);
       RowEpiArgs e = {};
@@ -529,6 +540,7 @@ int mrl_grpo_loss_fwd_bwd(const void* hidden, const void* lm_head_w, const int32
   }
   for (int64_t c = 0; c < n_passes; ++c) {
     const int64_t c0 = c * L.chunk_rows;
+    if (c > 0) prepare_chunk(hidden, lm_head_w, target_ids, d, bf16, L, ws, c0, RowPrepArgs{}, s);
     if (c > 0 || cfg->ratio_level == 0) forward_chunk(hidden, lm_head_w, d, V, bf16, L, ws, c0, bwd, s);
     {
       Scope sc(MRL_PROF_ROW_EPI, s);
@@ -555,18 +567,18 @@ int mrl_grpo_loss_fwd_bwd(const void* hidden, const void* lm_head_w, const int32
     {
       Scope sc(MRL_PROF_CONVERT, s);
       if (bf16) {
-        // the stash already holds the backward operand; only the ragged end of the last pass needs clearing
-        launch_zero_stash_tail(at<void>(ws, L.Z), L.ldz, n_scored, c0, L.chunk_rows, (int)L.Vp, s);
+        // the stash already holds the backward operand; the dW launch needs the pass's gathered rows, each
+        // times its row scale, transposed, and zeros behind the last valid row
+        if (out_dW)
+          launch_backward_rows_b16(at<void>(ws, L.Hc), L.ldh, at<float>(ws, L.row_scale) + c0, at<void>(ws, L.Ht), L.ldr,
+                                   n_scored, c0, L.chunk_rows, L.dp, at<void>(ws, L.Z), L.ldz, (int)L.Vp, s);
       } else {
         launch_convert_f32(at<float>(ws, L.Z), L.ldz, at<float>(ws, L.Pt), L.ldr, at<float>(ws, L.lse_c),
                            at<float>(ws, L.g_c), target_ids, row_index, n_scored, c0, L.chunk_rows, V, s);
+        if (out_dW)
+          launch_transpose_f32(hidden, d, row_index + c0, at<void>(ws, L.Ht), L.ldr, 0, n_scored, c0, L.chunk_rows, d,
+                               L.chunk_rows, s);
       }
-      if (out_dW && bf16)   // from the pass's gathered rows, each times its row scale
-        launch_transpose(at<void>(ws, L.Hc), L.ldh, nullptr, at<float>(ws, L.row_scale) + c0, at<void>(ws, L.Ht), L.ldr,
-                         0, n_scored, c0, L.chunk_rows, L.dp, L.chunk_rows, es, s);
-      else if (out_dW)
-        launch_transpose(hidden, d, row_index + c0, nullptr, at<void>(ws, L.Ht), L.ldr, 0, n_scored, c0,
-                         L.chunk_rows, d, L.chunk_rows, es, s);
     }
     if (out_dH) {
       Scope sc(MRL_PROF_GEMM_DH, s);

@@ -18,11 +18,29 @@ __device__ inline int valid_rows(const int64_t* n_scored, int64_t chunk_start, i
 }
 
 // ----------------------------------------------------------------------------
-// Compaction of scored slots (order preserving): count, scan, fill.
+// Compaction of scored slots (order preserving), zeros in the per-slot outputs of the others, and
+// the scored length of every sequence.  A launch that does next to nothing takes 4.5 - 5 us here,
+// which the preparation of a small call is made of, so independent pieces share a launch: up to
+// kPrepOneBlock slots one block compacts (and the other blocks of the launch count the sequences);
+// above, one launch counts per block of slots (and per sequence) and one places the slots, each
+// block adding up the counts before its own - up to kPrepMaxSelf blocks, beyond which a scan launch
+// in between is cheaper than every block reading them all.
+// Count, scan, fill, sequence lengths and the zeros were launches of their own, 19 us before a loss call
+// of 512 slots; now 5 us.
 // ----------------------------------------------------------------------------
 constexpr int PREP_PER_THREAD = 4;
 constexpr int PREP_BLOCK = 256;
 constexpr int PREP_PER_BLOCK = PREP_PER_THREAD * PREP_BLOCK;
+constexpr int kPrepThreads = 1024;
+constexpr int kPrepWaves = kPrepThreads / 64;
+constexpr int64_t kPrepOneBlock = 32 * kPrepThreads;    // one bit per slot of a thread in a 32-bit word
+constexpr int64_t kPrepMaxSelf = 4096;
+
+struct SlotOutputs { float* o[3]; };                    // per-slot outputs that are 0 for unscored slots (or nullptr)
+__device__ inline void zero_slot(const SlotOutputs& z, int64_t n) {
+#pragma unroll
+  for (int k = 0; k < 3; ++k) if (z.o[k] != nullptr) z.o[k][n] = 0.f;
+}
 
 __device__ inline int block_exclusive_scan(int val, int* total) {
   // 256 threads; returns the exclusive prefix of val, *total = block sum.
@@ -49,9 +67,78 @@ __device__ inline int block_exclusive_scan(int val, int* total) {
   return res;
 }
 
+// scored slots of sequence b, counted by one wave
+__device__ inline void count_sequence(const uint8_t* mask, const int32_t* targets, int64_t b, int64_t B, int T, int V,
+                                      int32_t* seq_len) {
+  if (b >= B) return;
+  const int lane = threadIdx.x & 63;
+  int cnt = 0;
+#pragma unroll 4
+  for (int t = lane; t < T; t += 64) cnt += slot_valid(mask, targets, b * T + t, V);
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) cnt += __shfl_xor(cnt, off);
+  if (lane == 0) seq_len[b] = cnt;
+}
+
+// Block 0: N <= kPrepOneBlock slots, a contiguous run of them per wave.  Blocks 1 ..: one sequence
+// per wave.
+__global__ __launch_bounds__(kPrepThreads) void k_prep_one(const uint8_t* mask, const int32_t* targets, int N, int V,
+                                                           int64_t* n_scored, int64_t* n_bad, int32_t* row_index,
+                                                           SlotOutputs zero, int64_t B, int T, int32_t* seq_len) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  if (blockIdx.x > 0) {
+    count_sequence(mask, targets, (int64_t)(blockIdx.x - 1) * kPrepWaves + wave, B, T, V, seq_len);
+    return;
+  }
+  __shared__ int sums[kPrepWaves], bads[kPrepWaves];
+  const int iters = (N + kPrepThreads - 1) / kPrepThreads;
+  const int first = wave * iters * 64;
+  uint32_t bits = 0;
+  int cnt = 0, bad = 0;
+#pragma unroll 8
+  for (int it = 0; it < iters; ++it) {
+    const int n = first + it * 64 + lane;
+    bool scored = false, ok = false;
+    if (n < N) {
+      const int32_t y = targets[n];
+      ok = y >= 0 && y < V;
+      scored = mask == nullptr || mask[n] != 0;
+    }
+    bits |= (uint32_t)(scored && ok) << it;
+    cnt += scored && ok;
+    bad += scored && !ok;
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) { cnt += __shfl_xor(cnt, off); bad += __shfl_xor(bad, off); }
+  if (lane == 0) { sums[wave] = cnt; bads[wave] = bad; }
+  __syncthreads();
+  int pos = 0, total = 0, total_bad = 0;
+#pragma unroll
+  for (int w = 0; w < kPrepWaves; ++w) {
+    pos += w < wave ? sums[w] : 0;
+    total += sums[w];
+    total_bad += bads[w];
+  }
+  if (threadIdx.x == 0) { *n_scored = total; *n_bad = total_bad; }
+  for (int it = 0; it < iters; ++it) {
+    const int n = first + it * 64 + lane;
+    const bool ok = (bits >> it) & 1;
+    const unsigned long long ball = __ballot(ok);
+    if (ok) row_index[pos + __popcll(ball & ((1ull << lane) - 1ull))] = n;
+    else if (n < N) zero_slot(zero, n);
+    pos += __popcll(ball);
+    if (n < N && n >= total) row_index[n] = 0;          // tail entries: a harmless valid slot
+  }
+}
+
+// Blocks below nblocks: counts of their slots.  Blocks from nblocks on: one sequence per wave.
 __global__ __launch_bounds__(PREP_BLOCK) void k_prep_count(const uint8_t* mask, const int32_t* targets,
                                                           int64_t N, int V, int32_t* block_counts,
-                                                          int64_t nblocks) {
+                                                          int64_t nblocks, int64_t B, int T, int32_t* seq_len) {
+  if (blockIdx.x >= nblocks) {
+    count_sequence(mask, targets, (blockIdx.x - nblocks) * (PREP_BLOCK / 64) + (threadIdx.x >> 6), B, T, V, seq_len);
+    return;
+  }
   const int64_t base = (int64_t)blockIdx.x * PREP_PER_BLOCK + threadIdx.x * PREP_PER_THREAD;
   int cnt = 0, bad = 0;
 #pragma unroll
@@ -111,9 +198,11 @@ __global__ __launch_bounds__(1024) void k_prep_scan(int32_t* block_counts, int64
   if (threadIdx.x == 0) { *n_scored = carry; *n_bad = bad_total; }
 }
 
+// block_offsets == nullptr: the block adds up the counts itself, and block 0 publishes the totals
 __global__ __launch_bounds__(PREP_BLOCK) void k_prep_fill(const uint8_t* mask, const int32_t* targets,
-                                                         int64_t N, int V, const int64_t* block_offsets,
-                                                         const int64_t* n_scored, int32_t* row_index) {
+                                                         int64_t N, int V, const int32_t* block_counts, int64_t nblocks,
+                                                         const int64_t* block_offsets, int64_t* n_scored,
+                                                         int64_t* n_bad, int32_t* row_index, SlotOutputs zero) {
   const int64_t base = (int64_t)blockIdx.x * PREP_PER_BLOCK + threadIdx.x * PREP_PER_THREAD;
   bool ok[PREP_PER_THREAD];
   int cnt = 0;
@@ -123,95 +212,106 @@ __global__ __launch_bounds__(PREP_BLOCK) void k_prep_fill(const uint8_t* mask, c
     ok[k] = n < N && slot_valid(mask, targets, n, V);
     cnt += ok[k];
   }
+  int64_t before, ns;
+  if (block_offsets == nullptr) {
+    // (kPrepMaxSelf blocks of 1024 slots: the sums fit 32 bits)
+    int own = 0, all = 0, bad = 0, sum_own, sum_all, sum_bad;
+#pragma unroll 4
+    for (int i = threadIdx.x; i < nblocks; i += PREP_BLOCK) {
+      const int c = block_counts[i];
+      all += c;
+      own += i < blockIdx.x ? c : 0;
+      if (blockIdx.x == 0) bad += block_counts[nblocks + i];
+    }
+    block_exclusive_scan(own, &sum_own);
+    block_exclusive_scan(all, &sum_all);
+    before = sum_own;
+    ns = sum_all;
+    if (blockIdx.x == 0) {
+      block_exclusive_scan(bad, &sum_bad);
+      if (threadIdx.x == 0) { *n_scored = sum_all; *n_bad = sum_bad; }
+    }
+  } else {
+    before = block_offsets[blockIdx.x];
+    ns = *n_scored;
+  }
   int total;
   const int excl = block_exclusive_scan(cnt, &total);
-  int64_t pos = block_offsets[blockIdx.x] + excl;
-  const int64_t ns = *n_scored;
+  int64_t pos = before + excl;
 #pragma unroll
   for (int k = 0; k < PREP_PER_THREAD; ++k) {
     const int64_t n = base + k;
     if (ok[k]) row_index[pos++] = (int32_t)n;
+    else if (n < N) zero_slot(zero, n);
     if (n < N && n >= ns) row_index[n] = 0;   // tail entries: a harmless valid slot
   }
 }
 
 // ----------------------------------------------------------------------------
-// Sequence lengths and the aggregation weights of Eq. (1) / Eq. (2).
+// The aggregation weights of Eq. (1) / Eq. (2): one block.
 // ----------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_seq_len(const uint8_t* mask, const int32_t* targets, int T,
-                                                 int V, int32_t* seq_len) {
-  const int64_t b = blockIdx.x;
-  int cnt = 0;
-  for (int t = threadIdx.x; t < T; t += 256) cnt += slot_valid(mask, targets, b * T + t, V);
-  int total;
-  block_exclusive_scan(cnt, &total);
-  if (threadIdx.x == 0) seq_len[b] = total;
+constexpr int kCoefLdsGroups = 4096;
+__device__ inline void block_sum3(long long (&v)[3], long long (*sh)[3]) {   // 256 threads; the sums in every thread
+#pragma unroll
+  for (int k = 0; k < 3; ++k)
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v[k] += __shfl_xor(v[k], off);
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0)
+    for (int k = 0; k < 3; ++k) sh[threadIdx.x >> 6][k] = v[k];
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < 3; ++k) v[k] = sh[0][k] + sh[1][k] + sh[2][k] + sh[3][k];
 }
 
-__global__ __launch_bounds__(1024) void k_seq_coef(const int32_t* seq_len, const int32_t* group_id,
-                                                  const uint8_t* seq_kind, int64_t B, int G,
-                                                  int loss_agg, int32_t* group_count, float* seq_coef,
-                                                  int64_t* n_bad_groups) {
-  __shared__ long long sh_a[1024];
-  __shared__ long long sh_b[1024];
-  __shared__ long long tot_aux, tot_tok, tot_groups;
-  for (int g = threadIdx.x; g < G; g += 1024) group_count[g] = 0;
+struct CoefArgs {
+  const int32_t* seq_len; const int32_t* group_id; const uint8_t* seq_kind; int64_t B; int G; int loss_agg;
+  int32_t* group_count; float* seq_coef; int64_t* n_bad_groups;
+};
+__device__ inline void seq_coef_block(const CoefArgs& a, int32_t* lds_count /*[kCoefLdsGroups]*/) {
+  __shared__ long long sh[4][3];
+  const bool in_lds = a.G <= kCoefLdsGroups;
+  // group counts: in LDS, or with device-scope atomics in global memory
+  auto count = [&](int g) { return in_lds ? lds_count[g] : __hip_atomic_load(&a.group_count[g], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+  for (int g = threadIdx.x; g < a.G; g += 256) {
+    if (in_lds) lds_count[g] = 0;
+    else __hip_atomic_store(&a.group_count[g], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
   __threadfence();
   __syncthreads();
-  long long aux = 0, tok = 0;
-  for (int64_t b = threadIdx.x; b < B; b += 1024) {
-    const int kind = seq_kind ? seq_kind[b] : 0;
-    const int L = seq_len[b];
-    const int g = group_id[b];
-    if (kind == 0) {
-      if (g >= 0 && g < G) { atomicAdd(&group_count[g], 1); tok += L; }
-    } else {
-      aux += (L > 0);
+  long long v[3] = {0, 0, 0};                         // auxiliary rows with tokens, GRPO tokens, bad group ids
+  for (int64_t b = threadIdx.x; b < a.B; b += 256) {
+    const int kind = a.seq_kind ? a.seq_kind[b] : 0;
+    const int L = a.seq_len[b];
+    const int g = a.group_id[b];
+    const bool ok = g >= 0 && g < a.G;
+    v[2] += !ok;
+    if (kind != 0) v[0] += (L > 0);
+    else if (ok) {
+      if (in_lds) atomicAdd(&lds_count[g], 1); else atomicAdd(&a.group_count[g], 1);
+      v[1] += L;
     }
   }
-  sh_a[threadIdx.x] = aux; sh_b[threadIdx.x] = tok;
   __threadfence();
-  __syncthreads();
-  for (int off = 512; off > 0; off >>= 1) {
-    if (threadIdx.x < off) { sh_a[threadIdx.x] += sh_a[threadIdx.x + off]; sh_b[threadIdx.x] += sh_b[threadIdx.x + off]; }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) { tot_aux = sh_a[0]; tot_tok = sh_b[0]; }
-  __syncthreads();
-  long long ng = 0;
-  for (int g = threadIdx.x; g < G; g += 1024) ng += (group_count[g] > 0);
-  sh_a[threadIdx.x] = ng;
-  __syncthreads();
-  for (int off = 512; off > 0; off >>= 1) {
-    if (threadIdx.x < off) sh_a[threadIdx.x] += sh_a[threadIdx.x + off];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) tot_groups = sh_a[0];
-  __syncthreads();
-  // sequences whose group id is out of range (they get weight 0 below)
-  long long nbad = 0;
-  for (int64_t b = threadIdx.x; b < B; b += 1024) nbad += (group_id[b] < 0 || group_id[b] >= G);
-  sh_b[threadIdx.x] = nbad;
-  __syncthreads();
-  for (int off = 512; off > 0; off >>= 1) {
-    if (threadIdx.x < off) sh_b[threadIdx.x] += sh_b[threadIdx.x + off];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) *n_bad_groups = sh_b[0];
-  const double P = (double)tot_groups, S = (double)tot_aux, NT = (double)tot_tok;
-  for (int64_t b = threadIdx.x; b < B; b += 1024) {
-    const int kind = seq_kind ? seq_kind[b] : 0;
-    const int L = seq_len[b];
-    const int g = group_id[b];
+  block_sum3(v, sh);                                  // (its barriers also publish the counts)
+  long long u[3] = {0, 0, 0};
+  for (int g = threadIdx.x; g < a.G; g += 256) u[0] += (count(g) > 0);
+  block_sum3(u, sh);
+  if (threadIdx.x == 0) *a.n_bad_groups = v[2];
+  const double P = (double)u[0], S = (double)v[0], NT = (double)v[1];
+  for (int64_t b = threadIdx.x; b < a.B; b += 256) {
+    const int kind = a.seq_kind ? a.seq_kind[b] : 0;
+    const int L = a.seq_len[b];
+    const int g = a.group_id[b];
     double c = 0.0;
     if (L > 0) {
       if (kind == 0) {
-        if (g >= 0 && g < G) c = loss_agg == 1 ? 1.0 / NT : 1.0 / (P * (double)group_count[g] * (double)L);
+        if (g >= 0 && g < a.G) c = a.loss_agg == 1 ? 1.0 / NT : 1.0 / (P * (double)count(g) * (double)L);
       } else {
         c = 1.0 / (S * (double)L);
       }
     }
-    seq_coef[b] = (float)c;
+    a.seq_coef[b] = (float)c;
   }
 }
 
@@ -241,69 +341,78 @@ __global__ __launch_bounds__(256) void k_seq_log_ratio(const uint8_t* mask, cons
 }
 
 // ----------------------------------------------------------------------------
-// Zero the outputs of unscored slots.
+// Row preparation: what needs the compaction and comes before a forward launch, in one launch.
+//   block 0 (loss)      : the sequence weights
+//   zero_blocks         : dH rows of unscored slots, ZERO_SLOTS_PER_BLOCK each
+//   the rest            : one wave per scored row of the pass: target logit z_t = <H[slot], W[y]> and,
+//                         on the bf16 path, the row's copy Hc[r][0:dp] = H[slot][0:d] | 0, which
+//                         gives the forward launch contiguous rows (no index lookups in that kernel)
+//                         and a K extent that is a multiple of its 128-wide panel pairs
+// As launches of their own the pieces took 37 us before the forward launch of 512 slots (now 12), and the
+// target logits read the hidden rows a second time.
 // ----------------------------------------------------------------------------
 constexpr int ZERO_SLOTS_PER_BLOCK = 16;
-__global__ __launch_bounds__(256) void k_zero_unscored(const uint8_t* mask, const int32_t* targets,
-                                                       int64_t N, int V, int64_t row_bytes,
-                                                       float* out_logp, float* out_lse,
-                                                       unsigned char* dH) {
-  const int64_t first = (int64_t)blockIdx.x * ZERO_SLOTS_PER_BLOCK;
+__device__ inline float bf16_bits_to_float(uint32_t bits16) { return __uint_as_float(bits16 << 16); }
+
+__device__ inline void zero_dh_rows(const RowPrepArgs& a, int64_t first) {
   for (int s = 0; s < ZERO_SLOTS_PER_BLOCK; ++s) {
     const int64_t n = first + s;
-    if (n >= N) return;
-    if (slot_valid(mask, targets, n, V)) continue;
-    if (threadIdx.x == 0) {
-      if (out_logp) out_logp[n] = 0.f;
-      if (out_lse) out_lse[n] = 0.f;
-    }
-    if (dH) {
-      unsigned char* row = dH + n * row_bytes;
-      if ((row_bytes & 15) == 0) {
-        uint4 z = make_uint4(0, 0, 0, 0);
-        for (int64_t o = threadIdx.x * 16; o < row_bytes; o += 256 * 16) *reinterpret_cast<uint4*>(row + o) = z;
-      } else {
-        for (int64_t o = threadIdx.x * 4; o < row_bytes; o += 256 * 4) *reinterpret_cast<uint32_t*>(row + o) = 0u;
-      }
+    if (n >= a.N) return;
+    if (slot_valid(a.mask, a.targets, n, a.V)) continue;
+    unsigned char* row = static_cast<unsigned char*>(a.dH) + n * a.dh_row_bytes;
+    if ((a.dh_row_bytes & 15) == 0 && (reinterpret_cast<uintptr_t>(a.dH) & 15) == 0) {
+      const uint4 z = make_uint4(0, 0, 0, 0);
+      for (int64_t o = threadIdx.x * 16; o < a.dh_row_bytes; o += 256 * 16) *reinterpret_cast<uint4*>(row + o) = z;
+    } else {
+      for (int64_t o = threadIdx.x * 4; o < a.dh_row_bytes; o += 256 * 4) *reinterpret_cast<uint32_t*>(row + o) = 0u;
     }
   }
 }
 
-// ----------------------------------------------------------------------------
-// Target logit z_t[i] = <H[slot_i], W[y_i]>, one wavefront per compacted row.
-// ----------------------------------------------------------------------------
-__device__ inline float bf16_bits_to_float(uint32_t bits16) { return __uint_as_float(bits16 << 16); }
-
 template <bool BF16>
-__global__ __launch_bounds__(256) void k_target_logit(const void* H, const void* W, const int32_t* targets,
-                                                      const int32_t* row_index, const int64_t* n_scored,
-                                                      int d, float* zt) {
-  const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (i >= *n_scored) return;
+__global__ __launch_bounds__(256) void k_row_prep(RowPrepArgs a) {
+  __shared__ int32_t lds_count[kCoefLdsGroups];
+  int64_t block = blockIdx.x;
+  if (a.seq_coef != nullptr) {
+    if (block == 0) {
+      const CoefArgs c = {a.seq_len, a.group_id, a.seq_kind, a.B, a.G, a.loss_agg, a.group_count, a.seq_coef, a.n_bad_groups};
+      seq_coef_block(c, lds_count);
+      return;
+    }
+    --block;
+  }
+  if (block < a.zero_blocks) { zero_dh_rows(a, block * ZERO_SLOTS_PER_BLOCK); return; }
+  block -= a.zero_blocks;
+  const int64_t r = block * 4 + (threadIdx.x >> 6);
+  if (r >= valid_rows(a.n_scored, a.chunk_start, a.chunk_rows)) return;
   const int lane = threadIdx.x & 63;
-  const int64_t slot = row_index[i];
-  const int64_t y = targets[slot];
+  const int64_t slot = a.row_index[a.chunk_start + r];
+  const int64_t y = a.targets[slot];
   float acc = 0.f;
   if (BF16) {
-    const uint4* h = reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(H) + slot * d);
-    const uint4* w = reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(W) + y * d);
-    for (int c = lane; c < d / 8; c += 64) {
-      const uint4 a = h[c], b = w[c];
-      const uint32_t av[4] = {a.x, a.y, a.z, a.w}, bv[4] = {b.x, b.y, b.z, b.w};
+    const uint4* h = reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(a.H) + slot * a.d);
+    const uint4* w = reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(a.W) + y * a.d);
+    uint4* out = reinterpret_cast<uint4*>(static_cast<uint16_t*>(a.Hc) + r * a.ldh);
+#pragma unroll 4
+    for (int c = lane; c < a.d / 8; c += 64) {
+      const uint4 u = h[c], b = w[c];
+      out[c] = u;
+      const uint32_t av[4] = {u.x, u.y, u.z, u.w}, bv[4] = {b.x, b.y, b.z, b.w};
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         acc = fmaf(bf16_bits_to_float(av[q] & 0xffffu), bf16_bits_to_float(bv[q] & 0xffffu), acc);
         acc = fmaf(bf16_bits_to_float(av[q] >> 16), bf16_bits_to_float(bv[q] >> 16), acc);
       }
     }
+    for (int c = a.d / 8 + lane; c < a.dp / 8; c += 64) out[c] = make_uint4(0, 0, 0, 0);
   } else {
-    const float* h = static_cast<const float*>(H) + slot * d;
-    const float* w = static_cast<const float*>(W) + y * d;
-    for (int c = lane; c < d; c += 64) acc = fmaf(h[c], w[c], acc);
+    const float* h = static_cast<const float*>(a.H) + slot * a.d;
+    const float* w = static_cast<const float*>(a.W) + y * a.d;
+    for (int c = lane; c < a.d; c += 64) acc = fmaf(h[c], w[c], acc);
   }
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
-  if (lane == 0) zt[i] = acc;
+  if (lane == 0) a.zt[a.chunk_start + r] = acc;
 }
 
 // ----------------------------------------------------------------------------
@@ -574,20 +683,6 @@ __global__ __launch_bounds__(FIN_THREADS) void k_finalize(const double* parts, i
 }
 
 // ----------------------------------------------------------------------------
-// bf16 path: rows of the stash from the pass's valid count up to its multiple of 128 are cleared
-// (the dW contraction runs over pairs of 64-row panels and must not meet stale bits there).
-// ----------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_zero_stash_tail(uint16_t* E, int64_t lde, const int64_t* n_scored,
-                                                         int64_t chunk_start, int chunk_rows, int Vp) {
-  const int nvalid = valid_rows(n_scored, chunk_start, chunk_rows);
-  const int nzero = (nvalid + 127) / 128 * 128 < chunk_rows ? (nvalid + 127) / 128 * 128 : chunk_rows;
-  const int i = nvalid + blockIdx.y;
-  if (i >= nzero) return;
-  const int v = (blockIdx.x * 256 + threadIdx.x) * 8;
-  if (v < Vp) *reinterpret_cast<uint4*>(E + (int64_t)i * lde + v) = make_uint4(0, 0, 0, 0);
-}
-
-// ----------------------------------------------------------------------------
 // dz conversion of the fp32 path (proof of Prop. 4: grad log pi(a_i) = e_i - pi).
 // ----------------------------------------------------------------------------
 // fp32 path: scalar, bounds-checked.
@@ -611,47 +706,48 @@ __global__ __launch_bounds__(256) void k_convert_f32(float* ZP, int64_t ldz, flo
 }
 
 // ----------------------------------------------------------------------------
-// Row gather with zero padding: Out[r][0:dp] = In[rows[r]][0:d] | 0.  Makes the forward launch's
-// token-row operand contiguous (no index lookups in the kernel) and its K extent a multiple of
-// the kernel's 128-wide panel pairs; the same routine pads W when d is not such a multiple.
+// Row copy with zero padding: Out[r][0:dp] = In[r][0:d] | 0, for a W whose width is no multiple of
+// the forward kernel's 128-wide panel pairs.
 // ----------------------------------------------------------------------------
-constexpr int GATHER_ROWS = 4;
-__global__ __launch_bounds__(256) void k_gather_rows_b16(const uint16_t* in, int64_t ld_in, const int32_t* rows,
-                                                         uint16_t* out, int64_t ld_out, int64_t n_rows_static,
-                                                         const int64_t* n_scored, int64_t chunk_start,
-                                                         int chunk_rows, int d, int dp) {
-  int64_t nrows = n_rows_static;
-  if (n_scored != nullptr) nrows = valid_rows(n_scored, chunk_start, chunk_rows);
+constexpr int PAD_ROWS = 4;
+__global__ __launch_bounds__(256) void k_pad_rows_b16(const uint16_t* in, int64_t ld_in, uint16_t* out, int64_t ld_out,
+                                                      int64_t n_rows, int d, int dp) {
 #pragma unroll
-  for (int k = 0; k < GATHER_ROWS; ++k) {
-    const int64_t r = (int64_t)blockIdx.x * GATHER_ROWS + k;
-    if (r >= nrows) return;
-    const int64_t src = rows ? (int64_t)rows[r] : r;
+  for (int k = 0; k < PAD_ROWS; ++k) {
+    const int64_t r = (int64_t)blockIdx.x * PAD_ROWS + k;
+    if (r >= n_rows) return;
     for (int c = threadIdx.x * 8; c < dp; c += 256 * 8) {
       uint4 v = make_uint4(0, 0, 0, 0);
-      if (c < d) v = *reinterpret_cast<const uint4*>(in + src * ld_in + c);
+      if (c < d) v = *reinterpret_cast<const uint4*>(in + r * ld_in + c);
       *reinterpret_cast<uint4*>(out + r * ld_out + c) = v;
     }
   }
 }
 
 // ----------------------------------------------------------------------------
-// Transposes.  Out[c][r] = In[rows[r]][c].
+// Transposes.
 // ----------------------------------------------------------------------------
-// 2-byte elements, vectorised: tile 64 rows x 64 cols; requires n_cols % 64 == 0,
-// 16-byte aligned rows on both sides and out_cols_pad % 64 == 0.
-__global__ __launch_bounds__(256) void k_transpose_b16(const uint16_t* in, int64_t ld_in, const int32_t* rows,
-                                                       const float* scale /*per row, or nullptr*/,
-                                                       uint16_t* out, int64_t ld_out, int64_t n_rows_static,
-                                                       const int64_t* n_scored, int64_t chunk_start,
-                                                       int chunk_rows) {
+// Backward operand of the dW launch, bf16: Ht[c][r] = scale[r] * Hc[r][c] for the pass's valid
+// rows, zeros up to the multiple of 128 the contraction runs over.  Tile 64 rows x 64 cols; n_cols a
+// multiple of 64, 16-byte aligned rows on both sides.  The blocks behind the tiles clear the stash
+// rows between the valid count and that multiple (the contraction must not meet stale bits there).
+__global__ __launch_bounds__(256) void k_backward_rows_b16(const uint16_t* in, int64_t ld_in, const float* scale,
+                                                           uint16_t* out, int64_t ld_out, const int64_t* n_scored,
+                                                           int64_t chunk_start, int chunk_rows, int row_tiles,
+                                                           uint16_t* E, int64_t lde, int Vp) {
   __shared__ __attribute__((aligned(16))) uint16_t tile[64 * 72];
-  int64_t nrows = n_rows_static;
-  if (n_scored != nullptr) nrows = valid_rows(n_scored, chunk_start, chunk_rows);
+  const int nrows = valid_rows(n_scored, chunk_start, chunk_rows);
+  const int nzero = (nrows + 127) / 128 * 128 < chunk_rows ? (nrows + 127) / 128 * 128 : chunk_rows;
+  if ((int)blockIdx.y >= row_tiles) {
+    const int i = nrows + blockIdx.y - row_tiles;
+    if (i >= nzero) return;
+    for (int v = (blockIdx.x * 256 + threadIdx.x) * 8; v < Vp; v += gridDim.x * 256 * 8)
+      *reinterpret_cast<uint4*>(E + (int64_t)i * lde + v) = make_uint4(0, 0, 0, 0);
+    return;
+  }
   const int64_t r0 = (int64_t)blockIdx.y * 64;
   const int c0 = blockIdx.x * 64;
-  // gathered rows: zero fill up to the multiple of 128 the dW contraction runs over, nothing beyond
-  if (n_scored != nullptr && r0 >= (nrows + 127) / 128 * 128) return;
+  if (r0 >= (nrows + 127) / 128 * 128) return;
   const int tc = threadIdx.x & 7, tr = threadIdx.x >> 3;
 #pragma unroll
   for (int k = 0; k < 2; ++k) {
@@ -659,23 +755,20 @@ __global__ __launch_bounds__(256) void k_transpose_b16(const uint16_t* in, int64
     const int64_t r = r0 + rr;
     uint4 v = make_uint4(0, 0, 0, 0);
     if (r < nrows) {
-      const int64_t src_row = rows ? (int64_t)rows[r] : r;
-      v = *reinterpret_cast<const uint4*>(in + src_row * ld_in + c0 + tc * 8);
-      if (scale != nullptr) {
-        // bf16 elements times the row's scale, rounded back to bf16 (nearest even)
-        const float sc = scale[r];
-        uint32_t w[4] = {v.x, v.y, v.z, v.w};
+      v = *reinterpret_cast<const uint4*>(in + r * ld_in + c0 + tc * 8);
+      // bf16 elements times the row's scale, rounded back to bf16 (nearest even)
+      const float sc = scale[r];
+      uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const __bf16 lo = (__bf16)(sc * bf16_bits_to_float(w[q] & 0xffffu));
-          const __bf16 hi = (__bf16)(sc * bf16_bits_to_float(w[q] >> 16));
-          uint16_t ul, uh;
-          __builtin_memcpy(&ul, &lo, 2);
-          __builtin_memcpy(&uh, &hi, 2);
-          w[q] = (uint32_t)ul | ((uint32_t)uh << 16);
-        }
-        v = make_uint4(w[0], w[1], w[2], w[3]);
+      for (int q = 0; q < 4; ++q) {
+        const __bf16 lo = (__bf16)(sc * bf16_bits_to_float(w[q] & 0xffffu));
+        const __bf16 hi = (__bf16)(sc * bf16_bits_to_float(w[q] >> 16));
+        uint16_t ul, uh;
+        __builtin_memcpy(&ul, &lo, 2);
+        __builtin_memcpy(&uh, &hi, 2);
+        w[q] = (uint32_t)ul | ((uint32_t)uh << 16);
       }
+      v = make_uint4(w[0], w[1], w[2], w[3]);
     }
     *reinterpret_cast<uint4*>(&tile[rr * 72 + tc * 8]) = v;
   }
@@ -694,7 +787,7 @@ __global__ __launch_bounds__(256) void k_transpose_b16(const uint16_t* in, int64
   }
 }
 
-// 4-byte elements, scalar, bounds-checked: tile 32 x 32.
+// fp32 path: Out[c][r] = In[rows[r]][c], scalar, bounds-checked: tile 32 x 32.
 __global__ __launch_bounds__(256) void k_transpose_b32(const uint32_t* in, int64_t ld_in, const int32_t* rows,
                                                        uint32_t* out, int64_t ld_out, int64_t n_rows_static,
                                                        const int64_t* n_scored, int64_t chunk_start,
@@ -726,26 +819,25 @@ __global__ __launch_bounds__(256) void k_transpose_b32(const uint32_t* in, int64
 }  // namespace
 
 // ------------------------------------------------------------------ launchers
-void launch_prep(const uint8_t* mask, const int32_t* targets, int64_t N, int V, const PrepOut& o,
-                 hipStream_t stream) {
-  const int64_t nblocks = (N + PREP_PER_BLOCK - 1) / PREP_PER_BLOCK;
+void launch_prep(const uint8_t* mask, const int32_t* targets, int64_t N, int V, const PrepOut& o, hipStream_t stream) {
+  const SlotOutputs zero = {{o.zero[0], o.zero[1], o.zero[2]}};
+  const int64_t B = o.seq_len != nullptr ? o.B : 0;
+  if (N <= kPrepOneBlock) {
+    hipLaunchKernelGGL(k_prep_one, dim3((unsigned)(1 + (B + kPrepWaves - 1) / kPrepWaves)), dim3(kPrepThreads), 0, stream,
+                       mask, targets, (int)N, V, o.n_scored, o.n_bad, o.row_index, zero, B, o.T, o.seq_len);
+    return;
+  }
+  const int64_t nblocks = (N + PREP_PER_BLOCK - 1) / PREP_PER_BLOCK, seq_blocks = (B + PREP_BLOCK / 64 - 1) / (PREP_BLOCK / 64);
   // block_counts: [2 * nblocks] int32 counts followed (8-byte aligned) by [nblocks] int64 offsets
   int64_t* block_offsets = reinterpret_cast<int64_t*>(o.block_counts + round_up(2 * nblocks, 2));
-  hipLaunchKernelGGL(k_prep_count, dim3((unsigned)nblocks), dim3(PREP_BLOCK), 0, stream, mask, targets, N, V,
-                     o.block_counts, nblocks);
-  hipLaunchKernelGGL(k_prep_scan, dim3(1), dim3(1024), 0, stream, o.block_counts, nblocks, block_offsets,
-                     o.n_scored, o.n_bad);
+  const bool scan = nblocks > kPrepMaxSelf;
+  hipLaunchKernelGGL(k_prep_count, dim3((unsigned)(nblocks + seq_blocks)), dim3(PREP_BLOCK), 0, stream, mask, targets, N, V,
+                     o.block_counts, nblocks, B, o.T, o.seq_len);
+  if (scan)
+    hipLaunchKernelGGL(k_prep_scan, dim3(1), dim3(1024), 0, stream, o.block_counts, nblocks, block_offsets,
+                       o.n_scored, o.n_bad);
   hipLaunchKernelGGL(k_prep_fill, dim3((unsigned)nblocks), dim3(PREP_BLOCK), 0, stream, mask, targets, N, V,
-                     block_offsets, o.n_scored, o.row_index);
-}
-
-void launch_seq_weights(const uint8_t* mask, const int32_t* targets, const int32_t* group_id,
-                        const uint8_t* seq_kind, int64_t B, int T, int G, int V, int loss_agg,
-                        int32_t* seq_len, float* seq_coef, int32_t* group_count, int64_t* n_bad_groups,
-                        hipStream_t stream) {
-  hipLaunchKernelGGL(k_seq_len, dim3((unsigned)B), dim3(256), 0, stream, mask, targets, T, V, seq_len);
-  hipLaunchKernelGGL(k_seq_coef, dim3(1), dim3(1024), 0, stream, seq_len, group_id, seq_kind, B, G, loss_agg,
-                     group_count, seq_coef, n_bad_groups);
+                     o.block_counts, nblocks, scan ? block_offsets : nullptr, o.n_scored, o.n_bad, o.row_index, zero);
 }
 
 void launch_seq_log_ratio(const uint8_t* mask, const int32_t* targets, const float* logp,
@@ -755,24 +847,11 @@ void launch_seq_log_ratio(const uint8_t* mask, const int32_t* targets, const flo
                      T, V, level, seq_expo);
 }
 
-void launch_zero_unscored(const uint8_t* mask, const int32_t* targets, int64_t N, int V, int d,
-                          float* out_logp, float* out_lse, void* dH, int dh_elem_bytes,
-                          hipStream_t stream) {
-  const int64_t blocks = (N + ZERO_SLOTS_PER_BLOCK - 1) / ZERO_SLOTS_PER_BLOCK;
-  hipLaunchKernelGGL(k_zero_unscored, dim3((unsigned)blocks), dim3(256), 0, stream, mask, targets, N, V,
-                     (int64_t)d * dh_elem_bytes, out_logp, out_lse, static_cast<unsigned char*>(dH));
-}
-
-void launch_target_logit(const void* H, const void* W, const int32_t* targets,
-                         const int32_t* row_index, const int64_t* n_scored, int64_t N_max,
-                         int d, int is_bf16, float* zt, hipStream_t stream) {
-  const int64_t blocks = (N_max + 3) / 4;
-  if (is_bf16)
-    hipLaunchKernelGGL(k_target_logit<true>, dim3((unsigned)blocks), dim3(256), 0, stream, H, W, targets,
-                       row_index, n_scored, d, zt);
-  else
-    hipLaunchKernelGGL(k_target_logit<false>, dim3((unsigned)blocks), dim3(256), 0, stream, H, W, targets,
-                       row_index, n_scored, d, zt);
+void launch_row_prep(RowPrepArgs a, int is_bf16, hipStream_t stream) {
+  a.zero_blocks = a.dH != nullptr ? (a.N + ZERO_SLOTS_PER_BLOCK - 1) / ZERO_SLOTS_PER_BLOCK : 0;
+  const int64_t blocks = (a.seq_coef != nullptr ? 1 : 0) + a.zero_blocks + (a.chunk_rows + 3) / 4;
+  if (is_bf16) hipLaunchKernelGGL(k_row_prep<true>, dim3((unsigned)blocks), dim3(256), 0, stream, a);
+  else hipLaunchKernelGGL(k_row_prep<false>, dim3((unsigned)blocks), dim3(256), 0, stream, a);
 }
 
 void launch_row_lse_f32(const float* Z, int64_t ldz, const int64_t* n_scored, int64_t chunk_start,
@@ -798,38 +877,28 @@ void launch_convert_f32(float* ZP, int64_t ldz, float* Pt, int64_t ldpt, const f
                      row_index, n_scored, chunk_start, chunk_rows, V);
 }
 
-void launch_zero_stash_tail(void* estash, int64_t lde, const int64_t* n_scored, int64_t chunk_start,
-                            int chunk_rows, int Vp, hipStream_t stream) {
-  dim3 grid((Vp / 8 + 255) / 256, 127);
-  hipLaunchKernelGGL(k_zero_stash_tail, grid, dim3(256), 0, stream, static_cast<uint16_t*>(estash), lde,
-                     n_scored, chunk_start, chunk_rows, Vp);
+void launch_pad_rows_b16(const void* in, int64_t ld_in, void* out, int64_t ld_out, int64_t n_rows, int d, int dp,
+                         hipStream_t stream) {
+  hipLaunchKernelGGL(k_pad_rows_b16, dim3((unsigned)((n_rows + PAD_ROWS - 1) / PAD_ROWS)), dim3(256), 0, stream,
+                     static_cast<const uint16_t*>(in), ld_in, static_cast<uint16_t*>(out), ld_out, n_rows, d, dp);
 }
 
-void launch_gather_rows_b16(const void* in, int64_t ld_in, const int32_t* rows, void* out, int64_t ld_out,
-                            int64_t n_rows_static, const int64_t* n_scored, int64_t chunk_start,
-                            int chunk_rows, int d, int dp, hipStream_t stream) {
-  const int64_t max_rows = n_scored != nullptr ? chunk_rows : n_rows_static;
-  if (max_rows <= 0) return;
-  hipLaunchKernelGGL(k_gather_rows_b16, dim3((unsigned)((max_rows + GATHER_ROWS - 1) / GATHER_ROWS)), dim3(256), 0,
-                     stream, static_cast<const uint16_t*>(in), ld_in, rows, static_cast<uint16_t*>(out), ld_out,
-                     n_rows_static, n_scored, chunk_start, chunk_rows, d, dp);
+void launch_backward_rows_b16(const void* Hc, int64_t ldh, const float* scale, void* Ht, int64_t ldht,
+                              const int64_t* n_scored, int64_t chunk_start, int chunk_rows, int dp, void* E, int64_t lde,
+                              int Vp, hipStream_t stream) {
+  const int row_tiles = chunk_rows / 64;
+  hipLaunchKernelGGL(k_backward_rows_b16, dim3(dp / 64, (unsigned)(row_tiles + 127)), dim3(256), 0, stream,
+                     static_cast<const uint16_t*>(Hc), ldh, scale, static_cast<uint16_t*>(Ht), ldht, n_scored,
+                     chunk_start, chunk_rows, row_tiles, static_cast<uint16_t*>(E), lde, Vp);
 }
 
-void launch_transpose(const void* in, int64_t ld_in, const int32_t* rows, const float* scale, void* out, int64_t ld_out,
-                      int64_t n_rows_static, const int64_t* n_scored, int64_t chunk_start,
-                      int chunk_rows, int n_cols, int64_t out_cols_pad, int elem_bytes,
-                      hipStream_t stream) {
-  if (elem_bytes == 2) {
-    dim3 grid(n_cols / 64, (unsigned)(out_cols_pad / 64));
-    hipLaunchKernelGGL(k_transpose_b16, grid, dim3(256), 0, stream, static_cast<const uint16_t*>(in), ld_in,
-                       rows, scale, static_cast<uint16_t*>(out), ld_out, n_rows_static, n_scored, chunk_start,
-                       chunk_rows);
-  } else {
-    dim3 grid((n_cols + 31) / 32, (unsigned)((out_cols_pad + 31) / 32));
-    hipLaunchKernelGGL(k_transpose_b32, grid, dim3(256), 0, stream, static_cast<const uint32_t*>(in), ld_in,
-                       rows, static_cast<uint32_t*>(out), ld_out, n_rows_static, n_scored, chunk_start,
-                       chunk_rows, n_cols, out_cols_pad);
-  }
+void launch_transpose_f32(const void* in, int64_t ld_in, const int32_t* rows, void* out, int64_t ld_out,
+                          int64_t n_rows_static, const int64_t* n_scored, int64_t chunk_start, int chunk_rows,
+                          int n_cols, int64_t out_cols_pad, hipStream_t stream) {
+  dim3 grid((n_cols + 31) / 32, (unsigned)((out_cols_pad + 31) / 32));
+  hipLaunchKernelGGL(k_transpose_b32, grid, dim3(256), 0, stream, static_cast<const uint32_t*>(in), ld_in,
+                     rows, static_cast<uint32_t*>(out), ld_out, n_rows_static, n_scored, chunk_start,
+                     chunk_rows, n_cols, out_cols_pad);
 }
 
 void launch_finalize(const double* loss_partials, int64_t n_blocks, const int64_t* n_scored,

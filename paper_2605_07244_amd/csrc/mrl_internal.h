@@ -106,18 +106,11 @@ struct PrepOut {
   int64_t* n_bad;       // [1] masked-in slots with a target outside [0, V)
   int32_t* block_counts; // scratch: per 1024-slot block a scored count and a bad-target count (int32),
                          // followed, 8-byte aligned, by the blocks' exclusive offsets (int64)
+  float* zero[3];       // per-slot outputs that unscored slots set to 0 (or nullptr)
+  int64_t B; int T; int32_t* seq_len;   // scored slots (valid targets only) per sequence of T slots, if not nullptr
 };
 void launch_prep(const uint8_t* mask, const int32_t* targets, int64_t N, int V, const PrepOut& o,
                  hipStream_t stream);
-
-// Per-sequence scored length (valid targets only) and loss weights.
-// seq_coef[b] = 1 / (P K_g L_b) for GRPO rows, lambda / (S_aux L_b) for SGT rows
-// (sign and lambda folded so that g = seq_coef * (...)), 0 for empty rows.
-void launch_seq_weights(const uint8_t* mask, const int32_t* targets, const int32_t* group_id,
-                        const uint8_t* seq_kind, int64_t B, int T, int G, int V, int loss_agg,
-                        int32_t* seq_len, float* seq_coef, int32_t* group_count /*[G] scratch*/,
-                        int64_t* n_bad_groups /*[1]: sequences whose group id is outside [0, G)*/,
-                        hipStream_t stream);
 
 // Response-level log-ratio (App. I.1): seq_expo[b] = sum over the scored tokens of sequence b of
 // (logp - behav_logp), divided by the number of scored tokens when level == 2.  Fixed-order
@@ -126,15 +119,22 @@ void launch_seq_log_ratio(const uint8_t* mask, const int32_t* targets, const flo
                           const float* behav_logp, int64_t B, int T, int V, int level, float* seq_expo,
                           hipStream_t stream);
 
-// Zero out_logp (and out_lse, dH rows) of unscored slots.
-void launch_zero_unscored(const uint8_t* mask, const int32_t* targets, int64_t N, int V, int d,
-                          float* out_logp, float* out_lse, void* dH, int dh_elem_bytes,
-                          hipStream_t stream);
-
-// Target logit z_t[i] = <H[row_index[i]], W[target]> for compacted rows (fp32 accumulate).
-void launch_target_logit(const void* H, const void* W, const int32_t* targets,
-                         const int32_t* row_index, const int64_t* n_scored, int64_t N_max,
-                         int d, int is_bf16, float* zt, hipStream_t stream);
+// Before a pass's forward launch: target logit z_t[i] = <H[row_index[i]], W[target]> of its rows (fp32
+// accumulate) and, on the bf16 path, their copies Hc[r][0:dp] = H[row][0:d] | 0 (16-byte vectors: d,
+// dp, ldh multiples of 8).  With the first pass of a loss call also the zero dH rows of unscored
+// slots (dH != nullptr) and the sequence weights (seq_coef != nullptr): seq_coef[b] = 1 / (P K_g L_b)
+// for GRPO rows, 1 / (S_aux L_b) for SGT rows, 0 for empty rows.
+struct RowPrepArgs {
+  const void* H; const void* W; const int32_t* targets; const int32_t* row_index; const int64_t* n_scored;
+  int64_t chunk_start; int chunk_rows; int d;
+  void* Hc; int64_t ldh; int dp;
+  float* zt;
+  const uint8_t* mask; int64_t N; int V; void* dH; int64_t dh_row_bytes; int64_t zero_blocks /*set by the launcher*/;
+  const int32_t* seq_len; const int32_t* group_id; const uint8_t* seq_kind; int64_t B; int G; int loss_agg;
+  int32_t* group_count /*[G] scratch*/; float* seq_coef;
+  int64_t* n_bad_groups /*[1]: sequences whose group id is outside [0, G)*/;
+};
+void launch_row_prep(RowPrepArgs a, int is_bf16, hipStream_t stream);
 
 // fp32 path: (max, sum-exp[, sum exp * z]) of each row of Z [rows, V] -> one partial per row.
 void launch_row_lse_f32(const float* Z, int64_t ldz, const int64_t* n_scored, int64_t chunk_start,
@@ -171,25 +171,23 @@ void launch_convert_f32(float* ZP, int64_t ldz, float* Pt, int64_t ldpt, const f
                         const int64_t* n_scored, int64_t chunk_start, int chunk_rows, int V,
                         hipStream_t stream);
 
-// bf16 path: zeroes the stash rows from the pass's valid count up to its multiple of 128 (the dW
-// contraction runs over pairs of 64-row panels; the forward kernel writes valid rows only).
-void launch_zero_stash_tail(void* estash, int64_t lde, const int64_t* n_scored, int64_t chunk_start,
-                            int chunk_rows, int Vp, hipStream_t stream);
+// Out[r][0:dp] = In[r][0:d], zero in [d, dp), r < n_rows.  16-byte vectors: d, dp, both row strides
+// multiples of 8 elements.
+void launch_pad_rows_b16(const void* in, int64_t ld_in, void* out, int64_t ld_out, int64_t n_rows, int d, int dp,
+                         hipStream_t stream);
 
-// bf16 path: Out[r][0:dp] = In[rows[r]][0:d], zero in [d, dp) (rows == nullptr: identity), for
-// r < valid rows of the chunk (n_scored != nullptr) or r < n_rows_static.  16-byte vectors: d, dp,
-// both row strides multiples of 8 elements.
-void launch_gather_rows_b16(const void* in, int64_t ld_in, const int32_t* rows, void* out, int64_t ld_out,
-                            int64_t n_rows_static, const int64_t* n_scored, int64_t chunk_start,
-                            int chunk_rows, int d, int dp, hipStream_t stream);
+// bf16 path, operands of the dW launch: Ht[c][r] = scale[r] * Hc[r][c] (c < dp, a multiple of 64) for the
+// pass's valid rows, zeros up to their multiple of 128; the stash rows in between are cleared (the
+// dW contraction runs over pairs of 64-row panels; the forward kernel writes valid rows only).
+void launch_backward_rows_b16(const void* Hc, int64_t ldh, const float* scale, void* Ht, int64_t ldht,
+                              const int64_t* n_scored, int64_t chunk_start, int chunk_rows, int dp, void* E, int64_t lde,
+                              int Vp, hipStream_t stream);
 
-// Out[c][r] = scale[r] * In[rows[r]][c] (rows == nullptr: identity; scale == nullptr: 1, 2-byte
-// elements only) for r < n_rows_valid, zero beyond, r in [0, out_cols_pad), c in [0, n_cols).
-// Used for Ht (gathered, dynamic, scaled) and the fp32 path's Wt (static).
-void launch_transpose(const void* in, int64_t ld_in, const int32_t* rows, const float* scale, void* out, int64_t ld_out,
-                      int64_t n_rows_static, const int64_t* n_scored, int64_t chunk_start,
-                      int chunk_rows, int n_cols, int64_t out_cols_pad, int elem_bytes,
-                      hipStream_t stream);
+// fp32 path: Out[c][r] = In[rows[r]][c] (rows == nullptr: identity) for r < n_rows_valid, zero
+// beyond, r in [0, out_cols_pad), c in [0, n_cols): Wt (static) and Ht (gathered, dynamic).
+void launch_transpose_f32(const void* in, int64_t ld_in, const int32_t* rows, void* out, int64_t ld_out,
+                          int64_t n_rows_static, const int64_t* n_scored, int64_t chunk_start, int chunk_rows,
+                          int n_cols, int64_t out_cols_pad, hipStream_t stream);
 
 // Group-relative advantages (Sec. 3) with pooled / own statistics and SGT gate flags.
 void launch_group_advantages(const float* rewards, const int32_t* group_id, const uint8_t* in_stats,

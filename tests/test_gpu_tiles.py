@@ -88,3 +88,26 @@ def test_dh_tiles_and_slices(mrl, scored, d, V, dh_f32):
     assert torch.all(out["dH"][mask == 0] == 0)
     again, _, _ = _step(mrl, H, W, y, mask, mrl.F32 if dh_f32 else mrl.BF16, scored)
     assert torch.equal(out["dH"], again["dH"])
+
+
+@pytest.mark.parametrize("N", [1, 63, 1025, 32768, 32769, 4096 * 1024, 4096 * 1024 + 5])
+def test_compaction_paths(mrl, N):
+    """One block, several blocks that add up the counts themselves, and the scan launch (above 4096 blocks of 1024
+    slots); masked slots, target ids outside the vocabulary, zeros in every per-slot output of an unscored slot."""
+    d, V = 8, 64
+    g = torch.Generator("cuda").manual_seed(N)
+    H = torch.randn((N, d), device="cuda", generator=g).bfloat16()
+    W = torch.randn((V, d), device="cuda", generator=g).bfloat16()
+    y = torch.randint(-2, V + 2, (N,), device="cuda", generator=g, dtype=torch.int32)
+    mask = (torch.rand(N, device="cuda", generator=g) < 0.6).to(torch.uint8)
+    logp, lse, ent = mrl.token_scores(H, W, y, mask)
+    torch.cuda.synchronize()
+    ok = (mask == 1) & (y >= 0) & (y < V)
+    z = H[ok].double() @ W.double().t()
+    want_lse = torch.logsumexp(z, 1)
+    want = z.gather(1, y[ok].long()[:, None])[:, 0] - want_lse
+    want_ent = want_lse - (torch.softmax(z, 1) * z).sum(1)
+    for got, ref in ((logp, want), (lse, want_lse), (ent, want_ent)):
+        assert torch.all(got[~ok] == 0)
+        # fp32 outputs of logits below 40: half a unit in the last place is 2e-6
+        assert not ok.any() or float((got[ok].double() - ref).abs().max()) <= 2e-5
