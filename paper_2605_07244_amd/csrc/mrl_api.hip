@@ -103,14 +103,14 @@ void* static_scratch_ptr() {
 struct Layout {
   size_t total = 0;
   size_t counters, row_index, block_counts, zt, part_max, part_sum, part_ez;
-  size_t seq_len, seq_coef, seq_expo, group_count, lse_c, g_c, row_scale, loss_partials, Z, Pt, Ht, Wt = 0;
+  size_t seq_len, seq_coef, seq_expo, group_count, lse_c, g_c, row_scale, loss_partials, Z, Ht = 0;
   size_t tail = 0;             // bf16: partial tiles of the dH and dW launches' K-split tails
   int tail_items = 0;          // ... how many
   size_t Hc = 0, Wp = 0;       // bf16: the pass's token rows, gathered and zero-padded to dp columns; W padded likewise (only if dp != d)
   int dp = 0;                  // bf16: d rounded up to the 128-wide panel pairs of the GEMM kernels
   int64_t ldh = 0;             // row stride of Hc and Wp
   int chunk_rows = 0, n_partials = 0;
-  int64_t n_chunks = 0, Vp = 0, ldz = 0, ldr = 0;   // ldz: row stride of the stash (Z; and of the fp32 path's Wt), ldr: of Ht (and the fp32 path's Pt)
+  int64_t n_chunks = 0, Vp = 0, ldz = 0, ldr = 0;   // ldz: row stride of the stash (Z), ldr: of Ht
   int64_t epi_blocks_total = 0;
 };
 
@@ -143,7 +143,7 @@ Layout make_layout(int64_t N, int64_t B, int d, int V, int dtype, int chunk_rows
   L.part_max = bf16 ? 0 : take(off, (size_t)L.n_partials * chunk_rows * 4);   // fp32 path only
   L.part_sum = take(off, (size_t)L.n_partials * chunk_rows * 4);
   L.part_ez = entropy ? take(off, (size_t)L.n_partials * chunk_rows * 4) : 0;
-  const int dk = bf16 ? (int)round_up(d, 128) : d;   // rows of Ht / Wt
+  const int dk = bf16 ? (int)round_up(d, 128) : d;   // rows of Ht
   if (bf16) {
     L.dp = dk;
     L.ldh = L.dp + 64;
@@ -160,8 +160,7 @@ Layout make_layout(int64_t N, int64_t B, int d, int V, int dtype, int chunk_rows
     L.row_scale = bf16 ? take(off, (size_t)(N + 1) * 4) : 0;
     L.loss_partials = take(off, (size_t)(L.epi_blocks_total + 1) * 10 * 8);
     L.Z = take(off, (size_t)chunk_rows * L.ldz * es);
-    L.Pt = bf16 ? 0 : take(off, (size_t)L.Vp * L.ldr * es);   // fp32 path only: the bf16 dW GEMM reads P itself
-    L.Ht = take(off, (size_t)dk * L.ldr * es);
+    if (bf16) L.Ht = take(off, (size_t)dk * L.ldr * es);
     if (bf16) {
       // 256 partial tiles for the dW launch; the dH launch's last round of up to 255 tiles can use up
       // to four per compute unit; a quarter of the size of the head, which has the longer tiles the larger it
@@ -169,8 +168,6 @@ Layout make_layout(int64_t N, int64_t B, int d, int V, int dtype, int chunk_rows
       const size_t extra = (size_t)dk * L.ldz * es / 4 / gemm_tail_tile_bytes();
       L.tail_items = gemm_dw_tail_items() + (int)(extra < 768 ? extra : 768);
       L.tail = take(off, L.tail_items * gemm_tail_tile_bytes());
-    } else {
-      L.Wt = take(off, (size_t)dk * L.ldz * es);         // fp32 path only: the bf16 dH GEMM reads W itself
     }
   } else if (!bf16) {
     L.Z = take(off, (size_t)chunk_rows * L.ldz * es);
@@ -512,10 +509,6 @@ int mrl_grpo_loss_fwd_bwd(const void* hidden, const void* lm_head_w, const int32
     if (counters[1] != 0) return MRL_ERR_TARGET_RANGE;
     if (counters[2] != 0) return MRL_ERR_GROUP_RANGE;
   }
-  if (out_dH && !bf16) {
-    Scope sc(MRL_PROF_CONVERT, s);
-    launch_transpose_f32(lm_head_w, d, nullptr, at<void>(ws, L.Wt), L.ldz, V, nullptr, 0, 0, d, L.Vp, s);
-  }
   if (cfg->ratio_level != 0) {
     // Response-level ratio: a response may span several passes, so the log-probs of all rows are
     // computed first, then summed per response; the main loop below recomputes them (same bits) on
@@ -573,11 +566,8 @@ int mrl_grpo_loss_fwd_bwd(const void* hidden, const void* lm_head_w, const int32
           launch_backward_rows_b16(at<void>(ws, L.Hc), L.ldh, at<float>(ws, L.row_scale) + c0, at<void>(ws, L.Ht), L.ldr,
                                    n_scored, c0, L.chunk_rows, L.dp, at<void>(ws, L.Z), L.ldz, (int)L.Vp, s);
       } else {
-        launch_convert_f32(at<float>(ws, L.Z), L.ldz, at<float>(ws, L.Pt), L.ldr, at<float>(ws, L.lse_c),
-                           at<float>(ws, L.g_c), target_ids, row_index, n_scored, c0, L.chunk_rows, V, s);
-        if (out_dW)
-          launch_transpose_f32(hidden, d, row_index + c0, at<void>(ws, L.Ht), L.ldr, 0, n_scored, c0, L.chunk_rows, d,
-                               L.chunk_rows, s);
+        launch_convert_f32(at<float>(ws, L.Z), L.ldz, at<float>(ws, L.lse_c), at<float>(ws, L.g_c), target_ids, row_index,
+                           n_scored, c0, L.chunk_rows, V, s);
       }
     }
     if (out_dH) {
@@ -588,8 +578,8 @@ int mrl_grpo_loss_fwd_bwd(const void* hidden, const void* lm_head_w, const int32
                             at<float>(ws, L.tail), L.tail_items, s);
       } else {
         GemmF32Args g = {};
-        g.A = at<float>(ws, L.Z); g.lda = L.ldz; g.a_rows = nullptr;
-        g.B = at<float>(ws, L.Wt); g.ldb = L.ldz;
+        g.A = at<float>(ws, L.Z); g.lda = L.ldz;
+        g.B = static_cast<const float*>(lm_head_w); g.ldb = d; g.b_kmajor = 1;
         g.C = static_cast<float*>(out_dH); g.ldc = d; g.c_rows = row_index + c0;
         g.M = L.chunk_rows; g.N = d; g.K = V;
         g.n_scored = n_scored; g.chunk_start = c0; g.chunk_rows = L.chunk_rows;
@@ -605,8 +595,8 @@ int mrl_grpo_loss_fwd_bwd(const void* hidden, const void* lm_head_w, const int32
                             L.chunk_rows, V, d, out_dW, overwrite, at<float>(ws, L.tail), s);
       } else {
         GemmF32Args g = {};
-        g.A = at<float>(ws, L.Pt); g.lda = L.ldr; g.a_rows = nullptr;
-        g.B = at<float>(ws, L.Ht); g.ldb = L.ldr;
+        g.A = at<float>(ws, L.Z); g.lda = L.ldz; g.a_kmajor = 1;
+        g.B = static_cast<const float*>(hidden); g.ldb = d; g.b_rows = row_index + c0; g.b_kmajor = 1;
         g.C = out_dW; g.ldc = d; g.c_rows = nullptr;
         g.M = V; g.N = d; g.K = L.chunk_rows;
         g.n_scored = n_scored; g.chunk_start = c0; g.chunk_rows = L.chunk_rows;

@@ -1,6 +1,6 @@
 // Memory-bound kernels of the scoring path: mask compaction, sequence weights,
 // target logits, partial-merge + token-loss epilogue (Eq. 1 / Eq. 2 terms), operand
-// transposes, the fp32 path's logits -> dz conversion, final reductions.
+// preparation, the fp32 path's logits -> dz conversion, final reductions.
 #include "mrl_internal.h"
 
 namespace mrl {
@@ -686,8 +686,7 @@ __global__ __launch_bounds__(FIN_THREADS) void k_finalize(const double* parts, i
 // dz conversion of the fp32 path (proof of Prop. 4: grad log pi(a_i) = e_i - pi).
 // ----------------------------------------------------------------------------
 // fp32 path: scalar, bounds-checked.
-__global__ __launch_bounds__(256) void k_convert_f32(float* ZP, int64_t ldz, float* Pt, int64_t ldpt,
-                                                     const float* lse_c, const float* g_c,
+__global__ __launch_bounds__(256) void k_convert_f32(float* ZP, int64_t ldz, const float* lse_c, const float* g_c,
                                                      const int32_t* targets, const int32_t* row_index,
                                                      const int64_t* n_scored, int64_t chunk_start,
                                                      int chunk_rows, int V) {
@@ -699,9 +698,7 @@ __global__ __launch_bounds__(256) void k_convert_f32(float* ZP, int64_t ldz, flo
   const int y = targets[row_index[ci]];
   for (int v = blockIdx.x * 256 + threadIdx.x; v < V; v += gridDim.x * 256) {
     const float p = expf(ZP[(int64_t)i * ldz + v] - lse);
-    const float val = g * ((v == y ? 1.f : 0.f) - p);
-    ZP[(int64_t)i * ldz + v] = val;
-    Pt[(int64_t)v * ldpt + i] = val;
+    ZP[(int64_t)i * ldz + v] = g * ((v == y ? 1.f : 0.f) - p);
   }
 }
 
@@ -724,9 +721,6 @@ __global__ __launch_bounds__(256) void k_pad_rows_b16(const uint16_t* in, int64_
   }
 }
 
-// ----------------------------------------------------------------------------
-// Transposes.
-// ----------------------------------------------------------------------------
 // Backward operand of the dW launch, bf16: Ht[c][r] = scale[r] * Hc[r][c] for the pass's valid
 // rows, zeros up to the multiple of 128 the contraction runs over.  Tile 64 rows x 64 cols; n_cols a
 // multiple of 64, 16-byte aligned rows on both sides.  The blocks behind the tiles clear the stash
@@ -787,35 +781,6 @@ __global__ __launch_bounds__(256) void k_backward_rows_b16(const uint16_t* in, i
   }
 }
 
-// fp32 path: Out[c][r] = In[rows[r]][c], scalar, bounds-checked: tile 32 x 32.
-__global__ __launch_bounds__(256) void k_transpose_b32(const uint32_t* in, int64_t ld_in, const int32_t* rows,
-                                                       uint32_t* out, int64_t ld_out, int64_t n_rows_static,
-                                                       const int64_t* n_scored, int64_t chunk_start,
-                                                       int chunk_rows, int n_cols, int64_t out_cols_pad) {
-  __shared__ uint32_t tile[32][33];
-  int64_t nrows = n_rows_static;
-  if (n_scored != nullptr) nrows = valid_rows(n_scored, chunk_start, chunk_rows);
-  const int64_t r0 = (int64_t)blockIdx.y * 32;
-  const int c0 = blockIdx.x * 32;
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-  for (int k = ty; k < 32; k += 8) {
-    const int64_t r = r0 + k;
-    const int c = c0 + tx;
-    uint32_t v = 0;
-    if (r < nrows && c < n_cols) {
-      const int64_t src_row = rows ? (int64_t)rows[r] : r;
-      v = in[src_row * ld_in + c];
-    }
-    tile[k][tx] = v;
-  }
-  __syncthreads();
-  for (int k = ty; k < 32; k += 8) {
-    const int c = c0 + k;
-    const int64_t r = r0 + tx;
-    if (c < n_cols && r < out_cols_pad) out[(int64_t)c * ld_out + r] = tile[tx][k];
-  }
-}
-
 }  // namespace
 
 // ------------------------------------------------------------------ launchers
@@ -867,13 +832,13 @@ void launch_row_epilogue(const RowEpiArgs& a, hipStream_t stream) {
   hipLaunchKernelGGL(k_row_epilogue, dim3(row_epilogue_blocks(a.chunk_rows)), dim3(EPI_THREADS), 0, stream, a);
 }
 
-void launch_convert_f32(float* ZP, int64_t ldz, float* Pt, int64_t ldpt, const float* lse_c,
+void launch_convert_f32(float* ZP, int64_t ldz, const float* lse_c,
                         const float* g_c, const int32_t* targets, const int32_t* row_index,
                         const int64_t* n_scored, int64_t chunk_start, int chunk_rows, int V,
                         hipStream_t stream) {
   int gx = (V + 255) / 256; gx = gx > 64 ? 64 : gx;
   dim3 grid(gx, chunk_rows);
-  hipLaunchKernelGGL(k_convert_f32, grid, dim3(256), 0, stream, ZP, ldz, Pt, ldpt, lse_c, g_c, targets,
+  hipLaunchKernelGGL(k_convert_f32, grid, dim3(256), 0, stream, ZP, ldz, lse_c, g_c, targets,
                      row_index, n_scored, chunk_start, chunk_rows, V);
 }
 
@@ -890,15 +855,6 @@ void launch_backward_rows_b16(const void* Hc, int64_t ldh, const float* scale, v
   hipLaunchKernelGGL(k_backward_rows_b16, dim3(dp / 64, (unsigned)(row_tiles + 127)), dim3(256), 0, stream,
                      static_cast<const uint16_t*>(Hc), ldh, scale, static_cast<uint16_t*>(Ht), ldht, n_scored,
                      chunk_start, chunk_rows, row_tiles, static_cast<uint16_t*>(E), lde, Vp);
-}
-
-void launch_transpose_f32(const void* in, int64_t ld_in, const int32_t* rows, void* out, int64_t ld_out,
-                          int64_t n_rows_static, const int64_t* n_scored, int64_t chunk_start, int chunk_rows,
-                          int n_cols, int64_t out_cols_pad, hipStream_t stream) {
-  dim3 grid((n_cols + 31) / 32, (unsigned)((out_cols_pad + 31) / 32));
-  hipLaunchKernelGGL(k_transpose_b32, grid, dim3(256), 0, stream, static_cast<const uint32_t*>(in), ld_in,
-                     rows, static_cast<uint32_t*>(out), ld_out, n_rows_static, n_scored, chunk_start,
-                     chunk_rows, n_cols, out_cols_pad);
 }
 
 void launch_finalize(const double* loss_partials, int64_t n_blocks, const int64_t* n_scored,

@@ -84,18 +84,20 @@ void launch_gemm_dw_bf16(const void* P, int64_t ldp, const void* Ht, int64_t ldh
                          const int64_t* n_scored, int64_t chunk_start, int chunk_rows,
                          int V, int d, float* dW, int overwrite, float* tail_part, hipStream_t stream);
 
-// ---- fp32 plain GEMM (sanity path): C[m][n] = sum_k A[m][k] * B[n][k] --------
-// a_rows / c_rows: optional row maps (index arrays already offset to the chunk);
-// m_valid is computed on the device from n_scored when m_dynamic != 0, and
-// k_valid likewise when k_dynamic != 0.
+// ---- fp32 GEMM (small-shape path): C[m][n] = sum_k A[m][k] * B[n][k] --------
+// An operand is k-contiguous (element (row, k) at row * ld + k) or, with its kmajor flag, stored with
+// k as the row (at k * ld + row).  a_rows / b_rows: optional maps of the operand's stored rows, c_rows
+// of the output's (index arrays already offset to the chunk).  Supported: neither k-major, B, both.
+// M is computed on the device from n_scored when m_dynamic != 0, K likewise when k_dynamic != 0.
 struct GemmF32Args {
-  const float* A; int64_t lda; const int32_t* a_rows;
-  const float* B; int64_t ldb;
+  const float* A; int64_t lda; const int32_t* a_rows; int a_kmajor;
+  const float* B; int64_t ldb; const int32_t* b_rows; int b_kmajor;
   float* C; int64_t ldc; const int32_t* c_rows;
   int M, N, K;
   const int64_t* n_scored; int64_t chunk_start; int chunk_rows;
   int m_dynamic, k_dynamic;
   int accumulate;
+  int m_on_x;   // set by the launcher
 };
 void launch_gemm_f32(const GemmF32Args& a, hipStream_t stream);
 
@@ -164,9 +166,8 @@ struct RowEpiArgs {
 int row_epilogue_blocks(int chunk_rows);
 void launch_row_epilogue(const RowEpiArgs& a, hipStream_t stream);
 
-// fp32 path, dz conversion: reads the chunk's float logits, writes P[i][v] = g_i (1[v = y_i] -
-// exp(z - lse_i)) in place and its transpose Pt[v][i].
-void launch_convert_f32(float* ZP, int64_t ldz, float* Pt, int64_t ldpt, const float* lse_c,
+// fp32 path, dz conversion: P[i][v] = g_i (1[v = y_i] - exp(z - lse_i)) in place of the chunk's logits.
+void launch_convert_f32(float* ZP, int64_t ldz, const float* lse_c,
                         const float* g_c, const int32_t* targets, const int32_t* row_index,
                         const int64_t* n_scored, int64_t chunk_start, int chunk_rows, int V,
                         hipStream_t stream);
@@ -182,12 +183,6 @@ void launch_pad_rows_b16(const void* in, int64_t ld_in, void* out, int64_t ld_ou
 void launch_backward_rows_b16(const void* Hc, int64_t ldh, const float* scale, void* Ht, int64_t ldht,
                               const int64_t* n_scored, int64_t chunk_start, int chunk_rows, int dp, void* E, int64_t lde,
                               int Vp, hipStream_t stream);
-
-// fp32 path: Out[c][r] = In[rows[r]][c] (rows == nullptr: identity) for r < n_rows_valid, zero
-// beyond, r in [0, out_cols_pad), c in [0, n_cols): Wt (static) and Ht (gathered, dynamic).
-void launch_transpose_f32(const void* in, int64_t ld_in, const int32_t* rows, void* out, int64_t ld_out,
-                          int64_t n_rows_static, const int64_t* n_scored, int64_t chunk_start, int chunk_rows,
-                          int n_cols, int64_t out_cols_pad, hipStream_t stream);
 
 // Group-relative advantages (Sec. 3) with pooled / own statistics and SGT gate flags.
 void launch_group_advantages(const float* rewards, const int32_t* group_id, const uint8_t* in_stats,

@@ -111,3 +111,24 @@ def test_compaction_paths(mrl, N):
         assert torch.all(got[~ok] == 0)
         # fp32 outputs of logits below 40: half a unit in the last place is 2e-6
         assert not ok.any() or float((got[ok].double() - ref).abs().max()) <= 2e-5
+
+
+@pytest.mark.parametrize("N,d,V", [(1, 1, 3), (17, 3, 33), (40, 5, 16), (100, 64, 512), (530, 66, 515), (600, 71, 1000)])
+def test_fp32_tiles_and_odd_widths(mrl, N, d, V):
+    """fp32 products: K below, at and beside a multiple of 4 and of the 16-wide step, single tiles and the 32 x 32 tile's
+    range (530 x 515 and 600 x 1000 outputs), ragged edges on every side."""
+    g = torch.Generator("cuda").manual_seed(d)
+    H = torch.randn((N, d), device="cuda", generator=g)
+    W = 0.2 * torch.randn((V, d), device="cuda", generator=g)
+    y = torch.randint(0, V, (N,), device="cuda", generator=g, dtype=torch.int32)
+    mask = (torch.rand(N, device="cuda", generator=g) < 0.9).to(torch.uint8)
+    mask[0] = 1
+    out, dH, dW = _step(mrl, H, W, y, mask, mrl.F32, 5)
+    ok = mask == 1
+    z = H[ok].double() @ W.double().t()
+    want = z.gather(1, y[ok].long()[:, None])[:, 0] - torch.logsumexp(z, 1)
+    # at most 1000 fp32 terms per sum: sqrt(1000) * 2^-24 relative, a hundred times below the bars
+    assert float((out["logp"][ok].double() - want).abs().max()) <= util.F32_LOGP_TOL
+    for name, got, ref in (("dH", out["dH"], dH), ("dW", out["dW"], dW)):
+        assert util.rel_fro(util.to_f64(got), ref) <= 1e-5 or np.linalg.norm(ref) < 1e-12, name
+    assert torch.all(out["dH"][~ok] == 0)
