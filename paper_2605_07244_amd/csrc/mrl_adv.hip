@@ -1,8 +1,8 @@
 // Group-relative advantages (Sec. 3), pool-wide (Sec. 5.1) and pooled-baseline
 // (App. I.1) variants, and the SGT gate flags (Sec. 5.3 / App. B).
 //
-// One wavefront per group scans all B entries (B is a few thousand: the whole
-// input is a few KB and stays in L2), so group members need not be contiguous
+// One wavefront per group finds its members among all B entries (B is a few thousand:
+// the whole input is a few KB and stays in L2), so group members need not be contiguous
 // and every sum has a fixed order: lane-strided partial sums in fp64, then a
 // fixed butterfly.  Mean and variance are taken in two passes so that binary
 // rewards give exact zeros for all-equal groups.
@@ -30,22 +30,59 @@ struct AdvArgs {
   float* out_adv; float* out_mean; float* out_std; uint8_t* out_flags;
 };
 
-__global__ __launch_bounds__(256) void k_group_adv(AdvArgs a) {
+// The entries of the wave's group among b = lane, lane + 64, ...: up to 64 steps of the wave are
+// remembered as a bit mask, so that a batch of up to kRemembered entries is scanned once (all group
+// ids loaded independently of each other) and the three passes touch the group's own entries only;
+// larger batches are scanned in every pass.  1024 entries, 128 groups: 1.5 + 9.6 us in two launches, 5.7 us now.
+constexpr int64_t kRemembered = 64 * 64;
+struct Members {
+  const int32_t* group_id; int64_t B; int g; uint64_t bits; bool remembered;
+  __device__ Members(const int32_t* ids, int64_t n, int group, int lane) : group_id(ids), B(n), g(group), bits(0), remembered(n <= kRemembered) {
+    if (!remembered) return;
+    const int n32 = (int)n;
+    for (int s0 = 0; s0 * 64 < n32; s0 += 16) {
+      int id[16];
+#pragma unroll
+      for (int k = 0; k < 16; ++k) {
+        const int b = (s0 + k) * 64 + lane;
+        id[k] = b < n32 ? ids[b] : -1;
+      }
+#pragma unroll
+      for (int k = 0; k < 16; ++k) bits |= (uint64_t)(id[k] == group) << ((s0 + k) & 63);
+    }
+  }
+  template <class F> __device__ void each(int lane, F f) const {   // in ascending order
+    if (remembered) {
+      for (uint64_t m = bits; m != 0; m &= m - 1) f((int64_t)__builtin_ctzll(m) * 64 + lane);
+    } else {
+      for (int64_t b = lane; b < B; b += 64) if (group_id[b] == g) f(b);
+    }
+  }
+};
+
+// Blocks below group_blocks: one wave per group.  The blocks behind them clear the entries whose group
+// id is outside [0, G), which no wave owns.
+__global__ __launch_bounds__(256) void k_group_adv(AdvArgs a, int group_blocks) {
+  if ((int)blockIdx.x >= group_blocks) {
+    const int64_t b = (int64_t)(blockIdx.x - group_blocks) * 256 + threadIdx.x;
+    if (b < a.B && (a.group_id[b] < 0 || a.group_id[b] >= a.G)) a.out_adv[b] = 0.f;
+    return;
+  }
   const int g = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (g >= a.G) return;
   const int lane = threadIdx.x & 63;
+  const Members members(a.group_id, a.B, g, lane);
   // pass 1: counts, sums, gate predicates
   double sum_p = 0.0, sum_o = 0.0;
   int cnt_p = 0, cnt_o = 0, n_own = 0, own_not_fail = 0, peer_succ = 0;
-  for (int64_t b = lane; b < a.B; b += 64) {
-    if (a.group_id[b] != g) continue;
+  members.each(lane, [&](int64_t b) {
     const float r = a.rewards[b];
     const bool st = a.in_stats == nullptr || a.in_stats[b] != 0;
     const bool own = a.is_own == nullptr || a.is_own[b] != 0;
     if (st) { sum_p += (double)r; cnt_p++; if (own) { sum_o += (double)r; cnt_o++; } }
     if (own) { n_own++; own_not_fail += !(r < a.neg_thresh); }
     else peer_succ += (r > a.pos_thresh);
-  }
+  });
   sum_p = wave_sum(sum_p); sum_o = wave_sum(sum_o);
   cnt_p = wave_sum_i(cnt_p); cnt_o = wave_sum_i(cnt_o);
   n_own = wave_sum_i(n_own); own_not_fail = wave_sum_i(own_not_fail); peer_succ = wave_sum_i(peer_succ);
@@ -53,15 +90,14 @@ __global__ __launch_bounds__(256) void k_group_adv(AdvArgs a) {
   const double mu_o = cnt_o > 0 ? sum_o / cnt_o : 0.0;
   // pass 2: squared deviations
   double sq_p = 0.0, sq_o = 0.0;
-  for (int64_t b = lane; b < a.B; b += 64) {
-    if (a.group_id[b] != g) continue;
+  members.each(lane, [&](int64_t b) {
     const bool st = a.in_stats == nullptr || a.in_stats[b] != 0;
-    if (!st) continue;
+    if (!st) return;
     const bool own = a.is_own == nullptr || a.is_own[b] != 0;
     const double r = (double)a.rewards[b];
     sq_p += (r - mu_p) * (r - mu_p);
     if (own) sq_o += (r - mu_o) * (r - mu_o);
-  }
+  });
   sq_p = wave_sum(sq_p); sq_o = wave_sum(sq_o);
   const double sd_p = cnt_p - a.ddof > 0 ? sqrt(sq_p / (cnt_p - a.ddof)) : 0.0;
   const double sd_o = cnt_o - a.ddof > 0 ? sqrt(sq_o / (cnt_o - a.ddof)) : 0.0;
@@ -71,8 +107,7 @@ __global__ __launch_bounds__(256) void k_group_adv(AdvArgs a) {
   // perturbed-baseline control (App. C.4): the shift moves the baseline, not the std
   const double shift = a.baseline_shift != nullptr ? (double)a.baseline_shift[g] : 0.0;
   const double bl_p = mu_p + shift, bl_o = mu_o + shift;
-  for (int64_t b = lane; b < a.B; b += 64) {
-    if (a.group_id[b] != g) continue;
+  members.each(lane, [&](int64_t b) {
     const bool sc = a.scored == nullptr || a.scored[b] != 0;
     double adv = 0.0;
     if (sc) {
@@ -86,7 +121,7 @@ __global__ __launch_bounds__(256) void k_group_adv(AdvArgs a) {
       }
     }
     a.out_adv[b] = (float)adv;
-  }
+  });
   if (lane == 0) {
     if (a.out_mean) a.out_mean[g] = (float)mu_p;
     if (a.out_std) a.out_std[g] = (float)sd_p;
@@ -98,50 +133,42 @@ __global__ __launch_bounds__(256) void k_group_adv(AdvArgs a) {
   }
 }
 
-// entries whose group id is outside [0, G) are owned by no wavefront: clear them first
-__global__ __launch_bounds__(256) void k_adv_clear_orphans(const int32_t* group_id, int64_t B, int G,
-                                                           float* out_adv) {
-  const int64_t b = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (b < B && (group_id[b] < 0 || group_id[b] >= G)) out_adv[b] = 0.f;
-}
-
 // batch normalisation (App. A): divide the group-centred advantages of scored,
 // in-range entries by their std over the batch (+ eps); single block, fixed order.
 __global__ __launch_bounds__(1024) void k_adv_batch_scale(const int32_t* group_id, const uint8_t* scored,
                                                          int64_t B, int G, float eps_norm, int ddof,
                                                          float* adv) {
-  __shared__ double sh[1024];
-  __shared__ long long shc[1024];
-  __shared__ double mean_s, sd_s;
-  double s = 0.0; long long c = 0;
+  __shared__ double sh[16];
+  __shared__ int shc[16];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  double s = 0.0;
+  int c = 0;
   for (int64_t b = threadIdx.x; b < B; b += 1024) {
     const bool sc = (scored == nullptr || scored[b] != 0) && group_id[b] >= 0 && group_id[b] < G;
     if (sc) { s += (double)adv[b]; c++; }
   }
-  sh[threadIdx.x] = s; shc[threadIdx.x] = c;
+  s = wave_sum(s);
+  c = wave_sum_i(c);                                  // (B is at most 2^30)
+  if (lane == 0) { sh[wave] = s; shc[wave] = c; }
   __syncthreads();
-  for (int off = 512; off > 0; off >>= 1) {
-    if (threadIdx.x < off) { sh[threadIdx.x] += sh[threadIdx.x + off]; shc[threadIdx.x] += shc[threadIdx.x + off]; }
-    __syncthreads();
-  }
-  const long long cnt = shc[0];
-  if (threadIdx.x == 0) mean_s = cnt > 0 ? sh[0] / (double)cnt : 0.0;
-  __syncthreads();
-  const double mu = mean_s;
+  double total = 0.0;
+  int cnt = 0;
+#pragma unroll
+  for (int w = 0; w < 16; ++w) { total += sh[w]; cnt += shc[w]; }
+  const double mu = cnt > 0 ? total / (double)cnt : 0.0;
   double q = 0.0;
   for (int64_t b = threadIdx.x; b < B; b += 1024) {
     const bool sc = (scored == nullptr || scored[b] != 0) && group_id[b] >= 0 && group_id[b] < G;
     if (sc) { const double dlt = (double)adv[b] - mu; q += dlt * dlt; }
   }
+  q = wave_sum(q);
   __syncthreads();
-  sh[threadIdx.x] = q;
+  if (lane == 0) sh[wave] = q;
   __syncthreads();
-  for (int off = 512; off > 0; off >>= 1) {
-    if (threadIdx.x < off) sh[threadIdx.x] += sh[threadIdx.x + off];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) sd_s = cnt - ddof > 0 ? sqrt(sh[0] / (double)(cnt - ddof)) : 0.0;
-  __syncthreads();
+  double sq = 0.0;
+#pragma unroll
+  for (int w = 0; w < 16; ++w) sq += sh[w];
+  const double sd_s = cnt - ddof > 0 ? sqrt(sq / (double)(cnt - ddof)) : 0.0;
   const double denom = sd_s + (double)eps_norm;
   for (int64_t b = threadIdx.x; b < B; b += 1024) {
     const bool sc = (scored == nullptr || scored[b] != 0) && group_id[b] >= 0 && group_id[b] < G;
@@ -158,9 +185,8 @@ void launch_group_advantages(const float* rewards, const int32_t* group_id, cons
                              uint8_t* out_flags, hipStream_t stream) {
   AdvArgs a = {rewards, group_id, in_stats, scored, is_own, baseline_shift, B, G, mode, eps_norm, ddof, mix_alpha,
                neg_thresh, pos_thresh, out_adv, out_mean, out_std, out_flags};
-  hipLaunchKernelGGL(k_adv_clear_orphans, dim3((unsigned)((B + 255) / 256)), dim3(256), 0, stream, group_id, B,
-                     G, out_adv);
-  hipLaunchKernelGGL(k_group_adv, dim3((G + 3) / 4), dim3(256), 0, stream, a);
+  const int group_blocks = (G + 3) / 4;
+  hipLaunchKernelGGL(k_group_adv, dim3((unsigned)(group_blocks + (B + 255) / 256)), dim3(256), 0, stream, a, group_blocks);
   if (mode == 2)
     hipLaunchKernelGGL(k_adv_batch_scale, dim3(1), dim3(1024), 0, stream, group_id, scored, B, G, eps_norm,
                        ddof, out_adv);
