@@ -32,3 +32,30 @@ def test_advantages_remembered_and_scanned(mrl, B, G, mode):
     # fp64 sums, one rounding to fp32 per value (two in mode 2)
     assert np.allclose(got[ok], a_o, rtol=3e-6, atol=1e-6)
     assert np.all(got[~ok] == 0) and np.all(got[sc == 0] == 0)
+
+
+@pytest.mark.parametrize("B,S_src,S_tgt,one_word", [(3, 1, 1, True), (5, 257, 700, True), (2, 8192, 8193, False), (2, 9100, 10000, False)])
+def test_alignment_segments_and_counts(mrl, B, S_src, S_tgt, one_word):
+    """Rows of several segments of 8192 positions, words of 1, 63, 64 and more target tokens, fixed-point rounding of
+    values over the whole range."""
+    from oracle import thl_oracle
+    from workloads import synth
+    b = synth.make_thl(B, S_src, S_tgt, seed=S_tgt)
+    if one_word:
+        cut = [1, 63, 64, 65, 640]                     # tokens of word 0 in row i, the rest are word 1
+        n = b["tgt_word_map"].shape[1]
+        for i in range(B):
+            b["src_word_map"][i] = torch.arange(S_src, device="cuda", dtype=torch.int32) % 2
+            b["tgt_word_map"][i] = (torch.arange(n, device="cuda") >= cut[i % 5]).int()
+        b["max_words"] = 2
+    g = torch.Generator("cuda").manual_seed(1)
+    b["src_logp"] = -torch.exp(12 * torch.randn(b["src_logp"].shape, device="cuda", generator=g)).clamp(max=2.0 ** 22)      # a word sums up to 257 of them: below 2^31
+    out, bad = mrl.thl_word_align(b["src_logp"], b["src_mask"], b["src_word_map"], b["src_map_len"], b["tgt_mask"],
+                                  b["tgt_word_map"], b["tgt_map_len"], b["max_words"])
+    torch.cuda.synchronize()
+    c = {k: (v.cpu().numpy() if isinstance(v, torch.Tensor) else v) for k, v in b.items()}
+    want = thl_oracle.word_align_logprobs(c["src_logp"].astype(np.float64), c["src_mask"], c["src_word_map"], c["src_map_len"],
+                                          c["tgt_mask"], c["tgt_word_map"], c["tgt_map_len"], -100.0)
+    # a word's sum is exact to 2^-33 per source token, the output rounded to fp32
+    assert np.all(np.abs(out.cpu().numpy() - want) <= 1e-6 + 2.0 ** -23 * np.abs(want))
+    assert int(bad.item()) == 0
