@@ -40,6 +40,7 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));   // 16-byte access, 4-byte alignment
 
 constexpr int BM = 256, BN = 256, BK = 64;
 constexpr int NTHREADS = 256;
@@ -530,7 +531,9 @@ __global__ __launch_bounds__(NTHREADS) void gemm_nt_bf16(Params p) {
     for (int g = 0; g < 8; ++g) {
 #pragma unroll
       for (int m = 0; m < 16; ++m) {
-        mfma16(acc[g][m >> 1], fax[g & 3][m & 1], fbx[set][m & 1][m >> 1]);
+        // (DW: operands swapped, the accumulator holds the transposed 16 x 16 block)
+        if (MODE == MODE_DW) mfma16(acc[g][m >> 1], fbx[set][m & 1][m >> 1], fax[g & 3][m & 1]);
+        else mfma16(acc[g][m >> 1], fax[g & 3][m & 1], fbx[set][m & 1][m >> 1]);
         side(g, m, set, st_cur, st_nxt, kt_nxt, slot_nxt, kt_load, slot_cur);
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -570,6 +573,7 @@ __global__ __launch_bounds__(NTHREADS) void gemm_nt_bf16(Params p) {
   // ---- epilogues.  Accumulator element (i, j, e) of this lane is
   //   row m = m0 + wm*128 + i*16 + 4*(lane>>4) + e      (FWD: the permuted row, see vrow below)
   //   col n = n0 + wn*128 + j*16 + (lane & 15)
+  // (DW: row m = m0 + wm*128 + i*16 + (lane & 15), col n = n0 + wn*128 + j*16 + 4*(lane>>4) + e)
   if (MODE == MODE_DH) __syncthreads();   // its staged epilogue reuses the panels' LDS
 
   if (MODE == MODE_FWD) {
@@ -713,10 +717,11 @@ __global__ __launch_bounds__(NTHREADS) void gemm_nt_bf16(Params p) {
   } else {
     const int lane = lane_now(), wave = wave_u;
     const int wm = wave >> 1, wn = wave & 1, frow = lane & 15, fq = lane >> 4;
-    const int mrow_base = m0 + wm * 128 + 4 * fq;
-    const int ncol_base = n0 + wn * 128 + frow;
-    // rows = vocabulary ids, cols = hidden index; fp32 accumulate into dW.  The old values of
-    // one 16-row band are fetched as a batch before any store, so their latencies overlap.
+    // rows = vocabulary ids, cols = hidden index; fp32 accumulate into dW.  With the operands swapped a
+    // lane holds four consecutive columns of a row, so that dW is read and written 16 bytes at a
+    // time (d is a multiple of 8; with 4-byte accesses the launch took 1128 instead of 1023 us for 512 rows,
+    // V = 151936, d = 4096, and 127 instead of 109 for V = 32000, d = 2048).  The old values of one 16-row band
+    // are fetched as a batch before any store, so their latencies overlap.
     // A K slice of a tail tile stores its partial tile as it is, [256][256] fp32, to the scratch
     // area instead (dw_tail_reduce adds the slices in their order): the same code with the
     // tile's own origin, row stride and bounds.
@@ -726,31 +731,26 @@ __global__ __launch_bounds__(NTHREADS) void gemm_nt_bf16(Params p) {
     const int v_org = tail ? m0 : 0, n_org = tail ? n0 : 0;
     const int v_end = tail ? m0 + BM : p.V, n_end = tail ? n0 + BN : p.d;
     const bool overwrite = tail || p.overwrite;
+    const int vbase = m0 + wm * 128 + frow, nbase = n0 + wn * 128 + 4 * fq;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      float old[8][4];
+      const int v = vbase + i * 16;
+      float* const row = dst + (int64_t)((v < v_end ? v : v_end - 1) - v_org) * ld - n_org;
+      f32x4 old[8];
       if (!overwrite) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int v = mrow_base + i * 16 + e;
-          const float* row = dst + (int64_t)((v < v_end ? v : v_end - 1) - v_org) * ld - n_org;
-#pragma unroll
-          for (int j = 0; j < 8; ++j) {
-            const int n = ncol_base + j * 16;
-            old[j][e] = row[n < n_end ? n : n_end - 1];
-          }
+        for (int j = 0; j < 8; ++j) {
+          const int n = nbase + j * 16;
+          old[j] = *reinterpret_cast<const f32x4_any*>(row + (n < n_end ? n : n_end - 4));
         }
       }
+      if (v < v_end) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int v = mrow_base + i * 16 + e;
-        if (v < v_end) {
-          float* row = dst + (int64_t)(v - v_org) * ld - n_org;
-#pragma unroll
-          for (int j = 0; j < 8; ++j) {
-            const int n = ncol_base + j * 16;
-            if (n < n_end) row[n] = overwrite ? acc[i][j][e] : old[j][e] + acc[i][j][e];
-          }
+        for (int j = 0; j < 8; ++j) {
+          const int n = nbase + j * 16;
+          f32x4 x = acc[i][j];
+          if (!overwrite) x = old[j] + x;
+          if (n < n_end) *reinterpret_cast<f32x4_any*>(row + n) = x;
         }
       }
     }
