@@ -200,11 +200,109 @@ __device__ inline float exp2_fast(float x) { return __builtin_amdgcn_exp2f(x); }
 __device__ __forceinline__ void mfma16(f32x4& c, const bf16x8& a, const bf16x8& b) {
   asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
 }
+// The last MFMA of a loop body whose accumulators the compiler may move behind the loop (it does, where
+// paths meet): the wait states before an ordinary read of the result are part of it.
+__device__ __forceinline__ void mfma16_then_wait(f32x4& c, const bf16x8& a, const bf16x8& b) {
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0\n\ts_nop 15\n\ts_nop 3" : "+a"(c) : "v"(a), "v"(b));
+}
 // Wait states between the last MFMAs of the K loop and the first ordinary read of their
 // results (the hazard checker of the compiler does not look into inline assembly).
 __device__ __forceinline__ void drain_mfma(f32x4 (&r)[8]) {
   asm volatile("s_nop 15\n\ts_nop 15"
                : "+a"(r[0]), "+a"(r[1]), "+a"(r[2]), "+a"(r[3]), "+a"(r[4]), "+a"(r[5]), "+a"(r[6]), "+a"(r[7]));
+}
+
+// Lane number as the code after the K loops takes it: recomputed there from the execution mask, so
+// that nothing lane-dependent has to stay alive (that is, be spilled to scratch memory) across the
+// loop, whose body owns every vector register.  A reload from scratch is a vector-memory load: the wait
+// for it would also wait for every store issued before it, and between the stores of the forward
+// epilogue that costs microseconds each time.
+__device__ __forceinline__ int lane_now() {
+  int l = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+  asm volatile("" : "+v"(l));   // opaque: what is derived from it is computed where it is used, not hoisted
+  return l;
+}
+
+// Forward epilogue of a wave's 128 x (16 NJ) sub-tile: vocabulary ids from m0 + 128 wm, token columns from
+// n0 + 16 NJ wn, partial sums with index pidx; accumulator element (i, j, e) of a lane is vocabulary
+// id vrow(i, e), token column ncol_base + 16 j.
+template <int NJ>
+__device__ __forceinline__ void forward_epilogue(const Params& p, f32x4 (&acc)[8][NJ], const unsigned char* zt_lds, int m0,
+                                                 int n0, int pidx, int wm, int wn, int N) {
+  const int lane = lane_now(), frow = lane & 15, fq = lane >> 4;
+  const int ncol_base = n0 + wn * (16 * NJ) + frow;
+      // rows = vocabulary ids, cols = token rows of the chunk.  Exponentials are taken relative to
+      // the row's offset c2 = z_target * log2(e) + margin (log2 domain), one offset for all
+      // vocabulary tiles of a row: e = 2^(z log2(e) - c2), clamped so that neither e nor any sum of
+      // it can overflow.  The sums over the wave's 128 vocabulary ids are this tile's partials; e
+      // itself, as bf16, is the backward pass's operand (dz = (-g / S)(e - S onehot)).
+      constexpr float LOG2E = 1.4426950408889634f;
+      const bool full = (m0 + wm * 128 + 128 <= p.V);
+          // vocabulary id of accumulator (i, e) of this lane
+      auto vrow = [&](int i, int e) {
+        return m0 + wm * 128 + 32 * (i >> 1) + 8 * fq + 4 * (i & 1) + e;
+      };
+      // The body is instantiated for full / ragged vocabulary tiles and with / without the entropy
+      // sums: both conditions are uniform, and left as run-time selects they cost four more
+      // instructions per logit (row id, compare, two selects) than the six the work needs
+      // (accumulator read, multiply-add, clamp, exponential, add, half a packed conversion).
+      auto body = [&](auto full_tile, auto with_ez) {
+        constexpr bool kFull = decltype(full_tile)::value, kEz = decltype(with_ez)::value;
+  #pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+          const int n = ncol_base + j * 16;
+          const bool live = n < N;
+          const float zt = *reinterpret_cast<const float*>(zt_lds + (wn * (NJ * 16) + frow + j * 16) * 4);
+          const float c2 = live ? fmaf(zt, LOG2E, kStashMargin2) : 0.f;
+          uint16_t* erow = p.estash + (int64_t)n * p.lde + m0 + wm * 128 + 8 * fq;
+          float s = 0.f, t = 0.f;
+  #pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            // accumulators 2q and 2q+1 hold 8 consecutive vocabulary ids of this lane
+            bf16x8 h;
+  #pragma unroll
+            for (int u = 0; u < 2; ++u)
+  #pragma unroll
+              for (int e = 0; e < 4; ++e) {
+                // (read where it is used: left to the compiler, the copies out of the accumulation
+                // registers are hoisted to the top of the epilogue and fill the register file)
+                float z;
+                asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(z) : "a"(acc[2 * q + u][j][e]));
+                float w = exp2_fast(fminf(fmaf(z, LOG2E, -c2), kStashClamp2));
+                if (!kFull) w = vrow(2 * q + u, e) < p.V ? w : 0.f;
+                s += w;
+                if (kEz) t = fmaf(w, z, t);     // for the entropy: sum e * z  (H = lse - E_p[z])
+                h[4 * u + e] = (__bf16)w;
+              }
+            if (p.estash != nullptr && live) {
+              // 16 bytes per lane, the four lanes of a token row side by side (64 bytes).  Streaming
+              // store (non-temporal, device scope): the stash is 5 GB per launch and is next read by
+              // the backward launches, so it should not displace operand panels from the L2 and the
+              // memory-side cache (2 % of the launch against a plain store).  Written in assembly
+              // for its cache policy bits; the two wait states after it are the ones the hardware
+              // needs before the data registers of a store wider than 8 bytes may be overwritten
+              // (the compiler inserts them for its own stores only).
+              asm volatile("global_store_dwordx4 %0, %1, off sc1 nt\n\ts_nop 1" :: "v"(erow + 32 * q), "v"(h) : "memory");
+            }
+          }
+          s += __shfl_xor(s, 16);
+          s += __shfl_xor(s, 32);
+          if (fq == 0 && live) p.part_sum[(int64_t)pidx * p.part_stride + n] = s;
+          if (kEz) {
+            t += __shfl_xor(t, 16);
+            t += __shfl_xor(t, 32);
+            if (fq == 0 && live) p.part_ez[(int64_t)pidx * p.part_stride + n] = t;
+          }
+          // one column block at a time: interleaving them runs the register allocator out of
+          // registers, and its reloads from scratch wait for the stores issued so far
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      };
+      if (full) {
+        if (p.part_ez != nullptr) body(Flag<true>{}, Flag<true>{}); else body(Flag<true>{}, Flag<false>{});
+      } else {
+        if (p.part_ez != nullptr) body(Flag<false>{}, Flag<true>{}); else body(Flag<false>{}, Flag<false>{});
+      }
 }
 
 template <int MODE>
@@ -214,18 +312,7 @@ __global__ __launch_bounds__(NTHREADS) void gemm_nt_bf16(Params p) {
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;
-  // Lane and wave number as the code after the K loop takes them: recomputed there from the
-  // execution mask and a scalar, so that nothing lane-dependent has to stay alive (that is, be
-  // spilled to scratch memory) across the loop, whose body owns every vector register.  A
-  // reload from scratch is a vector-memory load: the wait for it would also wait for every
-  // store issued before it, and between the stores of the forward epilogue that costs
-  // microseconds each time.
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-  auto lane_now = []() {
-    int l = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
-    asm volatile("" : "+v"(l));   // opaque: what is derived from it is computed where it is used, not hoisted
-    return l;
-  };
 
   // valid rows of this chunk (device-side, no host sync)
   int64_t nv64 = *p.n_scored - p.chunk_start;
@@ -577,82 +664,7 @@ __global__ __launch_bounds__(NTHREADS) void gemm_nt_bf16(Params p) {
   if (MODE == MODE_DH) __syncthreads();   // its staged epilogue reuses the panels' LDS
 
   if (MODE == MODE_FWD) {
-    const int lane = lane_now(), wave = wave_u;
-    const int wm = wave >> 1, wn = wave & 1, frow = lane & 15, fq = lane >> 4;
-    const int ncol_base = n0 + wn * 128 + frow;
-    // rows = vocabulary ids, cols = token rows of the chunk.  Exponentials are taken relative to
-    // the row's offset c2 = z_target * log2(e) + margin (log2 domain), one offset for all
-    // vocabulary tiles of a row: e = 2^(z log2(e) - c2), clamped so that neither e nor any sum of
-    // it can overflow.  The sums over the wave's 128 vocabulary ids are this tile's partials; e
-    // itself, as bf16, is the backward pass's operand (dz = (-g / S)(e - S onehot)).
-    constexpr float LOG2E = 1.4426950408889634f;
-    const bool full = (m0 + BM <= p.V);
-    const int pidx = tm * 2 + wm;
-    // vocabulary id of accumulator (i, e) of this lane
-    auto vrow = [&](int i, int e) {
-      return m0 + wm * 128 + 32 * (i >> 1) + 8 * fq + 4 * (i & 1) + e;
-    };
-    // The body is instantiated for full / ragged vocabulary tiles and with / without the entropy
-    // sums: both conditions are uniform, and left as run-time selects they cost four more
-    // instructions per logit (row id, compare, two selects) than the six the work needs
-    // (accumulator read, multiply-add, clamp, exponential, add, half a packed conversion).
-    auto body = [&](auto full_tile, auto with_ez) {
-      constexpr bool kFull = decltype(full_tile)::value, kEz = decltype(with_ez)::value;
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int n = ncol_base + j * 16;
-        const bool live = n < N;
-        const float zt = *reinterpret_cast<const float*>(smem + PIPE_BYTES + (wn * 128 + frow + j * 16) * 4);
-        const float c2 = live ? fmaf(zt, LOG2E, kStashMargin2) : 0.f;
-        uint16_t* erow = p.estash + (int64_t)n * p.lde + m0 + wm * 128 + 8 * fq;
-        float s = 0.f, t = 0.f;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          // accumulators 2q and 2q+1 hold 8 consecutive vocabulary ids of this lane
-          bf16x8 h;
-#pragma unroll
-          for (int u = 0; u < 2; ++u)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              // (read where it is used: left to the compiler, the copies out of the accumulation
-              // registers are hoisted to the top of the epilogue and fill the register file)
-              float z;
-              asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(z) : "a"(acc[2 * q + u][j][e]));
-              float w = exp2_fast(fminf(fmaf(z, LOG2E, -c2), kStashClamp2));
-              if (!kFull) w = vrow(2 * q + u, e) < p.V ? w : 0.f;
-              s += w;
-              if (kEz) t = fmaf(w, z, t);     // for the entropy: sum e * z  (H = lse - E_p[z])
-              h[4 * u + e] = (__bf16)w;
-            }
-          if (p.estash != nullptr && live) {
-            // 16 bytes per lane, the four lanes of a token row side by side (64 bytes).  Streaming
-            // store (non-temporal, device scope): the stash is 5 GB per launch and is next read by
-            // the backward launches, so it should not displace operand panels from the L2 and the
-            // memory-side cache (2 % of the launch against a plain store).  Written in assembly
-            // for its cache policy bits; the two wait states after it are the ones the hardware
-            // needs before the data registers of a store wider than 8 bytes may be overwritten
-            // (the compiler inserts them for its own stores only).
-            asm volatile("global_store_dwordx4 %0, %1, off sc1 nt\n\ts_nop 1" :: "v"(erow + 32 * q), "v"(h) : "memory");
-          }
-        }
-        s += __shfl_xor(s, 16);
-        s += __shfl_xor(s, 32);
-        if (fq == 0 && live) p.part_sum[(int64_t)pidx * p.part_stride + n] = s;
-        if (kEz) {
-          t += __shfl_xor(t, 16);
-          t += __shfl_xor(t, 32);
-          if (fq == 0 && live) p.part_ez[(int64_t)pidx * p.part_stride + n] = t;
-        }
-        // one column block at a time: interleaving them runs the register allocator out of
-        // registers, and its reloads from scratch wait for the stores issued so far
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    };
-    if (full) {
-      if (p.part_ez != nullptr) body(Flag<true>{}, Flag<true>{}); else body(Flag<true>{}, Flag<false>{});
-    } else {
-      if (p.part_ez != nullptr) body(Flag<false>{}, Flag<true>{}); else body(Flag<false>{}, Flag<false>{});
-    }
+    forward_epilogue<8>(p, acc, smem + PIPE_BYTES, m0, n0, tm * 2 + (wave_u >> 1), wave_u >> 1, wave_u & 1, N);
   } else if (MODE == MODE_DH) {
     const int lane = lane_now(), wave = wave_u, tid = wave * 64 + lane;
     const int wm = wave >> 1, wn = wave & 1, frow = lane & 15, fq = lane >> 4;
@@ -755,6 +767,112 @@ __global__ __launch_bounds__(NTHREADS) void gemm_nt_bf16(Params p) {
       }
     }
   }
+}
+
+// ---------------------------------------------------------------------------------------------
+// Forward of at most 256 rows: 128 x 256 tiles (vocabulary x tokens), two workgroups per compute unit.
+// With a single tile column every panel of W is read once, and the launch is bound by how fast W
+// streams in and by its last round: 594 tiles of 256 x 256 are three rounds of 256 for 2.3 rounds'
+// work, and one workgroup per compute unit has one panel of W in flight and nothing to do behind its
+// epilogue.  Tiles half as high and three stages of 32 K-elements let two workgroups share a compute
+// unit (72.5 KB of LDS, 208 registers).  Forward launch, 256 x 256 tiles and these: V = 151936, d = 4096, 64
+// rows 426 and 395 us, 256 rows 464 and 457; d = 1536 189 and 169, 212 and 198; V = 32000, d = 2048 70 and
+// 55, 85 and 64.  The line lies at one tile column because a panel-load byte buys half the products here
+// (24 KB per 512 MFMA cycles, more than the 43.5 bytes per clock a compute unit's load path delivers):
+// from two columns on the large tile wins (512 rows, d = 4096: 606 against 697 us).
+// ---------------------------------------------------------------------------------------------
+constexpr int FM = 128, FN = 256, FK = 32, FSTAGES = 3;
+constexpr int F_A = FM * FK * 2, F_STAGE = (FM + FN) * FK * 2;      // 8 KB of A, 24 KB per stage
+constexpr int F_LDS = FSTAGES * F_STAGE + FN * 4;
+constexpr int F_LOADS = 6;                                          // direct loads per wave and stage: 2 of A, 4 of B
+
+__global__ __launch_bounds__(NTHREADS, 2) void forward_few_bf16(Params p) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int frow = lane & 15, fq = lane >> 4;
+  int64_t nv64 = *p.n_scored - p.chunk_start;
+  const int N = nv64 < 0 ? 0 : (nv64 > p.chunk_rows ? p.chunk_rows : (int)nv64);
+  if (N == 0) return;
+  // one column of tiles over whole 256-wide pairs of them, so that every partial sum and every pad
+  // column of the stash is written; in order: all tiles share the token rows, and runs of 64 tiles per XCD
+  // measured the same
+  const int M = p.M, tm = blockIdx.x;
+  const int m0 = tm * FM, n0 = 0;
+
+  // direct loads: 16 rows x 64 bytes each; lane l fills slot l % 4 of row l / 4 and fetches logical
+  // chunk slot ^ f(row), f = (row >> 3) & 3 for A (permuted fragment rows), (row >> 2) & 3 for B
+  const uint16_t* src[F_LOADS];
+  uint32_t dst[F_LOADS];
+  const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
+#pragma unroll
+  for (int i = 0; i < F_LOADS; ++i) {
+    const int lr = lane >> 2;
+    if (i < 2) {
+      const int blk = wave * 2 + i, r = blk * 16 + lr;
+      const int row = m0 + r < M ? m0 + r : M - 1;
+      src[i] = p.A + (int64_t)row * p.lda + (((lane & 3) ^ ((r >> 3) & 3)) << 3);
+      dst[i] = __builtin_amdgcn_readfirstlane(lds_base + blk * 1024);
+    } else {
+      const int blk = wave * 4 + i - 2, r = blk * 16 + lr;
+      const int row = n0 + r < N ? n0 + r : N - 1;
+      src[i] = p.B + (int64_t)row * p.ldb + (((lane & 3) ^ ((r >> 2) & 3)) << 3);
+      dst[i] = __builtin_amdgcn_readfirstlane(lds_base + F_A + blk * 1024);
+    }
+  }
+  const int nk = p.K / FK;
+  auto load = [&](int i, int kt, uint32_t stage) {
+    uint64_t addr;
+    asm volatile("s_mov_b32 m0, %3\n\tv_lshl_add_u64 %0, %1, 0, %2\n\tglobal_load_lds_dwordx4 %0, off"
+                 : "=&v"(addr) : "v"(src[i]), "s"((int64_t)kt * (FK * 2)), "s"(dst[i] + stage) : "memory");
+  };
+  auto last_k = [&](int k) { return k < nk ? k : nk - 1; };
+  const int a_off = (8 * (frow >> 2) + (frow & 3)) * 64 + ((fq ^ (frow >> 2)) << 4);
+  const int b_off = F_A + (wave * 64 + frow) * 64 + ((fq ^ (frow >> 2)) << 4);
+
+  f32x4 acc[8][4];
+#pragma unroll
+  for (int i = 0; i < 8; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[i][j][e] = 0.f;
+  {
+    int n = n0 + wave * 64 + lane; n = n < N ? n : N - 1;
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off"
+                 :: "v"(p.zt + n), "s"(__builtin_amdgcn_readfirstlane(lds_base + FSTAGES * F_STAGE + wave * 256)) : "memory");
+  }
+#pragma unroll
+  for (int i = 0; i < F_LOADS; ++i) load(i, 0, 0);
+#pragma unroll
+  for (int i = 0; i < F_LOADS; ++i) load(i, 1, F_STAGE);
+  uint32_t st = 0, st_load = 2 * F_STAGE;
+  int kt = 0;
+  do {                                                // (K is at least 128)
+    // this panel's loads have landed when only the next panel's are outstanding; behind the barrier
+    // every wave's have, and every wave has read the slot that the loads below refill
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm(F_LOADS));
+    __syncthreads();
+    const int kl = last_k(kt + 2);
+#pragma unroll
+    for (int i = 0; i < F_LOADS; ++i) load(i, kl, st_load);
+    const unsigned char* base_a = smem + st + a_off;
+    const unsigned char* base_b = smem + st + b_off;
+    bf16x8 fb[4], fa[8];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) fb[j] = *reinterpret_cast<const bf16x8*>(base_b + j * 1024);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) fa[i] = *reinterpret_cast<const bf16x8*>(base_a + (i >> 1) * 2048 + (i & 1) * 256);
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        if (i < 7 || j < 3) mfma16(acc[i][j], fa[i], fb[j]); else mfma16_then_wait(acc[i][j], fa[i], fb[j]);
+      }
+    st = st == 2 * F_STAGE ? 0 : st + F_STAGE;
+    st_load = st_load == 2 * F_STAGE ? 0 : st_load + F_STAGE;
+  } while (++kt < nk);
+  __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
+  forward_epilogue<4>(p, acc, smem + FSTAGES * F_STAGE, m0, n0, tm, 0, wave, N);
 }
 
 // dW tail.  The workgroup -> tile mapping runs whole super-tile rows of sup_m tile rows; V / 256
@@ -919,6 +1037,13 @@ void launch_gemm_fwd_bf16(const void* W, int64_t ldw, const void* Hc, int64_t ld
   p.zt = zt + chunk_start;
   p.part_sum = part_sum; p.part_ez = part_ez; p.part_stride = part_stride;
   p.estash = static_cast<uint16_t*>(estash); p.lde = lde; p.V = V; p.d = d;
+  if (chunk_rows <= FN) {
+    static LdsLimit lds_limit;
+    lds_limit.ensure(reinterpret_cast<const void*>(&forward_few_bf16), F_LDS);
+    const int Mt = 2 * ((p.M + BM - 1) / BM);
+    hipLaunchKernelGGL(forward_few_bf16, dim3(Mt), dim3(NTHREADS), F_LDS, stream, p);
+    return;
+  }
   launch<MODE_FWD>(p, stream);
 }
 

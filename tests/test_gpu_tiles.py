@@ -132,3 +132,22 @@ def test_fp32_tiles_and_odd_widths(mrl, N, d, V):
     for name, got, ref in (("dH", out["dH"], dH), ("dW", out["dW"], dW)):
         assert util.rel_fro(util.to_f64(got), ref) <= 1e-5 or np.linalg.norm(ref) < 1e-12, name
     assert torch.all(out["dH"][~ok] == 0)
+
+
+@pytest.mark.parametrize("scored,d,V", [(1, 128, 100), (64, 136, 129), (65, 256, 256), (200, 1536, 5000), (256, 128, 8321)])
+def test_forward_of_few_rows(mrl, scored, d, V):
+    """Passes of at most 256 rows: vocabularies that end in the first or the second half of a pair of 128-wide tiles, token
+    counts around a wave's 64, log-probs, entropy and (through the stash) both gradients."""
+    H, W, y, mask = _head(scored, d, V, scored, d + V)
+    logp, lse, ent = mrl.token_scores(H, W, y, mask)
+    out, dH, dW = _step(mrl, H, W, y, mask, mrl.BF16, V)
+    torch.cuda.synchronize()
+    z = H.double() @ W.double().t()
+    want_lse = torch.logsumexp(z, 1)
+    want = z.gather(1, y.long()[:, None])[:, 0] - want_lse
+    # fp32 sums of at most 8321 exponentials and 1536 products: far below the bar
+    assert float((logp.double() - want).abs().max()) <= 1e-4 and float((lse.double() - want_lse).abs().max()) <= 1e-4
+    assert float((ent.double() - (want_lse - (torch.softmax(z, 1) * z).sum(1))).abs().max()) <= 1e-4
+    assert torch.equal(out["logp"], logp)
+    util.check_gradient("dH", util.to_f64(out["dH"]), dH)
+    util.check_gradient("dW", util.to_f64(out["dW"]), dW)
