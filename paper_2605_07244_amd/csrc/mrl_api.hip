@@ -19,6 +19,7 @@ namespace {
 constexpr int kDefaultChunkBf16 = 65536;   // rows per pass: amortises the fp32 dW read-modify-write (20 GB of stash at V = 151936)
 constexpr int kFwdSubChunk = 16384;        // forward launches cover this many rows: their H rows stay in the Infinity Cache
 constexpr int kDefaultChunkF32 = 2048;
+constexpr int kTailOnlyRows = 4096;        // (see head_tail_only)
 constexpr int64_t kMaxSlots = (int64_t)1 << 30;
 
 // ------------------------------------------------------------------ profiling
@@ -106,7 +107,7 @@ struct Layout {
   size_t seq_len, seq_coef, seq_expo, group_count, lse_c, g_c, row_scale, loss_partials, Z, Ht = 0;
   size_t tail = 0;             // bf16: partial tiles of the dH and dW launches' K-split tails
   int tail_items = 0;          // ... how many
-  size_t Hc = 0, Wp = 0;       // bf16: the pass's token rows, gathered and zero-padded to dp columns; W padded likewise (only if dp != d)
+  size_t Hc = 0, Wp = 0;       // bf16: the pass's token rows, gathered and zero-padded to dp columns; zero-padded tail of W (only if dp != d)
   int dp = 0;                  // bf16: d rounded up to the 128-wide panel pairs of the GEMM kernels
   int64_t ldh = 0;             // row stride of Hc and Wp
   int chunk_rows = 0, n_partials = 0;
@@ -240,18 +241,38 @@ void prepare_chunk(const void* H, const void* W, const int32_t* targets, int d, 
   launch_row_prep(more, bf16, s);
 }
 
+// bf16 path, widths that are no multiple of the forward kernel's 128-wide panel pairs: either the last
+// 128 columns of W are copied, zero-padded, into rows of W's own stride (so that the kernel reaches them
+// by one offset), or all of W is, into aligned rows.  The tail is an eighth and less of the bytes, but
+// where W's rows are no multiple of 128 bytes every panel row then straddles two lines.  Scoring call, all of
+// W copied and its tail only: V = 128256, d = 1000, 100 rows 183 and 118 us, 2000 rows 568 and 512, 4000 rows
+// 1022 and 991, 8000 rows 1888 and 1904; V = 50257, d = 712, 2000 rows 190 and 183, 4000 rows 323 and 324;
+// with rows of whole lines, d = 1984, 8000 rows 3277 and 3123.
+bool head_tail_only(int d, int chunk_rows) { return d > 128 && (d % 64 == 0 || chunk_rows <= kTailOnlyRows); }
+void pad_head(const void* W, int d, int V, const Layout& L, void* ws, hipStream_t s) {
+  if (L.Wp == 0) return;
+  if (head_tail_only(d, L.chunk_rows)) {
+    const int first = L.dp - 128;
+    launch_pad_rows_b16(static_cast<const uint16_t*>(W) + first, d, at<void>(ws, L.Wp), d, V, d - first, 128, s);
+  } else {
+    launch_pad_rows_b16(W, d, at<void>(ws, L.Wp), L.ldh, V, d, L.dp, s);
+  }
+}
+
 // forward of one chunk: logits tile GEMM with fused (or, in fp32, separate) log-sum-exp
 void forward_chunk(const void* H, const void* W, int d, int V, bool bf16, const Layout& L, void* ws,
                    int64_t c0, bool stash, hipStream_t s, bool entropy = false) {
   const int32_t* row_index = at<int32_t>(ws, L.row_index);
   const int64_t* n_scored = at<int64_t>(ws, L.counters);
   if (bf16) {
-    const void* Wk = L.dp != d ? at<void>(ws, L.Wp) : W;
-    const int64_t ldw = L.dp != d ? L.ldh : d;
+    const bool padded = L.dp != d && !head_tail_only(d, L.chunk_rows);
+    const void* Wk = padded ? at<void>(ws, L.Wp) : W;
+    const void* W_tail = L.dp != d && !padded ? at<void>(ws, L.Wp) : nullptr;
+    const int64_t ldw = padded ? L.ldh : d;
     for (int sub = 0; sub < L.chunk_rows; sub += kFwdSubChunk) {
       const int rows = L.chunk_rows - sub < kFwdSubChunk ? L.chunk_rows - sub : kFwdSubChunk;
       Scope sc(MRL_PROF_GEMM_FWD, s);   // one event pair per kernel launch
-      launch_gemm_fwd_bf16(Wk, ldw, at<uint16_t>(ws, L.Hc) + (size_t)sub * L.ldh, L.ldh, L.dp, at<float>(ws, L.zt),
+      launch_gemm_fwd_bf16(Wk, ldw, W_tail, at<uint16_t>(ws, L.Hc) + (size_t)sub * L.ldh, L.ldh, L.dp, at<float>(ws, L.zt),
                            n_scored, c0 + sub, rows, V, d,
                            at<float>(ws, L.part_sum) + sub, entropy ? at<float>(ws, L.part_ez) + sub : nullptr,
                            L.chunk_rows,
@@ -362,7 +383,7 @@ int mrl_token_scores(const void* hidden, const void* lm_head_w, const int32_t* t
     const PrepOut po = {row_index, n_scored, n_scored + 1, at<int32_t>(ws, L.block_counts),
                         {out_logp, out_lse, out_entropy}, 0, 0, nullptr};
     launch_prep(token_mask, target_ids, N, V, po, s);
-    if (L.Wp != 0) launch_pad_rows_b16(lm_head_w, d, at<void>(ws, L.Wp), L.ldh, V, d, L.dp, s);
+    pad_head(lm_head_w, d, V, L, ws, s);
   }
   for (int64_t c = 0; c < L.n_chunks; ++c) {
     const int64_t c0 = c * L.chunk_rows;
@@ -481,7 +502,7 @@ int mrl_grpo_loss_fwd_bwd(const void* hidden, const void* lm_head_w, const int32
     const PrepOut po = {row_index, n_scored, n_scored + 1, at<int32_t>(ws, L.block_counts),
                         {out_logp, nullptr, nullptr}, B, T, at<int32_t>(ws, L.seq_len)};
     launch_prep(token_mask, target_ids, N, V, po, s);
-    if (L.Wp != 0) launch_pad_rows_b16(lm_head_w, d, at<void>(ws, L.Wp), L.ldh, V, d, L.dp, s);
+    pad_head(lm_head_w, d, V, L, ws, s);
   }
   int64_t n_passes = L.n_chunks;
   if (cfg->scored_rows_hint > 0) {

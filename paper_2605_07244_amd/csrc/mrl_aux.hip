@@ -703,21 +703,22 @@ __global__ __launch_bounds__(256) void k_convert_f32(float* ZP, int64_t ldz, con
 }
 
 // ----------------------------------------------------------------------------
-// Row copy with zero padding: Out[r][0:dp] = In[r][0:d] | 0, for a W whose width is no multiple of
-// the forward kernel's 128-wide panel pairs.
+// Row copy with zero padding: Out[r][0:dp] = In[r][0:d] | 0, for the last 128 columns of a W whose width is
+// no multiple of the forward kernel's 128-wide panel pairs (or all of a W narrower than that).
 // ----------------------------------------------------------------------------
-constexpr int PAD_ROWS = 4;
+constexpr int PAD_VECTORS = 4;                          // 16-byte vectors per thread
 __global__ __launch_bounds__(256) void k_pad_rows_b16(const uint16_t* in, int64_t ld_in, uint16_t* out, int64_t ld_out,
                                                       int64_t n_rows, int d, int dp) {
+  const int per_row = dp / 8;
 #pragma unroll
-  for (int k = 0; k < PAD_ROWS; ++k) {
-    const int64_t r = (int64_t)blockIdx.x * PAD_ROWS + k;
+  for (int k = 0; k < PAD_VECTORS; ++k) {
+    const int64_t i = ((int64_t)blockIdx.x * PAD_VECTORS + k) * 256 + threadIdx.x;
+    const int64_t r = i / per_row;
     if (r >= n_rows) return;
-    for (int c = threadIdx.x * 8; c < dp; c += 256 * 8) {
-      uint4 v = make_uint4(0, 0, 0, 0);
-      if (c < d) v = *reinterpret_cast<const uint4*>(in + r * ld_in + c);
-      *reinterpret_cast<uint4*>(out + r * ld_out + c) = v;
-    }
+    const int c = (int)(i - r * per_row) * 8;
+    uint4 v = make_uint4(0, 0, 0, 0);
+    if (c < d) v = *reinterpret_cast<const uint4*>(in + r * ld_in + c);
+    *reinterpret_cast<uint4*>(out + r * ld_out + c) = v;
   }
 }
 
@@ -844,7 +845,8 @@ void launch_convert_f32(float* ZP, int64_t ldz, const float* lse_c,
 
 void launch_pad_rows_b16(const void* in, int64_t ld_in, void* out, int64_t ld_out, int64_t n_rows, int d, int dp,
                          hipStream_t stream) {
-  hipLaunchKernelGGL(k_pad_rows_b16, dim3((unsigned)((n_rows + PAD_ROWS - 1) / PAD_ROWS)), dim3(256), 0, stream,
+  const int64_t per_block = PAD_VECTORS * 256;
+  hipLaunchKernelGGL(k_pad_rows_b16, dim3((unsigned)((n_rows * (dp / 8) + per_block - 1) / per_block)), dim3(256), 0, stream,
                      static_cast<const uint16_t*>(in), ld_in, static_cast<uint16_t*>(out), ld_out, n_rows, d, dp);
 }
 

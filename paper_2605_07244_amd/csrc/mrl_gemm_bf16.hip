@@ -82,7 +82,9 @@ struct Params {
   const int32_t* row_index;   // already offset to the chunk start
   const int64_t* n_scored; int64_t chunk_start; int chunk_rows;
   int sup_m, sup_n;           // DW: super-tile shape of the workgroup -> tile mapping
-  // FWD
+  // FWD; a_tail_panel: the 64-wide panel from which A comes from its zero-padded tail copy, a_tail_delta
+  // bytes behind where it would be
+  int a_tail_panel; int64_t a_tail_delta;
   const float* zt; float* part_sum; float* part_ez; int64_t part_stride; uint16_t* estash; int64_t lde; int V;
   // DH
   const float* row_scale; void* dH; int dh_f32; int d; int max_items;   // max_items: partial tiles tail_part holds
@@ -552,12 +554,13 @@ __global__ __launch_bounds__(NTHREADS) void gemm_nt_bf16(Params p) {
                  :: "v"(voff), "s"(desc), "s"(lds_addr) : "memory");
   };
   auto issue_range = [&](int kt, int slot, int j0, int j1) {
+    const int64_t a_off = (int64_t)kt * a_kstep * 2 + (MODE == MODE_FWD && kt >= p.a_tail_panel ? p.a_tail_delta : 0);
 #pragma unroll
     for (int j = j0; j < j1; ++j) {
       const uint32_t st = slot * STAGE_BYTES + wave_lds;
       if (B_KMAJOR && (j & 1)) load_lds16_w(b_voff[j >> 1], w_desc, st + TILE_BYTES + lds_b[j >> 1]);
       else if (j & 1) load_lds16_at(b_ptr[j >> 1], (int64_t)kt * (BK * 2), st + TILE_BYTES + lds_b[j >> 1]);
-      else load_lds16_at(a_ptr[j >> 1], (int64_t)kt * a_kstep * 2, st + lds_a[j >> 1]);
+      else load_lds16_at(a_ptr[j >> 1], a_off, st + lds_a[j >> 1]);
     }
   };
   // One panel = 8 groups of 16 MFMAs.  A wave issues in order and the matrix pipe takes a new MFMA
@@ -822,8 +825,9 @@ __global__ __launch_bounds__(NTHREADS, 2) void forward_few_bf16(Params p) {
   const int nk = p.K / FK;
   auto load = [&](int i, int kt, uint32_t stage) {
     uint64_t addr;
+    const int64_t off = (int64_t)kt * (FK * 2) + (i < 2 && kt >= p.a_tail_panel * (BK / FK) ? p.a_tail_delta : 0);
     asm volatile("s_mov_b32 m0, %3\n\tv_lshl_add_u64 %0, %1, 0, %2\n\tglobal_load_lds_dwordx4 %0, off"
-                 : "=&v"(addr) : "v"(src[i]), "s"((int64_t)kt * (FK * 2)), "s"(dst[i] + stage) : "memory");
+                 : "=&v"(addr) : "v"(src[i]), "s"(off), "s"(dst[i] + stage) : "memory");
   };
   auto last_k = [&](int k) { return k < nk ? k : nk - 1; };
   const int a_off = (8 * (frow >> 2) + (frow & 3)) * 64 + ((fq ^ (frow >> 2)) << 4);
@@ -1025,7 +1029,7 @@ void launch(Params& p, hipStream_t stream) {
 
 }  // namespace
 
-void launch_gemm_fwd_bf16(const void* W, int64_t ldw, const void* Hc, int64_t ldh, int k_len, const float* zt,
+void launch_gemm_fwd_bf16(const void* W, int64_t ldw, const void* W_tail, const void* Hc, int64_t ldh, int k_len, const float* zt,
                           const int64_t* n_scored, int64_t chunk_start, int chunk_rows,
                           int V, int d, float* part_sum, float* part_ez,
                           int64_t part_stride, void* estash, int64_t lde, hipStream_t stream) {
@@ -1033,6 +1037,11 @@ void launch_gemm_fwd_bf16(const void* W, int64_t ldw, const void* Hc, int64_t ld
   p.A = static_cast<const uint16_t*>(W); p.lda = ldw; p.M = V;
   p.B = static_cast<const uint16_t*>(Hc); p.ldb = ldh; p.N = chunk_rows;
   p.K = k_len;
+  p.a_tail_panel = k_len / BK;                        // none
+  if (W_tail != nullptr) {
+    p.a_tail_panel = k_len / BK - 2;
+    p.a_tail_delta = (int64_t)(reinterpret_cast<uintptr_t>(W_tail) - reinterpret_cast<uintptr_t>(W)) - (int64_t)p.a_tail_panel * (BK * 2);
+  }
   p.n_scored = n_scored; p.chunk_start = chunk_start; p.chunk_rows = chunk_rows;
   p.zt = zt + chunk_start;
   p.part_sum = part_sum; p.part_ez = part_ez; p.part_stride = part_stride;

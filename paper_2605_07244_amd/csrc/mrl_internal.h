@@ -57,7 +57,9 @@ constexpr float kSaturatedLogp = -97.f;
 // = sum of e[n, v] over the partial's 128 vocabulary rows (e as defined above), when part_ez != nullptr
 // also sum e * z (for the entropy), and, when estash != nullptr, e itself as bf16 into
 // estash[n * lde + v] (n = row within this launch; columns V .. round_up(V, 256) get zeros).
-void launch_gemm_fwd_bf16(const void* W, int64_t ldw, const void* Hc, int64_t ldh, int k_len, const float* zt,
+// W_tail (nullptr: none): the last 128 columns of the K extent, zero-padded, in rows of the same stride
+// ldw; the other columns are read from W, whose rows need not reach that far.
+void launch_gemm_fwd_bf16(const void* W, int64_t ldw, const void* W_tail, const void* Hc, int64_t ldh, int k_len, const float* zt,
                           const int64_t* n_scored, int64_t chunk_start, int chunk_rows,
                           int V, int d, float* part_sum, float* part_ez,
                           int64_t part_stride, void* estash, int64_t lde, hipStream_t stream);
@@ -173,7 +175,7 @@ void launch_convert_f32(float* ZP, int64_t ldz, const float* lse_c,
                         hipStream_t stream);
 
 // Out[r][0:dp] = In[r][0:d], zero in [d, dp), r < n_rows.  16-byte vectors: d, dp, both row strides
-// multiples of 8 elements.
+// multiples of 8 elements, both pointers 16-byte aligned.
 void launch_pad_rows_b16(const void* in, int64_t ld_in, void* out, int64_t ld_out, int64_t n_rows, int d, int dp,
                          hipStream_t stream);
 

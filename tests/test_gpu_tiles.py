@@ -151,3 +151,17 @@ def test_forward_of_few_rows(mrl, scored, d, V):
     assert torch.equal(out["logp"], logp)
     util.check_gradient("dH", util.to_f64(out["dH"]), dH)
     util.check_gradient("dW", util.to_f64(out["dW"]), dW)
+
+
+@pytest.mark.parametrize("N,d,V", [(100, 120, 700), (300, 136, 700), (4096, 200, 900), (4200, 200, 900), (4200, 192, 900)])
+def test_padded_widths(mrl, N, d, V):
+    """Widths beside a multiple of 128: a head narrower than a panel pair, the head's zero-padded tail next to its own rows
+    (up to 4096 rows, and above for rows of whole lines), a padded copy of all of it."""
+    H, W, y, mask = _head(N, d, V, N - 3, d)
+    logp, lse = mrl.token_logprobs(H, W, y, mask)
+    torch.cuda.synchronize()
+    ok = mask == 1
+    z = H[ok].double() @ W.double().t()
+    want_lse = torch.logsumexp(z, 1)
+    assert float((lse[ok].double() - want_lse).abs().max()) <= 1e-4
+    assert float((logp[ok].double() - (z.gather(1, y[ok].long()[:, None])[:, 0] - want_lse)).abs().max()) <= 1e-4
