@@ -134,7 +134,7 @@ def _ptr(t, dtype=None, name="tensor"):
         raise TypeError(f"{name} must have dtype {dtype}, got {t.dtype}")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
-    return c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _dtype_code(t: torch.Tensor) -> int:
@@ -145,8 +145,15 @@ def _dtype_code(t: torch.Tensor) -> int:
     raise TypeError(f"hidden / lm_head_w must be bfloat16 or float32, got {t.dtype}")
 
 
-def _stream() -> c_void_p:
-    return c_void_p(torch.cuda.current_stream().cuda_stream)
+# the current stream's handle without the Stream object torch.cuda.current_stream() builds, which is 2.8 of the
+# 15 us of host time of a small call
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
+def _stream() -> int:
+    if _raw_stream is not None:
+        return _raw_stream(torch.cuda.current_device())
+    return torch.cuda.current_stream().cuda_stream
 
 
 def _check(rc: int, where: str):
