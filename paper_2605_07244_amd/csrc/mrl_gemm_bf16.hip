@@ -849,6 +849,7 @@ __global__ __launch_bounds__(NTHREADS, 2) void forward_few_bf16(Params p) {
   for (int i = 0; i < F_LOADS; ++i) load(i, 0, 0);
 #pragma unroll
   for (int i = 0; i < F_LOADS; ++i) load(i, 1, F_STAGE);
+  const bool has_rows = n0 + wave * 64 < N;           // a wave without tokens only loads its share
   uint32_t st = 0, st_load = 2 * F_STAGE;
   int kt = 0;
   do {                                                // (K is at least 128)
@@ -859,24 +860,26 @@ __global__ __launch_bounds__(NTHREADS, 2) void forward_few_bf16(Params p) {
     const int kl = last_k(kt + 2);
 #pragma unroll
     for (int i = 0; i < F_LOADS; ++i) load(i, kl, st_load);
-    const unsigned char* base_a = smem + st + a_off;
-    const unsigned char* base_b = smem + st + b_off;
-    bf16x8 fb[4], fa[8];
+    if (has_rows) {
+      const unsigned char* base_a = smem + st + a_off;
+      const unsigned char* base_b = smem + st + b_off;
+      bf16x8 fb[4], fa[8];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) fb[j] = *reinterpret_cast<const bf16x8*>(base_b + j * 1024);
+      for (int j = 0; j < 4; ++j) fb[j] = *reinterpret_cast<const bf16x8*>(base_b + j * 1024);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) fa[i] = *reinterpret_cast<const bf16x8*>(base_a + (i >> 1) * 2048 + (i & 1) * 256);
+      for (int i = 0; i < 8; ++i) fa[i] = *reinterpret_cast<const bf16x8*>(base_a + (i >> 1) * 2048 + (i & 1) * 256);
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
+      for (int i = 0; i < 8; ++i)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        if (i < 7 || j < 3) mfma16(acc[i][j], fa[i], fb[j]); else mfma16_then_wait(acc[i][j], fa[i], fb[j]);
-      }
+        for (int j = 0; j < 4; ++j) {
+          if (i < 7 || j < 3) mfma16(acc[i][j], fa[i], fb[j]); else mfma16_then_wait(acc[i][j], fa[i], fb[j]);
+        }
+    }
     st = st == 2 * F_STAGE ? 0 : st + F_STAGE;
     st_load = st_load == 2 * F_STAGE ? 0 : st_load + F_STAGE;
   } while (++kt < nk);
   __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
-  forward_epilogue<4>(p, acc, smem + FSTAGES * F_STAGE, m0, n0, tm, 0, wave, N);
+  if (has_rows) forward_epilogue<4>(p, acc, smem + FSTAGES * F_STAGE, m0, n0, tm, 0, wave, N);
 }
 
 // dW tail.  The workgroup -> tile mapping runs whole super-tile rows of sup_m tile rows; V / 256
