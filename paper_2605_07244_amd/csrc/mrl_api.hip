@@ -591,39 +591,41 @@ int mrl_grpo_loss_fwd_bwd(const void* hidden, const void* lm_head_w, const int32
                            n_scored, c0, L.chunk_rows, V, s);
       }
     }
+    const int overwrite = (c == 0 && !cfg->accumulate_dw) ? 1 : 0;
+    if (!bf16) {
+      GemmF32Args h = {};
+      h.A = at<float>(ws, L.Z); h.lda = L.ldz;
+      h.B = static_cast<const float*>(lm_head_w); h.ldb = d; h.b_kmajor = 1;
+      h.C = static_cast<float*>(out_dH); h.ldc = d; h.c_rows = row_index + c0;
+      h.M = L.chunk_rows; h.N = d; h.K = V;
+      h.n_scored = n_scored; h.chunk_start = c0; h.chunk_rows = L.chunk_rows;
+      h.m_dynamic = 1;
+      GemmF32Args w = {};
+      w.A = at<float>(ws, L.Z); w.lda = L.ldz; w.a_kmajor = 1;
+      w.B = static_cast<const float*>(hidden); w.ldb = d; w.b_rows = row_index + c0; w.b_kmajor = 1;
+      w.C = out_dW; w.ldc = d;
+      w.M = V; w.N = d; w.K = L.chunk_rows;
+      w.n_scored = n_scored; w.chunk_start = c0; w.chunk_rows = L.chunk_rows;
+      w.k_dynamic = 1; w.accumulate = !overwrite;
+      if (out_dH && out_dW && gemm_f32_pairs(h, w)) {
+        Scope sc(MRL_PROF_GEMM_DH, s);                  // (one launch for both counts as dH's)
+        launch_gemm_f32_pair(h, w, s);
+        continue;
+      }
+      if (out_dH) { Scope sc(MRL_PROF_GEMM_DH, s); launch_gemm_f32(h, s); }
+      if (out_dW) { Scope sc(MRL_PROF_GEMM_DW, s); launch_gemm_f32(w, s); }
+      continue;
+    }
     if (out_dH) {
       Scope sc(MRL_PROF_GEMM_DH, s);
-      if (bf16) {
-        launch_gemm_dh_bf16(at<void>(ws, L.Z), L.ldz, lm_head_w, d, V, row_index, at<float>(ws, L.row_scale),
-                            n_scored, c0, L.chunk_rows, d, out_dH, cfg->dh_dtype == MRL_F32,
-                            at<float>(ws, L.tail), L.tail_items, s);
-      } else {
-        GemmF32Args g = {};
-        g.A = at<float>(ws, L.Z); g.lda = L.ldz;
-        g.B = static_cast<const float*>(lm_head_w); g.ldb = d; g.b_kmajor = 1;
-        g.C = static_cast<float*>(out_dH); g.ldc = d; g.c_rows = row_index + c0;
-        g.M = L.chunk_rows; g.N = d; g.K = V;
-        g.n_scored = n_scored; g.chunk_start = c0; g.chunk_rows = L.chunk_rows;
-        g.m_dynamic = 1; g.k_dynamic = 0; g.accumulate = 0;
-        launch_gemm_f32(g, s);
-      }
+      launch_gemm_dh_bf16(at<void>(ws, L.Z), L.ldz, lm_head_w, d, V, row_index, at<float>(ws, L.row_scale),
+                          n_scored, c0, L.chunk_rows, d, out_dH, cfg->dh_dtype == MRL_F32,
+                          at<float>(ws, L.tail), L.tail_items, s);
     }
     if (out_dW) {
       Scope sc(MRL_PROF_GEMM_DW, s);
-      const int overwrite = (c == 0 && !cfg->accumulate_dw) ? 1 : 0;
-      if (bf16) {
-        launch_gemm_dw_bf16(at<void>(ws, L.Z), L.ldz, at<void>(ws, L.Ht), L.ldr, n_scored, c0,
-                            L.chunk_rows, V, d, out_dW, overwrite, at<float>(ws, L.tail), s);
-      } else {
-        GemmF32Args g = {};
-        g.A = at<float>(ws, L.Z); g.lda = L.ldz; g.a_kmajor = 1;
-        g.B = static_cast<const float*>(hidden); g.ldb = d; g.b_rows = row_index + c0; g.b_kmajor = 1;
-        g.C = out_dW; g.ldc = d; g.c_rows = nullptr;
-        g.M = V; g.N = d; g.K = L.chunk_rows;
-        g.n_scored = n_scored; g.chunk_start = c0; g.chunk_rows = L.chunk_rows;
-        g.m_dynamic = 0; g.k_dynamic = 1; g.accumulate = !overwrite;
-        launch_gemm_f32(g, s);
-      }
+      launch_gemm_dw_bf16(at<void>(ws, L.Z), L.ldz, at<void>(ws, L.Ht), L.ldr, n_scored, c0,
+                          L.chunk_rows, V, d, out_dW, overwrite, at<float>(ws, L.tail), s);
     }
   }
   {

@@ -102,6 +102,10 @@ struct GemmF32Args {
   int m_on_x;   // set by the launcher
 };
 void launch_gemm_f32(const GemmF32Args& a, hipStream_t stream);
+// Both products in one launch (a: B k-major; b: both k-major), where gemm_f32_pairs says that neither
+// fills the chip.
+bool gemm_f32_pairs(const GemmF32Args& a, const GemmF32Args& b);
+void launch_gemm_f32_pair(const GemmF32Args& a, const GemmF32Args& b, hipStream_t stream);
 
 // ---- auxiliary kernels ------------------------------------------------------
 struct PrepOut {
