@@ -36,13 +36,15 @@ __device__ inline long long to_fixed(float x) {
   return ((long long)(int)whole << 32) + ((long long)(int)hi << 16) + lo;
 }
 
-// One side's response tokens within a segment: steps of 64 consecutive positions per wave.
+// One side's response tokens within a segment: steps of 64 consecutive positions per wave.  Positions are
+// unsigned: rows may have up to 2^31 - 1 of them, and the run of the last segment reaches up to a
+// segment beyond.
 struct Run {
-  int first, steps;                                   // first position of the wave's run, its steps
+  uint32_t first; int steps;                                   // first position of the wave's run, its steps
   uint32_t bits;                                      // bit k: this lane's position of step k is a response token
-  __device__ void load(const uint8_t* mask, int j0, int S, int* wave_counts) {
+  __device__ void load(const uint8_t* mask, uint32_t j0, uint32_t S, int* wave_counts) {
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int len = S - j0 < THL_SEGMENT ? (S > j0 ? S - j0 : 0) : THL_SEGMENT;
+    const int len = S <= j0 ? 0 : (S - j0 < THL_SEGMENT ? (int)(S - j0) : THL_SEGMENT);
     steps = (len + THL_THREADS - 1) / THL_THREADS;
     first = j0 + wave * steps * 64;
     bits = 0;
@@ -51,7 +53,7 @@ struct Run {
       uint8_t m[THL_GROUP];
 #pragma unroll
       for (int k = 0; k < THL_GROUP; ++k) {
-        const int j = first + (k0 + k) * 64 + lane;
+        const uint32_t j = first + (k0 + k) * 64 + lane;
         m[k] = mask[j < S ? j : S - 1];
       }
 #pragma unroll
@@ -123,9 +125,9 @@ __global__ __launch_bounds__(THL_THREADS) void k_thl_word_align(
   // aggregation: Z_w = sum of the source log-probs of the response tokens mapped to w, C_w = number of
   // target response tokens mapped to w
   int base_s = 0, base_t = 0, bad_s = 0, bad_t = 0;
-  const int longest = S_src > S_tgt ? S_src : S_tgt;
+  const uint32_t longest = S_src > S_tgt ? S_src : S_tgt;
   Run rs, rt;
-  for (int j0 = 0; j0 < longest; j0 += THL_SEGMENT) {
+  for (uint32_t j0 = 0; j0 < longest; j0 += THL_SEGMENT) {
     if (j0 > 0) __syncthreads();                      // the counts of the segment before are consumed
     rs.load(sm, j0, S_src, counts_s);
     rt.load(tm, j0, S_tgt, counts_t);
@@ -136,8 +138,8 @@ __global__ __launch_bounds__(THL_THREADS) void k_thl_word_align(
     base_t += total_t;
     int32_t w[THL_GROUP];
     float x[THL_GROUP];
-    rs.each(before_s, slen, [&](int k, int j, int p) { w[k] = smap[p]; x[k] = lp[j]; },
-            [&](int k, int, bool in) {
+    rs.each(before_s, slen, [&](int k, uint32_t j, int p) { w[k] = smap[p]; x[k] = lp[j]; },
+            [&](int k, uint32_t, bool in) {
       if (!in) return;
       if (w[k] >= 0 && w[k] < max_words) {
         atomicAdd(reinterpret_cast<unsigned long long*>(&wsum[w[k]]), (unsigned long long)to_fixed(x[k]));
@@ -146,7 +148,7 @@ __global__ __launch_bounds__(THL_THREADS) void k_thl_word_align(
         ++bad_s;
       }
     });
-    rt.each(before_t, tlen, [&](int k, int, int p) { w[k] = tmap[p]; }, [&](int k, int, bool in) {
+    rt.each(before_t, tlen, [&](int k, uint32_t, int p) { w[k] = tmap[p]; }, [&](int k, uint32_t, bool in) {
       if (!in) return;
       if (w[k] >= 0 && w[k] < max_words) atomicAdd(&wcnt[w[k]], 1);
       else if (w[k] != -1) ++bad_t;
@@ -159,8 +161,8 @@ __global__ __launch_bounds__(THL_THREADS) void k_thl_word_align(
   // instructions; the product with the inverse of a small count is within 2^-52 of it before the
   // rounding to fp32.)
   base_t = 0;
-  for (int j0 = 0; j0 < S_tgt; j0 += THL_SEGMENT) {
-    if (longest > THL_SEGMENT) {                      // (else the only segment's bits and counts are still there)
+  for (uint32_t j0 = 0; j0 < (uint32_t)S_tgt; j0 += THL_SEGMENT) {
+    if (longest > (uint32_t)THL_SEGMENT) {                      // (else the only segment's bits and counts are still there)
       __syncthreads();
       rt.load(tm, j0, S_tgt, counts_t);
       __syncthreads();
@@ -169,8 +171,8 @@ __global__ __launch_bounds__(THL_THREADS) void k_thl_word_align(
     const int before_t = base_t + rt.before(counts_t, total_t);
     base_t += total_t;
     int32_t w[THL_GROUP];
-    rt.each(before_t, tlen, [&](int k, int, int p) { w[k] = tmap[p]; }, [&](int k, int j, bool in) {
-      if (j >= S_tgt) return;
+    rt.each(before_t, tlen, [&](int k, uint32_t, int p) { w[k] = tmap[p]; }, [&](int k, uint32_t j, bool in) {
+      if (j >= (uint32_t)S_tgt) return;
       float v = ignore_value;
       if (active && in && w[k] >= 0 && w[k] < max_words) {
         const int c = wcnt[w[k]];

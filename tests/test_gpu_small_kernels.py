@@ -59,3 +59,22 @@ def test_alignment_segments_and_counts(mrl, B, S_src, S_tgt, one_word):
     # a word's sum is exact to 2^-33 per source token, the output rounded to fp32
     assert np.all(np.abs(out.cpu().numpy() - want) <= 1e-6 + 2.0 ** -23 * np.abs(want))
     assert int(bad.item()) == 0
+
+
+def test_alignment_of_a_row_that_ends_below_2_31(mrl):
+    """The last segment of 8192 positions reaches beyond the largest 32-bit signed position; its tokens are found and
+    nothing behind the row is read."""
+    S = 2 ** 31 - 4096
+    lp, mask = torch.zeros((1, S), device="cuda"), torch.zeros((1, S), dtype=torch.uint8, device="cuda")
+    wmap = torch.zeros((1, S), dtype=torch.int32, device="cuda")
+    at = [0, 300, 8192, S - 8191, S - 2, S - 1]
+    for k, j in enumerate(at):
+        lp[0, j] = -2.0 ** k
+        mask[0, j] = 1
+        wmap[0, k] = k // 2
+    t = lambda v, dt: torch.tensor(v, dtype=dt, device="cuda")
+    out, bad = mrl.thl_word_align(lp, mask, wmap, t([6], torch.int32), t([[1] * 4], torch.uint8), t([[0, 1, 2, 2]], torch.int32),
+                                  t([4], torch.int32), 3)
+    # sums of powers of two and halves of them are exact
+    assert out.cpu().tolist() == [[-3.0, -12.0, -24.0, -24.0]]
+    assert int(bad.item()) == 0
