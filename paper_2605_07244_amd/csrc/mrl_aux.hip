@@ -268,6 +268,29 @@ struct CoefArgs {
   const int32_t* seq_len; const int32_t* group_id; const uint8_t* seq_kind; int64_t B; int G; int loss_agg;
   int32_t* group_count; float* seq_coef; int64_t* n_bad_groups;
 };
+// f(sequence, kind, scored length, group id, of_group(group id)) for the block's sequences (an id outside
+// [0, G) is looked up as 0), the loads of STEPS of them in flight together: one after the other they
+// cost the single block 0.2 us per 256 sequences and loop.  Loss call of 65536 sequences of one token, V = 1024,
+// d = 128: 8192 groups 1494 us, 8 together 1374 (4: 1385), 60000 groups 1559 and 1401 (1419).
+constexpr int kCoefSteps = 8;
+template <int STEPS, class Of, class F> __device__ inline void each_sequence(const CoefArgs& a, Of of_group, F f) {
+  for (int64_t b0 = threadIdx.x; b0 < a.B; b0 += 256 * STEPS) {
+    int kind[STEPS], len[STEPS], group[STEPS], of[STEPS];
+#pragma unroll
+    for (int k = 0; k < STEPS; ++k) {
+      const int64_t b = b0 + 256 * k < a.B ? b0 + 256 * k : a.B - 1;
+      kind[k] = a.seq_kind ? a.seq_kind[b] : 0;
+      len[k] = a.seq_len[b];
+      group[k] = a.group_id[b];
+    }
+#pragma unroll
+    for (int k = 0; k < STEPS; ++k) of[k] = of_group(group[k] >= 0 && group[k] < a.G ? group[k] : 0);
+#pragma unroll
+    for (int k = 0; k < STEPS; ++k)
+      if (b0 + 256 * k < a.B) f(b0 + 256 * k, kind[k], len[k], group[k], of[k]);
+  }
+}
+template <int STEPS>
 __device__ inline void seq_coef_block(const CoefArgs& a, int32_t* lds_count /*[kCoefLdsGroups]*/) {
   __shared__ long long sh[4][3];
   const bool in_lds = a.G <= kCoefLdsGroups;
@@ -280,10 +303,7 @@ __device__ inline void seq_coef_block(const CoefArgs& a, int32_t* lds_count /*[k
   __threadfence();
   __syncthreads();
   long long v[3] = {0, 0, 0};                         // auxiliary rows with tokens, GRPO tokens, bad group ids
-  for (int64_t b = threadIdx.x; b < a.B; b += 256) {
-    const int kind = a.seq_kind ? a.seq_kind[b] : 0;
-    const int L = a.seq_len[b];
-    const int g = a.group_id[b];
+  each_sequence<STEPS>(a, [](int) { return 0; }, [&](int64_t, int kind, int L, int g, int) {
     const bool ok = g >= 0 && g < a.G;
     v[2] += !ok;
     if (kind != 0) v[0] += (L > 0);
@@ -291,28 +311,31 @@ __device__ inline void seq_coef_block(const CoefArgs& a, int32_t* lds_count /*[k
       if (in_lds) atomicAdd(&lds_count[g], 1); else atomicAdd(&a.group_count[g], 1);
       v[1] += L;
     }
-  }
+  });
   __threadfence();
   block_sum3(v, sh);                                  // (its barriers also publish the counts)
   long long u[3] = {0, 0, 0};
-  for (int g = threadIdx.x; g < a.G; g += 256) u[0] += (count(g) > 0);
+  for (int g0 = threadIdx.x; g0 < a.G; g0 += 256 * STEPS) {
+    int n[STEPS];
+#pragma unroll
+    for (int k = 0; k < STEPS; ++k) n[k] = count(g0 + 256 * k < a.G ? g0 + 256 * k : a.G - 1);
+#pragma unroll
+    for (int k = 0; k < STEPS; ++k) u[0] += g0 + 256 * k < a.G && n[k] > 0;
+  }
   block_sum3(u, sh);
   if (threadIdx.x == 0) *a.n_bad_groups = v[2];
   const double P = (double)u[0], S = (double)v[0], NT = (double)v[1];
-  for (int64_t b = threadIdx.x; b < a.B; b += 256) {
-    const int kind = a.seq_kind ? a.seq_kind[b] : 0;
-    const int L = a.seq_len[b];
-    const int g = a.group_id[b];
+  each_sequence<STEPS>(a, count, [&](int64_t b, int kind, int L, int g, int K) {
     double c = 0.0;
     if (L > 0) {
       if (kind == 0) {
-        if (g >= 0 && g < a.G) c = a.loss_agg == 1 ? 1.0 / NT : 1.0 / (P * (double)count(g) * (double)L);
+        if (g >= 0 && g < a.G) c = a.loss_agg == 1 ? 1.0 / NT : 1.0 / (P * (double)K * (double)L);
       } else {
         c = 1.0 / (S * (double)L);
       }
     }
     a.seq_coef[b] = (float)c;
-  }
+  });
 }
 
 // ----------------------------------------------------------------------------
@@ -376,7 +399,7 @@ __global__ __launch_bounds__(256) void k_row_prep(RowPrepArgs a) {
   if (a.seq_coef != nullptr) {
     if (block == 0) {
       const CoefArgs c = {a.seq_len, a.group_id, a.seq_kind, a.B, a.G, a.loss_agg, a.group_count, a.seq_coef, a.n_bad_groups};
-      seq_coef_block(c, lds_count);
+      if (a.B <= 256) seq_coef_block<1>(c, lds_count); else seq_coef_block<kCoefSteps>(c, lds_count);
       return;
     }
     --block;

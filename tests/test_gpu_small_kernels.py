@@ -1,5 +1,5 @@
-"""Advantages and word alignment where their kernels change path: batches at the size up to which a wave
-remembers its group's entries."""
+"""Advantages, word alignment and the aggregation weights where their kernels change path: batches at the size up to
+which a wave remembers its group's entries, alignment segments, group counts in LDS and in global memory."""
 import numpy as np
 import pytest
 import torch
@@ -78,3 +78,43 @@ def test_alignment_of_a_row_that_ends_below_2_31(mrl):
     # sums of powers of two and halves of them are exact
     assert out.cpu().tolist() == [[-3.0, -12.0, -24.0, -24.0]]
     assert int(bad.item()) == 0
+
+
+@pytest.mark.parametrize("B,T,G,agg", [(300, 3, 4, 0), (2049, 2, 700, 1), (4500, 1, 4096, 0), (9001, 2, 4097, 0), (20000, 1, 20000, 0)])
+def test_sequence_weights_of_many_groups(mrl, B, T, G, agg):
+    """Group counts up to and above the 4096 that fit LDS, steps of sequences that end inside one, empty sequences, auxiliary
+    rows, group ids outside [0, G)."""
+    d, V = 16, 40
+    g = torch.Generator("cuda").manual_seed(B)
+    N = B * T
+    H, W = torch.randn((N, d), device="cuda", generator=g), 0.3 * torch.randn((V, d), device="cuda", generator=g)
+    y = torch.randint(0, V, (N,), device="cuda", generator=g, dtype=torch.int32)
+    mask = (torch.rand(N, device="cuda", generator=g) < 0.7).to(torch.uint8)
+    gid = torch.randint(-1, G + 1, (B,), device="cuda", generator=g, dtype=torch.int32)
+    kind = (torch.rand(B, device="cuda", generator=g) < 0.1).to(torch.uint8)
+    adv = torch.randn(B, device="cuda", generator=g)
+    z = H.double() @ W.double().t()
+    lp = z.gather(1, y.long()[:, None])[:, 0] - torch.logsumexp(z, 1)
+    behav = (lp + 0.1 * (torch.rand(N, device="cuda", generator=g) - 0.5)).float()       # ratios inside the clip range
+    cfg = mrl.LossConfig(kl_beta=0.0, sgt_lambda=0.1, loss_agg=agg, dh_dtype=mrl.F32)
+    out = mrl.grpo_loss_fwd_bwd(H, W, y, mask, behav, None, adv, gid, kind, B, T, G, cfg)
+    st = mrl.read_stats(out["stats"])
+    L = mask.view(B, T).sum(1).double()
+    ok = (gid >= 0) & (gid < G)
+    grpo, aux = (kind == 0) & ok, (kind != 0) & (L > 0)
+    count = torch.bincount(gid[grpo].long(), minlength=G)
+    if agg:
+        c = grpo / L[grpo].sum()
+    else:
+        c = torch.where(grpo, 1.0 / ((count > 0).sum() * count[gid.clamp(0, G - 1).long()].clamp(min=1) * L.clamp(min=1)), 0.0)
+    c = torch.where(aux, 1.0 / (aux.sum() * L.clamp(min=1)), torch.where(grpo, c, 0.0)).double().repeat_interleave(T) * mask
+    k, w = kind.repeat_interleave(T) != 0, torch.exp(lp - behav.double())
+    A = adv.double().repeat_interleave(T)
+    pg, sgt = -(c * w * A)[~k].sum(), -(c * lp)[k].sum()
+    gr = torch.where(k, -0.1 * c, -c * w * A)
+    dz = -gr[:, None] * torch.softmax(z, 1)
+    dz[torch.arange(N, device="cuda"), y.long()] += gr
+    # fp32 sums of at most 40 terms per row, fp64 sums over the rows
+    assert abs(st["loss_pg"] - float(pg)) <= 2e-6 * float((c * w * A.abs()).sum()) and abs(st["loss_sgt"] - float(sgt)) <= 2e-6 * abs(float(sgt))
+    assert float((out["dH"].double() - dz @ W.double()).norm() / (dz @ W.double()).norm()) <= 1e-5
+    assert st["n_scored_tokens"] == int(mask.sum())
