@@ -16,7 +16,7 @@ def mrl():
     return m
 
 
-@pytest.mark.parametrize("B,G,mode", [(63, 5, 1), (1025, 700, 2), (4096, 3, 1), (4097, 3, 1), (9001, 1200, 2)])
+@pytest.mark.parametrize("B,G,mode", [(63, 5, 1), (1025, 700, 2), (4096, 3, 1), (4097, 3, 1), (9001, 1200, 2), (4353, 1, 0), (20000, 5, 2)])
 def test_advantages_remembered_and_scanned(mrl, B, G, mode):
     rng = np.random.default_rng(B)
     gid = rng.integers(-1, G + 1, B).astype(np.int32)            # interleaved; some ids outside [0, G)
