@@ -3,6 +3,8 @@ symbol declared in include/*.h, and rejects bad arguments before touching a devi
 import ctypes
 import os
 import re
+import struct
+import subprocess
 
 import pytest
 
@@ -213,3 +215,33 @@ def test_static_logprobs_argument_errors():
     assert f(one, one, one, None, 1 << 23, 128, 512, 1, one, None, None) == -10   # 8 B per row > 32 MiB
     assert f(one, one, one, None, 1024, 128, 1 << 22, 1, one, None, None) == -10  # partials of one pass > 32 MiB
     assert "scratch" in m.status_string(-10)
+
+
+def _kernel_notes(tmp_path):
+    """The kernel descriptions (name -> {property: value}) of every gfx950 code object in the built library."""
+    blob = open(os.path.join(ROOT, "paper_2605_07244_amd", "libmrl.so"), "rb").read()
+    kernels = {}
+    for at in (x.start() for x in re.finditer(b"__CLANG_OFFLOAD_BUNDLE__", blob)):
+        pos = at + 32
+        for _ in range(struct.unpack_from("<Q", blob, at + 24)[0]):
+            offset, size, n = struct.unpack_from("<QQQ", blob, pos)
+            name = blob[pos + 24:pos + 24 + n]
+            pos += 24 + n
+            if b"gfx950" not in name or size == 0:
+                continue
+            path = tmp_path / "code_object"
+            path.write_bytes(blob[at + offset:at + offset + size])
+            text = subprocess.run(["/opt/rocm/llvm/bin/llvm-readelf", "--notes", str(path)], capture_output=True, text=True, check=True).stdout
+            for part in re.split(r"\n  - ", text)[1:]:
+                props = dict(re.findall(r"^\s*\.(\w+):\s+(\S+)$", part, flags=re.M))
+                if "private_segment_fixed_size" in props:
+                    kernels[re.findall(r"^    \.name:\s+(\S+)$", part, flags=re.M)[0]] = props
+    return kernels
+
+
+def test_no_kernel_uses_scratch_memory(tmp_path):
+    """Spills and address-selected locals: their reloads wait for every vector-memory access issued before them.
+    (k_mfma_rate, the probe of the matrix cores' rate, is no part of any call.)"""
+    kernels = {k: p for k, p in _kernel_notes(tmp_path).items() if "k_mfma_rate" not in k}
+    assert len(kernels) >= 25 and sum("gemm_nt_bf16" in k for k in kernels) == 3
+    assert {k: p["private_segment_fixed_size"] for k, p in kernels.items() if p["private_segment_fixed_size"] != "0"} == {}
