@@ -896,13 +896,15 @@ __global__ __launch_bounds__(NTHREADS, 2) void forward_few_bf16(Params p) {
 // tiles leave idle at the end.  The slices store their accumulators to a scratch area and
 // dw_tail_reduce adds them, slice 0 first, into dW: the result does not depend on execution order.
 // Workgroup b runs on XCD b % 8 whatever else is free, so the plan is made per XCD: a model of
-// the launch (32 compute units per XCD, whole tiles in id order, then the items) gives the time
-// the last item ends for every split and for the unsplit mapping; the best one is taken, and the
-// items are dealt to the XCDs as the model placed them.  (Host code that runs once per launch in
-// microseconds: not optimised, the optimiser takes very long over its nested constant loops.)
+// the launch (32 compute units per XCD, whole tiles in id order, then the items, each on the compute unit
+// that is free first) gives the time the last item ends for every split and for the unsplit mapping; the
+// best one is taken, and the items are dealt to the XCDs as the model placed them.  Host code of every
+// dW launch: an XCD's compute units are free at two times only (those with and without one whole tile
+// more), so the model keeps two groups of them per XCD and fills a group at a time.  With every compute unit
+// on its own, and compiled without optimisation, the plan took 650 us of host time at V = 151936, d = 4096
+// and 490 at V = 32000, d = 2048 (where the launch takes 110 us); now 3 and 1.
 struct DwTailPlan { int m0, rows, split, first[NXCD + 1]; };
-__attribute__((optnone, noinline)) DwTailPlan dw_tail_plan(int Mt, int Nt, int sup_m, int sup_n) {
-  constexpr int kCus = 32;                       // per XCD
+DwTailPlan dw_tail_plan(int Mt, int Nt, int sup_m, int sup_n) {
   constexpr double kItemOverhead = 0.02;         // prologue, partial-tile store, reduce: in tile times
   DwTailPlan best = {Mt / sup_m * sup_m, Mt % sup_m, 0, {}};
   const int tiles = best.rows * Nt;
@@ -920,25 +922,35 @@ __attribute__((optnone, noinline)) DwTailPlan dw_tail_plan(int Mt, int Nt, int s
   int t_all[NXCD], t_main[NXCD];
   tiles_per_xcd(Mt, t_all);
   tiles_per_xcd(best.m0, t_main);
-  double unsplit = 0;
-  for (int x = 0; x < NXCD; ++x) { const double e = (t_all[x] + kCus - 1) / kCus; unsplit = e > unsplit ? e : unsplit; }
+  double unsplit = 0, whole_end = 0;
+  for (int x = 0; x < NXCD; ++x) {
+    const double all = (t_all[x] + kXcdCus - 1) / kXcdCus, main = (t_main[x] + kXcdCus - 1) / kXcdCus;
+    unsplit = all > unsplit ? all : unsplit;
+    whole_end = main > whole_end ? main : whole_end;
+  }
   double best_end = unsplit - kItemOverhead;     // a split has to beat the plain mapping by a margin
   for (int split = 2; split <= 8 && tiles * split <= kDwTailMaxItems; ++split) {
-    // free[x][c]: when compute unit c of XCD x has finished its whole tiles
-    double free_at[NXCD][kCus];
-    for (int x = 0; x < NXCD; ++x)
-      for (int c = 0; c < kCus; ++c) free_at[x][c] = t_main[x] / kCus + (c < t_main[x] % kCus ? 1 : 0);
+    struct Group { double free_at; int units, left; };   // `left` of the units have not taken an item at this time yet
+    Group group[2 * NXCD];
+    for (int x = 0; x < NXCD; ++x) {
+      const int more = t_main[x] % kXcdCus;
+      const double base = t_main[x] / kXcdCus;
+      group[2 * x] = {base, kXcdCus - more, kXcdCus - more};
+      group[2 * x + 1] = {base + 1, more, more};
+    }
     int count[NXCD] = {};
-    double end = 0;
-    for (int x = 0; x < NXCD; ++x) for (int c = 0; c < kCus; ++c) end = free_at[x][c] > end ? free_at[x][c] : end;
-    for (int i = 0; i < tiles * split; ++i) {
-      int bx = 0, bc = 0;
-      for (int x = 0; x < NXCD; ++x)
-        for (int c = 0; c < kCus; ++c)
-          if (free_at[x][c] < free_at[bx][bc]) { bx = x; bc = c; }
-      free_at[bx][bc] += 1.0 / split + kItemOverhead;
-      end = free_at[bx][bc] > end ? free_at[bx][bc] : end;
-      count[bx]++;
+    double end = whole_end;
+    for (int items = tiles * split; items > 0;) {
+      int f = 0;                                 // free first (units - more is at least 1: group 0 is never empty)
+      for (int i = 1; i < 2 * NXCD; ++i)
+        if (group[i].units > 0 && group[i].free_at < group[f].free_at) f = i;
+      const int n = items < group[f].left ? items : group[f].left;
+      const double ends = group[f].free_at + (1.0 / split + kItemOverhead);
+      end = ends > end ? ends : end;
+      count[f / 2] += n;
+      items -= n;
+      group[f].left -= n;
+      if (group[f].left == 0) { group[f].free_at = ends; group[f].left = group[f].units; }
     }
     if (end < best_end - 1e-9) {
       best_end = end; best.split = split; best.first[0] = 0;

@@ -5,7 +5,9 @@ import os
 import re
 import struct
 import subprocess
+import time
 
+import numpy as np
 import pytest
 
 import paper_2605_07244_amd as m
@@ -177,6 +179,56 @@ def test_dw_tail_plan_host_logic():
     # the benchmark shapes: V = 151936 leaves two ragged tile rows
     assert f(151936, 4096, out) == 0 and (out[0], out[1], out[2]) == (592, 2, 8) and list(out[3:12]) == list(range(0, 257, 32))
     assert f(151936, 1536, out) == 0 and out[2] >= 2 and out[11] == 12 * out[2]
+
+
+def _modelled_tail_plan(V, d):
+    """The dW tail plan from its definition: every compute unit by itself, each item on the one that is free first."""
+    Mt, Nt = -(-V // 256), -(-d // 256)
+    sup_m, sup_n = (8, 4) if Nt % 4 == 0 else (16, 1) if Nt == 1 else (8, 2)
+    rows = Mt % sup_m
+    m0, tiles, cols = Mt - rows, rows * Nt, -(-Nt // sup_n)
+    plan = [m0, rows, 0] + [0] * 9
+    if tiles == 0 or m0 == 0:
+        return plan
+
+    def per_xcd(rows_m):
+        t = [0] * 8
+        for s in range(-(-rows_m // sup_m) * cols):
+            t[s % 8] += min(sup_m, rows_m - s // cols * sup_m) * min(sup_n, Nt - s % cols * sup_n)
+        return t
+
+    best = max(-(-t // 32) for t in per_xcd(Mt)) - 0.02
+    whole = per_xcd(m0)
+    for split in range(2, 9):
+        if tiles * split > 256:
+            break
+        free = np.array([[t // 32 + (c < t % 32) for c in range(32)] for t in whole], dtype=np.float64)
+        end, count = free.max(), [0] * 8
+        for _ in range(tiles * split):
+            x, c = divmod(int(free.argmin()), 32)
+            free[x, c] += 1.0 / split + 0.02
+            end = max(end, free[x, c])
+            count[x] += 1
+        if end < best - 1e-9:
+            best = end
+            plan[2:] = [split] + [sum(count[:x]) for x in range(9)]
+    return plan
+
+
+def test_dw_tail_plan_is_the_modelled_one_and_cheap():
+    f = m.lib().mrl_diag_dw_tail_plan
+    out = (ctypes.c_int32 * 12)()
+    for V in (2100, 4099, 8333, 32000, 50257, 128256, 151936):
+        for d in (64, 512, 712, 1536, 2048, 3584, 4096):
+            assert f(V, d, out) == 0 and list(out) == _modelled_tail_plan(V, d), (V, d)
+    # it runs on the host in every dW launch, the shortest of which take some 100 us: a few microseconds, and
+    # here at most a twentieth of what one unit after the other took
+    took = []
+    for _ in range(20):
+        t = time.perf_counter()
+        f(151936, 4096, out)
+        took.append(time.perf_counter() - t)
+    assert min(took) < 35e-6
 
 
 def test_thl_word_align_argument_errors():
