@@ -153,6 +153,17 @@ __host__ __device__ inline int dh_split(int tail_tiles, int panels, int max_item
 }
 // panels per slice: an even number (the K loop's body is two panels)
 __host__ __device__ inline int slice_panels(int panels, int split) { return ((panels + split - 1) / split + 1) & ~1; }
+// slices that have any panels: the dW plan does not know the scored rows, and 6 panels make three slices of the
+// planned 8.  (No panels at all: the first slice stores the zeros of an overwriting launch.)
+__device__ inline int slices_in_use(int panels, int split) {
+  const int per = slice_panels(panels, split);
+  return panels > 0 ? (panels + per - 1) / per : 1;
+}
+// panels of the dW contraction: the pass's valid rows, rounded up to panel pairs
+__device__ inline int dw_panels(int nvalid, int chunk_rows) {
+  const int k = (nvalid + 2 * BK - 1) / (2 * BK) * (2 * BK);
+  return (k < chunk_rows ? k : chunk_rows) / BK;
+}
 
 // Workgroup -> tile mapping of the dW launch (its tile counts do not depend on the scored rows):
 // sup_m x sup_n consecutive workgroups of one XCD form a super-tile (each A panel is used by sup_n
@@ -323,7 +334,7 @@ __global__ __launch_bounds__(NTHREADS) void gemm_nt_bf16(Params p) {
   int M = p.M, N = p.N, K = p.K;
   if (MODE == MODE_FWD) N = nvalid;
   if (MODE == MODE_DH) M = nvalid;
-  if (MODE == MODE_DW) { int kv = (nvalid + 2 * BK - 1) / (2 * BK) * (2 * BK); K = kv < K ? kv : K; }
+  if (MODE == MODE_DW) K = dw_panels(nvalid, K) * BK;
   if (MODE == MODE_FWD && nvalid == 0) return;
   if (MODE == MODE_DH && nvalid == 0) return;
   if (MODE == MODE_DW && nvalid == 0 && !p.overwrite) return;
@@ -370,10 +381,9 @@ __global__ __launch_bounds__(NTHREADS) void gemm_nt_bf16(Params p) {
       const int slice = item / tiles, t = item % tiles;
       sm = t / Nt; sn = t % Nt;
       tm = p.tail_m0 + sm; tn = sn;
-      // slices of an even number of panels (the loop body is two panels)
-      const int nk_all = K / BK;
-      const int per = ((nk_all + p.tail_split - 1) / p.tail_split + 1) & ~1;
+      const int nk_all = K / BK, per = slice_panels(nk_all, p.tail_split);
       k_first = slice * per;
+      if (slice >= slices_in_use(nk_all, p.tail_split)) return;   // empty: nothing to store, and nobody reads it
       const int k_end = k_first + per < nk_all ? k_first + per : nk_all;
       K = k_end > k_first ? (k_end - k_first) * BK : 0;
       tail_out = p.tail_part + (int64_t)item * (BM * BN);
@@ -963,15 +973,18 @@ DwTailPlan dw_tail_plan(int Mt, int Nt, int sup_m, int sup_n) {
 __global__ __launch_bounds__(256) void dw_tail_reduce(const float* __restrict__ part, int tiles, int split, int Nt,
                                                       int tail_m0, int V, int d, float* __restrict__ dW,
                                                       int overwrite, const int64_t* __restrict__ n_scored,
-                                                      int64_t chunk_start) {
-  if (!overwrite && *n_scored - chunk_start <= 0) return;   // the GEMM launch left dW (and part) alone
+                                                      int64_t chunk_start, int chunk_rows) {
+  int64_t nv64 = *n_scored - chunk_start;
+  const int nvalid = nv64 < 0 ? 0 : (nv64 > chunk_rows ? chunk_rows : (int)nv64);
+  if (!overwrite && nvalid == 0) return;              // the GEMM launch left dW (and part) alone
   const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
   const int t = (int)(q / (BM * BN)), within = (int)(q % (BM * BN));
   if (t >= tiles) return;
   const int v = (tail_m0 + t / Nt) * BM + within / BN, n = (t % Nt) * BN + within % BN;
   if (v >= V || n >= d) return;
   float s = 0.f;
-  for (int k = 0; k < split; ++k) s += part[((int64_t)k * tiles + t) * (BM * BN) + within];
+  const int slices = slices_in_use(dw_panels(nvalid, chunk_rows), split);
+  for (int k = 0; k < slices; ++k) s += part[((int64_t)k * tiles + t) * (BM * BN) + within];
   float* out = dW + (int64_t)v * d + n;
   *out = overwrite ? s : *out + s;
 }
@@ -1040,7 +1053,8 @@ void launch(Params& p, hipStream_t stream) {
   if (tail.split > 0) {
     const int tiles = tail.rows * Nt;
     hipLaunchKernelGGL(dw_tail_reduce, dim3(tiles * (BM * BN / 256)), dim3(256), 0, stream, p.tail_part, tiles,
-                       tail.split, Nt, tail.m0, p.V, p.d, p.dW, p.overwrite, p.n_scored, p.chunk_start);
+                       tail.split, Nt, tail.m0, p.V, p.d, p.dW, p.overwrite, p.n_scored, p.chunk_start,
+                       p.chunk_rows);
   }
   if (MODE == MODE_DH) {
     const int most = Mt * Nt < kRound ? Mt * Nt : kRound - 1;

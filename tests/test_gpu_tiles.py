@@ -46,8 +46,9 @@ def test_forward_tiles_cover_scored_rows(mrl, N, scored, d, V):
     assert torch.all(logp[mask == 0] == 0) and torch.all(lse[mask == 0] == 0)
 
 
-def _step(mrl, H, W, y, mask, dh_dtype, seed, chunk_rows=0):
-    """One loss step of a single sequence (its tokens' advantages and traces random) and the same in float64."""
+def _step(mrl, H, W, y, mask, dh_dtype, seed, chunk_rows=0, poison=False):
+    """One loss step of a single sequence (its tokens' advantages and traces random) and the same in float64.
+    poison: the workspace holds NaN before the call."""
     g = torch.Generator("cuda").manual_seed(seed)
     N, d = H.shape
     V = W.shape[0]
@@ -59,8 +60,12 @@ def _step(mrl, H, W, y, mask, dh_dtype, seed, chunk_rows=0):
     behav = torch.zeros(N, device="cuda")
     behav[rows] = (lp + 0.05 * torch.randn(rows.numel(), device="cuda", generator=g)).float()
     cfg = mrl.LossConfig(kl_beta=0.0, dh_dtype=dh_dtype, chunk_rows=chunk_rows)
+    ws = None
+    if poison:
+        code = mrl.F32 if H.dtype == torch.float32 else mrl.BF16
+        ws = torch.full((mrl.grpo_loss_workspace(1, N, d, V, code, cfg),), 255, dtype=torch.uint8, device="cuda")
     one = lambda v, t: torch.tensor([v], dtype=t, device="cuda")
-    out = mrl.grpo_loss_fwd_bwd(H, W, y, mask, behav, None, one(0.7, torch.float32), one(0, torch.int32), None, 1, N, 1, cfg)
+    out = mrl.grpo_loss_fwd_bwd(H, W, y, mask, behav, None, one(0.7, torch.float32), one(0, torch.int32), None, 1, N, 1, cfg, workspace=ws)
     torch.cuda.synchronize()
     w = torch.exp(lp - behav[rows].double())
     gr = torch.where(w <= 1.2, -0.7 * w, 0.0) / rows.numel()          # A > 0: clipped above 1.2
@@ -165,3 +170,15 @@ def test_padded_widths(mrl, N, d, V):
     want_lse = torch.logsumexp(z, 1)
     assert float((lse[ok].double() - want_lse).abs().max()) <= 1e-4
     assert float((logp[ok].double() - (z.gather(1, y[ok].long()[:, None])[:, 0] - want_lse)).abs().max()) <= 1e-4
+
+
+@pytest.mark.parametrize("scored", [1, 129, 327, 700, 1030])
+def test_dw_tail_slices_without_panels(mrl, scored):
+    """The tail of this head is planned as 8 slices; 2, 4, 6, 12 and 18 panels fill 1, 2, 3, 6 and 5 of them.  The others store
+    nothing and are not read: the scratch holds NaN before."""
+    d, V = 1024, 16405
+    assert mrl.dw_tail_plan(V, d)["split"] == 8
+    H, W, y, mask = _head(scored + 3, d, V, scored, scored)
+    out, dH, dW = _step(mrl, H, W, y, mask, mrl.BF16, scored, poison=True)
+    util.check_gradient("dW", util.to_f64(out["dW"]), dW)
+    util.check_gradient("dH", util.to_f64(out["dH"]), dH)
