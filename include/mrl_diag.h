@@ -66,6 +66,15 @@ int mrl_probe_mfma_rate(int32_t random_operands, double seconds, void* scratch /
  * ---------------------------------------------------------------------- */
 int mrl_diag_dw_tail_plan(int32_t V, int32_t d, int32_t* out12 /*host*/);
 
+/* ------------------------------------------------------------------------
+ * The slices of the contraction that each of the tail_tiles (1 .. 255) tiles of
+ * the dH launch's last, incomplete round of 256 is cut into (1: left whole), for
+ * a contraction of `panels` panels of 64 and scratch for max_items partial tiles:
+ * the function that the launch and its reduction evaluate on the device (host
+ * code here, no GPU call).  Errors: MRL_ERR_SHAPE.
+ * ---------------------------------------------------------------------- */
+int mrl_diag_dh_split(int32_t tail_tiles, int32_t panels, int32_t max_items);
+
 #ifdef __cplusplus
 }
 #endif

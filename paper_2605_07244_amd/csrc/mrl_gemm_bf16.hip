@@ -135,19 +135,19 @@ __device__ inline bool dealt_tile(int bid, int Mt, int Nt, int& tm, int& tn) {
 // accumulators to a scratch area; dh_tail_reduce adds them in slice order.  A dH tile is long (2374
 // panels at V = 151936, about 2.4 ms), so an idle compute unit in that round costs more than
 // writing and adding the partial tiles (256 KB per item): 327 rows at d = 4096 are 32 tiles.
-// The slice count is the one whose rounds of items end earliest, kItemCost covering an item's
-// prologue, partial store and share of the reduce.  Measured (launch and reduce, V = 151936; before:
+// The slice count is the one whose rounds of items end earliest, 1 / kItemCostInv of a tile covering an item's
+// prologue, partial store and share of the reduce.  In whole numbers: the launch and the reduction each work
+// it out on the device and have to come to the same answer.  Measured (launch and reduce, V = 151936; before:
 // whole tiles and a transposed copy of W in front): 327 rows, d = 4096, 32 tiles: 3480 -> 527 us;
 // 5120 rows, d = 1536, 120 tiles: 3251 -> 1720 us; 47360 rows, d = 3584, 2590 tiles: 39.1 -> 35.9 ms.
 constexpr int kMinSlicePanels = 16;
 __host__ __device__ inline int dh_split(int tail_tiles, int panels, int max_items) {
-  constexpr float kItemCost = 0.02f;
-  int best = 1;
-  float best_end = 1.f;
+  constexpr int kItemCostInv = 50;
+  int best = 1, best_num = 1, best_den = 1;        // when the last item ends, in tiles: rounds * (1 / s + 1 / kItemCostInv)
   for (int s = 2; s <= 64 && s * kMinSlicePanels <= panels && s * tail_tiles <= max_items; ++s) {
     const int rounds = (tail_tiles * s + kRound - 1) / kRound;
-    const float end = rounds * (1.f / s + kItemCost);
-    if (end < best_end) { best_end = end; best = s; }
+    const int num = rounds * (kItemCostInv + s), den = kItemCostInv * s;   // (cross products below 2^25)
+    if (num * best_den < best_num * den) { best_num = num; best_den = den; best = s; }
   }
   return best;
 }
@@ -1124,6 +1124,12 @@ void launch_gemm_dw_bf16(const void* E, int64_t lde, const void* Ht, int64_t ldh
 }
 
 }  // namespace mrl
+
+extern "C" int mrl_diag_dh_split(int32_t tail_tiles, int32_t panels, int32_t max_items) {
+  using namespace mrl;
+  if (tail_tiles <= 0 || tail_tiles >= kRound || panels <= 0 || max_items < tail_tiles) return MRL_ERR_SHAPE;
+  return dh_split(tail_tiles, panels, max_items);
+}
 
 extern "C" int mrl_diag_dw_tail_plan(int32_t V, int32_t d, int32_t* out12) {
   using namespace mrl;

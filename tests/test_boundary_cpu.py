@@ -231,6 +231,23 @@ def test_dw_tail_plan_is_the_modelled_one_and_cheap():
     assert min(took) < 35e-6
 
 
+def test_dh_split_is_the_earliest_end():
+    """Slices of the dH launch's last round: the smallest count whose rounds of 256 items end earliest (an item costs its share
+    and a fiftieth of a tile), no slice below 16 panels, no more items than the scratch holds."""
+    from fractions import Fraction
+    f = m.lib().mrl_diag_dh_split
+    assert f(0, 100, 256) == -2 and f(256, 100, 256) == -2 and f(1, 0, 256) == -2 and f(10, 100, 9) == -2
+    for tiles in list(range(1, 34)) + [64, 85, 86, 120, 127, 128, 129, 200, 254, 255]:
+        for panels in (2, 16, 31, 32, 48, 160, 782, 1023, 1024, 2374, 4096):
+            for room in (256, 300, 512, 777, 1024):
+                best, end = 1, Fraction(1)
+                for s in range(2, min(64, panels // 16, room // tiles) + 1):
+                    e = -(-tiles * s // 256) * (Fraction(1, s) + Fraction(1, 50))
+                    if e < end:
+                        best, end = s, e
+                assert f(tiles, panels, room) == best, (tiles, panels, room)
+
+
 def test_thl_word_align_argument_errors():
     f = m.lib().mrl_thl_word_align
     args = lambda **kw: [kw.get("p0", FAKE), FAKE, FAKE, FAKE, FAKE, FAKE, FAKE, kw.get("B", 4), kw.get("S", 16), 16,
