@@ -118,3 +118,18 @@ def test_sequence_weights_of_many_groups(mrl, B, T, G, agg):
     assert abs(st["loss_pg"] - float(pg)) <= 2e-6 * float((c * w * A.abs()).sum()) and abs(st["loss_sgt"] - float(sgt)) <= 2e-6 * abs(float(sgt))
     assert float((out["dH"].double() - dz @ W.double()).norm() / (dz @ W.double()).norm()) <= 1e-5
     assert st["n_scored_tokens"] == int(mask.sum())
+
+
+def test_alignment_of_values_outside_the_range(mrl):
+    """Log-probs of 2^31 and more in magnitude and infinities saturate the 64-bit fixed point, NaN counts as 0; the other
+    words of the row and the other rows are what they are without them."""
+    odd = [-float("inf"), float("inf"), float("nan"), -1e20, 1e20, -2.0 ** 31, -3e38, 2.0 ** 31]
+    n = len(odd)
+    lp = torch.full((2, n + 2), -0.75, device="cuda")
+    lp[0, 1:n + 1] = torch.tensor(odd, device="cuda")
+    ones, ids = torch.ones((2, n + 2), dtype=torch.uint8, device="cuda"), torch.arange(n + 2, dtype=torch.int32, device="cuda").repeat(2, 1)
+    length = torch.full((2,), n + 2, dtype=torch.int32, device="cuda")
+    out, bad = mrl.thl_word_align(lp, ones, ids, length, ones, ids, length, n + 2)
+    big = 2.0 ** 31
+    assert out.cpu().tolist() == [[-0.75, -big, big, 0.0, -big, big, -big, -big, big, -0.75], [-0.75] * (n + 2)]
+    assert int(bad.item()) == 0

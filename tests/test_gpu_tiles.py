@@ -118,10 +118,12 @@ def test_compaction_paths(mrl, N):
         assert not ok.any() or float((got[ok].double() - ref).abs().max()) <= 2e-5
 
 
-@pytest.mark.parametrize("N,d,V", [(1, 1, 3), (17, 3, 33), (40, 5, 16), (100, 64, 512), (530, 66, 515), (600, 71, 1000)])
+@pytest.mark.parametrize("N,d,V", [(1, 1, 3), (17, 3, 33), (40, 5, 16), (100, 64, 512), (530, 66, 515), (600, 71, 1000),
+                                   (1000, 515, 1001), (1030, 520, 1100)])
 def test_fp32_tiles_and_odd_widths(mrl, N, d, V):
-    """fp32 products: K below, at and beside a multiple of 4 and of the 16-wide step, single tiles and the 32 x 32 tile's
-    range (530 x 515 and 600 x 1000 outputs), ragged edges on every side."""
+    """fp32 products: K below, at and beside a multiple of 4 and of the 16-wide step, single tiles, ragged edges on every side.
+    The 32 x 32 tile starts at 512 tiles (rows rounded up to 256): the forward product of 600 x 1000 outputs runs on it, 530 x
+    515 (24 x 17 tiles) does not, and all three products of the last two shapes do."""
     g = torch.Generator("cuda").manual_seed(d)
     H = torch.randn((N, d), device="cuda", generator=g)
     W = 0.2 * torch.randn((V, d), device="cuda", generator=g)
@@ -132,7 +134,7 @@ def test_fp32_tiles_and_odd_widths(mrl, N, d, V):
     ok = mask == 1
     z = H[ok].double() @ W.double().t()
     want = z.gather(1, y[ok].long()[:, None])[:, 0] - torch.logsumexp(z, 1)
-    # at most 1000 fp32 terms per sum: sqrt(1000) * 2^-24 relative, a hundred times below the bars
+    # at most 1100 fp32 terms per sum: sqrt(1100) * 2^-24 relative, a hundred times below the bars
     assert float((out["logp"][ok].double() - want).abs().max()) <= util.F32_LOGP_TOL
     for name, got, ref in (("dH", out["dH"], dH), ("dW", out["dW"], dW)):
         assert util.rel_fro(util.to_f64(got), ref) <= 1e-5 or np.linalg.norm(ref) < 1e-12, name
@@ -182,3 +184,57 @@ def test_dw_tail_slices_without_panels(mrl, scored):
     out, dH, dW = _step(mrl, H, W, y, mask, mrl.BF16, scored, poison=True)
     util.check_gradient("dW", util.to_f64(out["dW"]), dW)
     util.check_gradient("dH", util.to_f64(out["dH"]), dH)
+
+
+@pytest.mark.parametrize("N,d,V", [(100, 64, 512), (1000, 515, 1001)])
+def test_fp32_one_gradient_alone(mrl, N, d, V):
+    """dH or dW alone: the launches of their own, on 16 x 16 and 32 x 32 tiles, give the bits of the call for both (which
+    shares a launch at the smaller shape)."""
+    g = torch.Generator("cuda").manual_seed(V)
+    H, W = torch.randn((N, d), device="cuda", generator=g), 0.2 * torch.randn((V, d), device="cuda", generator=g)
+    y = torch.randint(0, V, (N,), device="cuda", generator=g, dtype=torch.int32)
+    mask = torch.ones(N, dtype=torch.uint8, device="cuda")
+    behav = torch.full((N,), -6.0, device="cuda")
+    adv, gid = torch.tensor([0.5], device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda")
+    cfg = mrl.LossConfig(kl_beta=0.0, dh_dtype=mrl.F32)
+    call = lambda **kw: mrl.grpo_loss_fwd_bwd(H, W, y, mask, behav, None, adv, gid, None, 1, N, 1, cfg, **kw)
+    both, only_h, only_w = call(), call(want_dW=False), call(want_dH=False)
+    torch.cuda.synchronize()
+    assert torch.equal(both["dH"], only_h["dH"]) and torch.equal(both["dW"], only_w["dW"])
+    assert only_h["dW"] is None and only_w["dH"] is None and float(both["dH"].abs().max()) > 0
+
+
+@pytest.mark.parametrize("N,d,V", [(4200, 192, 900), (4200, 200, 900), (300, 136, 700)])
+def test_gradients_of_padded_widths(mrl, N, d, V):
+    """Both gradients beside the head's zero-padded tail (rows of whole lines above 4096 rows, any rows below) and its full copy."""
+    H, W, y, mask = _head(N, d, V, N - 5, d)
+    out, dH, dW = _step(mrl, H, W, y, mask, mrl.BF16, d, poison=True)
+    util.check_gradient("dH", util.to_f64(out["dH"]), dH)
+    util.check_gradient("dW", util.to_f64(out["dW"]), dW)
+
+
+@pytest.mark.parametrize("N,scored,chunk_rows", [
+    (16500, 16500, 0),            # forward parts of 16384 and 256 rows, the second with 116 valid ones
+    (16500, 9000, 0),             # ... and with none
+    (16640, 16640, 0),            # ... and with all 256
+    (700, 650, 256),              # three passes of at most 256 rows, the last with 138
+])
+def test_few_rows_behind_others(mrl, N, scored, chunk_rows):
+    """The forward kernel of at most 256 rows as the last part of a larger pass (rows, partial sums and stash at an offset, the
+    partials' stride that of the pass), and as every pass of a call."""
+    d, V = 64, 600
+    H, W, y, mask = _head(N, d, V, scored, N + scored)
+    out, dH, dW = _step(mrl, H, W, y, mask, mrl.BF16, scored, chunk_rows=chunk_rows, poison=True)
+    logp, lse, ent = mrl.token_scores(H, W, y, mask)
+    torch.cuda.synchronize()
+    ok = mask == 1
+    z = H[ok].double() @ W.double().t()
+    want_lse = torch.logsumexp(z, 1)
+    want = z.gather(1, y[ok].long()[:, None])[:, 0] - want_lse
+    want_ent = want_lse - (torch.softmax(z, 1) * z).sum(1)
+    # fp32 sums of 600 exponentials and 64 products: far below the bar
+    for got, ref in ((logp, want), (lse, want_lse), (ent, want_ent), (out["logp"], want)):
+        assert float((got[ok].double() - ref).abs().max()) <= 1e-4 and torch.all(got[~ok] == 0)
+    util.check_gradient("dH", util.to_f64(out["dH"]), dH)
+    util.check_gradient("dW", util.to_f64(out["dW"]), dW)
+    assert torch.all(out["dH"][~ok] == 0)
