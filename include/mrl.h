@@ -32,8 +32,8 @@
  *     the bf16 MFMA units with fp32 accumulation; d must be a multiple of 8 (rows of 16-byte
  *     vectors).  Widths that are not a multiple of 128 run on zero-padded copies of the operands
  *     (a little extra workspace and time); multiples of 256 use the matrix cores best.
- *     dtype MRL_F32: hidden / lm_head_w are float, plain fp32 arithmetic (a
- *     small-shape sanity path, not tuned); any d >= 1.
+ *     dtype MRL_F32: hidden / lm_head_w are float, fp32 products and sums (a path for small
+ *     shapes: the logits of a pass are materialised); any d >= 1.
  *   - Only gfx950 devices are supported; there is no fallback path.
  */
 #ifndef MRL_H

@@ -255,7 +255,7 @@ def grpo_loss_workspace(B: int, T: int, d: int, V: int, dtype: int, cfg: LossCon
 def grpo_loss_fwd_bwd(hidden, lm_head_w, target_ids, token_mask, behav_logp, ref_logp, seq_adv, group_id,
                       seq_kind, B, T, G, cfg: LossConfig, out_dH=None, out_dW=None, want_dH=True, want_dW=True,
                       workspace=None, out_logp=None, out_stats=None):
-    """mrl_grpo_loss_fwd_bwd.  Returns dict(logp, dH, dW, stats_tensor); `read_stats`
+    """mrl_grpo_loss_fwd_bwd.  Returns dict(logp, dH, dW, stats); `read_stats`
     turns the device stats block into a Python dict (synchronises)."""
     N, d = hidden.shape
     if N != B * T:

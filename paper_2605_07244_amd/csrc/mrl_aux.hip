@@ -726,8 +726,9 @@ __global__ __launch_bounds__(256) void k_convert_f32(float* ZP, int64_t ldz, con
 }
 
 // ----------------------------------------------------------------------------
-// Row copy with zero padding: Out[r][0:dp] = In[r][0:d] | 0, for the last 128 columns of a W whose width is
-// no multiple of the forward kernel's 128-wide panel pairs (or all of a W narrower than that).
+// Row copy with zero padding: Out[r][0:dp] = In[r][0:d] | 0, for a W whose width is no multiple of the forward
+// kernel's 128-wide panel pairs: its last 128 columns, or all of it where it is narrower than that or its
+// rows are no whole lines and the pass is long (head_tail_only in mrl_api.hip).
 // ----------------------------------------------------------------------------
 constexpr int PAD_VECTORS = 4;                          // 16-byte vectors per thread
 __global__ __launch_bounds__(256) void k_pad_rows_b16(const uint16_t* in, int64_t ld_in, uint16_t* out, int64_t ld_out,

@@ -541,7 +541,7 @@ __global__ __launch_bounds__(NTHREADS) void gemm_nt_bf16(Params p) {
   };
   // DH: the wave's 16 rows of W in the panel being loaded, as a buffer descriptor that ends with row
   // V - 1: the contraction runs over the vocabulary rounded up to whole panel pairs, and loads
-  // beyond the descriptor's end return zeros (the stash columns there are zeros as well).  b_advance
+  // beyond the descriptor's end return zeros (the stash columns there are zeros as well).  w_advance
   // moves it on by a panel.
   uint64_t w_addr = 0;
   int w_left = 0;                                     // rows of W from the wave's first one on
@@ -794,11 +794,14 @@ __global__ __launch_bounds__(NTHREADS) void gemm_nt_bf16(Params p) {
 // streams in and by its last round: 594 tiles of 256 x 256 are three rounds of 256 for 2.3 rounds'
 // work, and one workgroup per compute unit has one panel of W in flight and nothing to do behind its
 // epilogue.  Tiles half as high and three stages of 32 K-elements let two workgroups share a compute
-// unit (72.5 KB of LDS, 208 registers).  Forward launch, 256 x 256 tiles and these: V = 151936, d = 4096, 64
-// rows 426 and 395 us, 256 rows 464 and 457; d = 1536 189 and 169, 212 and 198; V = 32000, d = 2048 70 and
-// 55, 85 and 64.  The line lies at one tile column because a panel-load byte buys half the products here
-// (24 KB per 512 MFMA cycles, more than the 43.5 bytes per clock a compute unit's load path delivers):
-// from two columns on the large tile wins (512 rows, d = 4096: 606 against 697 us).
+// unit (72.5 KB of LDS, 208 registers); waves without tokens only load their share.  Scoring call, 256 x 256
+// tiles and these, us: V = 151936, d = 4096, 64 rows 367 and 317, 128 rows 377 and 351, 192 rows 387 and 382, 256
+// rows 408 and 422; d = 1536 154 and 133, 158 and 145, 164 and 156, 172 and 167; V = 32000, d = 2048 52.4 and 44.4,
+// 52.2 and 46.6, 52.7 and 50.0, 53.3 and 53.0.  The line lies at one tile column because a panel-load byte buys
+// half the products here (24 KB per 512 MFMA cycles, more than the 43.5 bytes per clock a compute unit's load
+// path delivers): above 192 rows of the widest heads this costs 3 %, and from two columns on the large tile
+// wins everywhere (512 rows, d = 4096: forward launch 606 against 697 us).  The rows that count are slots (rounded up
+// to 256), the scored ones being known on the device only.
 // ---------------------------------------------------------------------------------------------
 constexpr int FM = 128, FN = 256, FK = 32, FSTAGES = 3;
 constexpr int F_A = FM * FK * 2, F_STAGE = (FM + FN) * FK * 2;      // 8 KB of A, 24 KB per stage
@@ -911,7 +914,7 @@ __global__ __launch_bounds__(NTHREADS, 2) void forward_few_bf16(Params p) {
 // best one is taken, and the items are dealt to the XCDs as the model placed them.  Host code of every
 // dW launch: an XCD's compute units are free at two times only (those with and without one whole tile
 // more), so the model keeps two groups of them per XCD and fills a group at a time.  With every compute unit
-// on its own, and compiled without optimisation, the plan took 650 us of host time at V = 151936, d = 4096
+// on its own, and compiled without optimisation, the plan took 680 us of host time at V = 151936, d = 4096
 // and 490 at V = 32000, d = 2048 (where the launch takes 110 us); now 3 and 1.
 struct DwTailPlan { int m0, rows, split, first[NXCD + 1]; };
 DwTailPlan dw_tail_plan(int Mt, int Nt, int sup_m, int sup_n) {

@@ -20,7 +20,7 @@ constexpr double THL_SCALE = 4294967296.0;          // 2^32
 // the wave's run (one exchange through LDS per segment of THL_SEGMENT positions) plus a running
 // scalar and a bit count of the mask ballot; the mask bits stay in a register, one per step.  With
 // ranks exchanged by two barriers per 256 positions in each of three sweeps, fp64 conversions to
-// 64-bit integers and fp64 divisions, 2048 rows took 18.7 us, now 16.6 us (50 MB).
+// 64-bit integers and fp64 divisions, 2048 rows (50 MB) took 18.4 us in the kernel and 20.8 a call, now 16.3 and 17.1.
 constexpr int THL_WAVES = THL_THREADS / 64;
 constexpr int THL_SEGMENT = 32 * THL_THREADS;
 constexpr int THL_INVERSES = 64;
