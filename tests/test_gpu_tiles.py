@@ -79,10 +79,10 @@ def _step(mrl, H, W, y, mask, dh_dtype, seed, chunk_rows=0, poison=False):
 @pytest.mark.parametrize("scored,d,V,dh_f32", [
     (1, 256, 70, 0),              # one tile, a vocabulary shorter than a panel pair
     (300, 136, 1000, 1),          # two tiles of a padded width, too few panels to slice
-    (255, 512, 9001, 0),          # two tiles, eight slices and more
-    (700, 1000, 16500, 1),        # twelve tiles, 21 slices, float output, a width that ends inside a tile
-    (2500, 4096, 4200, 0),        # 160 tiles: more than half a round, slices run in several rounds
-    (4200, 4096, 5003, 0),        # 272 tiles: a whole round and 16 sliced tiles
+    (255, 512, 9001, 0),          # two tiles of eight slices
+    (700, 1000, 16500, 1),        # twelve tiles of 16 slices, float output, a width that ends inside a tile
+    (2500, 4096, 4200, 0),        # 160 tiles: more than half a round, left whole
+    (4200, 4096, 5003, 0),        # 272 tiles: a whole round and 16 tiles of five slices
 ])
 def test_dh_tiles_and_slices(mrl, scored, d, V, dh_f32):
     H, W, y, mask = _head(scored + 37, d, V, scored, scored)
@@ -238,3 +238,27 @@ def test_few_rows_behind_others(mrl, N, scored, chunk_rows):
     util.check_gradient("dH", util.to_f64(out["dH"]), dH)
     util.check_gradient("dW", util.to_f64(out["dW"]), dW)
     assert torch.all(out["dH"][~ok] == 0)
+
+
+def test_dh_slices_in_two_rounds(mrl):
+    """144 tiles of three slices: more items than compute units."""
+    scored, d, V = 2050, 4096, 24000
+    assert mrl.lib().mrl_diag_dh_split(144, 376, 444) == 3     # (444: partial tiles in this head's workspace)
+    H, W, y, mask = _head(scored + 5, d, V, scored, 9)
+    rows = torch.nonzero(mask)[:, 0]
+    z = H[rows].double() @ W.double().t()
+    lse = torch.logsumexp(z, 1)
+    at = torch.arange(scored, device="cuda")
+    lp = z[at, y[rows].long()] - lse
+    behav = torch.zeros(scored + 5, device="cuda")
+    behav[rows] = lp.float()
+    one = lambda v, t: torch.tensor([v], dtype=t, device="cuda")
+    out = mrl.grpo_loss_fwd_bwd(H, W, y, mask, behav, None, one(0.7, torch.float32), one(0, torch.int32), None, 1, scored + 5, 1,
+                                mrl.LossConfig(kl_beta=0.0), want_dW=False)
+    gr = -0.7 * torch.exp(lp - behav[rows].double()) / scored
+    dz = -gr[:, None] * torch.exp(z - lse[:, None])
+    dz[at, y[rows].long()] += gr
+    want = torch.zeros((scored + 5, d), dtype=torch.float64, device="cuda")
+    want[rows] = dz @ W.double()
+    util.check_gradient("dH", util.to_f64(out["dH"]), want.cpu().numpy())
+    assert torch.all(out["dH"][mask == 0] == 0)
