@@ -34,10 +34,12 @@ def test_advantages_remembered_and_scanned(mrl, B, G, mode):
     assert np.all(got[~ok] == 0) and np.all(got[sc == 0] == 0)
 
 
-@pytest.mark.parametrize("B,S_src,S_tgt,one_word", [(3, 1, 1, True), (5, 257, 700, True), (2, 8192, 8193, False), (2, 9100, 10000, False)])
+@pytest.mark.parametrize("B,S_src,S_tgt,one_word", [(3, 1, 1, True), (5, 257, 700, True), (2, 8192, 8193, False), (2, 9100, 10000, False),
+                                                     (7, 63, 65, False), (6, 64, 64, True), (9, 65, 200, True), (6, 256, 256, True),
+                                                     (40, 230, 256, False), (5, 256, 257, False), (5, 257, 250, True)])
 def test_alignment_segments_and_counts(mrl, B, S_src, S_tgt, one_word):
-    """Rows of several segments of 8192 positions, words of 1, 63, 64 and more target tokens, fixed-point rounding of
-    values over the whole range."""
+    """Rows of several segments of 8192 positions, rows of up to and above the 256 positions that a block takes one per
+    thread, words of 1, 63, 64 and more target tokens, fixed-point rounding of values over the whole range."""
     from oracle import thl_oracle
     from workloads import synth
     b = synth.make_thl(B, S_src, S_tgt, seed=S_tgt)
