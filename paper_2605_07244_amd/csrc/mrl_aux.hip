@@ -268,11 +268,13 @@ struct CoefArgs {
   const int32_t* seq_len; const int32_t* group_id; const uint8_t* seq_kind; int64_t B; int G; int loss_agg;
   int32_t* group_count; float* seq_coef; int64_t* n_bad_groups;
 };
-// f(sequence, kind, scored length, group id, of_group(group id)) for the block's sequences (an id outside
-// [0, G) is looked up as 0), the loads of STEPS of them in flight together: one after the other they
-// cost the single block 0.2 us per 256 sequences and loop.  Loss call of 65536 sequences of one token, V = 1024,
-// d = 128: 8192 groups 1494 us, 8 together 1374 (4: 1385), 60000 groups 1559 and 1401 (1419).
-constexpr int kCoefSteps = 8;
+// f(sequence, live, kind, scored length, group id or -1, of_group(group id)) for the block's sequences, the loads of
+// STEPS of them in flight together: one after the other they cost the single block 0.2 us per 256 sequences and
+// loop.  Steps beyond the last sequence see that one again, not live, and f has no branches: with one per
+// step the kernel needed 100 scalar registers, and the blocks that clear dH rows had fewer waves in flight (2^20 slots,
+// 500 scored, d = 64: 421 us a call, now 373).  Loss call of 65536 sequences of one token, V = 1024, d = 128: 8192
+// groups 1494 us one at a time, now 1316, 60000 groups 1559 and 1349.
+constexpr int kCoefSteps = 4;
 template <int STEPS, class Of, class F> __device__ inline void each_sequence(const CoefArgs& a, Of of_group, F f) {
   for (int64_t b0 = threadIdx.x; b0 < a.B; b0 += 256 * STEPS) {
     int kind[STEPS], len[STEPS], group[STEPS], of[STEPS];
@@ -284,10 +286,16 @@ template <int STEPS, class Of, class F> __device__ inline void each_sequence(con
       group[k] = a.group_id[b];
     }
 #pragma unroll
-    for (int k = 0; k < STEPS; ++k) of[k] = of_group(group[k] >= 0 && group[k] < a.G ? group[k] : 0);
+    for (int k = 0; k < STEPS; ++k) {
+      group[k] = group[k] >= 0 && group[k] < a.G ? group[k] : -1;
+      of[k] = of_group(group[k] < 0 ? 0 : group[k]);
+    }
 #pragma unroll
-    for (int k = 0; k < STEPS; ++k)
-      if (b0 + 256 * k < a.B) f(b0 + 256 * k, kind[k], len[k], group[k], of[k]);
+    for (int k = 0; k < STEPS; ++k) {
+      const bool live = b0 + 256 * k < a.B;
+      f(live ? b0 + 256 * k : a.B - 1, live, kind[k], len[k], group[k], of[k]);
+      __builtin_amdgcn_sched_barrier(0);              // (interleaved, they would keep their masks alive together)
+    }
   }
 }
 template <int STEPS>
@@ -303,14 +311,13 @@ __device__ inline void seq_coef_block(const CoefArgs& a, int32_t* lds_count /*[k
   __threadfence();
   __syncthreads();
   long long v[3] = {0, 0, 0};                         // auxiliary rows with tokens, GRPO tokens, bad group ids
-  each_sequence<STEPS>(a, [](int) { return 0; }, [&](int64_t, int kind, int L, int g, int) {
-    const bool ok = g >= 0 && g < a.G;
-    v[2] += !ok;
-    if (kind != 0) v[0] += (L > 0);
-    else if (ok) {
-      if (in_lds) atomicAdd(&lds_count[g], 1); else atomicAdd(&a.group_count[g], 1);
-      v[1] += L;
-    }
+  each_sequence<STEPS>(a, [](int) { return 0; }, [&](int64_t, bool live, int kind, int L, int g, int) {
+    const bool grpo = live && kind == 0 && g >= 0;
+    v[0] += live && kind != 0 && L > 0;
+    v[1] += grpo ? L : 0;
+    v[2] += live && g < 0;
+    const int at = g < 0 ? 0 : g;
+    if (in_lds) atomicAdd(&lds_count[at], (int)grpo); else atomicAdd(&a.group_count[at], (int)grpo);
   });
   __threadfence();
   block_sum3(v, sh);                                  // (its barriers also publish the counts)
@@ -325,16 +332,10 @@ __device__ inline void seq_coef_block(const CoefArgs& a, int32_t* lds_count /*[k
   block_sum3(u, sh);
   if (threadIdx.x == 0) *a.n_bad_groups = v[2];
   const double P = (double)u[0], S = (double)v[0], NT = (double)v[1];
-  each_sequence<STEPS>(a, count, [&](int64_t b, int kind, int L, int g, int K) {
-    double c = 0.0;
-    if (L > 0) {
-      if (kind == 0) {
-        if (g >= 0 && g < a.G) c = a.loss_agg == 1 ? 1.0 / NT : 1.0 / (P * (double)K * (double)L);
-      } else {
-        c = 1.0 / (S * (double)L);
-      }
-    }
-    a.seq_coef[b] = (float)c;
+  each_sequence<STEPS>(a, count, [&](int64_t b, bool, int kind, int L, int g, int K) {
+    const double mean = (kind == 0 ? P * (double)K : S) * (double)L;
+    const double weight = 1.0 / (kind == 0 && a.loss_agg == 1 ? NT : mean);
+    a.seq_coef[b] = L > 0 && (kind != 0 || g >= 0) ? (float)weight : 0.f;   // (the last sequence: the same from all)
   });
 }
 
