@@ -67,27 +67,47 @@ __device__ inline int block_exclusive_scan(int val, int* total) {
   return res;
 }
 
-// scored slots of sequence b, counted by one wave
-__device__ inline void count_sequence(const uint8_t* mask, const int32_t* targets, int64_t b, int64_t B, int T, int V,
-                                      int32_t* seq_len) {
-  if (b >= B) return;
-  const int lane = threadIdx.x & 63;
-  int cnt = 0;
+// Scored slots of the sequences, by blocks of WAVES waves: a wave per sequence, or the block together where a
+// sequence is long, since a wave alone is a chain of T / 256 load latencies.  Loss call of one sequence of 32768 slots
+// (V = 64, d = 8) 817 us by waves, now 707, two of 10^6 slots, 500 scored (V = 1000, d = 64) 5740 and 1930.
+constexpr int kLongSequence = 1024;
+template <int N> struct Stride { static constexpr int value = N; };
+template <int WAVES> __device__ inline void count_sequences(const uint8_t* mask, const int32_t* targets, int64_t block,
+                                                            int64_t B, int T, int V, int32_t* seq_len) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  auto wave_count = [&](int64_t b, int first, auto stride) {
+    int cnt = 0;
 #pragma unroll 4
-  for (int t = lane; t < T; t += 64) cnt += slot_valid(mask, targets, b * T + t, V);
+    for (int t = first; t < T; t += decltype(stride)::value) cnt += slot_valid(mask, targets, b * T + t, V);
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) cnt += __shfl_xor(cnt, off);
-  if (lane == 0) seq_len[b] = cnt;
+    for (int off = 32; off > 0; off >>= 1) cnt += __shfl_xor(cnt, off);
+    return cnt;
+  };
+  if (T > kLongSequence) {
+    __shared__ int part[WAVES];
+    const int cnt = wave_count(block, threadIdx.x, Stride<64 * WAVES>{});
+    if (lane == 0) part[wave] = cnt;
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    int sum = 0;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) sum += part[w];
+    seq_len[block] = sum;
+  } else if (block * WAVES + wave < B) {
+    const int cnt = wave_count(block * WAVES + wave, lane, Stride<64>{});
+    if (lane == 0) seq_len[block * WAVES + wave] = cnt;
+  }
 }
+// blocks the above takes
+inline int64_t sequence_blocks(int64_t B, int T, int waves) { return T > kLongSequence ? B : (B + waves - 1) / waves; }
 
-// Block 0: N <= kPrepOneBlock slots, a contiguous run of them per wave.  Blocks 1 ..: one sequence
-// per wave.
+// Block 0: N <= kPrepOneBlock slots, a contiguous run of them per wave.  Blocks 1 ..: the sequences.
 __global__ __launch_bounds__(kPrepThreads) void k_prep_one(const uint8_t* mask, const int32_t* targets, int N, int V,
                                                            int64_t* n_scored, int64_t* n_bad, int32_t* row_index,
                                                            SlotOutputs zero, int64_t B, int T, int32_t* seq_len) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   if (blockIdx.x > 0) {
-    count_sequence(mask, targets, (int64_t)(blockIdx.x - 1) * kPrepWaves + wave, B, T, V, seq_len);
+    count_sequences<kPrepWaves>(mask, targets, (int64_t)blockIdx.x - 1, B, T, V, seq_len);
     return;
   }
   __shared__ int sums[kPrepWaves], bads[kPrepWaves];
@@ -131,12 +151,12 @@ __global__ __launch_bounds__(kPrepThreads) void k_prep_one(const uint8_t* mask, 
   }
 }
 
-// Blocks below nblocks: counts of their slots.  Blocks from nblocks on: one sequence per wave.
+// Blocks below nblocks: counts of their slots.  Blocks from nblocks on: the sequences.
 __global__ __launch_bounds__(PREP_BLOCK) void k_prep_count(const uint8_t* mask, const int32_t* targets,
                                                           int64_t N, int V, int32_t* block_counts,
                                                           int64_t nblocks, int64_t B, int T, int32_t* seq_len) {
   if (blockIdx.x >= nblocks) {
-    count_sequence(mask, targets, (blockIdx.x - nblocks) * (PREP_BLOCK / 64) + (threadIdx.x >> 6), B, T, V, seq_len);
+    count_sequences<PREP_BLOCK / 64>(mask, targets, (int64_t)blockIdx.x - nblocks, B, T, V, seq_len);
     return;
   }
   const int64_t base = (int64_t)blockIdx.x * PREP_PER_BLOCK + threadIdx.x * PREP_PER_THREAD;
@@ -814,11 +834,11 @@ void launch_prep(const uint8_t* mask, const int32_t* targets, int64_t N, int V, 
   const SlotOutputs zero = {{o.zero[0], o.zero[1], o.zero[2]}};
   const int64_t B = o.seq_len != nullptr ? o.B : 0;
   if (N <= kPrepOneBlock) {
-    hipLaunchKernelGGL(k_prep_one, dim3((unsigned)(1 + (B + kPrepWaves - 1) / kPrepWaves)), dim3(kPrepThreads), 0, stream,
+    hipLaunchKernelGGL(k_prep_one, dim3((unsigned)(1 + sequence_blocks(B, o.T, kPrepWaves))), dim3(kPrepThreads), 0, stream,
                        mask, targets, (int)N, V, o.n_scored, o.n_bad, o.row_index, zero, B, o.T, o.seq_len);
     return;
   }
-  const int64_t nblocks = (N + PREP_PER_BLOCK - 1) / PREP_PER_BLOCK, seq_blocks = (B + PREP_BLOCK / 64 - 1) / (PREP_BLOCK / 64);
+  const int64_t nblocks = (N + PREP_PER_BLOCK - 1) / PREP_PER_BLOCK, seq_blocks = sequence_blocks(B, o.T, PREP_BLOCK / 64);
   // block_counts: [2 * nblocks] int32 counts followed (8-byte aligned) by [nblocks] int64 offsets
   int64_t* block_offsets = reinterpret_cast<int64_t*>(o.block_counts + round_up(2 * nblocks, 2));
   const bool scan = nblocks > kPrepMaxSelf;

@@ -82,10 +82,12 @@ def test_alignment_of_a_row_that_ends_below_2_31(mrl):
     assert int(bad.item()) == 0
 
 
-@pytest.mark.parametrize("B,T,G,agg", [(300, 3, 4, 0), (2049, 2, 700, 1), (4500, 1, 4096, 0), (9001, 2, 4097, 0), (20000, 1, 20000, 0)])
+@pytest.mark.parametrize("B,T,G,agg", [(300, 3, 4, 0), (2049, 2, 700, 1), (4500, 1, 4096, 0), (9001, 2, 4097, 0), (20000, 1, 20000, 0),
+                                       (3, 1024, 2, 0), (3, 1025, 2, 0), (2, 16384, 1, 0), (40, 1024, 4, 1), (33, 1030, 4, 0), (2, 20001, 1, 0)])
 def test_sequence_weights_of_many_groups(mrl, B, T, G, agg):
     """Group counts up to and above the 4096 that fit LDS, steps of sequences that end inside one, empty sequences, auxiliary
-    rows, group ids outside [0, G)."""
+    rows, group ids outside [0, G); sequences counted by a wave (up to 1024 slots) and by a block, in the launch of up to
+    32768 slots and in the one above."""
     d, V = 16, 40
     g = torch.Generator("cuda").manual_seed(B)
     N = B * T
@@ -94,6 +96,7 @@ def test_sequence_weights_of_many_groups(mrl, B, T, G, agg):
     mask = (torch.rand(N, device="cuda", generator=g) < 0.7).to(torch.uint8)
     gid = torch.randint(-1, G + 1, (B,), device="cuda", generator=g, dtype=torch.int32)
     kind = (torch.rand(B, device="cuda", generator=g) < 0.1).to(torch.uint8)
+    gid[0], kind[0], mask[0] = 0, 0, 1                   # one sequence at least has a weight
     adv = torch.randn(B, device="cuda", generator=g)
     z = H.double() @ W.double().t()
     lp = z.gather(1, y.long()[:, None])[:, 0] - torch.logsumexp(z, 1)
@@ -118,7 +121,9 @@ def test_sequence_weights_of_many_groups(mrl, B, T, G, agg):
     dz[torch.arange(N, device="cuda"), y.long()] += gr
     # fp32 sums of at most 40 terms per row, fp64 sums over the rows
     assert abs(st["loss_pg"] - float(pg)) <= 2e-6 * float((c * w * A.abs()).sum()) and abs(st["loss_sgt"] - float(sgt)) <= 2e-6 * abs(float(sgt))
-    assert float((out["dH"].double() - dz @ W.double()).norm() / (dz @ W.double()).norm()) <= 1e-5
+    want = dz @ W.double()
+    error, size = float((out["dH"].double() - want).norm()), float(want.norm())
+    assert 0 < size and error <= 1e-5 * size
     assert st["n_scored_tokens"] == int(mask.sum())
 
 
