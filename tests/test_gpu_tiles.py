@@ -262,3 +262,31 @@ def test_dh_slices_in_two_rounds(mrl):
     want[rows] = dz @ W.double()
     util.check_gradient("dH", util.to_f64(out["dH"]), want.cpu().numpy())
     assert torch.all(out["dH"][mask == 0] == 0)
+
+
+@pytest.mark.parametrize("level", [1, 2])
+def test_fp32_response_ratio_over_passes(mrl, level):
+    """Three fp32 passes, swept last to first for the log-probs: the target logits of all rows come with the first one swept."""
+    B, T, d, V = 40, 130, 24, 90
+    N = B * T
+    g = torch.Generator("cuda").manual_seed(level)
+    H, W = torch.randn((N, d), device="cuda", generator=g), 0.2 * torch.randn((V, d), device="cuda", generator=g)
+    y = torch.randint(0, V, (N,), device="cuda", generator=g, dtype=torch.int32)
+    mask = (torch.rand(N, device="cuda", generator=g) < 0.95).to(torch.uint8)
+    adv, gid = torch.randn(B, device="cuda", generator=g), torch.zeros(B, dtype=torch.int32, device="cuda")
+    z = H.double() @ W.double().t()
+    lp = z.gather(1, y.long()[:, None])[:, 0] - torch.logsumexp(z, 1)
+    behav = (lp + 0.01 * (torch.rand(N, device="cuda", generator=g) - 0.5)).float()      # ratios inside the clip range
+    out = mrl.grpo_loss_fwd_bwd(H, W, y, mask, behav, None, adv, gid, None, B, T, 1,
+                                mrl.LossConfig(kl_beta=0.0, dh_dtype=mrl.F32, ratio_level=level))
+    m = mask.double()
+    L = m.view(B, T).sum(1)
+    expo = ((lp - behav.double()) * m).view(B, T).sum(1) / (L if level == 2 else 1.0)
+    assert float(expo.abs().max()) < 0.18
+    gr = (-(torch.exp(expo) * adv.double()) / (B * (L if level == 2 else 1.0))).repeat_interleave(T) * m
+    dz = -gr[:, None] * torch.softmax(z, 1)
+    dz[torch.arange(N, device="cuda"), y.long()] += gr
+    for name, got, want in (("logp", out["logp"], lp * m), ("dH", out["dH"], dz @ W.double()), ("dW", out["dW"], dz.t() @ H.double())):
+        # fp32 sums of 24, 90 and 4940 terms
+        error, size = float((got.double() - want).norm()), float(want.norm())
+        assert error <= 1e-5 * size, (name, error, size)
