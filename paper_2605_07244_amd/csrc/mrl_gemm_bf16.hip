@@ -151,6 +151,15 @@ __host__ __device__ inline int dh_split(int tail_tiles, int panels, int max_item
   }
   return best;
 }
+// Work items of the last round at most, whatever the scored rows.  Launching what the scratch holds instead made
+// passes without rows slower than before the slices (47 passes of 1024 rows, 3 with rows, V = 705, d = 3040, no hint:
+// 1800 us a call before, 1911 and 1750 on two boxes with them, now 1640), and below 32 panels (V <= 1920) nothing is
+// sliced and the reduction is left out.
+inline int dh_most_split(int panels) { return panels / kMinSlicePanels < 2 ? 1 : (panels / kMinSlicePanels < 64 ? panels / kMinSlicePanels : 64); }
+inline int dh_most_items(int tiles, int panels, int max_items) {
+  const int n = (tiles < kRound ? tiles : kRound - 1) * dh_most_split(panels);
+  return n < max_items ? n : max_items;
+}
 // panels per slice: an even number (the K loop's body is two panels)
 __host__ __device__ inline int slice_panels(int panels, int split) { return ((panels + split - 1) / split + 1) & ~1; }
 // slices that have any panels: the dW plan does not know the scored rows, and 6 panels make three slices of the
@@ -1051,7 +1060,7 @@ void launch(Params& p, hipStream_t stream) {
     p.tail_first[NXCD] = tail.first[NXCD];
     blocks = p.main_blocks + most * NXCD;
   }
-  if (MODE == MODE_DH) blocks = (Mt * Nt) / kRound * kRound + (p.max_items + NXCD - 1) / NXCD * NXCD;
+  if (MODE == MODE_DH) blocks = (Mt * Nt) / kRound * kRound + (int)round_up(dh_most_items(Mt * Nt, p.K / BK, p.max_items), NXCD);
   hipLaunchKernelGGL(gemm_nt_bf16<MODE>, dim3(blocks), dim3(NTHREADS), lds_bytes<MODE>(), stream, p);
   if (tail.split > 0) {
     const int tiles = tail.rows * Nt;
@@ -1059,7 +1068,7 @@ void launch(Params& p, hipStream_t stream) {
                        tail.split, Nt, tail.m0, p.V, p.d, p.dW, p.overwrite, p.n_scored, p.chunk_start,
                        p.chunk_rows);
   }
-  if (MODE == MODE_DH) {
+  if (MODE == MODE_DH && dh_most_split(p.K / BK) > 1) {
     const int most = Mt * Nt < kRound ? Mt * Nt : kRound - 1;
     hipLaunchKernelGGL(dh_tail_reduce, dim3(most * (BM * BN / 2048)), dim3(256), 0, stream, p);
   }
