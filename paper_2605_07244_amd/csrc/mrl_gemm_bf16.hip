@@ -446,7 +446,11 @@ __global__ __launch_bounds__(NTHREADS) void gemm_nt_bf16(Params p) {
       int64_t rowa = ra, rowb = rb;
       if (A_KMAJOR) {
         const int k = 2 * (wave * 8 + ia) + (lane >> 5);  // k row within the panel
-        a_ptr[i] = p.A + ((int64_t)k_first * BK + k) * p.lda + m0 + (((lane & 31) ^ (kswz(k) << 1)) << 3);
+        // (columns from V on, whose products are not stored, come from the tile's first chunk again: the pad
+        // columns of the stash are written past the caches and no other launch reads them, and with few tiles
+        // this one lasts as long as the tile that fetches them: 41444 rows, V = 329, d = 240 924 us, now 671)
+        const int col = m0 + (((lane & 31) ^ (kswz(k) << 1)) << 3);
+        a_ptr[i] = p.A + ((int64_t)k_first * BK + k) * p.lda + (col < p.V ? col : m0);
       } else {
         a_ptr[i] = p.A + rowa * p.lda + lchunk_a * 8 + (MODE == MODE_DH ? k_first * BK : 0);
       }

@@ -290,3 +290,13 @@ def test_fp32_response_ratio_over_passes(mrl, level):
         # fp32 sums of 24, 90 and 4940 terms
         error, size = float((got.double() - want).norm()), float(want.norm())
         assert error <= 1e-5 * size, (name, error, size)
+
+
+@pytest.mark.parametrize("scored,d,V", [(200, 128, 129), (700, 256, 8), (1500, 240, 329), (600, 512, 2057)])
+def test_dw_beside_the_pad_columns(mrl, scored, d, V):
+    """Vocabularies that end in the first chunk of a tile, a chunk behind a 128-wide half and inside one: the launch reads other
+    columns in the pad's place, and the rows of dW do not see it."""
+    H, W, y, mask = _head(scored + 3, d, V, scored, V)
+    out, dH, dW = _step(mrl, H, W, y, mask, mrl.BF16, V, poison=True)
+    util.check_gradient("dW", util.to_f64(out["dW"]), dW)
+    util.check_gradient("dH", util.to_f64(out["dH"]), dH)
