@@ -153,7 +153,7 @@ __host__ __device__ inline int dh_split(int tail_tiles, int panels, int max_item
 }
 // Work items of the last round at most, whatever the scored rows.  Launching what the scratch holds instead made
 // passes without rows slower than before the slices (47 passes of 1024 rows, 3 with rows, V = 705, d = 3040, no hint:
-// 1800 us a call before, 1911 and 1750 on two boxes with them, now 1640), and below 32 panels (V <= 1920) nothing is
+// 1800 us a call before, 1750 - 1911 with them, now 1640), and below 32 panels (V <= 1920) nothing is
 // sliced and the reduction is left out.
 inline int dh_most_split(int panels) { return panels / kMinSlicePanels < 2 ? 1 : (panels / kMinSlicePanels < 64 ? panels / kMinSlicePanels : 64); }
 inline int dh_most_items(int tiles, int panels, int max_items) {
