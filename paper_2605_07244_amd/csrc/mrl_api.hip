@@ -274,14 +274,16 @@ void forward_chunk(const void* H, const void* W, int d, int V, bool bf16, const 
     const void* Wk = padded ? at<void>(ws, L.Wp) : W;
     const void* W_tail = L.dp != d && !padded ? at<void>(ws, L.Wp) : nullptr;
     const int64_t ldw = padded ? L.ldh : d;
+    const bool blocks = rows_in_blocks(L.chunk_rows);
     for (int sub = 0; sub < L.chunk_rows; sub += kFwdSubChunk) {
       const int rows = L.chunk_rows - sub < kFwdSubChunk ? L.chunk_rows - sub : kFwdSubChunk;
       Scope sc(MRL_PROF_GEMM_FWD, s);   // one event pair per kernel launch
-      launch_gemm_fwd_bf16(Wk, ldw, W_tail, at<uint16_t>(ws, L.Hc) + (size_t)sub * L.ldh, L.ldh, L.dp, at<float>(ws, L.zt),
+      launch_gemm_fwd_bf16(Wk, ldw, W_tail, at<uint16_t>(ws, L.Hc) + (size_t)sub * L.ldh, blocks ? L.chunk_rows : L.ldh,
+                           L.dp, at<float>(ws, L.zt),
                            n_scored, c0 + sub, rows, V, d,
                            at<float>(ws, L.part_sum) + sub, entropy ? at<float>(ws, L.part_ez) + sub : nullptr,
                            L.chunk_rows,
-                           stash ? at<uint16_t>(ws, L.Z) + (size_t)sub * L.ldz : nullptr, L.ldz, s);
+                           stash ? at<uint16_t>(ws, L.Z) + (size_t)sub * L.ldz : nullptr, L.ldz, blocks, s);
     }
   } else {
     Scope sc(MRL_PROF_GEMM_FWD, s);

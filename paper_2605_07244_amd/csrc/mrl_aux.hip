@@ -436,11 +436,15 @@ __global__ __launch_bounds__(256) void k_row_prep(RowPrepArgs a) {
   if (BF16) {
     const uint4* h = reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(a.H) + slot * a.d);
     const uint4* w = reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(a.W) + y * a.d);
-    uint4* out = reinterpret_cast<uint4*>(static_cast<uint16_t*>(a.Hc) + r * a.ldh);
+    // the row's vectors, side by side or in blocks of kRowBlock columns
+    const bool blocks = rows_in_blocks(a.chunk_rows);
+    uint4* const out = static_cast<uint4*>(a.Hc) + r * (blocks ? kRowBlock / 8 : a.ldh / 8);
+    const int64_t block_step = (int64_t)a.chunk_rows * (kRowBlock / 8);
+    auto at = [&](int c) { return blocks ? c / (kRowBlock / 8) * block_step + c % (kRowBlock / 8) : c; };
 #pragma unroll 4
     for (int c = lane; c < a.d / 8; c += 64) {
       const uint4 u = h[c], b = w[c];
-      out[c] = u;
+      out[at(c)] = u;
       const uint32_t av[4] = {u.x, u.y, u.z, u.w}, bv[4] = {b.x, b.y, b.z, b.w};
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
@@ -448,7 +452,7 @@ __global__ __launch_bounds__(256) void k_row_prep(RowPrepArgs a) {
         acc = fmaf(bf16_bits_to_float(av[q] >> 16), bf16_bits_to_float(bv[q] >> 16), acc);
       }
     }
-    for (int c = a.d / 8 + lane; c < a.dp / 8; c += 64) out[c] = make_uint4(0, 0, 0, 0);
+    for (int c = a.d / 8 + lane; c < a.dp / 8; c += 64) out[at(c)] = make_uint4(0, 0, 0, 0);
   } else {
     const float* h = static_cast<const float*>(a.H) + slot * a.d;
     const float* w = static_cast<const float*>(a.W) + y * a.d;
@@ -795,7 +799,9 @@ __global__ __launch_bounds__(256) void k_backward_rows_b16(const uint16_t* in, i
     const int64_t r = r0 + rr;
     uint4 v = make_uint4(0, 0, 0, 0);
     if (r < nrows) {
-      v = *reinterpret_cast<const uint4*>(in + r * ld_in + c0 + tc * 8);
+      const int c = c0 + tc * 8;
+      v = *reinterpret_cast<const uint4*>(rows_in_blocks(chunk_rows) ? in + ((int64_t)(c / kRowBlock) * chunk_rows + r) * kRowBlock + c % kRowBlock
+                                                                     : in + r * ld_in + c);
       // bf16 elements times the row's scale, rounded back to bf16 (nearest even)
       const float sc = scale[r];
       uint32_t w[4] = {v.x, v.y, v.z, v.w};

@@ -246,10 +246,10 @@ __device__ __forceinline__ int lane_now() {
 }
 
 // Forward epilogue of a wave's 128 x (16 NJ) sub-tile: vocabulary ids from m0 + 128 wm, token columns from
-// n0 + 16 NJ wn, partial sums with index pidx; accumulator element (i, j, e) of a lane is vocabulary
+// n0 + 16 NJ wn, partial sums with index pidx; target_logit(j): that of the lane's token in column block j; accumulator element (i, j, e) of a lane is vocabulary
 // id vrow(i, e), token column ncol_base + 16 j.
-template <int NJ>
-__device__ __forceinline__ void forward_epilogue(const Params& p, f32x4 (&acc)[8][NJ], const unsigned char* zt_lds, int m0,
+template <int NJ, class Zt>
+__device__ __forceinline__ void forward_epilogue(const Params& p, f32x4 (&acc)[8][NJ], Zt target_logit, int m0,
                                                  int n0, int pidx, int wm, int wn, int N) {
   const int lane = lane_now(), frow = lane & 15, fq = lane >> 4;
   const int ncol_base = n0 + wn * (16 * NJ) + frow;
@@ -274,7 +274,7 @@ __device__ __forceinline__ void forward_epilogue(const Params& p, f32x4 (&acc)[8
         for (int j = 0; j < NJ; ++j) {
           const int n = ncol_base + j * 16;
           const bool live = n < N;
-          const float zt = *reinterpret_cast<const float*>(zt_lds + (wn * (NJ * 16) + frow + j * 16) * 4);
+          const float zt = target_logit(j);
           const float c2 = live ? fmaf(zt, LOG2E, kStashMargin2) : 0.f;
           uint16_t* erow = p.estash + (int64_t)n * p.lde + m0 + wm * 128 + 8 * fq;
           float s = 0.f, t = 0.f;
@@ -690,7 +690,9 @@ __global__ __launch_bounds__(NTHREADS) void gemm_nt_bf16(Params p) {
   if (MODE == MODE_DH) __syncthreads();   // its staged epilogue reuses the panels' LDS
 
   if (MODE == MODE_FWD) {
-    forward_epilogue<8>(p, acc, smem + PIPE_BYTES, m0, n0, tm * 2 + (wave_u >> 1), wave_u >> 1, wave_u & 1, N);
+    const unsigned char* const zt_lds = smem + PIPE_BYTES + (((wave_u & 1) * 128 + (lane_now() & 15)) << 2);
+    forward_epilogue<8>(p, acc, [&](int j) { return *reinterpret_cast<const float*>(zt_lds + j * 64); }, m0, n0,
+                        tm * 2 + (wave_u >> 1), wave_u >> 1, wave_u & 1, N);
   } else if (MODE == MODE_DH) {
     const int lane = lane_now(), wave = wave_u, tid = wave * 64 + lane;
     const int wm = wave >> 1, wn = wave & 1, frow = lane & 15, fq = lane >> 4;
@@ -806,20 +808,27 @@ __global__ __launch_bounds__(NTHREADS) void gemm_nt_bf16(Params p) {
 // With a single tile column every panel of W is read once, and the launch is bound by how fast W
 // streams in and by its last round: 594 tiles of 256 x 256 are three rounds of 256 for 2.3 rounds'
 // work, and one workgroup per compute unit has one panel of W in flight and nothing to do behind its
-// epilogue.  Tiles half as high and three stages of 32 K-elements let two workgroups share a compute
-// unit (72.5 KB of LDS, 208 registers); waves without tokens only load their share.  Scoring call, 256 x 256
-// tiles and these, us: V = 151936, d = 4096, 64 rows 367 and 317, 128 rows 377 and 351, 192 rows 387 and 382, 256
-// rows 408 and 422; d = 1536 154 and 133, 158 and 145, 164 and 156, 172 and 167; V = 32000, d = 2048 52.4 and 44.4,
-// 52.2 and 46.6, 52.7 and 50.0, 53.3 and 53.0.  The line lies at one tile column because a panel-load byte buys
-// half the products here (24 KB per 512 MFMA cycles, more than the 43.5 bytes per clock a compute unit's load
-// path delivers): above 192 rows of the widest heads this costs 3 %, and from two columns on the large tile
-// wins everywhere (512 rows, d = 4096: forward launch 606 against 697 us).  The rows that count are slots (rounded up
-// to 256), the scored ones being known on the device only.
+// epilogue.  Tiles half as high let two workgroups share a compute unit (80 KB of LDS, 216 registers each).
+// The L2 takes one request per clock and channel, of 64 or of 128 bytes: with both operands fetched in
+// 64-byte pieces (32 K-elements of a row) the launch was bound by those requests.  W comes in chunks of 64
+// K-elements, two steps of the loop, and the token rows lie in blocks of 32 columns ([dp / 32][rows][32],
+// written that way by the row preparation), so that both are fetched in whole lines.  Waves without tokens
+// only load their share of W.  A tile starts its walk along K where its place among the tiles of its XCD says:
+// rows of a power of two of bytes lie on the same L2 and memory channels, and tiles that all start at column 0
+// ask the same channels at the same time (64 rows, d = 4096 316 us, now 254; d = 2048 128 and 109; others the same).
+// Scoring call, us, 256 x 256 tiles, these in 64-byte pieces from column 0, now: V = 151936, d = 4096, 64 rows 367,
+// 315 and 254, 128 rows 377, 350 and 267, 201 rows 387, 404 and 336, 256 rows 408, 417 and 338; d = 1536 154, 134
+// and 114, 158, 144 and 117, 164, 164 and 143, 172, 167 and 143; V = 32000, d = 2048, 256 rows 53, 52 and 50.
+// The line lies at one tile column because the load path of a compute unit (23 clocks per
+// KB) then has to deliver 24 KB per 512 MFMA cycles: used for every column, 4096 rows, d = 1536 / 2048 / 4096
+// take 1830 / 1876 / 4163 us in the launch against 1740 / 1769 / 3805 with the large tile.  The rows that count are
+// slots (rounded up to 256), the scored ones being known on the device only.
 // ---------------------------------------------------------------------------------------------
-constexpr int FM = 128, FN = 256, FK = 32, FSTAGES = 3;
-constexpr int F_A = FM * FK * 2, F_STAGE = (FM + FN) * FK * 2;      // 8 KB of A, 24 KB per stage
-constexpr int F_LDS = FSTAGES * F_STAGE + FN * 4;
-constexpr int F_LOADS = 6;                                          // direct loads per wave and stage: 2 of A, 4 of B
+constexpr int FM = 128, FN = kFewRows, FK = kRowBlock;
+constexpr int F_CHUNK = FM * BK * 2, F_STAGE = FN * FK * 2;         // 16 KB: 64 K-elements of W; 16 KB: 32 of the tokens
+constexpr int F_CHUNKS = 2, F_STAGES = 3;
+constexpr int F_B = F_CHUNKS * F_CHUNK, F_LDS = F_B + F_STAGES * F_STAGE;
+constexpr int F_LOADS = 4;                                          // direct loads per wave and chunk, or stage
 
 __global__ __launch_bounds__(NTHREADS, 2) void forward_few_bf16(Params p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -832,38 +841,68 @@ __global__ __launch_bounds__(NTHREADS, 2) void forward_few_bf16(Params p) {
   // column of the stash is written; in order: all tiles share the token rows, and runs of 64 tiles per XCD
   // measured the same
   const int M = p.M, tm = blockIdx.x;
-  const int m0 = tm * FM, n0 = 0;
+  const int m0 = tm * FM;
 
-  // direct loads: 16 rows x 64 bytes each; lane l fills slot l % 4 of row l / 4 and fetches logical
-  // chunk slot ^ f(row), f = (row >> 3) & 3 for A (permuted fragment rows), (row >> 2) & 3 for B
-  const uint16_t* src[F_LOADS];
-  uint32_t dst[F_LOADS];
-  const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
+  // direct loads, 1 KB each, as byte offsets of the lane from the tile's first row.  W: 8 rows x 128 bytes; lane l
+  // fills slot l % 8 of row l / 8 and fetches logical chunk slot ^ f(row), f = the row bits 1, 3, 4 that vary
+  // inside a (permuted) fragment.  Token rows: 16 rows x 64 bytes, contiguous; slot l % 4 of row l / 4, f = (row >> 2) & 3.
+  const int first = m0 < M ? m0 : M - 1;
+  uint32_t va[F_LOADS], vb[F_LOADS];
 #pragma unroll
   for (int i = 0; i < F_LOADS; ++i) {
-    const int lr = lane >> 2;
-    if (i < 2) {
-      const int blk = wave * 2 + i, r = blk * 16 + lr;
-      const int row = m0 + r < M ? m0 + r : M - 1;
-      src[i] = p.A + (int64_t)row * p.lda + (((lane & 3) ^ ((r >> 3) & 3)) << 3);
-      dst[i] = __builtin_amdgcn_readfirstlane(lds_base + blk * 1024);
-    } else {
-      const int blk = wave * 4 + i - 2, r = blk * 16 + lr;
-      const int row = n0 + r < N ? n0 + r : N - 1;
-      src[i] = p.B + (int64_t)row * p.ldb + (((lane & 3) ^ ((r >> 2) & 3)) << 3);
-      dst[i] = __builtin_amdgcn_readfirstlane(lds_base + F_A + blk * 1024);
-    }
+    const int r = (wave * F_LOADS + i) * 8 + (lane >> 3);
+    const int row = m0 + r < M ? m0 + r : M - 1;      // (at most 127 rows of 2 MB behind `first`)
+    va[i] = (uint32_t)(row - first) * (uint32_t)(p.lda * 2) + (((lane & 7) ^ (((r >> 1) & 1) | (((r >> 3) & 3) << 1))) << 4);
+    const int q = (wave * F_LOADS + i) * 16 + (lane >> 2);
+    vb[i] = (uint32_t)(q < N ? q : N - 1) * (FK * 2) + (((lane & 3) ^ ((q >> 2) & 3)) << 4);
   }
-  const int nk = p.K / FK;
-  auto load = [&](int i, int kt, uint32_t stage) {
-    uint64_t addr;
-    const int64_t off = (int64_t)kt * (FK * 2) + (i < 2 && kt >= p.a_tail_panel * (BK / FK) ? p.a_tail_delta : 0);
-    asm volatile("s_mov_b32 m0, %3\n\tv_lshl_add_u64 %0, %1, 0, %2\n\tglobal_load_lds_dwordx4 %0, off"
-                 : "=&v"(addr) : "v"(src[i]), "s"(off), "s"(dst[i] + stage) : "memory");
+  const uint64_t a_base = (uint64_t)(p.A + (int64_t)first * p.lda), b_base = (uint64_t)p.B;
+  const uint32_t lds_wave = __builtin_amdgcn_readfirstlane(
+      (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem + wave * (F_LOADS * 1024));
+  auto load = [](uint32_t voff, uint64_t base, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" :: "v"(voff), "s"(base), "s"(lds) : "memory");
   };
-  auto last_k = [&](int k) { return k < nk ? k : nk - 1; };
-  const int a_off = (8 * (frow >> 2) + (frow & 3)) * 64 + ((fq ^ (frow >> 2)) << 4);
-  const int b_off = F_A + (wave * 64 + frow) * 64 + ((fq ^ (frow >> 2)) << 4);
+  const int nk = p.K / FK, nc = p.K / BK;             // (nk is a multiple of 4)
+  // chunk c of the walk, which starts at chunk `turn` and goes round; loads that would run past its end fetch
+  // its first ones again into slots nobody reads
+  const int turn = tm / NXCD % nc;
+  auto load_a = [&](int c, uint32_t slot) {
+    c += turn;
+    c = c < nc ? c : c - nc;
+    const uint64_t base = a_base + (uint64_t)c * (BK * 2) + (c >= p.a_tail_panel ? p.a_tail_delta : 0);
+#pragma unroll
+    for (int i = 0; i < F_LOADS; ++i) load(va[i], base, lds_wave + slot + i * 1024);
+  };
+  auto load_b = [&](int kt, uint32_t slot) {
+    kt += 2 * turn;
+    kt = kt < nk ? kt : kt - nk;
+    const uint64_t base = b_base + (uint64_t)kt * (uint64_t)p.ldb * (FK * 2);
+#pragma unroll
+    for (int i = 0; i < F_LOADS; ++i) load(vb[i], base, lds_wave + slot + i * 1024);
+  };
+
+  if (wave * 64 >= N) {
+    // no tokens: this wave's share of W, and the barriers
+    load_a(0, 0);
+    for (int c = 0; c < nc; ++c) {
+      __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
+      __syncthreads();
+      load_a(c + 1, (c & 1) ? 0 : F_CHUNK);
+      __syncthreads();
+    }
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));        // no direct load may outlive the wave
+    return;
+  }
+
+  float zt[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int n = wave * 64 + j * 16 + frow;
+    zt[j] = p.zt[n < N ? n : N - 1];
+  }
+  const int chunk_x = ((frow >> 1) & 1) | ((frow >> 2) << 1), a_row = (8 * (frow >> 2) + (frow & 3)) * (BK * 2);
+  const int a_off[2] = {a_row + ((fq ^ chunk_x) << 4), a_row + (((4 | fq) ^ chunk_x) << 4)};
+  const int b_off = F_B + (wave * 64 + frow) * (FK * 2) + ((fq ^ (frow >> 2)) << 4);
 
   f32x4 acc[8][4];
 #pragma unroll
@@ -872,46 +911,43 @@ __global__ __launch_bounds__(NTHREADS, 2) void forward_few_bf16(Params p) {
     for (int j = 0; j < 4; ++j)
 #pragma unroll
       for (int e = 0; e < 4; ++e) acc[i][j][e] = 0.f;
-  {
-    int n = n0 + wave * 64 + lane; n = n < N ? n : N - 1;
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off"
-                 :: "v"(p.zt + n), "s"(__builtin_amdgcn_readfirstlane(lds_base + FSTAGES * F_STAGE + wave * 256)) : "memory");
-  }
-#pragma unroll
-  for (int i = 0; i < F_LOADS; ++i) load(i, 0, 0);
-#pragma unroll
-  for (int i = 0; i < F_LOADS; ++i) load(i, 1, F_STAGE);
-  const bool has_rows = n0 + wave * 64 < N;           // a wave without tokens only loads its share
-  uint32_t st = 0, st_load = 2 * F_STAGE;
+  load_a(0, 0);
+  load_b(0, F_B);
+  load_b(1, F_B + F_STAGE);
+  uint32_t sa = 0, sb = 0, sb_load = 2 * F_STAGE;
+  auto next = [](uint32_t s) { return s == (F_STAGES - 1) * F_STAGE ? 0u : s + F_STAGE; };
   int kt = 0;
   do {                                                // (K is at least 128)
-    // this panel's loads have landed when only the next panel's are outstanding; behind the barrier
-    // every wave's have, and every wave has read the slot that the loads below refill
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm(F_LOADS));
-    __syncthreads();
-    const int kl = last_k(kt + 2);
 #pragma unroll
-    for (int i = 0; i < F_LOADS; ++i) load(i, kl, st_load);
-    if (has_rows) {
-      const unsigned char* base_a = smem + st + a_off;
-      const unsigned char* base_b = smem + st + b_off;
+    for (int ks = 0; ks < 2; ++ks) {
+      // Stage kt + 2 is issued in step kt, chunk c + 1 before it in the first step of chunk c.  So this step's stage
+      // (and chunk) have landed when what the step before issued is outstanding: a stage, or a chunk and a
+      // stage.  Behind the barrier every wave's have, and every wave has read the slots that the loads refill.
+      if (ks == 0) __builtin_amdgcn_s_waitcnt(waitcnt_vm(F_LOADS)); else __builtin_amdgcn_s_waitcnt(waitcnt_vm(2 * F_LOADS));
+      __syncthreads();
+      if (ks == 0) load_a(kt / 2 + 1, sa ^ F_CHUNK);
+      load_b(kt + ks + 2, F_B + sb_load);
+      const unsigned char* base_a = smem + sa + a_off[ks];
+      const unsigned char* base_b = smem + sb + b_off;
       bf16x8 fb[4], fa[8];
 #pragma unroll
       for (int j = 0; j < 4; ++j) fb[j] = *reinterpret_cast<const bf16x8*>(base_b + j * 1024);
 #pragma unroll
-      for (int i = 0; i < 8; ++i) fa[i] = *reinterpret_cast<const bf16x8*>(base_a + (i >> 1) * 2048 + (i & 1) * 256);
+      for (int i = 0; i < 8; ++i) fa[i] = *reinterpret_cast<const bf16x8*>(base_a + (i >> 1) * 4096 + (i & 1) * 512);
 #pragma unroll
       for (int i = 0; i < 8; ++i)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
           if (i < 7 || j < 3) mfma16(acc[i][j], fa[i], fb[j]); else mfma16_then_wait(acc[i][j], fa[i], fb[j]);
         }
+      sb = next(sb);
+      sb_load = next(sb_load);
     }
-    st = st == 2 * F_STAGE ? 0 : st + F_STAGE;
-    st_load = st_load == 2 * F_STAGE ? 0 : st_load + F_STAGE;
-  } while (++kt < nk);
+    sa ^= F_CHUNK;
+    kt += 2;
+  } while (kt < nk);
   __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
-  if (has_rows) forward_epilogue<4>(p, acc, smem + FSTAGES * F_STAGE, m0, n0, tm, 0, wave, N);
+  forward_epilogue<4>(p, acc, [&](int j) { return zt[j]; }, m0, 0, tm, 0, wave, N);
 }
 
 // dW tail.  The workgroup -> tile mapping runs whole super-tile rows of sup_m tile rows; V / 256
@@ -1083,7 +1119,7 @@ void launch(Params& p, hipStream_t stream) {
 void launch_gemm_fwd_bf16(const void* W, int64_t ldw, const void* W_tail, const void* Hc, int64_t ldh, int k_len, const float* zt,
                           const int64_t* n_scored, int64_t chunk_start, int chunk_rows,
                           int V, int d, float* part_sum, float* part_ez,
-                          int64_t part_stride, void* estash, int64_t lde, hipStream_t stream) {
+                          int64_t part_stride, void* estash, int64_t lde, bool in_blocks, hipStream_t stream) {
   Params p = {};
   p.A = static_cast<const uint16_t*>(W); p.lda = ldw; p.M = V;
   p.B = static_cast<const uint16_t*>(Hc); p.ldb = ldh; p.N = chunk_rows;
@@ -1097,7 +1133,7 @@ void launch_gemm_fwd_bf16(const void* W, int64_t ldw, const void* W_tail, const 
   p.zt = zt + chunk_start;
   p.part_sum = part_sum; p.part_ez = part_ez; p.part_stride = part_stride;
   p.estash = static_cast<uint16_t*>(estash); p.lde = lde; p.V = V; p.d = d;
-  if (chunk_rows <= FN) {
+  if (in_blocks) {
     static LdsLimit lds_limit;
     lds_limit.ensure(reinterpret_cast<const void*>(&forward_few_bf16), F_LDS);
     const int Mt = 2 * ((p.M + BM - 1) / BM);

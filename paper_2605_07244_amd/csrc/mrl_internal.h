@@ -27,6 +27,12 @@ struct LdsLimit {
   }
 };
 
+// Passes of at most kFewRows rows hold the gathered rows in blocks of kRowBlock columns, [dp / 32][chunk_rows][32],
+// instead of row by row: what the forward kernel of such passes loads at a time is then contiguous.  (The last part
+// of a longer pass may have as few rows; it runs on the large tile like the other parts.)
+constexpr int kFewRows = 256, kRowBlock = 32;
+__host__ __device__ inline bool rows_in_blocks(int chunk_rows) { return chunk_rows <= kFewRows; }
+
 // Number of sum-exp partials each token row receives from the forward kernel: the bf16
 // kernel emits two per 256-wide vocabulary tile (one per wave row), the fp32 path a single
 // (max, sum-exp) pair per row.
@@ -51,8 +57,8 @@ constexpr float kSaturatedLogp = -97.f;
 // n_scored: device pointer to the number of compacted rows; chunk_start/chunk_rows
 // select the rows this launch covers (valid rows = clamp(n_scored - chunk_start, 0, chunk_rows)).
 
-// Forward: A = W [V, k_len] (row stride ldw), B = Hc [chunk_rows, k_len] (row stride ldh): the
-// launch's token rows, gathered and contiguous; k_len = d rounded up to 128, the columns beyond d
+// Forward: A = W [V, k_len] (row stride ldw), B = Hc [chunk_rows, k_len] (row stride ldh, or, in_blocks, in
+// blocks of kRowBlock columns of ldh rows each): the launch's token rows, gathered; k_len = d rounded up to 128, the columns beyond d
 // zero in both operands; zt[chunk_start + n] is the row's target logit.  Writes per-row partials part_sum[(2*tile_m + wave_m) * part_stride + n]
 // = sum of e[n, v] over the partial's 128 vocabulary rows (e as defined above), when part_ez != nullptr
 // also sum e * z (for the entropy), and, when estash != nullptr, e itself as bf16 into
@@ -62,7 +68,7 @@ constexpr float kSaturatedLogp = -97.f;
 void launch_gemm_fwd_bf16(const void* W, int64_t ldw, const void* W_tail, const void* Hc, int64_t ldh, int k_len, const float* zt,
                           const int64_t* n_scored, int64_t chunk_start, int chunk_rows,
                           int V, int d, float* part_sum, float* part_ez,
-                          int64_t part_stride, void* estash, int64_t lde, hipStream_t stream);
+                          int64_t part_stride, void* estash, int64_t lde, bool in_blocks, hipStream_t stream);
 
 // dH: A = E [chunk_rows, Vp] (the patched bf16 stash), B = W^T read in place from W [V, d] (row
 // stride ldw); row m, multiplied by row_scale[chunk_start + m], goes to
@@ -135,7 +141,7 @@ void launch_seq_log_ratio(const uint8_t* mask, const int32_t* targets, const flo
 struct RowPrepArgs {
   const void* H; const void* W; const int32_t* targets; const int32_t* row_index; const int64_t* n_scored;
   int64_t chunk_start; int chunk_rows; int d;
-  void* Hc; int64_t ldh; int dp;
+  void* Hc; int64_t ldh; int dp;   // (in blocks of kRowBlock columns, chunk_rows rows each, where rows_in_blocks says so)
   float* zt;
   const uint8_t* mask; int64_t N; int V; void* dH; int64_t dh_row_bytes; int64_t zero_blocks /*set by the launcher*/;
   const int32_t* seq_len; const int32_t* group_id; const uint8_t* seq_kind; int64_t B; int G; int loss_agg;
@@ -183,7 +189,7 @@ void launch_convert_f32(float* ZP, int64_t ldz, const float* lse_c,
 void launch_pad_rows_b16(const void* in, int64_t ld_in, void* out, int64_t ld_out, int64_t n_rows, int d, int dp,
                          hipStream_t stream);
 
-// bf16 path, operands of the dW launch: Ht[c][r] = scale[r] * Hc[r][c] (c < dp, a multiple of 64) for the
+// bf16 path, operands of the dW launch (Hc as the row preparation wrote it): Ht[c][r] = scale[r] * Hc[r][c] (c < dp, a multiple of 64) for the
 // pass's valid rows, zeros up to their multiple of 128; the stash rows in between are cleared (the
 // dW contraction runs over pairs of 64-row panels; the forward kernel writes valid rows only).
 void launch_backward_rows_b16(const void* Hc, int64_t ldh, const float* scale, void* Ht, int64_t ldht,

@@ -160,6 +160,24 @@ def test_forward_of_few_rows(mrl, scored, d, V):
     util.check_gradient("dW", util.to_f64(out["dW"]), dW)
 
 
+@pytest.mark.parametrize("N,d,V", [(1, 72, 4000), (70, 200, 3000), (129, 136, 5000), (256, 448, 8200)])
+def test_forward_of_few_rows_from_any_column(mrl, N, d, V):
+    """Passes of at most 256 rows whose tiles start at different columns: the walk goes round behind the zero-padded end of K
+    (all of the head copied, or its last 128 columns), waves with and without tokens."""
+    H, W, y, mask = _head(N, d, V, N, N + d)
+    logp, lse, ent = mrl.token_scores(H, W, y, mask)
+    out, dH, dW = _step(mrl, H, W, y, mask, mrl.F32, V, poison=True)
+    torch.cuda.synchronize()
+    z = H.double() @ W.double().t()
+    want_lse = torch.logsumexp(z, 1)
+    # fp32 sums of at most 8200 exponentials and 448 products: far below the bar
+    assert float((logp.double() - (z.gather(1, y.long()[:, None])[:, 0] - want_lse)).abs().max()) <= 1e-4
+    assert float((ent.double() - (want_lse - (torch.softmax(z, 1) * z).sum(1))).abs().max()) <= 1e-4
+    assert torch.equal(out["logp"], logp)
+    util.check_gradient("dH", util.to_f64(out["dH"]), dH)
+    util.check_gradient("dW", util.to_f64(out["dW"]), dW)
+
+
 @pytest.mark.parametrize("N,d,V", [(100, 120, 700), (300, 136, 700), (4096, 200, 900), (4200, 200, 900), (4200, 192, 900)])
 def test_padded_widths(mrl, N, d, V):
     """Widths beside a multiple of 128: a head narrower than a panel pair, the head's zero-padded tail next to its own rows
