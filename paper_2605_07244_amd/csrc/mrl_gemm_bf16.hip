@@ -63,8 +63,8 @@ constexpr int kLoadsCarriedOver = kLoadsInGroup[0] + kLoadsInGroup[1] + kLoadsIn
 static_assert(kLoadsCarriedOver + kLoadsInGroup[5] + kLoadsInGroup[6] + kLoadsInGroup[7] == 16, "a slot takes 16 loads per wave");
 constexpr int kDwTailMaxItems = 256;                // K slices of dW tail tiles per launch: one per compute unit
 constexpr int ZT_BYTES = BN * 4;                   // forward: the tile's 256 target logits, behind the panels
-template <int MODE> constexpr int lds_bytes() {
-  return MODE == 0 ? PIPE_BYTES + ZT_BYTES : (DHSTAGE_BYTES > PIPE_BYTES ? DHSTAGE_BYTES : PIPE_BYTES);
+template <int MODE> constexpr int lds_bytes() {     // (forward: the half-column tiles keep three stages of 48 KB)
+  return MODE == 0 ? PIPE_BYTES + TILE_BYTES / 2 + ZT_BYTES : (DHSTAGE_BYTES > PIPE_BYTES ? DHSTAGE_BYTES : PIPE_BYTES);
 }
 
 // s_waitcnt immediates (gfx9 encoding): wait until at most N vector-memory loads are
@@ -327,6 +327,124 @@ __device__ __forceinline__ void forward_epilogue(const Params& p, f32x4 (&acc)[8
       }
 }
 
+// ---------------------------------------------------------------------------------------------
+// Forward, last column of tiles with at most 128 tokens: 256 x 128 tiles, waves 2 x 2, each 128 x 64.  A panel takes half
+// the MFMAs, so the fragments of two panels fit into registers and three panels into LDS: a panel's MFMAs run
+// on fragments read during the panel before, while the loads of the third next one go into the slot those left.
+// The load path bounds it (48 KB per 1024 MFMA cycles): a tile takes 0.55 - 0.6 of a 256 x 256 one.  Forward launch, rows
+// padded to 256 and now, us: V = 151936, d = 4096, 300 rows 565 and 506, 384 rows 554 and 481, 600 rows 739 and
+// 630, 1877 rows 1859 and 1676; d = 1536, 300 rows 243 and 207, 1877 rows 798 and 764; V = 50257, d = 712, 1877 rows 184 and 175.
+// The same for the dH launch's last row of tiles was slower (327 rows, d = 4096 460 -> 576 us): its panels of W come from
+// memory, and the shorter panel leaves them half the time to arrive.
+// The kernel's arguments are read again behind the branch: kept alive across both paths they cost scalar
+// spills that slowed every tile (d = 712: 3 %).
+// ---------------------------------------------------------------------------------------------
+constexpr int HALF_COLS = 128;
+constexpr int HALF_STAGE = TILE_BYTES + TILE_BYTES / 2, HALF_PIPE = 3 * HALF_STAGE;   // A and half as much B, 48 KB
+constexpr int HALF_LOADS = 12;                                      // direct loads per wave and panel: 8 of A, 4 of B
+
+__device__ __forceinline__ void half_column_tile(unsigned char* smem, int tm, int n0, int N) {
+  typedef const __attribute__((address_space(4))) Params* KernArg;
+  KernArg arg = (KernArg)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(arg));
+  const Params& p = *(const Params*)arg;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave >> 1, wn = wave & 1, frow = lane & 15, fq = lane >> 4;
+  const int m0 = tm * BM, M = p.M, nk = p.K / BK;
+  const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
+  // panels, swizzles and fragment rows as in the full tile
+  const uint16_t* src[HALF_LOADS];
+#pragma unroll
+  for (int i = 0; i < HALF_LOADS; ++i) {
+    const bool a = i < 8;
+    const int r = (a ? wave * 8 + i : wave * 4 + i - 8) * 8 + (lane >> 3);
+    const int row = a ? (m0 + r < M ? m0 + r : M - 1) : (n0 + r < N ? n0 + r : N - 1);
+    const int swz = a ? ((r >> 1) & 1) | (((r >> 3) & 3) << 1) : (r >> 1) & 7;
+    src[i] = (a ? p.A + (int64_t)row * p.lda : p.B + (int64_t)row * p.ldb) + ((lane & 7) ^ swz) * 8;
+  }
+  const uint32_t lds_a = __builtin_amdgcn_readfirstlane(lds_base + wave * 8192);
+  const uint32_t lds_b = __builtin_amdgcn_readfirstlane(lds_base + TILE_BYTES + wave * 4096);
+  // load l of panel kt (behind the end: the last one again, into a slot nobody reads)
+  auto load = [&](int l, int kt, uint32_t stage) {
+    kt = kt < nk ? kt : nk - 1;
+    const int64_t off = (int64_t)kt * (BK * 2) + (l < 8 && kt >= p.a_tail_panel ? p.a_tail_delta : 0);
+    const uint32_t lds = (l < 8 ? lds_a + l * 1024 : lds_b + (l - 8) * 1024) + stage;
+    uint64_t addr;
+    asm volatile("s_mov_b32 m0, %3\n\tv_lshl_add_u64 %0, %1, 0, %2\n\tglobal_load_lds_dwordx4 %0, off"
+                 : "=&v"(addr) : "v"(src[l]), "s"(off), "s"(lds) : "memory");
+  };
+  int a_off[2], b_off[2];
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks) {
+    const int chunk = (ks << 2) | fq;
+    a_off[ks] = (wm * 128 + 8 * (frow >> 2) + (frow & 3)) * 128 + ((chunk ^ (((frow >> 1) & 1) | ((frow >> 2) << 1))) << 4);
+    b_off[ks] = TILE_BYTES + (wn * 64 + frow) * 128 + ((chunk ^ ((frow >> 1) & 7)) << 4);
+  }
+  f32x4 acc[8][4];
+#pragma unroll
+  for (int i = 0; i < 8; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[i][j][e] = 0.f;
+  bf16x8 fa[2][8][2], fb[2][4][2];                    // [this panel / the next][block][K step]
+  // fragment n of a panel: the 8 of B first
+  auto read = [&](int set, uint32_t stage, int n) {
+    if (n < 8) fb[set][n / 2][n & 1] = *reinterpret_cast<const bf16x8*>(smem + stage + b_off[n & 1] + (n / 2) * 2048);
+    else fa[set][(n - 8) / 2][n & 1] = *reinterpret_cast<const bf16x8*>(smem + stage + a_off[n & 1] + ((n - 8) >> 2) * 4096 + (((n - 8) >> 1) & 1) * 512);
+  };
+  // 64 MFMAs, between them one piece at a time: a load, two fragments, a load, ...  The barrier: every wave has the
+  // fragments of this panel in registers (its slot can be refilled), and the next panel has landed (only the
+  // loads of the one behind it are outstanding).
+  auto panel = [&](auto second, int kt, uint32_t st_this, uint32_t st_next) {
+    constexpr int set = decltype(second)::value ? 1 : 0;
+    constexpr int kPieces = 3 * HALF_LOADS, kFirst = 3, kSlots = 54;
+#pragma unroll
+    for (int m = 0; m < 64; ++m) {
+      const int g = m / 8, j = m / 2 % 4, ks = m & 1;
+      if (set == 1 && m == 63) mfma16_then_wait(acc[g][j], fa[set][g][ks], fb[set][j][ks]);
+      else mfma16(acc[g][j], fa[set][g][ks], fb[set][j][ks]);
+      if (m == kFirst - 1) {
+        __builtin_amdgcn_s_waitcnt(waitcnt_vm(HALF_LOADS) & ~(15 << 8));   // (and no LDS read)
+        __syncthreads();
+      }
+      if (m >= kFirst && m < kFirst + kSlots) {
+        const int n = m - kFirst, q = n * kPieces / kSlots;
+        if (n == 0 || q != (n - 1) * kPieces / kSlots) {
+          if (q % 3 == 0) load(q / 3, kt + 3, st_this); else read(set ^ 1, st_next, q - q / 3 - 1);
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  {
+    int n = n0 + wave * 64 + lane; n = n < N ? n : N - 1;
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off"
+                 :: "v"(p.zt + n), "s"(__builtin_amdgcn_readfirstlane(lds_base + HALF_PIPE + wave * 256)) : "memory");
+  }
+#pragma unroll
+  for (int s = 0; s < 3; ++s)
+#pragma unroll
+    for (int l = 0; l < HALF_LOADS; ++l) load(l, s, s * HALF_STAGE);
+  __builtin_amdgcn_s_waitcnt(waitcnt_vm(2 * HALF_LOADS));
+  __syncthreads();
+#pragma unroll
+  for (int n = 0; n < 24; ++n) read(0, 0, n);
+  uint32_t st = 0;
+  auto next = [](uint32_t x) { return x == 2 * HALF_STAGE ? 0u : x + HALF_STAGE; };
+  int kt = 0;
+  do {                                                // (an even number of panels, at least two)
+    panel(Flag<false>{}, kt, st, next(st));
+    st = next(st);
+    panel(Flag<true>{}, kt + 1, st, next(st));
+    st = next(st);
+    kt += 2;
+  } while (kt < nk);
+  __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));          // no direct load may outlive the wave
+  const unsigned char* const zt_lds = smem + HALF_PIPE + ((wn * 64 + (lane_now() & 15)) << 2);
+  forward_epilogue<4>(p, acc, [&](int j) { return *reinterpret_cast<const float*>(zt_lds + j * 64); }, m0, n0, tm * 2 + wm, wm, wn, N);
+}
+
 template <int MODE>
 __global__ __launch_bounds__(NTHREADS) void gemm_nt_bf16(Params p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -400,6 +518,15 @@ __global__ __launch_bounds__(NTHREADS) void gemm_nt_bf16(Params p) {
   } else {
     sup_m = p.sup_m; sup_n = p.sup_n;
     if (!tile_coords(blockIdx.x, Mt, Nt, sup_m, sup_n, tm, tn, sm, sn)) return;
+  }
+  if (MODE == MODE_FWD && __builtin_expect(N - (Nt - 1) * BN <= HALF_COLS, 0)) {
+    // A last column of at most 128 tokens takes half tiles.  They are dealt like the others, to every XCD its share: the
+    // columns of a band start at another one in every band (with 8 columns, XCDs would else have all of them or none).
+    int columns = Nt;
+    asm volatile("" : "+s"(columns));                 // (the division stays in this branch)
+    tn += tm / kBand % columns;
+    tn = tn < Nt ? tn : tn - Nt;
+    if (tn == Nt - 1) { half_column_tile(smem, tm, tn * BN, N); return; }
   }
   const int m0 = tm * BM, n0 = tn * BN;
 

@@ -178,6 +178,26 @@ def test_forward_of_few_rows_from_any_column(mrl, N, d, V):
     util.check_gradient("dW", util.to_f64(out["dW"]), dW)
 
 
+@pytest.mark.parametrize("scored,d,V", [(257, 128, 700), (320, 200, 2500), (384, 256, 6000), (385, 128, 1000), (1921, 136, 4400)])
+def test_forward_half_columns(mrl, scored, d, V):
+    """A last column of at most 128 tokens (one, those of one wave, all, one too many) behind one or seven whole ones, over one and
+    several bands of tile rows: log-probs, entropy and both gradients."""
+    H, W, y, mask = _head(scored + 40, d, V, scored, scored + d)
+    logp, lse, ent = mrl.token_scores(H, W, y, mask)
+    out, dH, dW = _step(mrl, H, W, y, mask, mrl.F32, V, poison=True)
+    torch.cuda.synchronize()
+    ok = mask == 1
+    z = H[ok].double() @ W.double().t()
+    want_lse = torch.logsumexp(z, 1)
+    want = z.gather(1, y[ok].long()[:, None])[:, 0] - want_lse
+    # fp32 sums of at most 6000 exponentials and 256 products: far below the bar
+    assert float((logp[ok].double() - want).abs().max()) <= 1e-4 and float((lse[ok].double() - want_lse).abs().max()) <= 1e-4
+    assert float((ent[ok].double() - (want_lse - (torch.softmax(z, 1) * z).sum(1))).abs().max()) <= 1e-4
+    assert torch.equal(out["logp"], logp)
+    util.check_gradient("dH", util.to_f64(out["dH"]), dH)
+    util.check_gradient("dW", util.to_f64(out["dW"]), dW)
+
+
 @pytest.mark.parametrize("N,d,V", [(100, 120, 700), (300, 136, 700), (4096, 200, 900), (4200, 200, 900), (4200, 192, 900)])
 def test_padded_widths(mrl, N, d, V):
     """Widths beside a multiple of 128: a head narrower than a panel pair, the head's zero-padded tail next to its own rows
