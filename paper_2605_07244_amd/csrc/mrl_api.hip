@@ -585,6 +585,10 @@ int mrl_grpo_loss_fwd_bwd(const void* hidden, const void* lm_head_w, const int32
       launch_row_epilogue(e, s);
     }
     if (!bwd) continue;
+    const int overwrite = (c == 0 && !cfg->accumulate_dw) ? 1 : 0;
+    // (rows of the pass at most, as far as the caller says)
+    const int64_t hinted = cfg->scored_rows_hint > 0 ? cfg->scored_rows_hint - c0 : L.chunk_rows;
+    const bool dw_blocks = bf16 && dw_rows_in_blocks((int)(hinted < L.chunk_rows ? hinted : L.chunk_rows), V, d, overwrite);
     {
       Scope sc(MRL_PROF_CONVERT, s);
       if (bf16) {
@@ -592,13 +596,12 @@ int mrl_grpo_loss_fwd_bwd(const void* hidden, const void* lm_head_w, const int32
         // times its row scale, transposed, and zeros behind the last valid row
         if (out_dW)
           launch_backward_rows_b16(at<void>(ws, L.Hc), L.ldh, at<float>(ws, L.row_scale) + c0, at<void>(ws, L.Ht), L.ldr,
-                                   n_scored, c0, L.chunk_rows, L.dp, at<void>(ws, L.Z), L.ldz, (int)L.Vp, s);
+                                   n_scored, c0, L.chunk_rows, L.dp, at<void>(ws, L.Z), L.ldz, (int)L.Vp, dw_blocks, s);
       } else {
         launch_convert_f32(at<float>(ws, L.Z), L.ldz, at<float>(ws, L.lse_c), at<float>(ws, L.g_c), target_ids, row_index,
                            n_scored, c0, L.chunk_rows, V, s);
       }
     }
-    const int overwrite = (c == 0 && !cfg->accumulate_dw) ? 1 : 0;
     if (!bf16) {
       GemmF32Args h = {};
       h.A = at<float>(ws, L.Z); h.lda = L.ldz;
@@ -631,8 +634,8 @@ int mrl_grpo_loss_fwd_bwd(const void* hidden, const void* lm_head_w, const int32
     }
     if (out_dW) {
       Scope sc(MRL_PROF_GEMM_DW, s);
-      launch_gemm_dw_bf16(at<void>(ws, L.Z), L.ldz, at<void>(ws, L.Ht), L.ldr, n_scored, c0,
-                          L.chunk_rows, V, d, out_dW, overwrite, at<float>(ws, L.tail), s);
+      launch_gemm_dw_bf16(at<void>(ws, L.Z), L.ldz, at<void>(ws, L.Ht), dw_blocks ? L.dp : L.ldr, n_scored, c0,
+                          L.chunk_rows, V, d, out_dW, overwrite, at<float>(ws, L.tail), dw_blocks, s);
     }
   }
   {

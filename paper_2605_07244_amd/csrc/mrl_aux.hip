@@ -771,14 +771,14 @@ __global__ __launch_bounds__(256) void k_pad_rows_b16(const uint16_t* in, int64_
   }
 }
 
-// Backward operand of the dW launch, bf16: Ht[c][r] = scale[r] * Hc[r][c] for the pass's valid
+// Backward operand of the dW launch, bf16: Ht[c][r] (or, in blocks of 32 rows, Ht[r / 32][c][r % 32]) = scale[r] * Hc[r][c] for the pass's valid
 // rows, zeros up to the multiple of 128 the contraction runs over.  Tile 64 rows x 64 cols; n_cols a
 // multiple of 64, 16-byte aligned rows on both sides.  The blocks behind the tiles clear the stash
 // rows between the valid count and that multiple (the contraction must not meet stale bits there).
 __global__ __launch_bounds__(256) void k_backward_rows_b16(const uint16_t* in, int64_t ld_in, const float* scale,
                                                            uint16_t* out, int64_t ld_out, const int64_t* n_scored,
                                                            int64_t chunk_start, int chunk_rows, int row_tiles,
-                                                           uint16_t* E, int64_t lde, int Vp) {
+                                                           uint16_t* E, int64_t lde, int Vp, bool in_blocks) {
   __shared__ __attribute__((aligned(16))) uint16_t tile[64 * 72];
   const int nrows = valid_rows(n_scored, chunk_start, chunk_rows);
   const int nzero = (nrows + 127) / 128 * 128 < chunk_rows ? (nrows + 127) / 128 * 128 : chunk_rows;
@@ -829,7 +829,10 @@ __global__ __launch_bounds__(256) void k_backward_rows_b16(const uint16_t* in, i
       const uint32_t hi = tile[(tc * 8 + q * 2 + 1) * 72 + cc];
       ow[q] = lo | (hi << 16);
     }
-    *reinterpret_cast<uint4*>(out + (int64_t)(c0 + cc) * ld_out + r0 + tc * 8) = make_uint4(ow[0], ow[1], ow[2], ow[3]);
+    const int64_t r = r0 + tc * 8;
+    uint16_t* const at = in_blocks ? out + ((r / kRowBlock) * (gridDim.x * 64) + c0 + cc) * kRowBlock + r % kRowBlock
+                                   : out + (int64_t)(c0 + cc) * ld_out + r;
+    *reinterpret_cast<uint4*>(at) = make_uint4(ow[0], ow[1], ow[2], ow[3]);
   }
 }
 
@@ -903,11 +906,11 @@ void launch_pad_rows_b16(const void* in, int64_t ld_in, void* out, int64_t ld_ou
 
 void launch_backward_rows_b16(const void* Hc, int64_t ldh, const float* scale, void* Ht, int64_t ldht,
                               const int64_t* n_scored, int64_t chunk_start, int chunk_rows, int dp, void* E, int64_t lde,
-                              int Vp, hipStream_t stream) {
+                              int Vp, bool in_blocks, hipStream_t stream) {
   const int row_tiles = chunk_rows / 64;
   hipLaunchKernelGGL(k_backward_rows_b16, dim3(dp / 64, (unsigned)(row_tiles + 127)), dim3(256), 0, stream,
                      static_cast<const uint16_t*>(Hc), ldh, scale, static_cast<uint16_t*>(Ht), ldht, n_scored,
-                     chunk_start, chunk_rows, row_tiles, static_cast<uint16_t*>(E), lde, Vp);
+                     chunk_start, chunk_rows, row_tiles, static_cast<uint16_t*>(E), lde, Vp, in_blocks);
 }
 
 void launch_finalize(const double* loss_partials, int64_t n_blocks, const int64_t* n_scored,

@@ -89,7 +89,7 @@ struct Params {
   // DH
   const float* row_scale; void* dH; int dh_f32; int d; int max_items;   // max_items: partial tiles tail_part holds
   // DW
-  float* dW; int overwrite;
+  float* dW; int overwrite; int streaming;
   // DW, K-split tail (see dw_tail_plan): workgroups from main_blocks on take the tiles of the
   // tile rows tail_m0 .. tail_m0 + tail_rows - 1, each cut into tail_split slices of the
   // contraction, and store their accumulators to tail_part instead of dW
@@ -1077,6 +1077,154 @@ __global__ __launch_bounds__(NTHREADS, 2) void forward_few_bf16(Params p) {
   forward_epilogue<4>(p, acc, [&](int j) { return zt[j]; }, m0, 0, tm, 0, wave, N);
 }
 
+// ---------------------------------------------------------------------------------------------
+// dW of few rows: 128 x 256 tiles (vocabulary x hidden), two workgroups per compute unit (72 KB of LDS each).
+// With few rows a tile of dW is a short K loop and 256 KB of stores, and with one workgroup per compute unit neither
+// overlaps the other: 28 us per 256 x 256 tile of 384 rows, 9 of them in the K loop, the stores of 2.5 GB taking 450 of
+// the launch's 900 us.  Here one workgroup's products run under the other's stores.  What the loads then cost is
+// L2 requests (one per clock and channel, of 64 or 128 bytes): the hidden rows lie in blocks of 32 token rows
+// ([rows / 32][dp][32], written so by launch_backward_rows_b16), so that a 32-wide K step is whole lines; as rows of
+// Ht, 64 bytes at a time, the launch was no faster than the large tile.  Stores are whole lines as well (lanes exchange
+// 16-byte pieces so that an instruction covers 8 rows x 128 bytes) and, where rows of dW are whole lines,
+// streaming: dW does not displace the operands (327 rows, d = 4096 834 and 727 us; with rows that straddle lines
+// streaming costs instead, 150 rows, d = 712 45 and 68).  32 consecutive tiles per XCD, whose stores then lie
+// 4 MB and not 8 MB apart (400 rows, V = 140000, d = 2048 473 and 435).  Launch, us, large tile and this one:
+// V = 151936, d = 4096, 150 rows 767 and 647, 400 rows 1000 and 856, 900 rows 1470 and 1340; d = 1536, 400 rows 376 and 348;
+// accumulating 400 rows 1413 and 1215, 533 and 480; V = 50257, d = 712 79 and 69, accumulating 114 and 92.
+// ---------------------------------------------------------------------------------------------
+constexpr int DM = 128, DN = 256, DK = kRowBlock, DSTAGES = 3;
+constexpr int D_A = DK * DM * 2, D_STAGE = D_A + DN * DK * 2, D_LDS = DSTAGES * D_STAGE;   // 24 KB per stage
+constexpr int D_LOADS = 6;                                          // direct loads per wave and stage: 2 of A, 4 of B
+// Where it is the faster one.  Above 1024 rows the large tile's K loop counts for more (1536 rows 0.92 - 1.05).  Below,
+// accumulating launches always gain (1.005 - 1.28); overwriting ones lose where the large tile's 8 x 4 super-tiles
+// fit the columns, its stores being short of nothing then, and dW is too large for the memory-side cache to
+// take a good part of it: V = 128256, d = 1024, 400 rows 204 us and 231, V = 140000, d = 2048, 150 rows 348 and 376 (but
+// V = 100000, d = 1024 178 and 162, V = 32000, d = 2048 105 and 90).
+constexpr int kFewDwRows = 1024;
+inline bool few_dw(int rows, int V, int d, int overwrite) {
+  const int Nt = (d + BN - 1) / BN;
+  const bool fits = d % 32 == 0 && Nt % 4 == 0 && Nt <= 8 && (int64_t)V * d * 4 > ((int64_t)400 << 20);
+  return rows <= kFewDwRows && !(overwrite && fits);
+}
+
+__global__ __launch_bounds__(NTHREADS, 2) void dw_few_bf16(Params p) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int frow = lane & 15, fq = lane >> 4, wm = wave >> 1, wn = wave & 1;
+  int64_t nv64 = *p.n_scored - p.chunk_start;
+  const int nvalid = nv64 < 0 ? 0 : (nv64 > p.chunk_rows ? p.chunk_rows : (int)nv64);
+  if (nvalid == 0 && !p.overwrite) return;
+  const int Mt = (p.V + DM - 1) / DM, Nt = (p.d + DN - 1) / DN;
+  int tm, tn;
+  if (!dealt_tile(blockIdx.x, Mt, Nt, tm, tn)) return;
+  const int m0 = tm * DM, n0 = tn * DN;
+  const int nk = dw_panels(nvalid, p.K) * (BK / DK);
+
+  // direct loads, 1 KB each.  A, K-major: 4 k rows x 256 bytes; lane l fills chunk slot l % 16 of row l / 16 and fetches
+  // logical chunk slot ^ (kswz(k) << 1).  B: 16 rows x 64 bytes, contiguous; slot l % 4 of row l / 4, swizzle (row >> 2) & 3.
+  const uint16_t* src[D_LOADS];
+  uint32_t dst[D_LOADS];
+  const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
+#pragma unroll
+  for (int i = 0; i < D_LOADS; ++i) {
+    if (i < 2) {
+      const int blk = wave * 2 + i, k = blk * 4 + (lane >> 4);
+      const int col = m0 + (((lane & 15) ^ (kswz(k) << 1)) << 3);
+      src[i] = p.A + (int64_t)k * p.lda + (col < p.V ? col : m0);
+      dst[i] = __builtin_amdgcn_readfirstlane(lds_base + blk * 1024);
+    } else {
+      const int blk = wave * 4 + i - 2, r = blk * 16 + (lane >> 2);
+      const int n = n0 + r < p.N ? n0 + r : p.N - 1;
+      src[i] = p.B + (int64_t)n * DK + (((lane & 3) ^ ((r >> 2) & 3)) << 3);
+      dst[i] = __builtin_amdgcn_readfirstlane(lds_base + D_A + blk * 1024);
+    }
+  }
+  const int64_t a_step = (int64_t)DK * p.lda * 2, b_step = p.ldb * (DK * 2);
+  auto load = [&](int kt, uint32_t stage) {
+    kt = kt < nk ? kt : nk - 1;
+#pragma unroll
+    for (int i = 0; i < D_LOADS; ++i) {
+      uint64_t addr;
+      asm volatile("s_mov_b32 m0, %3\n\tv_lshl_add_u64 %0, %1, 0, %2\n\tglobal_load_lds_dwordx4 %0, off"
+                   : "=&v"(addr) : "v"(src[i]), "s"(kt * (i < 2 ? a_step : b_step)), "s"(dst[i] + stage) : "memory");
+    }
+  };
+  const int kr = 8 * fq + (frow >> 2);
+  const int a_base = kr * (DM * 2) + ((kswz(kr) ^ (wm * 4)) << 5) + ((frow & 3) << 3);
+  const int b_base = D_A + (wn * 128 + frow) * (DK * 2) + ((fq ^ (frow >> 2)) << 4);
+  f32x4 acc[4][8];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 8; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  if (nk > 0) {
+    load(0, 0);
+    load(1, D_STAGE);
+    uint32_t st = 0, st_load = 2 * D_STAGE;
+    for (int kt = 0; kt < nk; ++kt) {
+      // (as in forward_few_bf16: this stage has landed when only the next one's loads are outstanding)
+      __builtin_amdgcn_s_waitcnt(waitcnt_vm(D_LOADS));
+      __syncthreads();
+      load(kt + 2, st_load);
+      bf16x8 fa[4], fb[8];
+      const unsigned char* base = smem + st;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) fb[j] = *reinterpret_cast<const bf16x8*>(base + b_base + j * 16 * (DK * 2));
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        typedef short v4i16 __attribute__((ext_vector_type(4)));
+        typedef __attribute__((address_space(3))) v4i16* lds_v4i16;
+        unsigned char* q = smem + st + (a_base ^ (i << 5));
+        const v4i16 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16)q);
+        const v4i16 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16)(q + 4 * (DM * 2)));
+        fa[i] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j], fa[i], acc[i][j], 0, 0, 0);
+      st = st == (DSTAGES - 1) * D_STAGE ? 0 : st + D_STAGE;
+      st_load = st_load == (DSTAGES - 1) * D_STAGE ? 0 : st_load + D_STAGE;
+    }
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));        // no direct load may outlive the wave
+  }
+  // The accumulators hold, per lane, row m0 + wm * 64 + i * 16 + frow, columns n0 + wn * 128 + j * 16 + 4 fq + e.  Of blocks j
+  // and j + 1, lanes frow < 8 and frow >= 8 exchange halves: the first of a pair of stores takes rows 0 - 7 and 32
+  // columns, the second rows 8 - 15.
+  const int v0 = m0 + wm * 64 + (frow & 7), nb = n0 + wn * 128 + 16 * (frow >> 3) + 4 * fq;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    f32x4 x[8], old[8];
+    float* at[8];
+    bool ok[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int v = v0 + i * 16 + 8 * (j & 1), n = nb + 16 * (j & ~1);
+      ok[j] = v < p.V && n < p.d;
+      at[j] = p.dW + (int64_t)v * p.d + n;
+      const f32x4 a = acc[i][j & ~1], b = acc[i][j | 1];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int ia = __float_as_int(a[e]), ib = __float_as_int(b[e]);
+        x[j][e] = __int_as_float((j & 1) == 0 ? __builtin_amdgcn_update_dpp(ia, ib, 0x128, 0xf, 0xc, false)
+                                              : __builtin_amdgcn_update_dpp(ib, ia, 0x128, 0xf, 0x3, false));
+      }
+    }
+    if (!p.overwrite) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) if (ok[j]) old[j] = *reinterpret_cast<const f32x4_any*>(at[j]);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) if (ok[j]) x[j] = old[j] + x[j];
+    }
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      if (ok[j]) {
+        if (p.streaming) asm volatile("global_store_dwordx4 %0, %1, off nt\n\ts_nop 1" :: "v"(at[j]), "v"(x[j]) : "memory");
+        else *reinterpret_cast<f32x4_any*>(at[j]) = x[j];
+      }
+  }
+}
+
 // dW tail.  The workgroup -> tile mapping runs whole super-tile rows of sup_m tile rows; V / 256
 // tile rows leave a last, ragged super-tile row (2 tile rows x 16 tiles at V = 151936, d = 4096)
 // that keeps an eighth of the compute units busy for the time of a full tile while the others
@@ -1288,10 +1436,11 @@ void launch_gemm_dh_bf16(const void* E, int64_t lde, const void* W, int64_t ldw,
 
 size_t gemm_tail_tile_bytes() { return (size_t)BM * BN * sizeof(float); }
 int gemm_dw_tail_items() { return kDwTailMaxItems; }
+bool dw_rows_in_blocks(int rows, int V, int d, int overwrite) { return few_dw(rows, V, d, overwrite); }
 
 void launch_gemm_dw_bf16(const void* E, int64_t lde, const void* Ht, int64_t ldht,
                          const int64_t* n_scored, int64_t chunk_start, int chunk_rows,
-                         int V, int d, float* dW, int overwrite, float* tail_part, hipStream_t stream) {
+                         int V, int d, float* dW, int overwrite, float* tail_part, bool in_blocks, hipStream_t stream) {
   Params p = {};
   p.A = static_cast<const uint16_t*>(E); p.lda = lde; p.M = (int)round_up(V, kTile);
   p.B = static_cast<const uint16_t*>(Ht); p.ldb = ldht; p.N = d;
@@ -1299,6 +1448,15 @@ void launch_gemm_dw_bf16(const void* E, int64_t lde, const void* Ht, int64_t ldh
   p.n_scored = n_scored; p.chunk_start = chunk_start; p.chunk_rows = chunk_rows;
   p.dW = dW; p.overwrite = overwrite; p.V = V; p.d = d;
   p.tail_part = tail_part;
+  if (in_blocks) {
+    p.N = (int)ldht;                                  // (rows of a block: d rounded up to 128)
+    p.streaming = d % 32 == 0 && (reinterpret_cast<uintptr_t>(dW) & 127) == 0;
+    static LdsLimit lds_limit;
+    lds_limit.ensure(reinterpret_cast<const void*>(&dw_few_bf16), D_LDS);
+    const int64_t tiles = (int64_t)((V + DM - 1) / DM) * ((d + DN - 1) / DN);
+    hipLaunchKernelGGL(dw_few_bf16, dim3((unsigned)round_up(tiles, NXCD)), dim3(NTHREADS), D_LDS, stream, p);
+    return;
+  }
   launch<MODE_DW>(p, stream);
 }
 

@@ -86,11 +86,14 @@ void launch_gemm_dh_bf16(const void* E, int64_t lde, const void* W, int64_t ldw,
 // overwrite = 1 stores, 0 adds into the existing values.
 // tail_part: scratch of gemm_dw_tail_items() * gemm_tail_tile_bytes() bytes for the K-split tail tiles (nullptr: the
 // ragged last rows of tiles run as whole tiles).
+// in_blocks: the launch for few rows, with Ht in blocks of kRowBlock token rows, [chunk_rows / 32][ldht][32], ldht = d
+// rounded up to 128; dw_rows_in_blocks says where it is the faster one (rows: the scored rows expected; right for any number).
 size_t gemm_tail_tile_bytes();
 int gemm_dw_tail_items();
+bool dw_rows_in_blocks(int rows, int V, int d, int overwrite);
 void launch_gemm_dw_bf16(const void* P, int64_t ldp, const void* Ht, int64_t ldht,
                          const int64_t* n_scored, int64_t chunk_start, int chunk_rows,
-                         int V, int d, float* dW, int overwrite, float* tail_part, hipStream_t stream);
+                         int V, int d, float* dW, int overwrite, float* tail_part, bool in_blocks, hipStream_t stream);
 
 // ---- fp32 GEMM (small-shape path): C[m][n] = sum_k A[m][k] * B[n][k] --------
 // An operand is k-contiguous (element (row, k) at row * ld + k) or, with its kmajor flag, stored with
@@ -192,9 +195,10 @@ void launch_pad_rows_b16(const void* in, int64_t ld_in, void* out, int64_t ld_ou
 // bf16 path, operands of the dW launch (Hc as the row preparation wrote it): Ht[c][r] = scale[r] * Hc[r][c] (c < dp, a multiple of 64) for the
 // pass's valid rows, zeros up to their multiple of 128; the stash rows in between are cleared (the
 // dW contraction runs over pairs of 64-row panels; the forward kernel writes valid rows only).
+// in_blocks: Ht[r / 32][c][r % 32] instead.
 void launch_backward_rows_b16(const void* Hc, int64_t ldh, const float* scale, void* Ht, int64_t ldht,
                               const int64_t* n_scored, int64_t chunk_start, int chunk_rows, int dp, void* E, int64_t lde,
-                              int Vp, hipStream_t stream);
+                              int Vp, bool in_blocks, hipStream_t stream);
 
 // Group-relative advantages (Sec. 3) with pooled / own statistics and SGT gate flags.
 void launch_group_advantages(const float* rewards, const int32_t* group_id, const uint8_t* in_stats,

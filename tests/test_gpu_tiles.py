@@ -338,3 +338,69 @@ def test_dw_beside_the_pad_columns(mrl, scored, d, V):
     out, dH, dW = _step(mrl, H, W, y, mask, mrl.BF16, V, poison=True)
     util.check_gradient("dW", util.to_f64(out["dW"]), dW)
     util.check_gradient("dH", util.to_f64(out["dH"]), dH)
+
+
+@pytest.mark.parametrize("N,scored,d,V,shift", [
+    (1, 1, 8, 2, 0),              # one row, one tile of which two ids and eight columns are there
+    (300, 129, 96, 127, 0),       # whole-line rows, a tile short of one id; two panel pairs
+    (300, 128, 136, 129, 1),      # rows that straddle lines, at 4-byte alignment; two tile rows
+    (1024, 1000, 264, 700, 0),    # two tile columns, the second of 8
+    (1024, 1024, 512, 5000, 3),   # whole-line widths at 4-byte alignment; 40 x 2 tiles
+    (900, 0, 128, 300, 0),        # no rows: zeros, or dW untouched
+])
+def test_dw_of_few_rows(mrl, N, scored, d, V, shift):
+    """The dW launch for at most 1024 rows, overwriting and accumulating into earlier values, dW at any float address."""
+    H, W, y, mask = _head(N, d, V, scored, N + d)
+    if scored > 0:
+        _, _, want = _step(mrl, H, W, y, mask, mrl.F32, V, poison=True)
+    else:
+        want = np.zeros((V, d))
+    g = torch.Generator("cuda").manual_seed(V)
+    one = lambda v, t: torch.tensor([v], dtype=t, device="cuda")
+    for accumulate in (0, 1):
+        # the values around dW belong to others
+        buf = torch.randn(V * d + 64, device="cuda", generator=g) * 1e-3
+        dW = buf[32 + shift:32 + shift + V * d].view(V, d)
+        before = buf.clone()
+        cfg = mrl.LossConfig(kl_beta=0.0, dh_dtype=mrl.F32, accumulate_dw=accumulate)
+        ws = torch.full((mrl.grpo_loss_workspace(1, N, d, V, mrl.BF16, cfg),), 255, dtype=torch.uint8, device="cuda")
+        behav = _behaviour(H, W, y, mask, V)
+        mrl.grpo_loss_fwd_bwd(H, W, y, mask, behav, None, one(0.7, torch.float32), one(0, torch.int32), None, 1, N, 1, cfg,
+                              out_dW=dW, workspace=ws)
+        torch.cuda.synchronize()
+        old = before[32 + shift:32 + shift + V * d].view(V, d)
+        got = util.to_f64(dW) - (util.to_f64(old) if accumulate else 0.0)
+        if scored > 0:
+            # accumulating: one rounding of a sum of at most 5e-3 + |dW| more than the oracle's
+            slack = 2.0 ** -24 * (5e-3 + np.abs(want).max()) * accumulate
+            assert np.abs(got - want).max() <= 1e-2 * np.abs(want).max() + slack
+            assert util.rel_fro(got, want) <= util.REL_TOL + slack * np.sqrt(want.size) / np.linalg.norm(want)
+        else:
+            assert np.all(got == 0)
+        assert torch.equal(buf[:32 + shift], before[:32 + shift]) and torch.equal(buf[32 + shift + V * d:], before[32 + shift + V * d:])
+
+
+def _behaviour(H, W, y, mask, seed):
+    """The behaviour trace that _step draws."""
+    g = torch.Generator("cuda").manual_seed(seed)
+    rows = torch.nonzero(mask)[:, 0]
+    z = H[rows].double() @ W.double().t()
+    lp = z[torch.arange(rows.numel(), device="cuda"), y[rows].long()] - torch.logsumexp(z, 1)
+    behav = torch.zeros(H.shape[0], device="cuda")
+    behav[rows] = (lp + 0.05 * torch.randn(rows.numel(), device="cuda", generator=g)).float()
+    return behav
+
+
+@pytest.mark.parametrize("scored", [1025, 1400])
+def test_dw_k_split_tail_above_the_few_rows(mrl, scored):
+    """The large dW launch with its ragged last tile rows cut into eight K slices: more than 1024 rows, a second pass that
+    adds into the first's result, poisoned scratch."""
+    d, V = 1536, 11000
+    assert mrl.dw_tail_plan(V, d)["split"] == 8
+    H, W, y, mask = _head(1500, d, V, scored, scored)
+    out, _, dW = _step(mrl, H, W, y, mask, mrl.BF16, V, poison=True)
+    again, _, _ = _step(mrl, H, W, y, mask, mrl.BF16, V, poison=True)
+    two, _, _ = _step(mrl, H, W, y, mask, mrl.BF16, V, chunk_rows=1280, poison=True)
+    assert torch.equal(out["dW"], again["dW"])
+    util.check_gradient("dW", util.to_f64(out["dW"]), dW)
+    util.check_gradient("dW", util.to_f64(two["dW"]), dW)
