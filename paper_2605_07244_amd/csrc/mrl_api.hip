@@ -265,8 +265,9 @@ void pad_head(const void* W, int d, int V, const Layout& L, void* ws, hipStream_
 }
 
 // forward of one chunk: logits tile GEMM with fused (or, in fp32, separate) log-sum-exp
+// (lse: fp32, the latter wanted)
 void forward_chunk(const void* H, const void* W, int d, int V, bool bf16, const Layout& L, void* ws,
-                   int64_t c0, bool stash, hipStream_t s, bool entropy = false) {
+                   int64_t c0, bool stash, hipStream_t s, bool entropy = false, bool lse = true) {
   const int32_t* row_index = at<int32_t>(ws, L.row_index);
   const int64_t* n_scored = at<int64_t>(ws, L.counters);
   if (bf16) {
@@ -295,8 +296,9 @@ void forward_chunk(const void* H, const void* W, int d, int V, bool bf16, const 
     g.n_scored = n_scored; g.chunk_start = c0; g.chunk_rows = L.chunk_rows;
     g.m_dynamic = 1; g.k_dynamic = 0; g.accumulate = 0;
     launch_gemm_f32(g, s);
-    launch_row_lse_f32(at<float>(ws, L.Z), L.ldz, n_scored, c0, L.chunk_rows, V, at<float>(ws, L.part_max),
-                       at<float>(ws, L.part_sum), entropy ? at<float>(ws, L.part_ez) : nullptr, s);
+    if (lse)
+      launch_row_lse_f32(at<float>(ws, L.Z), L.ldz, n_scored, c0, L.chunk_rows, V, at<float>(ws, L.part_max),
+                         at<float>(ws, L.part_sum), entropy ? at<float>(ws, L.part_ez) : nullptr, s);
   }
 }
 
@@ -559,10 +561,15 @@ int mrl_grpo_loss_fwd_bwd(const void* hidden, const void* lm_head_w, const int32
     launch_seq_log_ratio(token_mask, target_ids, out_logp, behav_logp, B, T, V, cfg->ratio_level,
                          at<float>(ws, L.seq_expo), s);
   }
+  // fp32, small vocabularies: one launch from the logits to dz, with a loss partial per 16 rows; the partials of N rows
+  // take less than lse_c, g_c and loss_partials, which lie in a row and of which that launch needs none
+  const bool row_f32 = !bf16 && row_f32_fits(V);
+  double* const partials = at<double>(ws, row_f32 ? L.lse_c : L.loss_partials);
+  int64_t n_partials = 0;
   for (int64_t c = 0; c < n_passes; ++c) {
     const int64_t c0 = c * L.chunk_rows;
     if (c > 0) prepare_chunk(hidden, lm_head_w, target_ids, d, bf16, L, ws, c, n_passes, false, RowPrepArgs{}, s);
-    if (c > 0 || cfg->ratio_level == 0) forward_chunk(hidden, lm_head_w, d, V, bf16, L, ws, c0, bwd, s);
+    if (c > 0 || cfg->ratio_level == 0) forward_chunk(hidden, lm_head_w, d, V, bf16, L, ws, c0, bwd, s, false, !row_f32);
     {
       Scope sc(MRL_PROF_ROW_EPI, s);
       RowEpiArgs e = {};
@@ -576,13 +583,18 @@ int mrl_grpo_loss_fwd_bwd(const void* hidden, const void* lm_head_w, const int32
       e.eps_lo = cfg->clip_eps_low; e.eps_hi = cfg->clip_eps_high; e.beta = beta; e.lambda = cfg->sgt_lambda;
       e.out_logp = out_logp; e.out_lse = nullptr;
       e.lse_c = at<float>(ws, L.lse_c); e.g_c = at<float>(ws, L.g_c);
-      if (bf16 && bwd) {
-        e.row_scale = at<float>(ws, L.row_scale); e.estash = at<uint16_t>(ws, L.Z); e.lde = L.ldz;
-        e.targets = target_ids;
+      if (bf16 && bwd) { e.row_scale = at<float>(ws, L.row_scale); e.estash = at<uint16_t>(ws, L.Z); e.lde = L.ldz; }
+      e.targets = target_ids;
+      e.loss_partials = partials;
+      e.partial_block_offset = n_partials;
+      if (row_f32) {
+        const int rows = (int)(N - c0 < L.chunk_rows ? N - c0 : L.chunk_rows);
+        launch_row_f32(e, at<float>(ws, L.Z), L.ldz, V, rows, bwd, s);
+        n_partials += row_f32_blocks(rows);
+      } else {
+        launch_row_epilogue(e, s);
+        n_partials += row_epilogue_blocks(L.chunk_rows);
       }
-      e.loss_partials = at<double>(ws, L.loss_partials);
-      e.partial_block_offset = c * row_epilogue_blocks(L.chunk_rows);
-      launch_row_epilogue(e, s);
     }
     if (!bwd) continue;
     const int overwrite = (c == 0 && !cfg->accumulate_dw) ? 1 : 0;
@@ -597,7 +609,7 @@ int mrl_grpo_loss_fwd_bwd(const void* hidden, const void* lm_head_w, const int32
         if (out_dW)
           launch_backward_rows_b16(at<void>(ws, L.Hc), L.ldh, at<float>(ws, L.row_scale) + c0, at<void>(ws, L.Ht), L.ldr,
                                    n_scored, c0, L.chunk_rows, L.dp, at<void>(ws, L.Z), L.ldz, (int)L.Vp, dw_blocks, s);
-      } else {
+      } else if (!row_f32) {
         launch_convert_f32(at<float>(ws, L.Z), L.ldz, at<float>(ws, L.lse_c), at<float>(ws, L.g_c), target_ids, row_index,
                            n_scored, c0, L.chunk_rows, V, s);
       }
@@ -640,7 +652,7 @@ int mrl_grpo_loss_fwd_bwd(const void* hidden, const void* lm_head_w, const int32
   }
   {
     Scope sc(MRL_PROF_FINAL, s);
-    launch_finalize(at<double>(ws, L.loss_partials), n_passes * row_epilogue_blocks(L.chunk_rows), n_scored,
+    launch_finalize(partials, n_partials, n_scored,
                     n_scored + 1, beta, cfg->sgt_lambda, n_passes * (int64_t)L.chunk_rows, row_index, out_logp,
                     out_stats, s);
   }

@@ -181,6 +181,13 @@ struct RowEpiArgs {
 int row_epilogue_blocks(int chunk_rows);
 void launch_row_epilogue(const RowEpiArgs& a, hipStream_t stream);
 
+// fp32 path, V small enough (row_f32_fits): log-sum-exp of the materialised logits, row epilogue and, with write_dz, conversion
+// to dz in one launch.  Of a: part_max .. out_entropy, lse_c, g_c and row_scale are not used; a loss partial per
+// row_f32_blocks' block of rows.  rows: those the pass can have (at most chunk_rows).
+bool row_f32_fits(int V);
+int row_f32_blocks(int64_t rows);
+void launch_row_f32(const RowEpiArgs& a, float* Z, int64_t ldz, int V, int rows, int write_dz, hipStream_t stream);
+
 // fp32 path, dz conversion: P[i][v] = g_i (1[v = y_i] - exp(z - lse_i)) in place of the chunk's logits.
 void launch_convert_f32(float* ZP, int64_t ldz, const float* lse_c,
                         const float* g_c, const int32_t* targets, const int32_t* row_index,

@@ -404,3 +404,26 @@ def test_dw_k_split_tail_above_the_few_rows(mrl, scored):
     assert torch.equal(out["dW"], again["dW"])
     util.check_gradient("dW", util.to_f64(out["dW"]), dW)
     util.check_gradient("dW", util.to_f64(two["dW"]), dW)
+
+
+@pytest.mark.parametrize("N,scored,V,chunk_rows", [
+    (1, 1, 2, 0), (40, 17, 64, 0), (300, 300, 65, 256), (500, 260, 2047, 256), (272, 257, 2048, 0), (272, 257, 2049, 0),
+])
+def test_fp32_rows_in_one_launch(mrl, N, scored, V, chunk_rows):
+    """fp32 loss calls around the vocabulary up to which a row's log-sum-exp, loss terms and dz share a launch: rows beside a
+    multiple of its 16 per block, a second pass with one row or a part of them, poisoned scratch; gradients and statistics."""
+    d = 40
+    H, W, y, mask = _head(N, d, V, scored, N + V)
+    H, W = H.float(), 10 * W.float()
+    out, dH, dW = _step(mrl, H, W, y, mask, mrl.F32, V, chunk_rows=chunk_rows, poison=True)
+    rows = torch.nonzero(mask)[:, 0]
+    z = H[rows].double() @ W.double().t()
+    lp = z.gather(1, y[rows].long()[:, None])[:, 0] - torch.logsumexp(z, 1)
+    # fp32 sums of at most 2049 terms: 2^-24 * sqrt(2049) relative, times the depth of the chain
+    assert float((out["logp"][rows].double() - lp).abs().max()) <= 2e-5
+    assert util.rel_fro(util.to_f64(out["dH"]), dH) <= 2e-5 and util.rel_fro(util.to_f64(out["dW"]), dW) <= 2e-5
+    st = mrl.read_stats(out["stats"])
+    w = torch.exp(lp - _behaviour(H, W, y, mask, V)[rows].double())
+    loss = -float(torch.minimum(0.7 * w, 0.7 * w.clamp(0.8, 1.2)).mean())
+    assert abs(st["loss_pg"] - loss) <= 1e-5 * abs(loss) and st["n_scored_tokens"] == scored
+    assert abs(st["mean_ratio"] - float(w.mean())) <= 2e-5 and abs(st["max_ratio"] - float(w.max())) <= 5e-5
