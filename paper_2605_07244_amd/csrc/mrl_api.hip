@@ -387,16 +387,18 @@ int mrl_token_scores(const void* hidden, const void* lm_head_w, const int32_t* t
   void* ws = workspace;
   int32_t* row_index = at<int32_t>(ws, L.row_index);
   int64_t* n_scored = at<int64_t>(ws, L.counters);
+  const PrepOut po = {row_index, n_scored, n_scored + 1, at<int32_t>(ws, L.block_counts), {out_logp, out_lse, out_entropy},
+                      0, 0, nullptr};
+  RowPrepArgs once = {};
   {
     Scope sc(MRL_PROF_PREP, s);
-    const PrepOut po = {row_index, n_scored, n_scored + 1, at<int32_t>(ws, L.block_counts),
-                        {out_logp, out_lse, out_entropy}, 0, 0, nullptr};
-    launch_prep(token_mask, target_ids, N, V, po, s);
+    if (prep_inline(N)) { once.prep = &po; once.mask = token_mask; once.N = N; once.V = V; }
+    else launch_prep(token_mask, target_ids, N, V, po, s);
     pad_head(lm_head_w, d, V, L, ws, s);
   }
   for (int64_t c = 0; c < L.n_chunks; ++c) {
     const int64_t c0 = c * L.chunk_rows;
-    prepare_chunk(hidden, lm_head_w, target_ids, d, bf16, L, ws, c, L.n_chunks, c == 0, RowPrepArgs{}, s);
+    prepare_chunk(hidden, lm_head_w, target_ids, d, bf16, L, ws, c, L.n_chunks, c == 0, c == 0 ? once : RowPrepArgs{}, s);
     forward_chunk(hidden, lm_head_w, d, V, bf16, L, ws, c0, false, s, entropy);
     Scope sc(MRL_PROF_ROW_EPI, s);
     RowEpiArgs e = {};
@@ -506,11 +508,11 @@ int mrl_grpo_loss_fwd_bwd(const void* hidden, const void* lm_head_w, const int32
   int64_t* n_scored = at<int64_t>(ws, L.counters);
   const float beta = ref_logp ? cfg->kl_beta : 0.f;
 
+  const PrepOut po = {row_index, n_scored, n_scored + 1, at<int32_t>(ws, L.block_counts), {out_logp, nullptr, nullptr},
+                      B, T, at<int32_t>(ws, L.seq_len)};
   {
     Scope sc(MRL_PROF_PREP, s);
-    const PrepOut po = {row_index, n_scored, n_scored + 1, at<int32_t>(ws, L.block_counts),
-                        {out_logp, nullptr, nullptr}, B, T, at<int32_t>(ws, L.seq_len)};
-    launch_prep(token_mask, target_ids, N, V, po, s);
+    if (!prep_inline(N)) launch_prep(token_mask, target_ids, N, V, po, s);
     pad_head(lm_head_w, d, V, L, ws, s);
   }
   int64_t n_passes = L.n_chunks;
@@ -520,6 +522,7 @@ int mrl_grpo_loss_fwd_bwd(const void* hidden, const void* lm_head_w, const int32
   }
   // the first pass that is prepared carries the sequence weights and the zero dH rows along
   RowPrepArgs once = {};
+  once.prep = prep_inline(N) ? &po : nullptr;
   once.mask = token_mask; once.N = N; once.V = V;
   once.dH = out_dH; once.dh_row_bytes = (int64_t)d * (cfg->dh_dtype == MRL_BF16 ? 2 : 4);
   once.seq_len = at<int32_t>(ws, L.seq_len); once.group_id = group_id; once.seq_kind = seq_kind;

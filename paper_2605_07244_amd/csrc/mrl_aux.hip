@@ -413,12 +413,86 @@ __device__ inline void zero_dh_rows(const RowPrepArgs& a, int64_t first) {
   }
 }
 
-template <bool BF16>
-__global__ __launch_bounds__(256) void k_row_prep(RowPrepArgs a) {
+// Compaction of N <= kPrepInline slots by one block of 256: a contiguous run of slots per wave, f(slot, rank among the scored
+// ones, scored, masked in with a bad target) per slot; returns the number of scored ones.  Every block of the
+// launch that needs it does it for itself (20 KB from the L2), which takes less than a launch that does it once.
+template <class F>
+__device__ inline int compact_block(const uint8_t* mask, const int32_t* targets, int N, int V, F f) {
+  constexpr int kIters = kPrepInline / 256;
+  __shared__ int sums[4];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int iters = (N + 255) / 256, first = wave * iters * 64;
+  uint32_t scored = 0, bad = 0;
+  int cnt = 0;
+#pragma unroll
+  for (int it = 0; it < kIters; ++it) {
+    const int n = first + it * 64 + lane;
+    if (it < iters && n < N) {
+      const int32_t y = targets[n];
+      const bool in = mask == nullptr || mask[n] != 0, ok = y >= 0 && y < V;
+      scored |= (uint32_t)(in && ok) << it;
+      bad |= (uint32_t)(in && !ok) << it;
+    }
+  }
+#pragma unroll
+  for (int it = 0; it < kIters; ++it) cnt += __popcll(__ballot((scored >> it) & 1));
+  if (lane == 0) sums[wave] = cnt;
+  __syncthreads();
+  int pos = 0, total = 0;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) { pos += w < wave ? sums[w] : 0; total += sums[w]; }
+#pragma unroll
+  for (int it = 0; it < kIters; ++it) {
+    const int n = first + it * 64 + lane;
+    const bool ok = (scored >> it) & 1;
+    const unsigned long long ball = __ballot(ok);
+    if (it < iters && n < N) f(n, pos + __popcll(ball & ((1ull << lane) - 1ull)), ok, ((bad >> it) & 1) != 0);
+    pos += __popcll(ball);
+  }
+  return total;
+}
+
+// PREP: what k_prep_one does comes with this launch
+template <bool BF16, bool PREP>
+__global__ __launch_bounds__(256) void k_row_prep(RowPrepArgs a, PrepOut prep) {
   __shared__ int32_t lds_count[kCoefLdsGroups];
   int64_t block = blockIdx.x;
+  if (PREP) {
+    if (block == 0) {
+      // the compaction's outputs
+      int bad = 0;
+      const int N = (int)a.N;
+      const SlotOutputs zero = {{prep.zero[0], prep.zero[1], prep.zero[2]}};
+      const int total = compact_block(a.mask, a.targets, N, a.V, [&](int n, int rank, bool ok, bool wrong) {
+        if (ok) prep.row_index[rank] = n;
+        else zero_slot(zero, n);
+        bad += wrong;
+      });
+      for (int n = total + threadIdx.x; n < N; n += 256) prep.row_index[n] = 0;     // tail entries: a harmless valid slot
+      __shared__ int bads[4];
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) bad += __shfl_xor(bad, off);
+      if ((threadIdx.x & 63) == 0) bads[threadIdx.x >> 6] = bad;
+      __syncthreads();
+      if (threadIdx.x == 0) { *prep.n_scored = total; *prep.n_bad = bads[0] + bads[1] + bads[2] + bads[3]; }
+      return;
+    }
+    --block;
+  }
   if (a.seq_coef != nullptr) {
     if (block == 0) {
+      if (PREP) {
+        // scored slots of the sequences (B <= N <= kPrepInline)
+        static_assert(kPrepInline <= kCoefLdsGroups, "a count per sequence");
+        for (int b = threadIdx.x; b < prep.B; b += 256) lds_count[b] = 0;
+        __syncthreads();
+        for (int n = threadIdx.x; n < (int)a.N; n += 256)
+          if (slot_valid(a.mask, a.targets, n, a.V)) atomicAdd(&lds_count[n / prep.T], 1);
+        __syncthreads();
+        for (int b = threadIdx.x; b < prep.B; b += 256) prep.seq_len[b] = lds_count[b];
+        __threadfence_block();
+        __syncthreads();
+      }
       const CoefArgs c = {a.seq_len, a.group_id, a.seq_kind, a.B, a.G, a.loss_agg, a.group_count, a.seq_coef, a.n_bad_groups};
       if (a.B <= 256) seq_coef_block<1>(c, lds_count); else seq_coef_block<kCoefSteps>(c, lds_count);
       return;
@@ -428,9 +502,22 @@ __global__ __launch_bounds__(256) void k_row_prep(RowPrepArgs a) {
   if (block < a.zero_blocks) { zero_dh_rows(a, block * ZERO_SLOTS_PER_BLOCK); return; }
   block -= a.zero_blocks;
   const int64_t r = block * 4 + (threadIdx.x >> 6);
-  if (r >= valid_rows(a.n_scored, a.chunk_start, a.chunk_rows)) return;
   const int lane = threadIdx.x & 63;
-  const int64_t slot = a.row_index[a.chunk_start + r];
+  int64_t slot;
+  if (PREP) {
+    __shared__ int32_t slots[4];
+    const int r0 = (int)(a.chunk_start + block * 4);  // (rank of the block's first row)
+    if (r0 >= (int)a.N) return;
+    const int total = compact_block(a.mask, a.targets, (int)a.N, a.V, [&](int n, int rank, bool ok, bool) {
+      if (ok && rank >= r0 && rank < r0 + 4) slots[rank - r0] = n;
+    });
+    __syncthreads();
+    if (r >= a.chunk_rows || a.chunk_start + r >= total) return;
+    slot = slots[threadIdx.x >> 6];
+  } else {
+    if (r >= valid_rows(a.n_scored, a.chunk_start, a.chunk_rows)) return;
+    slot = a.row_index[a.chunk_start + r];
+  }
   const int64_t y = a.targets[slot];
   float acc = 0.f;
   if (BF16) {
@@ -934,9 +1021,12 @@ void launch_seq_log_ratio(const uint8_t* mask, const int32_t* targets, const flo
 
 void launch_row_prep(RowPrepArgs a, int is_bf16, hipStream_t stream) {
   a.zero_blocks = a.dH != nullptr ? (a.N + ZERO_SLOTS_PER_BLOCK - 1) / ZERO_SLOTS_PER_BLOCK : 0;
-  const int64_t blocks = (a.seq_coef != nullptr ? 1 : 0) + a.zero_blocks + (a.chunk_rows + 3) / 4;
-  if (is_bf16) hipLaunchKernelGGL(k_row_prep<true>, dim3((unsigned)blocks), dim3(256), 0, stream, a);
-  else hipLaunchKernelGGL(k_row_prep<false>, dim3((unsigned)blocks), dim3(256), 0, stream, a);
+  const int64_t blocks = (a.prep != nullptr ? 1 : 0) + (a.seq_coef != nullptr ? 1 : 0) + a.zero_blocks + (a.chunk_rows + 3) / 4;
+  const PrepOut prep = a.prep != nullptr ? *a.prep : PrepOut{};
+  auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(256), 0, stream, a, prep); };
+  if (a.prep != nullptr) { if (is_bf16) go(k_row_prep<true, true>); else go(k_row_prep<false, true>); }
+  else if (is_bf16) go(k_row_prep<true, false>);
+  else go(k_row_prep<false, false>);
 }
 
 void launch_row_lse_f32(const float* Z, int64_t ldz, const int64_t* n_scored, int64_t chunk_start,

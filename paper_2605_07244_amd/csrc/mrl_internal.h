@@ -128,6 +128,9 @@ struct PrepOut {
 };
 void launch_prep(const uint8_t* mask, const int32_t* targets, int64_t N, int V, const PrepOut& o,
                  hipStream_t stream);
+// Calls of at most kPrepInline slots take no launch_prep: the first launch_row_prep of the call is given its outputs.
+constexpr int64_t kPrepInline = 4096;
+inline bool prep_inline(int64_t N) { return N <= kPrepInline; }
 
 // Response-level log-ratio (App. I.1): seq_expo[b] = sum over the scored tokens of sequence b of
 // (logp - behav_logp), divided by the number of scored tokens when level == 2.  Fixed-order
@@ -150,6 +153,7 @@ struct RowPrepArgs {
   const int32_t* seq_len; const int32_t* group_id; const uint8_t* seq_kind; int64_t B; int G; int loss_agg;
   int32_t* group_count /*[G] scratch*/; float* seq_coef;
   int64_t* n_bad_groups /*[1]: sequences whose group id is outside [0, G)*/;
+  const PrepOut* prep;             // not nullptr: mask and targets are compacted here, too (prep_inline; mask, N, V are set)
 };
 void launch_row_prep(RowPrepArgs a, int is_bf16, hipStream_t stream);
 

@@ -427,3 +427,43 @@ def test_fp32_rows_in_one_launch(mrl, N, scored, V, chunk_rows):
     loss = -float(torch.minimum(0.7 * w, 0.7 * w.clamp(0.8, 1.2)).mean())
     assert abs(st["loss_pg"] - loss) <= 1e-5 * abs(loss) and st["n_scored_tokens"] == scored
     assert abs(st["mean_ratio"] - float(w.mean())) <= 2e-5 and abs(st["max_ratio"] - float(w.max())) <= 5e-5
+
+
+@pytest.mark.parametrize("B,T,extra", [(4096, 1, 8), (1, 4096, 1), (7, 585, 8), (64, 64, 2)])
+def test_prep_inside_the_row_preparation(mrl, B, T, extra):
+    """Up to 4096 slots the mask is compacted by the row preparation's own blocks.  The same call with `extra` empty auxiliary
+    sequences behind it has more slots and a preparation launch: the same bits.  Bad targets and group ids in both."""
+    d, V, G = 72, 300, 3 if B > 1 else 1
+    N, M = B * T, (B + extra) * T
+    assert N <= 4096 < M
+    g = torch.Generator("cuda").manual_seed(B)
+    H = torch.randn((M, d), device="cuda", generator=g).bfloat16()
+    W = (0.1 * torch.randn((V, d), device="cuda", generator=g)).bfloat16()
+    y = torch.randint(0, V, (M,), device="cuda", generator=g, dtype=torch.int32)
+    mask = (torch.rand(M, device="cuda", generator=g) < 0.6).to(torch.uint8)
+    mask[N:] = 0
+    y[torch.randperm(N, device="cuda", generator=g)[:5]] = V
+    behav = torch.randn(M, device="cuda", generator=g) * 0.1 - 6
+    adv = torch.randn(B + extra, device="cuda", generator=g)
+    group = torch.randint(0, G, (B + extra,), device="cuda", generator=g, dtype=torch.int32)
+    if B > 1:
+        group[1] = G
+    kind = torch.zeros(B + extra, dtype=torch.uint8, device="cuda")
+    kind[B:] = 1
+    cfg = mrl.LossConfig(kl_beta=0.0, dh_dtype=mrl.F32)
+
+    def call(b):
+        n = b * T
+        ws = torch.full((mrl.grpo_loss_workspace(b, T, d, V, mrl.BF16, cfg),), 255, dtype=torch.uint8, device="cuda")
+        out = mrl.grpo_loss_fwd_bwd(H[:n], W, y[:n], mask[:n], behav[:n], None, adv[:b], group[:b], kind[:b], b, T, G, cfg,
+                                    workspace=ws)
+        scores = mrl.token_scores(H[:n], W, y[:n], mask[:n])
+        torch.cuda.synchronize()
+        return out, mrl.read_stats(out["stats"]), scores
+
+    (a, sa, ca), (b, sb, cb) = call(B), call(B + extra)
+    assert sa == sb and sa["n_bad_targets"] > 0 and sa["n_scored_tokens"] > 0
+    assert torch.equal(a["logp"], b["logp"][:N]) and torch.equal(a["dH"], b["dH"][:N])
+    assert torch.equal(a["dW"], b["dW"])
+    assert all(torch.equal(p, q[:N]) and torch.all(q[N:] == 0) for p, q in zip(ca, cb))
+    assert torch.all(a["logp"][mask[:N] == 0] == 0) and torch.all(a["dH"][mask[:N] == 0] == 0)
