@@ -652,39 +652,36 @@ __device__ __forceinline__ float token_terms(const RowEpiArgs& a, int64_t slot, 
   const int64_t b = slot / a.T;
   const float c = a.seq_coef[b];
   const int kind = a.seq_kind ? a.seq_kind[b] : 0;
-  float g;
-  if (kind == 0) {
-    const float A = a.seq_adv[b];
-    // token ratio of Eq. (1), or the response's ratio (App. I.1) whose derivative with
-    // respect to each token's log-prob is rho (summed form) or rho / L_b (mean form)
-    const float w = a.seq_expo ? expf(a.seq_expo[b]) : expf(logp - a.behav_logp[slot]);
-    const float s1 = w * A;
-    const float wc = fminf(fmaxf(w, 1.f - a.eps_lo), 1.f + a.eps_hi);
-    const float s2 = wc * A;
-    const float J = fminf(s1, s2);
-    float dJ = s1 <= s2 ? s1 : 0.f;
-    if (a.seq_expo && a.ratio_level == 1) dJ *= (float)a.seq_len[b];
-    float k3 = 0.f, dk3 = 0.f;
-    if (a.ref_logp != nullptr) {
-      const float rho = a.ref_logp[slot] - logp;
-      const float em1 = expm1f(rho);
-      k3 = em1 - rho;
-      dk3 = -em1;
-    }
-    g = c * (-dJ + a.beta * dk3);
-    q[0] = -(double)c * (double)J;
-    q[1] = (double)c * (double)k3;
-    q[3] = (double)w;
-    q[4] = w > 0.f ? (double)w : 0.0;            // (a NaN ratio is left out of the maximum)
-    q[5] = (double)k3;
-    q[6] = (w < 1.f - a.eps_lo || w > 1.f + a.eps_hi) ? 1.0 : 0.0;
-    q[7] = s2 < s1 ? 1.0 : 0.0;
-    q[8] = 1.0;
-  } else {
-    g = -a.lambda * c;
+  if (kind != 0) {
     q[2] = -(double)c * (double)logp;
+    return -a.lambda * c;
   }
-  return g;
+  const float A = a.seq_adv[b];
+  // token ratio of Eq. (1), or the response's ratio (App. I.1) whose derivative with
+  // respect to each token's log-prob is rho (summed form) or rho / L_b (mean form)
+  const float w = a.seq_expo ? expf(a.seq_expo[b]) : expf(logp - a.behav_logp[slot]);
+  const float s1 = w * A;
+  const float wc = fminf(fmaxf(w, 1.f - a.eps_lo), 1.f + a.eps_hi);
+  const float s2 = wc * A;
+  const float J = fminf(s1, s2);
+  float dJ = s1 <= s2 ? s1 : 0.f;
+  if (a.seq_expo && a.ratio_level == 1) dJ *= (float)a.seq_len[b];
+  float k3 = 0.f, dk3 = 0.f;
+  if (a.ref_logp != nullptr) {
+    const float rho = a.ref_logp[slot] - logp;
+    const float em1 = expm1f(rho);
+    k3 = em1 - rho;
+    dk3 = -em1;
+  }
+  q[0] = -(double)c * (double)J;
+  q[1] = (double)c * (double)k3;
+  q[3] = (double)w;
+  q[4] = w > 0.f ? (double)w : 0.0;            // (a NaN ratio is left out of the maximum)
+  q[5] = (double)k3;
+  q[6] = (w < 1.f - a.eps_lo || w > 1.f + a.eps_hi) ? 1.0 : 0.0;
+  q[7] = s2 < s1 ? 1.0 : 0.0;
+  q[8] = 1.0;
+  return c * (-dJ + a.beta * dk3);
 }
 
 __global__ __launch_bounds__(EPI_THREADS) void k_row_epilogue(RowEpiArgs a) {
