@@ -8,6 +8,7 @@ PyTorch fallback: if the shared library is missing, loading raises.
 from __future__ import annotations
 
 import ctypes
+import importlib.util
 import os
 from ctypes import POINTER, c_char_p, c_double, c_float, c_int, c_int32, c_int64, c_size_t, c_void_p
 from dataclasses import dataclass
@@ -117,6 +118,25 @@ def lib() -> ctypes.CDLL:
     return L
 
 
+_HOST = None
+
+
+def _host():
+    """The native part of the binding (once).  Its functions return None for what they do not take as it is; the ctypes
+    path below, whose checks raise, is for that."""
+    global _HOST
+    if _HOST is None:
+        lib()                                  # (first, so that a missing library is reported as such)
+        path = os.path.join(_HERE, "mrl_host.so")
+        if not os.path.exists(path):
+            raise FileNotFoundError(f"{path} not found: build it with `python -m paper_2605_07244_amd.build`")
+        spec = importlib.util.spec_from_file_location("mrl_host", path)
+        module = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(module)
+        _HOST = module
+    return _HOST
+
+
 def status_string(status: int) -> str:
     return lib().mrl_status_string(int(status)).decode()
 
@@ -148,6 +168,8 @@ def _dtype_code(t: torch.Tensor) -> int:
 # the current stream's handle without the Stream object torch.cuda.current_stream() builds, which is 2.8 of the
 # 15 us of host time of a small call
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_get_device = getattr(torch._C, "_cuda_getDevice", None)
+_native = _raw_stream is not None and _get_device is not None
 
 
 def _stream() -> int:
@@ -230,6 +252,12 @@ def token_scores(hidden, lm_head_w, target_ids, token_mask=None, workspace=None,
 def group_advantages(rewards, group_id, G, in_stats=None, scored=None, is_own=None, mode=ADV_GROUP_ZN,
                      eps_norm=1e-6, ddof=0, mix_alpha=1.0, neg_thresh=0.2, pos_thresh=0.8, baseline_shift=None):
     """mrl_group_advantages: returns (adv[B], mean[G], std[G], flags[G] uint8)."""
+    if _native and type(rewards) is torch.Tensor and rewards.is_cuda:
+        r = (_HOST or _host()).advantages(rewards, group_id, G, in_stats, scored, is_own, mode, eps_norm, ddof, mix_alpha, neg_thresh,
+                                          pos_thresh, baseline_shift, _raw_stream(_get_device()))
+        if r is not None:
+            _check(r[0], "mrl_group_advantages")
+            return r[1:]
     if baseline_shift is not None and baseline_shift.numel() != G:
         raise ValueError("baseline_shift must have G entries")
     B = rewards.numel()
@@ -325,6 +353,12 @@ def probe_mfma_rate(random_operands: bool, seconds: float = 0.5, device="cuda:0"
 def thl_word_align(src_logp, src_mask, src_word_map, src_map_len, tgt_mask, tgt_word_map, tgt_map_len,
                    max_words: int, ignore_value: float = -100.0, want_bad_count: bool = True):
     """Word-level trace alignment (App. D, Alg. 2).  Returns (out [B, S_tgt] float32, bad-entry count tensor)."""
+    if _native and type(src_logp) is torch.Tensor and src_logp.is_cuda:
+        r = (_HOST or _host()).align(src_logp, src_mask, src_word_map, src_map_len, tgt_mask, tgt_word_map, tgt_map_len, max_words,
+                                     ignore_value, want_bad_count, _raw_stream(_get_device()))
+        if r is not None:
+            _check(r[0], "mrl_thl_word_align")
+            return r[1:]
     B, S_src = src_logp.shape
     S_tgt = tgt_mask.shape[1]
     dev = src_logp.device

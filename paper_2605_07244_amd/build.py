@@ -8,6 +8,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmrl.so")
+HOST = os.path.join(HERE, "mrl_host.so")       # the binding's native part (a CPython extension on torch's headers)
 SOURCES = ["mrl_api.hip", "mrl_gemm_bf16.hip", "mrl_gemm_f32.hip", "mrl_aux.hip", "mrl_adv.hip", "mrl_probe.hip", "mrl_thl.hip"]
 FLAGS = ["-O3", "--offload-arch=gfx950", "-fPIC", "-std=c++17", "-fno-gpu-rdc",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
@@ -34,7 +35,24 @@ def build(verbose: bool = True, jobs: int = 4) -> str:
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)
+    _build_host(verbose)
     return LIB
+
+
+def _build_host(verbose: bool):
+    """The CPython extension of the binding, linked against libmrl.so beside it."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension as ext
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           *("-I" + p for p in [*ext.include_paths(), sysconfig.get_paths()["include"]]),
+           os.path.join(CSRC, "mrl_host.cpp"), "-o", HOST, *("-L" + p for p in [*ext.library_paths(), HERE]),
+           "-lc10", "-ltorch_cpu", "-ltorch_python", "-l:libmrl.so", "-Wl,-rpath,$ORIGIN"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
 
 
 def _drain(procs):

@@ -140,3 +140,58 @@ def test_alignment_of_values_outside_the_range(mrl):
     big = 2.0 ** 31
     assert out.cpu().tolist() == [[-0.75, -big, big, 0.0, -big, big, -big, -big, big, -0.75], [-0.75] * (n + 2)]
     assert int(bad.item()) == 0
+
+
+def _both_paths(monkeypatch, call):
+    """What `call` returns or raises through the binding's native part and without it."""
+    from paper_2605_07244_amd import binding
+    got = []
+    for native in (True, False):
+        monkeypatch.setattr(binding, "_native", native)
+        try:
+            r = call()
+            torch.cuda.synchronize()
+            got.append(tuple(r))
+        except Exception as e:
+            got.append((type(e), str(e)))
+    return got
+
+
+def _same(a, b):
+    if isinstance(a, torch.Tensor) and isinstance(b, torch.Tensor):
+        return a.dtype == b.dtype and a.shape == b.shape and a.device == b.device and torch.equal(a, b)
+    return type(a) is type(b) and a == b
+
+
+def test_native_binding_advantages(mrl, monkeypatch):
+    g = torch.Generator("cuda").manual_seed(5)
+    r = torch.rand(24, device="cuda", generator=g)
+    gid = torch.arange(3, device="cuda").repeat_interleave(8).int()
+    own = (torch.arange(24, device="cuda") % 2).to(torch.uint8)
+    shift = torch.rand(3, device="cuda", generator=g)
+    forms = [((r, gid, 3), {}), ((r.view(3, 8), gid, 3), dict(is_own=own, scored=own, in_stats=own, mode=2, mix_alpha=0.5, ddof=1)),
+             ((r, gid, 3), dict(baseline_shift=shift, eps_norm=1)), ((torch.nn.Parameter(r), gid, 3), {}), ((r[:0], gid[:0], 3), {}),
+             # refused: dtype, device, stride, sizes, options
+             ((r.double(), gid, 3), {}), ((r.cpu(), gid, 3), {}), ((r, gid.long(), 3), {}), ((r[::2], gid[::2], 3), {}),
+             ((r, gid, 3), dict(baseline_shift=shift[:2])), ((r, gid, 0), {}), ((r, gid, 3), dict(mode=7)), ((r, gid, 3), dict(ddof=5)),
+             ((r, gid, 3), dict(is_own=own.float())), ((None, gid, 3), {}), ((r, None, 3), {})]
+    for args, kw in forms:
+        a, b = _both_paths(monkeypatch, lambda: mrl.group_advantages(*args, **kw))
+        assert len(a) == len(b) and all(_same(p, q) for p, q in zip(a, b)), (kw, a, b)
+
+
+def test_native_binding_alignment(mrl, monkeypatch):
+    from workloads import synth
+    t = synth.make_thl(6, 90, 120, seed=3)
+    args = [t[k] for k in ("src_logp", "src_mask", "src_word_map", "src_map_len", "tgt_mask", "tgt_word_map", "tgt_map_len")]
+    forms = [(args, {}), (args, dict(ignore_value=-7.5, want_bad_count=False)), (args, dict(ignore_value=-3))]
+    for i, bad in enumerate([args[0].double(), args[1].bool(), args[2].long(), args[3].cpu(), args[4][:, ::2], args[5][:, :5], None]):
+        forms.append((args[:i] + [bad] + args[i + 1:], {}))
+    for a7, kw in forms:
+        if a7[5] is not None and a7[5].shape != args[5].shape:
+            continue                                   # (sizes of the other arrays are not checked: not called)
+        a, b = _both_paths(monkeypatch, lambda: mrl.thl_word_align(*a7, t["max_words"], **kw))
+        assert len(a) == len(b) and all(_same(p, q) for p, q in zip(a, b)), (kw, a, b)
+    for words in (0, 1 << 20):
+        a, b = _both_paths(monkeypatch, lambda: mrl.thl_word_align(*args, words))
+        assert len(a) == len(b) and all(_same(p, q) for p, q in zip(a, b)), (words, a, b)
