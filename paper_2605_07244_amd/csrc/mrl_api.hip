@@ -569,6 +569,12 @@ int mrl_grpo_loss_fwd_bwd(const void* hidden, const void* lm_head_w, const int32
   const bool row_f32 = !bf16 && row_f32_fits(V);
   double* const partials = at<double>(ws, row_f32 ? L.lse_c : L.loss_partials);
   int64_t n_partials = 0;
+  auto finalize = [&](int64_t blocks) {
+    double* const d7 = reinterpret_cast<double*>(out_stats);
+    return FinalizeArgs{partials, blocks, n_scored, n_scored + 1, beta, cfg->sgt_lambda, n_passes * (int64_t)L.chunk_rows, row_index,
+                        out_logp, d7, reinterpret_cast<int64_t*>(d7 + 7)};
+  };
+  bool finalized = false;
   for (int64_t c = 0; c < n_passes; ++c) {
     const int64_t c0 = c * L.chunk_rows;
     if (c > 0) prepare_chunk(hidden, lm_head_w, target_ids, d, bf16, L, ws, c, n_passes, false, RowPrepArgs{}, s);
@@ -633,8 +639,10 @@ int mrl_grpo_loss_fwd_bwd(const void* hidden, const void* lm_head_w, const int32
       w.n_scored = n_scored; w.chunk_start = c0; w.chunk_rows = L.chunk_rows;
       w.k_dynamic = 1; w.accumulate = !overwrite;
       if (out_dH && out_dW && gemm_f32_pairs(h, w)) {
-        Scope sc(MRL_PROF_GEMM_DH, s);                  // (one launch for both counts as dH's)
-        launch_gemm_f32_pair(h, w, s);
+        Scope sc(MRL_PROF_GEMM_DH, s);                  // (one launch for both, and the end of the call, counts as dH's)
+        finalized = c == n_passes - 1;
+        const FinalizeArgs last = finalize(n_partials);
+        launch_gemm_f32_pair(h, w, finalized ? &last : nullptr, s);
         continue;
       }
       if (out_dH) { Scope sc(MRL_PROF_GEMM_DH, s); launch_gemm_f32(h, s); }
@@ -653,11 +661,9 @@ int mrl_grpo_loss_fwd_bwd(const void* hidden, const void* lm_head_w, const int32
                           L.chunk_rows, V, d, out_dW, overwrite, at<float>(ws, L.tail), dw_blocks, s);
     }
   }
-  {
+  if (!finalized) {
     Scope sc(MRL_PROF_FINAL, s);
-    launch_finalize(partials, n_partials, n_scored,
-                    n_scored + 1, beta, cfg->sgt_lambda, n_passes * (int64_t)L.chunk_rows, row_index, out_logp,
-                    out_stats, s);
+    launch_finalize(finalize(n_partials), s);
   }
   return last_error();
 }

@@ -1,6 +1,7 @@
 // Memory-bound kernels of the scoring path: mask compaction, sequence weights,
 // target logits, partial-merge + token-loss epilogue (Eq. 1 / Eq. 2 terms), operand
 // preparation, the fp32 path's logits -> dz conversion, final reductions.
+#include "mrl_finalize.h"
 #include "mrl_internal.h"
 
 namespace mrl {
@@ -603,21 +604,6 @@ __global__ __launch_bounds__(256) void k_row_lse_f32(const float* Z, int64_t ldz
 constexpr int EPI_ROWS = 64;
 constexpr int EPI_THREADS = 1024;
 constexpr int EPI_LANES = EPI_THREADS / (EPI_ROWS / 4);
-constexpr int EPI_NQ = 10;   // doubles per block in loss_partials
-// loss_partials layout per block: 0 pg, 1 kl, 2 sgt, 3 sum_ratio, 4 max_ratio, 5 sum_k3,
-// 6 n_clipped, 7 n_zero_grad, 8 n_grpo_tokens, 9 n_saturated_rows
-
-__device__ inline double wave_sum64(double x) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off);
-  return x;
-}
-__device__ inline double wave_max64(double x) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) { const double o = __shfl_xor(x, off); x = o > x ? o : x; }
-  return x;
-}
-
 // Sum over all partials of this block's 64 rows; the result is valid in threads 0 .. 63 (one row
 // each).  Fixed order.  src points at the block's first row; rows beyond the valid ones hold
 // whatever the buffer held.  All threads must call it.
@@ -826,58 +812,7 @@ __global__ __launch_bounds__(kRowWaves * 64) void k_row_f32(RowEpiArgs a, float*
 }
 
 constexpr int FIN_THREADS = 512;
-__global__ __launch_bounds__(FIN_THREADS) void k_finalize(const double* parts, int64_t n_blocks,
-                                                  const int64_t* n_scored, const int64_t* n_bad,
-                                                  float beta, float lambda, int64_t rows_enqueued,
-                                                  const int32_t* row_index, float* out_logp,
-                                                  double* out_d, int64_t* out_i) {
-  // rows the enqueued passes did not cover (only when the caller's hint was too small)
-  for (int64_t i = rows_enqueued + threadIdx.x; i < *n_scored; i += FIN_THREADS)
-    out_logp[row_index[i]] = __builtin_nanf("");
-  __shared__ double sh[FIN_THREADS / 64][EPI_NQ];
-  __shared__ double tot[EPI_NQ];
-  double q[EPI_NQ];
-#pragma unroll
-  for (int k = 0; k < EPI_NQ; ++k) q[k] = 0.0;
-  for (int64_t b = threadIdx.x; b < n_blocks; b += FIN_THREADS) {
-#pragma unroll
-    for (int k = 0; k < EPI_NQ; ++k) {
-      const double v = parts[b * EPI_NQ + k];
-      q[k] = k == 4 ? (v > q[k] ? v : q[k]) : q[k] + v;
-    }
-  }
-#pragma unroll
-  for (int k = 0; k < EPI_NQ; ++k) {
-    const double v = k == 4 ? wave_max64(q[k]) : wave_sum64(q[k]);
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6][k] = v;
-  }
-  __syncthreads();
-  if (threadIdx.x < EPI_NQ) {
-    double acc = 0.0;
-    for (int w = 0; w < FIN_THREADS / 64; ++w) {
-      const double v = sh[w][threadIdx.x];
-      acc = threadIdx.x == 4 ? (v > acc ? v : acc) : acc + v;
-    }
-    tot[threadIdx.x] = acc;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    const double ng = tot[8];
-    out_d[0] = tot[0] + (double)beta * tot[1] + (double)lambda * tot[2];
-    out_d[1] = tot[0];
-    out_d[2] = tot[1];
-    out_d[3] = tot[2];
-    out_d[4] = ng > 0 ? tot[3] / ng : 0.0;
-    out_d[5] = tot[4];
-    out_d[6] = ng > 0 ? tot[5] / ng : 0.0;
-    out_i[0] = *n_scored;
-    out_i[1] = (int64_t)(tot[6] + 0.5);
-    out_i[2] = (int64_t)(tot[7] + 0.5);
-    out_i[3] = *n_bad;
-    out_i[4] = *n_scored > rows_enqueued ? *n_scored - rows_enqueued : 0;
-    out_i[5] = (int64_t)(tot[9] + 0.5);
-  }
-}
+__global__ __launch_bounds__(FIN_THREADS) void k_finalize(FinalizeArgs a) { finalize_block<FIN_THREADS>(a); }
 
 // ----------------------------------------------------------------------------
 // dz conversion of the fp32 path (proof of Prop. 4: grad log pi(a_i) = e_i - pi).
@@ -1071,13 +1006,8 @@ void launch_backward_rows_b16(const void* Hc, int64_t ldh, const float* scale, v
                      chunk_start, chunk_rows, row_tiles, static_cast<uint16_t*>(E), lde, Vp, in_blocks);
 }
 
-void launch_finalize(const double* loss_partials, int64_t n_blocks, const int64_t* n_scored,
-                     const int64_t* n_bad, float beta, float lambda, int64_t rows_enqueued,
-                     const int32_t* row_index, float* out_logp, void* out_stats, hipStream_t stream) {
-  double* out_d = static_cast<double*>(out_stats);
-  int64_t* out_i = reinterpret_cast<int64_t*>(out_d + 7);
-  hipLaunchKernelGGL(k_finalize, dim3(1), dim3(FIN_THREADS), 0, stream, loss_partials, n_blocks, n_scored, n_bad,
-                     beta, lambda, rows_enqueued, row_index, out_logp, out_d, out_i);
+void launch_finalize(const FinalizeArgs& a, hipStream_t stream) {
+  hipLaunchKernelGGL(k_finalize, dim3(1), dim3(FIN_THREADS), 0, stream, a);
 }
 
 }  // namespace mrl

@@ -113,8 +113,10 @@ struct GemmF32Args {
 void launch_gemm_f32(const GemmF32Args& a, hipStream_t stream);
 // Both products in one launch (a: B k-major; b: both k-major), where gemm_f32_pairs says that neither
 // fills the chip.
+// `last`, if not nullptr: the call's last launch, and the statistics come with it.
+struct FinalizeArgs;
 bool gemm_f32_pairs(const GemmF32Args& a, const GemmF32Args& b);
-void launch_gemm_f32_pair(const GemmF32Args& a, const GemmF32Args& b, hipStream_t stream);
+void launch_gemm_f32_pair(const GemmF32Args& a, const GemmF32Args& b, const FinalizeArgs* last, hipStream_t stream);
 
 // ---- auxiliary kernels ------------------------------------------------------
 struct PrepOut {
@@ -218,11 +220,13 @@ void launch_group_advantages(const float* rewards, const int32_t* group_id, cons
                              float pos_thresh, float* out_adv, float* out_mean, float* out_std,
                              uint8_t* out_flags, hipStream_t stream);
 
-// rows_enqueued: number of compacted rows covered by the enqueued passes; scored rows beyond
+// End of a loss call.  rows_enqueued: number of compacted rows covered by the enqueued passes; scored rows beyond
 // it (a wrong scored_rows_hint) get NaN log-probs and are counted in the stats.
-void launch_finalize(const double* loss_partials, int64_t n_blocks, const int64_t* n_scored,
-                     const int64_t* n_bad, float beta, float lambda, int64_t rows_enqueued,
-                     const int32_t* row_index, float* out_logp, void* out_stats, hipStream_t stream);
+struct FinalizeArgs {
+  const double* parts; int64_t n_blocks; const int64_t* n_scored; const int64_t* n_bad; float beta, lambda;
+  int64_t rows_enqueued; const int32_t* row_index; float* out_logp; double* out_d; int64_t* out_i;
+};
+void launch_finalize(const FinalizeArgs& a, hipStream_t stream);
 
 // MRL_OK when the current device is a gfx950, else MRL_ERR_UNSUPPORTED_ARCH / MRL_ERR_DEVICE.
 int require_gfx950();
