@@ -195,3 +195,23 @@ def test_native_binding_alignment(mrl, monkeypatch):
     for words in (0, 1 << 20):
         a, b = _both_paths(monkeypatch, lambda: mrl.thl_word_align(*args, words))
         assert len(a) == len(b) and all(_same(p, q) for p, q in zip(a, b)), (words, a, b)
+
+
+@pytest.mark.parametrize("B,S_src,S_tgt", [(5, 768, 769), (3, 769, 40), (4, 1000, 1537), (3, 2048, 2048), (3, 30, 2048), (2, 2049, 2000)])
+def test_alignment_with_kept_words(mrl, B, S_src, S_tgt):
+    """Rows around the sizes whose target words stay in registers: against the oracle, bad word ids included."""
+    from oracle import thl_oracle
+    from workloads import synth
+    t = synth.make_thl(B, S_src, S_tgt, seed=S_tgt)
+    t["tgt_word_map"][0, :3] = t["max_words"]
+    out, bad = mrl.thl_word_align(t["src_logp"], t["src_mask"], t["src_word_map"], t["src_map_len"], t["tgt_mask"], t["tgt_word_map"],
+                                  t["tgt_map_len"], t["max_words"])
+    torch.cuda.synchronize()
+    c = {k: (v.cpu().numpy() if isinstance(v, torch.Tensor) else v) for k, v in t.items()}
+    maps = np.where(c["tgt_word_map"] >= t["max_words"], -1, c["tgt_word_map"])
+    want = thl_oracle.word_align_logprobs(c["src_logp"].astype(np.float64), c["src_mask"], c["src_word_map"], c["src_map_len"],
+                                          c["tgt_mask"], maps, c["tgt_map_len"], -100.0)
+    # fp32 output of sums exact to 2^-33 per term
+    assert np.all(np.abs(out.cpu().numpy() - want) <= 1e-6 * np.maximum(1, np.abs(want)))
+    used = (c["tgt_word_map"][0, :3] >= t["max_words"]) & (np.arange(3) < min(int(c["tgt_mask"][0].sum()), int(c["tgt_map_len"][0])))
+    assert int(bad) == int(used.sum())
