@@ -416,7 +416,7 @@ __device__ inline void zero_dh_rows(const RowPrepArgs& a, int64_t first) {
 
 // Compaction of N <= kPrepInline slots by one block of 256: a contiguous run of slots per wave, f(slot, rank among the scored
 // ones, scored, masked in with a bad target) per slot; returns the number of scored ones.  Every block of the
-// launch that needs it does it for itself (20 KB from the L2), which takes less than a launch that does it once.
+// launch that needs it does it for itself (10 KB from the L2), which takes less than a launch that does it once.
 template <class F>
 __device__ inline int compact_block(const uint8_t* mask, const int32_t* targets, int N, int V, F f) {
   constexpr int kIters = kPrepInline / 256;
@@ -758,7 +758,8 @@ __global__ __launch_bounds__(EPI_THREADS) void k_row_epilogue(RowEpiArgs a) {
 // As three launches (a block per row, 64 rows per block, a grid of rows) they are three latencies of 4 - 5 us each
 // on kilobytes (loss call of 256 slots, V = 512, d = 64, which the host bounds: 35.1 us, now 31.6).
 // ----------------------------------------------------------------------------
-constexpr int kRowLogits = 2048, kRowWaves = 16;
+constexpr int kRowLogits = 2048, kFewLogits = 512, kRowWaves = 16;
+template <int LOGITS>                                 // (the loops over a lane's logits are unrolled: V = 512 9.5 us with 2048, 8.3 with 512)
 __global__ __launch_bounds__(kRowWaves * 64) void k_row_f32(RowEpiArgs a, float* Z, int64_t ldz, int V, int write_dz) {
   __shared__ double sh[kRowWaves][EPI_NQ];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -768,10 +769,10 @@ __global__ __launch_bounds__(kRowWaves * 64) void k_row_f32(RowEpiArgs a, float*
   for (int k = 0; k < EPI_NQ; ++k) q[k] = 0.0;
   if (i < valid_rows(a.n_scored, a.chunk_start, a.chunk_rows)) {
     float* const row = Z + (int64_t)i * ldz;
-    float z[kRowLogits / 64];
+    float z[LOGITS / 64];
     float mx = -INFINITY;
 #pragma unroll
-    for (int k = 0; k < kRowLogits / 64; ++k) {
+    for (int k = 0; k < LOGITS / 64; ++k) {
       const int v = k * 64 + lane;
       z[k] = v < V ? row[v] : -INFINITY;
       mx = fmaxf(mx, z[k]);
@@ -780,7 +781,7 @@ __global__ __launch_bounds__(kRowWaves * 64) void k_row_f32(RowEpiArgs a, float*
     for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
     float s = 0.f;
 #pragma unroll
-    for (int k = 0; k < kRowLogits / 64; ++k)
+    for (int k = 0; k < LOGITS / 64; ++k)
       if (k * 64 < V) s += k * 64 + lane < V ? expf(z[k] - mx) : 0.f;
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
@@ -792,7 +793,7 @@ __global__ __launch_bounds__(kRowWaves * 64) void k_row_f32(RowEpiArgs a, float*
     if (write_dz) {
       const int y = a.targets[slot];
 #pragma unroll
-      for (int k = 0; k < kRowLogits / 64; ++k) {
+      for (int k = 0; k < LOGITS / 64; ++k) {
         const int v = k * 64 + lane;
         if (v < V) row[v] = g * ((v == y ? 1.f : 0.f) - expf(z[k] - lse));
       }
@@ -977,7 +978,7 @@ void launch_row_epilogue(const RowEpiArgs& a, hipStream_t stream) {
 bool row_f32_fits(int V) { return V <= kRowLogits; }
 int row_f32_blocks(int64_t rows) { return (int)((rows + kRowWaves - 1) / kRowWaves); }
 void launch_row_f32(const RowEpiArgs& a, float* Z, int64_t ldz, int V, int rows, int write_dz, hipStream_t stream) {
-  hipLaunchKernelGGL(k_row_f32, dim3(row_f32_blocks(rows)), dim3(kRowWaves * 64), 0, stream, a, Z, ldz, V, write_dz);
+  hipLaunchKernelGGL(V <= kFewLogits ? k_row_f32<kFewLogits> : k_row_f32<kRowLogits>, dim3(row_f32_blocks(rows)), dim3(kRowWaves * 64), 0, stream, a, Z, ldz, V, write_dz);
 }
 
 void launch_convert_f32(float* ZP, int64_t ldz, const float* lse_c,
