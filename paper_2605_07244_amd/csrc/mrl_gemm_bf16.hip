@@ -940,12 +940,14 @@ __global__ __launch_bounds__(NTHREADS) void gemm_nt_bf16(Params p) {
 // 64-byte pieces (32 K-elements of a row) the launch was bound by those requests.  W comes in chunks of 64
 // K-elements, two steps of the loop, and the token rows lie in blocks of 32 columns ([dp / 32][rows][32],
 // written that way by the row preparation), so that both are fetched in whole lines.  Waves without tokens
-// only load their share of W.  A tile starts its walk along K where its place among the tiles of its XCD says:
-// rows of a power of two of bytes lie on the same L2 and memory channels, and tiles that all start at column 0
-// ask the same channels at the same time (64 rows, d = 4096 316 us, now 254; d = 2048 128 and 109; others the same).
-// Scoring call, us, 256 x 256 tiles, these in 64-byte pieces from column 0, now: V = 151936, d = 4096, 64 rows 367,
-// 315 and 254, 128 rows 377, 350 and 267, 201 rows 387, 404 and 336, 256 rows 408, 417 and 338; d = 1536 154, 134
-// and 114, 158, 144 and 117, 164, 164 and 143, 172, 167 and 143; V = 32000, d = 2048, 256 rows 53, 52 and 50.
+// only load their share of W.  Every tile walks K from column 0, as the large tile does: a logit's products are
+// added in one order in every forward kernel, and a token's scores have the same bits in a pass of any length.  (Rows of a
+// power of two of bytes lie on the same L2 and memory channels, and tiles that are all at one column ask the same
+// channels at the same time; tiles that each start at another column avoid that, V = 151936, d = 4096, 64 rows 253 us
+// instead of 316, 256 rows 330 and 340, but give other bits than the large tile.)
+// Scoring call, us, 256 x 256 tiles, these in 64-byte pieces, now: V = 151936, d = 4096, 64 rows 367, 315 and 316,
+// 128 rows 377, 348 and 321, 201 rows 387, 395 and 334, 256 rows 408, 412 and 340; d = 1536 154, 132 and 113, 158, 143
+// and 115, 164, 162 and 138, 172, 162 and 140; V = 32000, d = 2048, 256 rows 53, 52 and 45.
 // The line lies at one tile column because the load path of a compute unit (23 clocks per
 // KB) then has to deliver 24 KB per 512 MFMA cycles: used for every column, 4096 rows, d = 1536 / 2048 / 4096
 // take 1830 / 1876 / 4163 us in the launch against 1740 / 1769 / 3805 with the large tile.  The rows that count are
@@ -990,18 +992,14 @@ __global__ __launch_bounds__(NTHREADS, 2) void forward_few_bf16(Params p) {
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" :: "v"(voff), "s"(base), "s"(lds) : "memory");
   };
   const int nk = p.K / FK, nc = p.K / BK;             // (nk is a multiple of 4)
-  // chunk c of the walk, which starts at chunk `turn` and goes round; loads that would run past its end fetch
-  // its first ones again into slots nobody reads
-  const int turn = tm / NXCD % nc;
+  // (loads that would run past the end fetch the first chunk or stage again, into slots nobody reads)
   auto load_a = [&](int c, uint32_t slot) {
-    c += turn;
     c = c < nc ? c : c - nc;
     const uint64_t base = a_base + (uint64_t)c * (BK * 2) + (c >= p.a_tail_panel ? p.a_tail_delta : 0);
 #pragma unroll
     for (int i = 0; i < F_LOADS; ++i) load(va[i], base, lds_wave + slot + i * 1024);
   };
   auto load_b = [&](int kt, uint32_t slot) {
-    kt += 2 * turn;
     kt = kt < nk ? kt : kt - nk;
     const uint64_t base = b_base + (uint64_t)kt * (uint64_t)p.ldb * (FK * 2);
 #pragma unroll

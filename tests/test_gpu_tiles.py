@@ -330,6 +330,31 @@ def test_fp32_response_ratio_over_passes(mrl, level):
         assert error <= 1e-5 * size, (name, error, size)
 
 
+@pytest.mark.parametrize("scored,d,V", [
+    (800, 512, 5003),             # a last half column in the long pass; 40 vocabulary tiles of 128, eight K chunks
+    (1000, 712, 2057),            # a padded width, the last column a whole tile
+    (513, 4096, 1300),            # power-of-two rows, 64 K chunks; one row in the last column
+])
+def test_scores_do_not_depend_on_the_pass(mrl, scored, d, V):
+    """Every forward kernel adds a logit's products in the same order: the bits of a token's scores are those of a long pass, of
+    passes of 256 rows (a workspace that holds no longer one, or chunk_rows) and of a call of a few slots."""
+    N = scored + 20
+    H, W, y, mask = _head(N, d, V, scored, V)
+    want = mrl.token_scores(H, W, y, mask)
+    # 16 KB more than 256 slots take hold the arrays by slot, and no pass of 512 rows
+    small = int(mrl.lib().mrl_token_scores_workspace(256, d, V, mrl.BF16)) + 16384
+    assert small < int(mrl.lib().mrl_token_scores_workspace(512, d, V, mrl.BF16))
+    passes = mrl.token_scores(H, W, y, mask, workspace=torch.empty(small, dtype=torch.uint8, device="cuda"))
+    alone = [mrl.token_scores(H[r:r + 190], W, y[r:r + 190], mask[r:r + 190]) for r in range(0, N, 190)]
+    torch.cuda.synchronize()
+    for k in range(3):
+        assert torch.equal(passes[k], want[k])
+        assert torch.equal(torch.cat([a[k] for a in alone]), want[k])
+    for chunk_rows in (0, 256):
+        out, _, _ = _step(mrl, H, W, y, mask, mrl.BF16, V, chunk_rows=chunk_rows)
+        assert torch.equal(out["logp"], want[0])
+
+
 @pytest.mark.parametrize("scored,d,V", [(200, 128, 129), (700, 256, 8), (1500, 240, 329), (600, 512, 2057)])
 def test_dw_beside_the_pad_columns(mrl, scored, d, V):
     """Vocabularies that end in the first chunk of a tile, a chunk behind a 128-wide half and inside one: the launch reads other
