@@ -66,13 +66,15 @@ PyObject* advantages(PyObject*, PyObject* const* a, Py_ssize_t n) {
     if (B == 0) Py_RETURN_NONE;
     at::Tensor adv = new_like(r, {B}, at::kFloat), mean = new_like(r, {G}, at::kFloat), std = new_like(r, {G}, at::kFloat);
     at::Tensor flags = new_like(r, {G}, at::kByte);
-    auto out = [](at::Tensor& t) { return t.mutable_data_ptr(); };
+    // (whatever may throw stands before the GIL is given up: the handler below needs it)
+    float *const adv_ptr = static_cast<float*>(adv.mutable_data_ptr()), *const mean_ptr = static_cast<float*>(mean.mutable_data_ptr());
+    float* const std_ptr = static_cast<float*>(std.mutable_data_ptr());
+    uint8_t* const flags_ptr = static_cast<uint8_t*>(flags.mutable_data_ptr());
     int rc;
     Py_BEGIN_ALLOW_THREADS
     rc = mrl_group_advantages(static_cast<float*>(rewards), static_cast<int32_t*>(group), static_cast<uint8_t*>(in_stats),
                               static_cast<uint8_t*>(scored), static_cast<uint8_t*>(own), static_cast<float*>(shift), B, G, mode, eps, ddof,
-                              mix, neg, pos, static_cast<float*>(out(adv)), static_cast<float*>(out(mean)), static_cast<float*>(out(std)),
-                              static_cast<uint8_t*>(out(flags)), reinterpret_cast<void*>(stream));
+                              mix, neg, pos, adv_ptr, mean_ptr, std_ptr, flags_ptr, reinterpret_cast<void*>(stream));
     Py_END_ALLOW_THREADS
     return Py_BuildValue("(iNNNN)", rc, THPVariable_Wrap(std::move(adv)), THPVariable_Wrap(std::move(mean)),
                          THPVariable_Wrap(std::move(std)), THPVariable_Wrap(std::move(flags)));

@@ -180,6 +180,26 @@ def test_native_binding_advantages(mrl, monkeypatch):
         assert len(a) == len(b) and all(_same(p, q) for p, q in zip(a, b)), (kw, a, b)
 
 
+def test_native_binding_outputs_without_memory(mrl):
+    """A dispatch mode whose new tensors refuse their data pointer: an exception on either path, and the next call works."""
+    from torch.utils._python_dispatch import TorchDispatchMode
+    from workloads import synth
+
+    class Locked(TorchDispatchMode):
+        def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+            out = func(*args, **(kwargs or {}))
+            torch._C._set_throw_on_mutable_data_ptr(out)
+            return out
+
+    r, gid = torch.rand(24, device="cuda"), torch.arange(3, device="cuda").repeat_interleave(8).int()
+    t = synth.make_thl(6, 90, 120, seed=3)
+    align = [t[k] for k in ("src_logp", "src_mask", "src_word_map", "src_map_len", "tgt_mask", "tgt_word_map", "tgt_map_len", "max_words")]
+    for call in (lambda: mrl.group_advantages(r, gid, 3), lambda: mrl.thl_word_align(*align)):
+        with Locked(), pytest.raises(RuntimeError, match="data pointer"):
+            call()
+        assert bool(torch.isfinite(call()[0]).all())
+
+
 def test_native_binding_alignment(mrl, monkeypatch):
     from workloads import synth
     t = synth.make_thl(6, 90, 120, seed=3)
