@@ -609,7 +609,7 @@ int mrl_grpo_loss_fwd_bwd(const void* hidden, const void* lm_head_w, const int32
     const int overwrite = (c == 0 && !cfg->accumulate_dw) ? 1 : 0;
     // (rows of the pass at most, as far as the caller says)
     const int64_t hinted = cfg->scored_rows_hint > 0 ? cfg->scored_rows_hint - c0 : L.chunk_rows;
-    const bool dw_blocks = bf16 && dw_rows_in_blocks((int)(hinted < L.chunk_rows ? hinted : L.chunk_rows), V, d, overwrite);
+    const bool dw_blocks = bf16 && dw_rows_in_blocks((int)(hinted < L.chunk_rows ? hinted : L.chunk_rows));
     {
       Scope sc(MRL_PROF_CONVERT, s);
       if (bf16) {

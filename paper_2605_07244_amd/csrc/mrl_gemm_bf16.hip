@@ -1093,17 +1093,14 @@ __global__ __launch_bounds__(NTHREADS, 2) void forward_few_bf16(Params p) {
 constexpr int DM = 128, DN = 256, DK = kRowBlock, DSTAGES = 3;
 constexpr int D_A = DK * DM * 2, D_STAGE = D_A + DN * DK * 2, D_LDS = DSTAGES * D_STAGE;   // 24 KB per stage
 constexpr int D_LOADS = 6;                                          // direct loads per wave and stage: 2 of A, 4 of B
-// Where it is the faster one.  Above 1024 rows the large tile's K loop counts for more (1536 rows 0.92 - 1.05).  Below,
-// accumulating launches always gain (1.005 - 1.28); overwriting ones lose where the large tile's 8 x 4 super-tiles
-// fit the columns, its stores being short of nothing then, and dW is too large for the memory-side cache to
-// take a good part of it: V = 128256, d = 1024, 400 rows 204 us and 231, V = 140000, d = 2048, 150 rows 348 and 376 (but
-// V = 100000, d = 1024 178 and 162, V = 32000, d = 2048 105 and 90).
+// Passes of at most kFewDwRows rows: from there on the large tile's K loop, which moves half the panel bytes per product, counts
+// for more than the stores.  Call with dW alone, overwriting, us, large tile and this one: d = 1024 (4 tile columns),
+// V = 38405, 150 rows 125 and 105, 900 rows 229 and 209; V = 151936, 150 rows 373 and 336, 1000 rows 716 and 700; d = 2048,
+// V = 38405 213 and 170, 379 and 353; V = 151936 656 and 617, 1278 and 1291; d = 3072, V = 102405, 150 rows 646 and
+// 595, 900 rows 1277 and 1243; d = 4096, V = 153605 1235 and 1140, 2427 and 2364; accumulating launches gain as much or more; 1536
+// rows 0.92 - 1.05.  The other way up to there: V = 128256, d = 1024, behind a dH launch, whose 7.8 rounds of large
+// tiles leave little to gain, 327 rows 483 and 484, 1000 rows 825 and 846 a call.
 constexpr int kFewDwRows = 1024;
-inline bool few_dw(int rows, int V, int d, int overwrite) {
-  const int Nt = (d + BN - 1) / BN;
-  const bool fits = d % 32 == 0 && Nt % 4 == 0 && Nt <= 8 && (int64_t)V * d * 4 > ((int64_t)400 << 20);
-  return rows <= kFewDwRows && !(overwrite && fits);
-}
 
 __global__ __launch_bounds__(NTHREADS, 2) void dw_few_bf16(Params p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -1434,7 +1431,7 @@ void launch_gemm_dh_bf16(const void* E, int64_t lde, const void* W, int64_t ldw,
 
 size_t gemm_tail_tile_bytes() { return (size_t)BM * BN * sizeof(float); }
 int gemm_dw_tail_items() { return kDwTailMaxItems; }
-bool dw_rows_in_blocks(int rows, int V, int d, int overwrite) { return few_dw(rows, V, d, overwrite); }
+bool dw_rows_in_blocks(int rows) { return rows <= kFewDwRows; }
 
 void launch_gemm_dw_bf16(const void* E, int64_t lde, const void* Ht, int64_t ldht,
                          const int64_t* n_scored, int64_t chunk_start, int chunk_rows,

@@ -90,7 +90,7 @@ void launch_gemm_dh_bf16(const void* E, int64_t lde, const void* W, int64_t ldw,
 // rounded up to 128; dw_rows_in_blocks says where it is the faster one (rows: the scored rows expected; right for any number).
 size_t gemm_tail_tile_bytes();
 int gemm_dw_tail_items();
-bool dw_rows_in_blocks(int rows, int V, int d, int overwrite);
+bool dw_rows_in_blocks(int rows);
 void launch_gemm_dw_bf16(const void* P, int64_t ldp, const void* Ht, int64_t ldht,
                          const int64_t* n_scored, int64_t chunk_start, int chunk_rows,
                          int V, int d, float* dW, int overwrite, float* tail_part, bool in_blocks, hipStream_t stream);
