@@ -67,6 +67,13 @@ int mrl_probe_mfma_rate(int32_t random_operands, double seconds, void* scratch /
 int mrl_diag_dw_tail_plan(int32_t V, int32_t d, int32_t* out12 /*host*/);
 
 /* ------------------------------------------------------------------------
+ * Rows up to which a pass of the bf16 loss takes the dW launch for few rows, which has
+ * no tail (host code only): as many as the pass can hold, or as scored_rows_hint says
+ * that it will.  For tests that mean to run the one launch or the other.
+ * ---------------------------------------------------------------------- */
+int mrl_diag_dw_few_rows(void);
+
+/* ------------------------------------------------------------------------
  * The slices of the contraction that each of the tail_tiles (1 .. 255) tiles of
  * the dH launch's last, incomplete round of 256 is cut into (1: left whole), for
  * a contraction of `panels` panels of 64 and scratch for max_items partial tiles:

@@ -112,6 +112,8 @@ def lib() -> ctypes.CDLL:
                                                       c_void_p, c_void_p]
     L.mrl_diag_dw_tail_plan.restype = c_int
     L.mrl_diag_dw_tail_plan.argtypes = [c_int32, c_int32, POINTER(c_int32)]
+    L.mrl_diag_dw_few_rows.restype = c_int
+    L.mrl_diag_dw_few_rows.argtypes = []
     L.mrl_probe_mfma_rate.restype = c_int
     L.mrl_probe_mfma_rate.argtypes = [c_int32, c_double, c_void_p, c_size_t, POINTER(c_double)]
     _LIB = L
@@ -338,6 +340,11 @@ def dw_tail_plan(V: int, d: int) -> dict:
     out = (c_int32 * 12)()
     _check(lib().mrl_diag_dw_tail_plan(int(V), int(d), out), "mrl_diag_dw_tail_plan")
     return dict(first_tile_row=out[0], tile_rows=out[1], split=out[2], items_before_xcd=list(out[3:12]))
+
+
+def dw_few_rows() -> int:
+    """Rows of a bf16 pass up to which dW takes the launch for few rows, without a tail (host code only)."""
+    return int(lib().mrl_diag_dw_few_rows())
 
 
 def probe_mfma_rate(random_operands: bool, seconds: float = 0.5, device="cuda:0") -> float:

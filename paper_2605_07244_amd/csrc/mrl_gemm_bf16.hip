@@ -1463,6 +1463,8 @@ extern "C" int mrl_diag_dh_split(int32_t tail_tiles, int32_t panels, int32_t max
   return dh_split(tail_tiles, panels, max_items);
 }
 
+extern "C" int mrl_diag_dw_few_rows(void) { return mrl::kFewDwRows; }
+
 extern "C" int mrl_diag_dw_tail_plan(int32_t V, int32_t d, int32_t* out12) {
   using namespace mrl;
   if (out12 == nullptr) return MRL_ERR_NULL;

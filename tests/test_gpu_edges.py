@@ -151,12 +151,14 @@ def test_runs_are_bit_reproducible(mrl, synth):
 
 def test_dw_with_k_split_tail_is_bit_reproducible_and_accumulates(mrl, synth):
     # V = 151936, d = 1536: the ragged last rows of dW tiles are cut into K slices whose partial tiles a
-    # second kernel adds in slice order; two passes, so that the second adds into the first's result
-    sp, b = _small(synth, n_prompts=2, T=48, V=151936, d=1536)
-    a = _gpu_loss(mrl, sp, b)
-    c = _gpu_loss(mrl, sp, b)
-    assert int(b["mask"].sum()) > 256 and torch.equal(a["dW"], c["dW"]) and torch.equal(a["dH"], c["dH"])
-    one = _gpu_loss(mrl, sp, b, cfg=dict(chunk_rows=512))          # one pass
+    # second kernel adds in slice order; two passes, longer than the launch for few rows takes, so that the
+    # second adds into the first's result
+    sp, b = _small(synth, n_prompts=5, T=64, V=151936, d=1536)
+    assert mrl.dw_few_rows() < 1280 < int(b["mask"].sum()) <= 2560 and mrl.dw_tail_plan(151936, 1536)["split"] > 1
+    a = _gpu_loss(mrl, sp, b, cfg=dict(chunk_rows=1280))
+    c = _gpu_loss(mrl, sp, b, cfg=dict(chunk_rows=1280))
+    assert torch.equal(a["dW"], c["dW"]) and torch.equal(a["dH"], c["dH"])
+    one = _gpu_loss(mrl, sp, b, cfg=dict(chunk_rows=2560))         # one pass
     scale = float(one["dW"].abs().max())
     assert float((a["dW"] - one["dW"]).abs().max()) <= 1e-5 * scale   # fp32 sums in a different order
     tail = a["dW"][151936 // 256 // 8 * 8 * 256:]                     # the rows of the split tiles

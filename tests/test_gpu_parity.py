@@ -144,9 +144,11 @@ def test_mini_config5_full_vocab_and_width(mrl, synth):
 
 def test_mini_config2_full_vocab_uneven_dw_tail(mrl, synth):
     # full V = 151936 at d = 1536: the last two rows of dW tiles (12 tiles) are cut into K slices that
-    # the launch plan deals to the XCDs unevenly (those that finish their whole tiles early take them)
+    # the launch plan deals to the XCDs unevenly (those that finish their whole tiles early take them); a pass that could
+    # hold more rows than the launch for few rows takes, with a part of the slices filled
     sp = synth.spec(2, n_prompts=1, T=40)
-    _run_both(mrl, synth, sp, chunk_rows=256)
+    assert mrl.dw_few_rows() < 1280
+    _run_both(mrl, synth, sp, chunk_rows=1280)
 
 
 @pytest.mark.parametrize("V,d", [(8627, 2048), (20224, 2304), (7424, 2304), (11008, 1536), (16819, 640),
@@ -154,11 +156,13 @@ def test_mini_config2_full_vocab_uneven_dw_tail(mrl, synth):
 def test_dw_tail_plans(mrl, synth, V, d):
     """Head shapes whose dW launch cuts its ragged last rows of tiles into K slices, with 1 to 7 such rows,
     2 to 8 slices, item counts that differ from XCD to XCD, and widths of a whole and of a ragged number of
-    256-wide tiles; two passes, so that the second adds the slices into the first's result."""
+    256-wide tiles; two passes of the length that takes this launch, so that the second adds the slices into the first's
+    result."""
     plan = mrl.dw_tail_plan(V, d)
-    assert plan["split"] >= 2
-    sp = synth.spec(2, n_prompts=2, T=40, V=V, d=d)
-    _run_both(mrl, synth, sp, chunk_rows=256)
+    assert plan["split"] >= 2 and mrl.dw_few_rows() < 1280
+    sp = synth.spec(2, n_prompts=5, T=64, V=V, d=d)
+    batch, _, _, _ = _run_both(mrl, synth, sp, chunk_rows=1280)
+    assert int(batch["mask"].sum()) > 1280
 
 
 def test_single_chunk_default_and_fp32_dh(mrl, synth):

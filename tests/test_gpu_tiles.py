@@ -215,11 +215,11 @@ def test_padded_widths(mrl, N, d, V):
 @pytest.mark.parametrize("scored", [1, 129, 327, 700, 1030])
 def test_dw_tail_slices_without_panels(mrl, scored):
     """The tail of this head is planned as 8 slices; 2, 4, 6, 12 and 18 panels fill 1, 2, 3, 6 and 5 of them.  The others store
-    nothing and are not read: the scratch holds NaN before."""
+    nothing and are not read: the scratch holds NaN before.  (A pass that can hold 1280 rows, which is what the launch goes by.)"""
     d, V = 1024, 16405
-    assert mrl.dw_tail_plan(V, d)["split"] == 8
+    assert mrl.dw_tail_plan(V, d)["split"] == 8 and mrl.dw_few_rows() < 1280
     H, W, y, mask = _head(scored + 3, d, V, scored, scored)
-    out, dH, dW = _step(mrl, H, W, y, mask, mrl.BF16, scored, poison=True)
+    out, dH, dW = _step(mrl, H, W, y, mask, mrl.BF16, scored, chunk_rows=1280, poison=True)
     util.check_gradient("dW", util.to_f64(out["dW"]), dW)
     util.check_gradient("dH", util.to_f64(out["dH"]), dH)
 
@@ -421,7 +421,7 @@ def test_dw_k_split_tail_above_the_few_rows(mrl, scored):
     """The large dW launch with its ragged last tile rows cut into eight K slices: more than 1024 rows, a second pass that
     adds into the first's result, poisoned scratch."""
     d, V = 1536, 11000
-    assert mrl.dw_tail_plan(V, d)["split"] == 8
+    assert mrl.dw_tail_plan(V, d)["split"] == 8 and mrl.dw_few_rows() == 1024
     H, W, y, mask = _head(1500, d, V, scored, scored)
     out, _, dW = _step(mrl, H, W, y, mask, mrl.BF16, V, poison=True)
     again, _, _ = _step(mrl, H, W, y, mask, mrl.BF16, V, poison=True)
