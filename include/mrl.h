@@ -223,7 +223,13 @@ typedef struct {
                                ceil(hint / chunk_rows) passes are enqueued instead of the worst case
                                ceil(B*T / chunk_rows).  If the mask holds more scored slots than the
                                hint, the excess rows are NOT processed: their out_logp is NaN and
-                               n_unprocessed_rows reports how many.                              */
+                               n_unprocessed_rows reports how many.  (Rows that a pass holds beyond
+                               the hint are processed.)  The bf16 path also goes by the hint where it
+                               chooses between two dW launches, one for passes of at most 1024
+                               expected rows: both are right for any number of rows, but where the
+                               other one splits the contraction they add in another order, so that
+                               dW with a hint and without one agrees to fp32 rounding and not bit
+                               for bit.  The other outputs have the same bits.                   */
   int32_t ratio_level;   /* which importance ratio enters Eq. (1):
                             0 = per token, w_t = exp(l_t - l_beh,t)                (Sec. 3)
                             1 = per response, exp{L_theta - L_behavior}, L = sums over the

@@ -46,7 +46,7 @@ def test_forward_tiles_cover_scored_rows(mrl, N, scored, d, V):
     assert torch.all(logp[mask == 0] == 0) and torch.all(lse[mask == 0] == 0)
 
 
-def _step(mrl, H, W, y, mask, dh_dtype, seed, chunk_rows=0, poison=False):
+def _step(mrl, H, W, y, mask, dh_dtype, seed, chunk_rows=0, poison=False, hint=0):
     """One loss step of a single sequence (its tokens' advantages and traces random) and the same in float64.
     poison: the workspace holds NaN before the call."""
     g = torch.Generator("cuda").manual_seed(seed)
@@ -59,7 +59,7 @@ def _step(mrl, H, W, y, mask, dh_dtype, seed, chunk_rows=0, poison=False):
     lp = z[at, y[rows].long()] - lse
     behav = torch.zeros(N, device="cuda")
     behav[rows] = (lp + 0.05 * torch.randn(rows.numel(), device="cuda", generator=g)).float()
-    cfg = mrl.LossConfig(kl_beta=0.0, dh_dtype=dh_dtype, chunk_rows=chunk_rows)
+    cfg = mrl.LossConfig(kl_beta=0.0, dh_dtype=dh_dtype, chunk_rows=chunk_rows, scored_rows_hint=hint)
     ws = None
     if poison:
         code = mrl.F32 if H.dtype == torch.float32 else mrl.BF16
@@ -429,6 +429,25 @@ def test_dw_k_split_tail_above_the_few_rows(mrl, scored):
     assert torch.equal(out["dW"], again["dW"])
     util.check_gradient("dW", util.to_f64(out["dW"]), dW)
     util.check_gradient("dW", util.to_f64(two["dW"]), dW)
+
+
+@pytest.mark.parametrize("scored,chunk_rows", [(900, 0), (900, 4096), (1500, 1280)])
+def test_hint_and_dw_launch(mrl, scored, chunk_rows):
+    """The hint chooses the dW launch for few rows inside a pass that could hold more (and, as 300, more than it says): dW to
+    rounding and everything else bit for bit what the call without a hint gives.  In the last case the second of two passes takes
+    that launch, by what the hint leaves to it."""
+    d, V = 1536, 11000
+    assert mrl.dw_tail_plan(V, d)["split"] == 8 and mrl.dw_few_rows() == 1024
+    H, W, y, mask = _head(1530, d, V, scored, scored)
+    out, _, dW = _step(mrl, H, W, y, mask, mrl.BF16, V, chunk_rows=chunk_rows, poison=True)
+    stats = mrl.read_stats(out["stats"])
+    util.check_gradient("dW", util.to_f64(out["dW"]), dW)
+    for hint in (scored, 300) if scored < 1024 else (scored,):
+        got, _, _ = _step(mrl, H, W, y, mask, mrl.BF16, V, chunk_rows=chunk_rows, poison=True, hint=hint)
+        assert torch.equal(got["logp"], out["logp"]) and torch.equal(got["dH"], out["dH"])
+        assert mrl.read_stats(got["stats"]) == stats and stats["n_unprocessed_rows"] == 0
+        # fp32 sums of at most 1500 products in two orders: 2^-24 * sqrt(1500) of the largest sum of absolute terms
+        assert float((got["dW"] - out["dW"]).abs().max()) <= 1e-5 * float(out["dW"].abs().max())
 
 
 @pytest.mark.parametrize("N,scored,V,chunk_rows", [
