@@ -1,15 +1,18 @@
-"""ctypes binding of include/mrl.h.  Argument marshalling only.
+"""Binding of include/mrl.h: ctypes, and a CPython extension for the calls whose
+host side would take longer than their kernels.  Argument marshalling only.
 
 Every function takes torch tensors that already live on the GPU (the library
 only accepts device pointers), checks dtype / contiguity / device on the host,
 and forwards raw pointers plus the current torch stream.  There is no CPU or
-PyTorch fallback: if the shared library is missing, loading raises.
+PyTorch fallback: if the shared library is missing, loading raises.  The
+extension only marshals faster: without it every call goes through ctypes.
 """
 from __future__ import annotations
 
 import ctypes
 import importlib.util
 import os
+import warnings
 from ctypes import POINTER, c_char_p, c_double, c_float, c_int, c_int32, c_int64, c_size_t, c_void_p
 from dataclasses import dataclass
 
@@ -123,19 +126,36 @@ def lib() -> ctypes.CDLL:
 _HOST = None
 
 
+class _NoHost:
+    """Takes nothing as it is: every call goes through ctypes."""
+    advantages = align = staticmethod(lambda *args: None)
+
+
+def _load_host():
+    """mrl_host.so, or None with a warning where it is not there, does not load, or was built against another torch (whose C++
+    interface it uses: a tree built elsewhere still has its C library)."""
+    path = os.path.join(_HERE, "mrl_host.so")
+    try:
+        spec = importlib.util.spec_from_file_location("mrl_host", path)
+        module = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(module)
+        if module.torch_version == str(torch.__version__):
+            return module
+        why = f"was built against torch {module.torch_version}, this is {torch.__version__}"
+    except (ImportError, OSError) as e:        # (a file that is not there is an ImportError or FileNotFoundError)
+        why = str(e)
+    warnings.warn(f"{path}: {why}; advantages and alignment go through ctypes, which takes 4 - 5 us more a call "
+                  "(`python -m paper_2605_07244_amd.build` builds it)", RuntimeWarning, stacklevel=4)
+    return None
+
+
 def _host():
     """The native part of the binding (once).  Its functions return None for what they do not take as it is; the ctypes
     path below, whose checks raise, is for that."""
     global _HOST
     if _HOST is None:
         lib()                                  # (first, so that a missing library is reported as such)
-        path = os.path.join(_HERE, "mrl_host.so")
-        if not os.path.exists(path):
-            raise FileNotFoundError(f"{path} not found: build it with `python -m paper_2605_07244_amd.build`")
-        spec = importlib.util.spec_from_file_location("mrl_host", path)
-        module = importlib.util.module_from_spec(spec)
-        spec.loader.exec_module(module)
-        _HOST = module
+        _HOST = _load_host() or _NoHost
     return _HOST
 
 

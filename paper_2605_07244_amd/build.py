@@ -39,14 +39,26 @@ def build(verbose: bool = True, jobs: int = 4) -> str:
     return LIB
 
 
-def _build_host(verbose: bool):
-    """The CPython extension of the binding, linked against libmrl.so beside it."""
+def _build_host(verbose: bool) -> bool:
+    """The CPython extension of the binding, linked against libmrl.so beside it.  It needs torch's headers and a host compiler, which
+    libmrl.so does not: without them the binding goes through ctypes, and this says so."""
+    if os.path.exists(HOST):
+        os.remove(HOST)                        # (a stale one must not stay beside a new library)
+    try:
+        _compile_host(verbose)
+        return True
+    except (ImportError, OSError, subprocess.CalledProcessError) as e:
+        sys.stderr.write(f"warning: {HOST} was not built ({e}); the binding will go through ctypes only\n")
+        return False
+
+
+def _compile_host(verbose: bool):
     import sysconfig
 
     import torch
     from torch.utils import cpp_extension as ext
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
-           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", f'-DMRL_TORCH_VERSION="{torch.__version__}"',
            *("-I" + p for p in [*ext.include_paths(), sysconfig.get_paths()["include"]]),
            os.path.join(CSRC, "mrl_host.cpp"), "-o", HOST, *("-L" + p for p in [*ext.library_paths(), HERE]),
            "-lc10", "-ltorch_cpu", "-ltorch_python", "-l:libmrl.so", "-Wl,-rpath,$ORIGIN"]

@@ -130,4 +130,9 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "mrl_host", nullptr, -1, methods, n
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit_mrl_host() { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit_mrl_host() {
+  PyObject* m = PyModule_Create(&module);
+  // (the torch whose C++ interface this was compiled against: the caller compares before the first use)
+  if (m != nullptr && PyModule_AddStringConstant(m, "torch_version", MRL_TORCH_VERSION) != 0) Py_CLEAR(m);
+  return m;
+}

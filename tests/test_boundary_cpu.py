@@ -314,3 +314,34 @@ def test_no_kernel_uses_scratch_memory(tmp_path):
     kernels = {k: p for k, p in _kernel_notes(tmp_path).items() if "k_mfma_rate" not in k}
     assert len(kernels) >= 25 and sum("gemm_nt_bf16" in k for k in kernels) == 3
     assert {k: p["private_segment_fixed_size"] for k, p in kernels.items() if p["private_segment_fixed_size"] != "0"} == {}
+
+
+def test_native_binding_is_optional(tmp_path, monkeypatch):
+    """The CPython extension only marshals faster: where it is missing, broken or built against another torch, the binding
+    warns once and every call goes through ctypes; so does a build that cannot compile it."""
+    import shutil
+
+    m.lib()                                                      # (the C library itself is not optional)
+    here = binding._HERE
+    host = os.path.join(here, "mrl_host.so")
+    assert os.path.exists(host) and binding._load_host().torch_version == binding.torch.__version__
+    monkeypatch.setattr(binding, "_HERE", str(tmp_path))
+    for content in (None, b"", b"not a shared object"):
+        if content is not None:
+            (tmp_path / "mrl_host.so").write_bytes(content)
+        monkeypatch.setattr(binding, "_HOST", None)
+        with pytest.warns(RuntimeWarning, match="ctypes"):
+            none = binding._host()
+        assert none.advantages(*range(14)) is None and none.align(*range(11)) is None
+        assert binding._host() is none                           # (once)
+    monkeypatch.setattr(binding, "_HERE", here)
+    monkeypatch.setattr(binding, "_HOST", None)
+    monkeypatch.setattr(binding.torch, "__version__", "0.0")
+    with pytest.warns(RuntimeWarning, match="built against torch"):
+        assert binding._host().advantages(*range(14)) is None
+
+    from paper_2605_07244_amd import build
+    shutil.copy(host, tmp_path / "mrl_host.so")
+    monkeypatch.setattr(build, "HOST", str(tmp_path / "mrl_host.so"))
+    monkeypatch.setenv("CXX", str(tmp_path / "no-such-compiler"))
+    assert build._build_host(False) is False and not (tmp_path / "mrl_host.so").exists()
