@@ -25,14 +25,14 @@ extern "C" {
  * Arrays are HOST memory of MRL_PROF_NCLASS entries.
  * ---------------------------------------------------------------------- */
 enum {
-  MRL_PROF_PREP = 0,      /* mask scan, compaction, scored lengths, zeros of unscored slots' outputs but dH, padded copy of W's columns */
+  MRL_PROF_PREP = 0,      /* mask scan, compaction, scored lengths, zeros of unscored slots' outputs but dH (calls of more than 2048 slots), padded copy of W's columns */
   MRL_PROF_ADV = 1,       /* group advantages */
   MRL_PROF_GEMM_FWD = 2,  /* logits tile GEMM with fused log-sum-exp */
-  MRL_PROF_ROW_EPI = 3,   /* partial merge, ratio / clip / KL, loss partials */
-  MRL_PROF_CONVERT = 4,   /* operand preparation: row gather and target logits, sequence weights, zero dH rows, scaled transpose (fp32 path: logits -> dz) */
-  MRL_PROF_GEMM_DH = 5,   /* dH = dz W; fp32 passes too small to fill the chip with either product: both, as the one launch they are */
+  MRL_PROF_ROW_EPI = 3,   /* partial merge, ratio / clip / KL, loss partials (fp32 loss calls of at most 2048 ids: log-sum-exp and logits -> dz as well, one launch) */
+  MRL_PROF_CONVERT = 4,   /* operand preparation: row gather and target logits, sequence weights, zero dH rows, and up to 2048 slots what PREP does with the mask above; scaled transpose (fp32 loss calls of more ids: logits -> dz) */
+  MRL_PROF_GEMM_DH = 5,   /* dH = dz W; fp32 passes too small to fill the chip with either product: both, and in the last pass the final reductions, as the one launch they are */
   MRL_PROF_GEMM_DW = 6,   /* dW += dz^T H (nothing for those fp32 passes) */
-  MRL_PROF_FINAL = 7,     /* final reductions */
+  MRL_PROF_FINAL = 7,     /* final reductions (nothing where they came with that launch) */
   MRL_PROF_NCLASS = 8
 };
 int mrl_profile_enable(int on);

@@ -264,6 +264,15 @@ void pad_head(const void* W, int d, int V, const Layout& L, void* ws, hipStream_
   }
 }
 
+// What comes before the first pass's row preparation: the compaction, unless that does it itself, and the padded columns of W.
+void prepare_call(const uint8_t* mask, const int32_t* targets, const void* W, int64_t N, int d, int V, const PrepOut& po,
+                  const Layout& L, void* ws, hipStream_t s) {
+  if (prep_inline(N) && L.Wp == 0) return;
+  Scope sc(MRL_PROF_PREP, s);
+  if (!prep_inline(N)) launch_prep(mask, targets, N, V, po, s);
+  pad_head(W, d, V, L, ws, s);
+}
+
 // forward of one chunk: logits tile GEMM with fused (or, in fp32, separate) log-sum-exp
 // (lse: fp32, the latter wanted)
 void forward_chunk(const void* H, const void* W, int d, int V, bool bf16, const Layout& L, void* ws,
@@ -390,12 +399,8 @@ int mrl_token_scores(const void* hidden, const void* lm_head_w, const int32_t* t
   const PrepOut po = {row_index, n_scored, n_scored + 1, at<int32_t>(ws, L.block_counts), {out_logp, out_lse, out_entropy},
                       0, 0, nullptr};
   RowPrepArgs once = {};
-  {
-    Scope sc(MRL_PROF_PREP, s);
-    if (prep_inline(N)) { once.prep = &po; once.mask = token_mask; once.N = N; once.V = V; }
-    else launch_prep(token_mask, target_ids, N, V, po, s);
-    pad_head(lm_head_w, d, V, L, ws, s);
-  }
+  if (prep_inline(N)) { once.prep = &po; once.mask = token_mask; once.N = N; once.V = V; }
+  prepare_call(token_mask, target_ids, lm_head_w, N, d, V, po, L, ws, s);
   for (int64_t c = 0; c < L.n_chunks; ++c) {
     const int64_t c0 = c * L.chunk_rows;
     prepare_chunk(hidden, lm_head_w, target_ids, d, bf16, L, ws, c, L.n_chunks, c == 0, c == 0 ? once : RowPrepArgs{}, s);
@@ -510,11 +515,7 @@ int mrl_grpo_loss_fwd_bwd(const void* hidden, const void* lm_head_w, const int32
 
   const PrepOut po = {row_index, n_scored, n_scored + 1, at<int32_t>(ws, L.block_counts), {out_logp, nullptr, nullptr},
                       B, T, at<int32_t>(ws, L.seq_len)};
-  {
-    Scope sc(MRL_PROF_PREP, s);
-    if (!prep_inline(N)) launch_prep(token_mask, target_ids, N, V, po, s);
-    pad_head(lm_head_w, d, V, L, ws, s);
-  }
+  prepare_call(token_mask, target_ids, lm_head_w, N, d, V, po, L, ws, s);
   int64_t n_passes = L.n_chunks;
   if (cfg->scored_rows_hint > 0) {
     const int64_t by_hint = (cfg->scored_rows_hint + L.chunk_rows - 1) / L.chunk_rows;
@@ -610,18 +611,16 @@ int mrl_grpo_loss_fwd_bwd(const void* hidden, const void* lm_head_w, const int32
     // (rows of the pass at most, as far as the caller says)
     const int64_t hinted = cfg->scored_rows_hint > 0 ? cfg->scored_rows_hint - c0 : L.chunk_rows;
     const bool dw_blocks = bf16 && dw_rows_in_blocks((int)(hinted < L.chunk_rows ? hinted : L.chunk_rows));
-    {
+    if (bf16 && out_dW) {
+      // the stash already holds the backward operand; the dW launch needs the pass's gathered rows, each
+      // times its row scale, transposed, and zeros behind the last valid row
       Scope sc(MRL_PROF_CONVERT, s);
-      if (bf16) {
-        // the stash already holds the backward operand; the dW launch needs the pass's gathered rows, each
-        // times its row scale, transposed, and zeros behind the last valid row
-        if (out_dW)
-          launch_backward_rows_b16(at<void>(ws, L.Hc), L.ldh, at<float>(ws, L.row_scale) + c0, at<void>(ws, L.Ht), L.ldr,
-                                   n_scored, c0, L.chunk_rows, L.dp, at<void>(ws, L.Z), L.ldz, (int)L.Vp, dw_blocks, s);
-      } else if (!row_f32) {
-        launch_convert_f32(at<float>(ws, L.Z), L.ldz, at<float>(ws, L.lse_c), at<float>(ws, L.g_c), target_ids, row_index,
-                           n_scored, c0, L.chunk_rows, V, s);
-      }
+      launch_backward_rows_b16(at<void>(ws, L.Hc), L.ldh, at<float>(ws, L.row_scale) + c0, at<void>(ws, L.Ht), L.ldr,
+                               n_scored, c0, L.chunk_rows, L.dp, at<void>(ws, L.Z), L.ldz, (int)L.Vp, dw_blocks, s);
+    } else if (!bf16 && !row_f32) {
+      Scope sc(MRL_PROF_CONVERT, s);
+      launch_convert_f32(at<float>(ws, L.Z), L.ldz, at<float>(ws, L.lse_c), at<float>(ws, L.g_c), target_ids, row_index,
+                         n_scored, c0, L.chunk_rows, V, s);
     }
     if (!bf16) {
       GemmF32Args h = {};

@@ -310,3 +310,33 @@ def test_token_scores_entropy(mrl, synth, dtype, scale):
     torch.cuda.synchronize()
     assert torch.equal(lp0, lp) and torch.equal(lse0, lse) and torch.equal(lp1, lp)
     assert none_lse is None and none_ent is None
+
+
+def test_profile_classes_count_launches(mrl):
+    """The classes of the timing hooks hold what the header says: a launch where there is one and none where there is none."""
+    def score(N, d):
+        H, W = torch.randn((N, d), device="cuda").bfloat16(), torch.randn((300, d), device="cuda").bfloat16()
+        return lambda: mrl.token_logprobs(H, W, torch.zeros(N, dtype=torch.int32, device="cuda"))
+
+    def loss(V):
+        N, d = 256, 64
+        z = lambda n, t=torch.float32: torch.zeros(n, dtype=t, device="cuda")  # noqa: E731
+        cfg = mrl.LossConfig(kl_beta=0.0, dh_dtype=mrl.F32)
+        H, W = torch.randn((N, d), device="cuda"), torch.randn((V, d), device="cuda")
+        return lambda: mrl.grpo_loss_fwd_bwd(H, W, z(N, torch.int32), z(N, torch.uint8) + 1, z(N) - 6, None, z(1) + 1, z(1, torch.int32),
+                                             None, 1, N, 1, cfg)
+
+    forms = [(score(2048, 128), dict(prep=0, operand_prep=1, gemm_fwd=1, row_epilogue=1)),
+             (score(2049, 128), dict(prep=1, operand_prep=1, gemm_fwd=1, row_epilogue=1)),
+             (score(100, 136), dict(prep=1, operand_prep=1, gemm_fwd=1, row_epilogue=1)),        # (the padded columns)
+             (loss(512), dict(prep=0, operand_prep=1, gemm_fwd=1, row_epilogue=1, gemm_dh=1, gemm_dw=0, final=0)),
+             (loss(2049), dict(prep=0, operand_prep=2, row_epilogue=1, gemm_dh=1, gemm_dw=0, final=0))]
+    mrl.profile_enable(True)
+    try:
+        for call, want in forms:
+            mrl.profile_collect()
+            call()
+            got = mrl.profile_collect()
+            assert {k: got[k][1] for k in want} == want
+    finally:
+        mrl.profile_enable(False)
