@@ -22,12 +22,13 @@ __device__ inline int valid_rows(const int64_t* n_scored, int64_t chunk_start, i
 // Compaction of scored slots (order preserving), zeros in the per-slot outputs of the others, and
 // the scored length of every sequence.  A launch that does next to nothing takes 4.5 - 5 us here,
 // which the preparation of a small call is made of, so independent pieces share a launch: up to
+// kPrepInline slots they are part of the row preparation (below); up to
 // kPrepOneBlock slots one block compacts (and the other blocks of the launch count the sequences);
 // above, one launch counts per block of slots (and per sequence) and one places the slots, each
 // block adding up the counts before its own - up to kPrepMaxSelf blocks, beyond which a scan launch
 // in between is cheaper than every block reading them all.
-// Count, scan, fill, sequence lengths and the zeros were launches of their own, 19 us before a loss call
-// of 512 slots; now 5 us.
+// As launches of their own count, scan, fill, sequence lengths and the zeros took 19 us before a loss call of 512 slots; the
+// one launch takes 5.6 us for 3003 slots.
 // ----------------------------------------------------------------------------
 constexpr int PREP_PER_THREAD = 4;
 constexpr int PREP_BLOCK = 256;
@@ -387,7 +388,8 @@ __global__ __launch_bounds__(256) void k_seq_log_ratio(const uint8_t* mask, cons
 
 // ----------------------------------------------------------------------------
 // Row preparation: what needs the compaction and comes before a forward launch, in one launch.
-//   block 0 (loss)      : the sequence weights
+//   one block (PREP)    : the compaction's outputs
+//   one block (loss)    : with PREP the scored lengths, and the sequence weights
 //   zero_blocks         : dH rows of unscored slots, ZERO_SLOTS_PER_BLOCK each
 //   the rest            : one wave per scored row of the pass: target logit z_t = <H[slot], W[y]> and,
 //                         on the bf16 path, the row's copy Hc[r][0:dp] = H[slot][0:d] | 0, which
@@ -757,9 +759,13 @@ __global__ __launch_bounds__(EPI_THREADS) void k_row_epilogue(RowEpiArgs a) {
 // row, which keeps the row's logits in registers in between; 16 rows per block and entry of the loss partials.
 // As three launches (a block per row, 64 rows per block, a grid of rows) they are three latencies of 4 - 5 us each
 // on kilobytes (loss call of 256 slots, V = 512, d = 64, which the host bounds: 35.1 us, now 31.6).
+// The loops over a lane's logits are unrolled, and what lies behind V costs its issue: two lengths.  Loss calls, us, of 232
+// and of 20000 rows, d = 64, with loops of 2048 and of 512: V = 300 23.1 and 22.0, 473 and 462; V = 400 23.6 and 22.9, 495 and
+// 486; V = 512 24.5 and 23.6, 513 and 507.  A third length, of 1024, would take 1 % off 513 to 1024 ids (V = 600 25.9 and 25.4,
+// 526 and 521), and is not worth another instance; one in the place of 512 adds 0.5 % below that.
 // ----------------------------------------------------------------------------
 constexpr int kRowLogits = 2048, kFewLogits = 512, kRowWaves = 16;
-template <int LOGITS>                                 // (the loops over a lane's logits are unrolled: V = 512 9.5 us with 2048, 8.3 with 512)
+template <int LOGITS>
 __global__ __launch_bounds__(kRowWaves * 64) void k_row_f32(RowEpiArgs a, float* Z, int64_t ldz, int V, int write_dz) {
   __shared__ double sh[kRowWaves][EPI_NQ];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);

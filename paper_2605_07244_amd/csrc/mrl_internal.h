@@ -131,7 +131,9 @@ struct PrepOut {
 void launch_prep(const uint8_t* mask, const int32_t* targets, int64_t N, int V, const PrepOut& o,
                  hipStream_t stream);
 // Calls of at most kPrepInline slots take no launch_prep: the first launch_row_prep of the call is given its outputs.
-// (Every block scans all of them: 3003 slots 9.9 us with the preparation, 4.7 + 5.0 as two launches; 201 slots 8.1 and 9.9.)
+// (Every block scans all slots, in a loop unrolled to this length.  Scoring calls, d = 64, V = 1000, us, with a launch and inline: 201
+// slots 22.3 and 19.1, 1024 25.4 and 22.9, 2048 26.2 and 23.8.  Unrolled to 4096 it takes 24.9 at 2048 slots, 26.0 at 3003
+// and 27.2 at 4096 against 26.5 and 27.1 with a launch: what the longer loop gives there it costs the smaller calls.)
 constexpr int64_t kPrepInline = 2048;
 inline bool prep_inline(int64_t N) { return N <= kPrepInline; }
 

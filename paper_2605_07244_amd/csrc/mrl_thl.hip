@@ -25,8 +25,11 @@ constexpr int THL_WAVES = THL_THREADS / 64;
 constexpr int THL_SEGMENT = 32 * THL_THREADS;
 constexpr int THL_INVERSES = 64;
 constexpr int THL_KEPT = 8;                         // KEEP: steps of a wave at most, rows of 2048 positions
-constexpr int THL_KEPT_FROM = 3 * THL_THREADS;      // ... and more than three steps, below which most of what it unrolls is idle (10000 rows of
-                                                    // 300 + 300 positions 37.8 us a call against 30.2, 5000 of 500 + 700 22.6 against 21.5)
+// ... and more than three steps, below which most of what it unrolls is idle.  Calls, us, without and with: 10000 rows of 800 positions
+// (four steps) 49.4 and 42.5, of 1024 50.8 and 43.9, 2048 rows 13.2 and 13.4, 14.1 and 13.8; three steps: 10000 rows of
+// 600 42.7 and 40.1, but 5000 of 500 + 700 21.5 and 22.6, 2048 of 520 11.7 and 12.4, of 768 12.6 and 12.7; two: 10000
+// of 300 + 300 30.2 and 37.8.
+constexpr int THL_KEPT_FROM = 3 * THL_THREADS;
 constexpr int THL_GROUP = 2;                        // steps whose loads are in flight together (the call: 17.1 us; 4 and 8: 17.7, 1: 18.9)
 
 // round(x * 2^32) to nearest even for |x| < 2^30, with fp32 operations that are all exact but the last

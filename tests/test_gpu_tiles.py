@@ -258,8 +258,8 @@ def test_gradients_of_padded_widths(mrl, N, d, V):
     (700, 650, 256),              # three passes of at most 256 rows, the last with 138
 ])
 def test_few_rows_behind_others(mrl, N, scored, chunk_rows):
-    """The forward kernel of at most 256 rows as the last part of a larger pass (rows, partial sums and stash at an offset, the
-    partials' stride that of the pass), and as every pass of a call."""
+    """Up to 256 rows as the last part of a larger pass, on the large tile or a half column of it (rows, partial sums and stash at
+    an offset, the partials' stride that of the pass), and passes of 256 rows, on the forward kernel for few rows."""
     d, V = 64, 600
     H, W, y, mask = _head(N, d, V, scored, N + scored)
     out, dH, dW = _step(mrl, H, W, y, mask, mrl.BF16, scored, chunk_rows=chunk_rows, poison=True)
