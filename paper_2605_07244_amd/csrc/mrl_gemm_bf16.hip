@@ -1084,7 +1084,7 @@ __global__ __launch_bounds__(NTHREADS, 2) void forward_few_bf16(Params p) {
 // ([rows / 32][dp][32], written so by launch_backward_rows_b16), so that a 32-wide K step is whole lines; as rows of
 // Ht, 64 bytes at a time, the launch was no faster than the large tile.  Stores are whole lines as well (lanes exchange
 // 16-byte pieces so that an instruction covers 8 rows x 128 bytes) and, where rows of dW are whole lines,
-// streaming: dW does not displace the operands (327 rows, d = 4096 834 and 727 us; with rows that straddle lines
+// streaming: dW does not displace the operands (327 rows, d = 4096, in a loss call 957 and 748 us, 893 on the large tile; with rows that straddle lines
 // streaming costs instead, 150 rows, d = 712 45 and 68).  32 consecutive tiles per XCD, whose stores then lie
 // 4 MB and not 8 MB apart (400 rows, V = 140000, d = 2048 473 and 435).  Launch, us, large tile and this one:
 // V = 151936, d = 4096, 150 rows 767 and 647, 400 rows 1000 and 856, 900 rows 1470 and 1340; d = 1536, 400 rows 376 and 348;
