@@ -941,12 +941,20 @@ __global__ __launch_bounds__(NTHREADS) void gemm_nt_bf16(Params p) {
 // K-elements, two steps of the loop, and the token rows lie in blocks of 32 columns ([dp / 32][rows][32],
 // written that way by the row preparation), so that both are fetched in whole lines.  Waves without tokens
 // only load their share of W.  Every tile walks K from column 0, as the large tile does: a logit's products are
-// added in one order in every forward kernel, and a token's scores have the same bits in a pass of any length.  (Rows of a
-// power of two of bytes lie on the same L2 and memory channels, and tiles that are all at one column ask the same
-// channels at the same time; tiles that each start at another column avoid that, V = 151936, d = 4096, 64 rows 253 us
-// instead of 316, 256 rows 330 and 340, but give other bits than the large tile.)
-// Scoring call, us, 256 x 256 tiles, these in 64-byte pieces, now: V = 151936, d = 4096, 64 rows 367, 315 and 316,
-// 128 rows 377, 348 and 321, 201 rows 387, 395 and 334, 256 rows 408, 412 and 340; d = 1536 154, 132 and 113, 158, 143
+// added in one order in every forward kernel, and a token's scores have the same bits in a pass of any length.
+// Rows of a power of two of bytes lie on the same L2 and memory channels, and tiles that are all at one column ask the
+// same channels at the same time.  Tiles that each start at another column avoid that but give other bits than the
+// large tile; instead the first tile of every place on the chip starts up to 31 x 2048 clocks late, by its number among the tiles of
+// its XCD, and those behind it stay apart.  Scoring call, us, at once and one after another: V = 151936, d = 4096, 1 row
+// 310 and 264, 64 rows 318 and 274, 128 rows 317 and 293; d = 2048 162 and 139, 169 and 143, 181 and 163; V = 65536,
+// d = 4096 145 and 126, 147 and 127, 144 and 134; V = 128256, d = 8192 434 and 418, 418 and 418, 455 and 437.  Where the
+// MFMAs bind, or the launch is too short for the delay, it costs: 201 rows, V = 151936, d = 4096 341 and 344, d = 2048 186
+// and 194; one round of short tiles (V = 65536, d = 2048) 51 and 69; half a round (V = 34000, d = 4096) 72 and 92; rows of
+// 12 KB, 128 rows 342 and 357, of 32 KB, V = 34000, 1 row 256 and 285.  Hence the bounds: rows of 4, 8 and 16 KB, two waves with
+// tokens at most, more than half of the places taken, at least 48 chunks of W per place (V = 50000, d = 4096, where that
+// lies: 1 row 110 and 102, 128 rows 114 and 121).
+// Scoring call, us, 256 x 256 tiles, these in 64-byte pieces, now: V = 151936, d = 4096, 64 rows 367, 315 and 274,
+// 128 rows 377, 348 and 293, 201 rows 387, 395 and 334, 256 rows 408, 412 and 340; d = 1536 154, 132 and 113, 158, 143
 // and 115, 164, 162 and 138, 172, 162 and 140; V = 32000, d = 2048, 256 rows 53, 52 and 45.
 // The line lies at one tile column because the load path of a compute unit (23 clocks per
 // KB) then has to deliver 24 KB per 512 MFMA cycles: used for every column, 4096 rows, d = 1536 / 2048 / 4096
@@ -958,6 +966,7 @@ constexpr int F_CHUNK = FM * BK * 2, F_STAGE = FN * FK * 2;         // 16 KB: 64
 constexpr int F_CHUNKS = 2, F_STAGES = 3;
 constexpr int F_B = F_CHUNKS * F_CHUNK, F_LDS = F_B + F_STAGES * F_STAGE;
 constexpr int F_LOADS = 4;                                          // direct loads per wave and chunk, or stage
+constexpr int F_PLACES = 512;                                       // workgroups on the chip at a time
 
 __global__ __launch_bounds__(NTHREADS, 2) void forward_few_bf16(Params p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -971,6 +980,10 @@ __global__ __launch_bounds__(NTHREADS, 2) void forward_few_bf16(Params p) {
   // measured the same
   const int M = p.M, tm = blockIdx.x;
   const int m0 = tm * FM;
+
+  if ((p.lda == 2048 || p.lda == 4096 || p.lda == 8192) && N <= 128 && gridDim.x > F_PLACES / 2 &&
+      (int64_t)gridDim.x * (p.K / BK) >= 48 * F_PLACES && tm < F_PLACES)
+    for (int i = tm / NXCD % 32; i > 0; --i) __builtin_amdgcn_s_sleep(32);   // (2048 clocks each)
 
   // direct loads, 1 KB each, as byte offsets of the lane from the tile's first row.  W: 8 rows x 128 bytes; lane l
   // fills slot l % 8 of row l / 8 and fetches logical chunk slot ^ f(row), f = the row bits 1, 3, 4 that vary

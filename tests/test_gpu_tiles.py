@@ -330,15 +330,16 @@ def test_fp32_response_ratio_over_passes(mrl, level):
         assert error <= 1e-5 * size, (name, error, size)
 
 
-@pytest.mark.parametrize("scored,d,V", [
-    (800, 512, 5003),             # a last half column in the long pass; 40 vocabulary tiles of 128, eight K chunks
-    (1000, 712, 2057),            # a padded width, the last column a whole tile
-    (513, 4096, 1300),            # power-of-two rows, 64 K chunks; one row in the last column
+@pytest.mark.parametrize("N,scored,d,V", [
+    (820, 800, 512, 5003),        # a last half column in the long pass; 40 vocabulary tiles of 128, eight K chunks
+    (1020, 1000, 712, 2057),      # a padded width, the last column a whole tile
+    (533, 513, 4096, 1300),       # power-of-two rows, 64 K chunks; one row in the last column
+    (700, 100, 4096, 50001),      # ... and tiles enough that they start one after another
+    (700, 129, 2048, 100003),     # ... and one row too many for that
 ])
-def test_scores_do_not_depend_on_the_pass(mrl, scored, d, V):
+def test_scores_do_not_depend_on_the_pass(mrl, N, scored, d, V):
     """Every forward kernel adds a logit's products in the same order: the bits of a token's scores are those of a long pass, of
     passes of 256 rows (a workspace that holds no longer one, or chunk_rows) and of a call of a few slots."""
-    N = scored + 20
     H, W, y, mask = _head(N, d, V, scored, V)
     want = mrl.token_scores(H, W, y, mask)
     # 16 KB more than 256 slots take hold the arrays by slot, and no pass of 512 rows
@@ -350,8 +351,10 @@ def test_scores_do_not_depend_on_the_pass(mrl, scored, d, V):
     for k in range(3):
         assert torch.equal(passes[k], want[k])
         assert torch.equal(torch.cat([a[k] for a in alone]), want[k])
+    one = lambda v, t: torch.tensor([v], dtype=t, device="cuda")
     for chunk_rows in (0, 256):
-        out, _, _ = _step(mrl, H, W, y, mask, mrl.BF16, V, chunk_rows=chunk_rows)
+        out = mrl.grpo_loss_fwd_bwd(H, W, y, mask, torch.zeros(N, device="cuda"), None, one(0.7, torch.float32), one(0, torch.int32),
+                                    None, 1, N, 1, mrl.LossConfig(kl_beta=0.0, chunk_rows=chunk_rows), want_dW=False)
         assert torch.equal(out["logp"], want[0])
 
 
