@@ -59,6 +59,28 @@ def test_static_entry_point_matches_workspace_variant_twice_in_a_row():
         assert np.max(np.abs(got_lse[rows].cpu().numpy() - lse_o)) <= util.LOGP_TOL
 
 
+def test_static_entry_point_in_passes_of_256_rows():
+    """Slots enough that the buffer holds passes of 256 rows only, on the kernel for few rows, where a workspace holds long ones:
+    the same bits."""
+    import paper_2605_07244_amd as mrl
+    N, d, V = 4_110_000, 128, 30000
+    # 8 bytes per slot and 24 per 1024 slots leave 0.61 MB: 0.34 for a pass of 256 rows (partial sums and rows), 0.68 for 512
+    row = 2 * ((V + 255) // 256) * 4 + (d + 64) * 2
+    left = mrl.binding.STATIC_SCRATCH_BYTES - 8 * (N + 1) - 24 * ((N + 1023) // 1024)
+    assert 256 * row < left - 4096 and left < 512 * row
+    g = torch.Generator("cuda").manual_seed(15)
+    H = torch.randn((N, d), device="cuda", generator=g, dtype=torch.bfloat16)
+    W = (0.02 * torch.randn((V, d), device="cuda", generator=g)).bfloat16()
+    y = torch.randint(0, V, (N,), device="cuda", generator=g, dtype=torch.int32)
+    mask = torch.zeros(N, dtype=torch.uint8, device="cuda")
+    mask[torch.randint(0, N, (900,), device="cuda", generator=g)] = 1
+    want_lp, want_lse = mrl.token_logprobs(H, W, y, mask)
+    got_lp, got_lse = torch.full((N,), 7.0, device="cuda"), torch.full((N,), 7.0, device="cuda")
+    mrl.token_logprobs_static(H, W, y, mask, got_lp, got_lse)
+    torch.cuda.synchronize()
+    assert torch.equal(got_lp, want_lp) and torch.equal(got_lse, want_lse) and float(got_lp.min()) < -5
+
+
 def test_static_entry_point_fp32_and_binding():
     import paper_2605_07244_amd as mrl
     H, W, y, mask = _inputs(300, 72, 777, 13, dtype=torch.float32)
