@@ -89,6 +89,9 @@ int mrl_version(void);
  * be NULL (= every row is scored); rows with mask 0 or with a target id
  * outside [0, V) are skipped and report out_logp = out_lse = 0.  out_lse may
  * be NULL.  N >= 0 (N = 0 is a no-op).
+ * On the bf16 path a row's results have the same bits whatever other rows the call
+ * holds and however the workspace cuts it into passes, in this call, the two below
+ * and the log-probs of the loss.
  * ---------------------------------------------------------------------- */
 size_t mrl_token_logprobs_workspace(int64_t N, int32_t d, int32_t V, int32_t dtype);
 int mrl_token_logprobs(const void* hidden /*[N,d] dev*/, const void* lm_head_w /*[V,d] dev*/,
