@@ -55,8 +55,9 @@ int mrl_probe_mfma_rate(int32_t random_operands, double seconds, void* scratch /
                         size_t scratch_bytes, double* out_tflops /*host*/);
 
 /* ------------------------------------------------------------------------
- * The launch plan of the dW GEMM for an LM head of V rows and d columns (host
- * code only, no GPU call): which rows of 256 x 256 tiles are cut into slices of
+ * The launch plan of the dW GEMM for an LM head of V rows and d columns where
+ * it runs on 256 x 256 tiles (short contractions; else on 384 x 256 ones, whose
+ * last round is cut on the device) (host code only, no GPU call): which rows of 256 x 256 tiles are cut into slices of
  * the contraction at the end of the launch, into how many, and how many of the
  * resulting work items each of the 8 XCDs takes.  For tests of the host logic
  * and for reading profiles.  out12 (host): [0] first tile row of the tail,

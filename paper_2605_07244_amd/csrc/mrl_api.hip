@@ -16,8 +16,10 @@ static __device__ __align__(256) unsigned char scratch[MRL_STATIC_SCRATCH_BYTES]
 namespace mrl {
 namespace {
 
-constexpr int kDefaultChunkBf16 = 65536;   // rows per pass: amortises the fp32 dW read-modify-write (20 GB of stash at V = 151936)
-constexpr int kFwdSubChunk = 16384;        // forward launches cover this many rows: their H rows stay in the Infinity Cache
+constexpr int kDefaultChunkBf16 = 61440;   // rows per pass: amortises the fp32 dW read-modify-write (19 GB of stash at V = 151936); four forward launches
+// forward launches cover this many rows: their H rows stay in the Infinity Cache, and 40 columns of tiles make whole groups of 8 x 4 in a
+// band (V = 151936, d = 4096: 15360 rows 314 us a column, 16384 rows - 42 and one of 256 - 321, 16512 rows 328)
+constexpr int kFwdSubChunk = 15360;
 constexpr int kDefaultChunkF32 = 2048;
 constexpr int kTailOnlyRows = 4096;        // (see head_tail_only)
 constexpr int64_t kMaxSlots = (int64_t)1 << 30;
@@ -107,6 +109,7 @@ struct Layout {
   size_t seq_len, seq_coef, seq_expo, group_count, lse_c, g_c, row_scale, loss_partials, Z, Ht = 0;
   size_t tail = 0;             // bf16: partial tiles of the dH and dW launches' K-split tails
   int tail_items = 0;          // ... how many
+  size_t head_bytes = 0;
   size_t Hc = 0, Wp = 0;       // bf16: the pass's token rows, gathered and zero-padded to dp columns; zero-padded tail of W (only if dp != d)
   int dp = 0;                  // bf16: d rounded up to the 128-wide panel pairs of the GEMM kernels
   int64_t ldh = 0;             // row stride of Hc and Wp
@@ -163,11 +166,9 @@ Layout make_layout(int64_t N, int64_t B, int d, int V, int dtype, int chunk_rows
     L.Z = take(off, (size_t)chunk_rows * L.ldz * es);
     if (bf16) L.Ht = take(off, (size_t)dk * L.ldr * es);
     if (bf16) {
-      // 256 partial tiles for the dW launch; the dH launch's last round of up to 255 tiles can use up
-      // to four per compute unit; a quarter of the size of the head, which has the longer tiles the larger it
-      // is, bounds the extra ones
-      const size_t extra = (size_t)dk * L.ldz * es / 4 / gemm_tail_tile_bytes();
-      L.tail_items = gemm_dw_tail_items() + (int)(extra < 768 ? extra : 768);
+      // last of all: pick_chunk makes it shorter where a workspace has no room for all of it
+      L.head_bytes = (size_t)dk * L.ldz * es;
+      L.tail_items = gemm_tail_items(L.head_bytes);
       L.tail = take(off, L.tail_items * gemm_tail_tile_bytes());
     }
   } else if (!bf16) {
@@ -205,17 +206,26 @@ int check_cfg(const mrl_loss_config* c) {
   return MRL_OK;
 }
 
+// the layout fits, if need be with fewer partial tiles
+bool fits(Layout& L, size_t workspace_bytes) {
+  if (L.total <= workspace_bytes) return true;
+  if (L.tail_items == 0 || L.tail + gemm_tail_bytes_least(L.head_bytes) > workspace_bytes) return false;
+  L.tail_items = (int)((workspace_bytes - L.tail) / gemm_tail_tile_bytes());
+  L.total = workspace_bytes;
+  return true;
+}
+
 // pick the chunk size: the configured one, or the largest default-capped multiple of
 // 256 whose layout fits into the caller's workspace
 int pick_chunk(int64_t N, int64_t B, int d, int V, int dtype, int cfg_chunk, bool loss,
                size_t workspace_bytes, Layout& L, bool entropy = false) {
   if (cfg_chunk > 0) {
     L = make_layout(N, B, d, V, dtype, cfg_chunk, loss, entropy);
-    return L.total <= workspace_bytes ? MRL_OK : MRL_ERR_WORKSPACE;
+    return fits(L, workspace_bytes) ? MRL_OK : MRL_ERR_WORKSPACE;
   }
   for (int r = default_chunk(N, dtype); r >= kTile; r = (r / 2) / kTile * kTile) {
     L = make_layout(N, B, d, V, dtype, r, loss, entropy);
-    if (L.total <= workspace_bytes) return MRL_OK;
+    if (fits(L, workspace_bytes)) return MRL_OK;
     if (r == kTile) break;
   }
   return MRL_ERR_WORKSPACE;
@@ -610,7 +620,8 @@ int mrl_grpo_loss_fwd_bwd(const void* hidden, const void* lm_head_w, const int32
     const int overwrite = (c == 0 && !cfg->accumulate_dw) ? 1 : 0;
     // (rows of the pass at most, as far as the caller says)
     const int64_t hinted = cfg->scored_rows_hint > 0 ? cfg->scored_rows_hint - c0 : L.chunk_rows;
-    const bool dw_blocks = bf16 && dw_rows_in_blocks((int)(hinted < L.chunk_rows ? hinted : L.chunk_rows));
+    const int expected = (int)(hinted < L.chunk_rows ? hinted : L.chunk_rows);
+    const bool dw_blocks = bf16 && dw_rows_in_blocks(expected);
     if (bf16 && out_dW) {
       // the stash already holds the backward operand; the dW launch needs the pass's gathered rows, each
       // times its row scale, transposed, and zeros behind the last valid row
@@ -657,7 +668,7 @@ int mrl_grpo_loss_fwd_bwd(const void* hidden, const void* lm_head_w, const int32
     if (out_dW) {
       Scope sc(MRL_PROF_GEMM_DW, s);
       launch_gemm_dw_bf16(at<void>(ws, L.Z), L.ldz, at<void>(ws, L.Ht), dw_blocks ? L.dp : L.ldr, n_scored, c0,
-                          L.chunk_rows, V, d, out_dW, overwrite, at<float>(ws, L.tail), dw_blocks, s);
+                          L.chunk_rows, V, d, out_dW, overwrite, at<float>(ws, L.tail), L.tail_items, expected, dw_blocks, s);
     }
   }
   if (!finalized) {

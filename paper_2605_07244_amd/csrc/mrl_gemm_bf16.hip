@@ -1,13 +1,15 @@
 // bf16 MFMA tile GEMM for gfx950 with three fused epilogues.
 //
-// One kernel body computes C[m][n] = sum_k A[m][k] * B[n][k] for a 256 x 256
-// tile per workgroup (both operands K-contiguous, "NT" form).  Four wave64
-// wavefronts form a 2 x 2 grid, each owning a 128 x 128 sub-tile as 8 x 8
-// MFMA 16x16x32 accumulators (256 accumulator registers per lane).  The
-// 16x16x32 shape is chosen over 32x32x16 for energy: with real (random-mantissa)
-// operands the chip is power-limited, and an MFMA-only loop sustains about 13 %
-// more FLOP/s with the 16 x 16 shape.  Operand panels of 64 K-elements go from
-// global memory straight into LDS (global_load ... lds, no staging registers)
+// One kernel body computes C[m][n] = sum_k A[m][k] * B[n][k] for a 384 x 256 tile per workgroup: four wave64 wavefronts in a
+// 2 x 2 grid, each owning a 192 x 128 sub-tile as 12 x 8 MFMA 16x16x32 accumulators (384 accumulator registers per lane, 256 of them
+// in the accumulation file).  What bounds these launches is the energy and the issue of moving operands: with random mantissas the
+// chip is at its power limit, and of two loops with the same products the one that moves fewer bytes runs at the higher clock.
+// 384 x 256 is the largest tile that fits registers and LDS (two panels of 80 KB); per product it takes 17 % less from the L2
+// and from LDS than 256 x 256.  Launches of 15360 rows, V = 151936, d = 4096, 256 x 256 and now, us: forward with the stash 12660 and
+// 12340, dH 12740 and 11750, dW 13010 and 12080 (clock 1.78 - 1.88 and 1.83 - 1.95 GHz, matrix cores 73 - 78 % busy in either);
+// 28672 rows, V = 128256, d = 2048 11055 and 10680, 10080 and 9420, 9905 and 9000.
+// The 16x16x32 shape is chosen over 32x32x16 for energy: an MFMA-only loop sustains about 13 % more FLOP/s with it.  Operand
+// panels of 64 K-elements go from global memory straight into LDS (buffer_load ... lds, no staging registers)
 // into a double buffer.  LDS rows are 128 bytes whose 16-byte chunks are
 // XOR-swizzled with (row / 2) % 8: a 128-bit LDS read is served 16 lanes (16
 // rows of one chunk column) per cycle over 64 banks, rows 2 apart share a bank
@@ -42,30 +44,9 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));   // 16-byte access, 4-byte alignment
 
-constexpr int BM = 256, BN = 256, BK = 64;
+constexpr int BK = 64;
 constexpr int NTHREADS = 256;
-constexpr int NSTAGE = 2;                          // LDS double buffer of K panels
-constexpr int TILE_BYTES = BM * BK * 2;            // one operand panel: 32 KB (256 rows x 128 B)
-constexpr int STAGE_BYTES = 2 * TILE_BYTES;        // A + B
-constexpr int DHSTAGE_LD = BM + 8;                   // bf16 elements per row of the dH epilogue's staging tile
-constexpr int DHSTAGE_BYTES = BN * DHSTAGE_LD * 2;     // 132 KB
-constexpr int PIPE_BYTES = NSTAGE * STAGE_BYTES;   // 128 KB
-// Direct loads of a slot's 16 (per wave), by the group of the K loop that issues them: the slot is
-// released by the barrier in group 5, so its refill starts there and may run on into groups 0 - 4
-// of the next panel (it is needed at that panel's barrier).
-constexpr int kLoadsInGroup[8] = {4, 0, 0, 0, 0, 4, 4, 4};
-constexpr int load_index_base(int g) {      // loads issued before group g, in the order 5, 6, 7, 0, 1, ...
-  int n = 0;
-  for (int h = 5; h != g; h = (h + 1) & 7) n += kLoadsInGroup[h];
-  return n;
-}
-constexpr int kLoadsCarriedOver = kLoadsInGroup[0] + kLoadsInGroup[1] + kLoadsInGroup[2] + kLoadsInGroup[3] + kLoadsInGroup[4];
-static_assert(kLoadsCarriedOver + kLoadsInGroup[5] + kLoadsInGroup[6] + kLoadsInGroup[7] == 16, "a slot takes 16 loads per wave");
 constexpr int kDwTailMaxItems = 256;                // K slices of dW tail tiles per launch: one per compute unit
-constexpr int ZT_BYTES = BN * 4;                   // forward: the tile's 256 target logits, behind the panels
-template <int MODE> constexpr int lds_bytes() {     // (forward: the half-column tiles keep three stages of 48 KB)
-  return MODE == 0 ? PIPE_BYTES + TILE_BYTES / 2 + ZT_BYTES : (DHSTAGE_BYTES > PIPE_BYTES ? DHSTAGE_BYTES : PIPE_BYTES);
-}
 
 // s_waitcnt immediates (gfx9 encoding): wait until at most N vector-memory loads are
 // outstanding, no wait on the export / LDS counters.
@@ -89,7 +70,7 @@ struct Params {
   // DH
   const float* row_scale; void* dH; int dh_f32; int d; int max_items;   // max_items: partial tiles tail_part holds
   // DW
-  float* dW; int overwrite; int streaming;
+  float* dW; int overwrite; int streaming; int wide;
   // DW, K-split tail (see dw_tail_plan): workgroups from main_blocks on take the tiles of the
   // tile rows tail_m0 .. tail_m0 + tail_rows - 1, each cut into tail_split slices of the
   // contraction, and store their accumulators to tail_part instead of dW
@@ -97,25 +78,24 @@ struct Params {
   int tail_first[NXCD + 1];   // items tail_first[x] .. tail_first[x + 1] - 1 run on XCD x
 };
 
-// Workgroup -> tile mapping of the forward and dH launches.  Workgroups are dealt round-robin to the
+// Workgroup -> tile mapping of the launches.  Workgroups are dealt round-robin to the
 // 8 XCDs, each with its own L2 and 32 compute units; 32 consecutive workgroups of one XCD take 32
-// consecutive tiles, numbered down the columns of bands of 8 tile rows (8 x 4 tiles when the N extent
-// allows), so that they share operand panels in that L2 and all XCDs walk the same A rows at the same
-// time.  The numbering runs over the VALID tiles (the scored rows are counted on the device) without
+// consecutive tiles, numbered down the columns of bands of BAND tile rows, so that they share operand panels in that L2 and all XCDs
+// walk the same A rows at the same time.  Bands of 8 rows of 256 in the forward (8 x 4 tiles, the tokens' side of 384), of 4 rows of 384 in dH
+// and dW (4 x 8): either takes 3584 rows of panels per group, the other shape 4096 (dH of 15360 rows, d = 4096 12920 and 12775 us).  The numbering runs over the VALID tiles (the scored rows are counted on the device) without
 // holes: numbering super-tiles over the launch's upper bound gave each XCD fixed tile columns, and
 // with 20 of 32 tile columns valid three XCDs had nothing to do (scoring 5120 of 8192 slots,
 // V = 128256, d = 2048: 3233 us a call against 2088 us now).  The tiles of the last, incomplete round
 // of 256 are dealt evenly.
-constexpr int kBand = 8;
 constexpr int kXcdCus = 32;
 constexpr int kRound = NXCD * kXcdCus;
-__device__ inline void tile_at(int t, int Mt, int Nt, int& tm, int& tn) {
-  const int band = t / (kBand * Nt), in_band = t - band * kBand * Nt;
-  const int rows = Mt - band * kBand < kBand ? Mt - band * kBand : kBand;
+template <int BAND> __device__ inline void tile_at(int t, int Mt, int Nt, int& tm, int& tn) {
+  const int band = t / (BAND * Nt), in_band = t - band * BAND * Nt;
+  const int rows = Mt - band * BAND < BAND ? Mt - band * BAND : BAND;
   tn = in_band / rows;
-  tm = band * kBand + in_band - tn * rows;
+  tm = band * BAND + in_band - tn * rows;
 }
-__device__ inline bool dealt_tile(int bid, int Mt, int Nt, int& tm, int& tn) {
+template <int BAND> __device__ inline bool dealt_tile(int bid, int Mt, int Nt, int& tm, int& tn) {
   const int tiles = Mt * Nt, whole = tiles / kRound * kRound;
   const int xcd = bid % NXCD, local = bid / NXCD;
   int t;
@@ -126,7 +106,7 @@ __device__ inline bool dealt_tile(int bid, int Mt, int Nt, int& tm, int& tn) {
     t = whole + xcd * per + k;
     if (k >= per || t >= tiles) return false;
   }
-  tile_at(t, Mt, Nt, tm, tn);
+  tile_at<BAND>(t, Mt, Nt, tm, tn);
   return true;
 }
 
@@ -157,8 +137,8 @@ __host__ __device__ inline int dh_split(int tail_tiles, int panels, int max_item
 // sliced and the reduction is left out.
 inline int dh_most_split(int panels) { return panels / kMinSlicePanels < 2 ? 1 : (panels / kMinSlicePanels < 64 ? panels / kMinSlicePanels : 64); }
 inline int dh_most_items(int tiles, int panels, int max_items) {
-  const int n = (tiles < kRound ? tiles : kRound - 1) * dh_most_split(panels);
-  return n < max_items ? n : max_items;
+  const int rest = tiles < kRound ? tiles : kRound - 1, n = rest * dh_most_split(panels);
+  return n < max_items ? n : max_items > rest ? max_items : rest;
 }
 // panels per slice: an even number (the K loop's body is two panels)
 __host__ __device__ inline int slice_panels(int panels, int split) { return ((panels + split - 1) / split + 1) & ~1; }
@@ -167,6 +147,39 @@ __host__ __device__ inline int slice_panels(int panels, int split) { return ((pa
 __device__ inline int slices_in_use(int panels, int split) {
   const int per = slice_panels(panels, split);
   return panels > 0 ? (panels + per - 1) / per : 1;
+}
+// dW on 384 x 256 tiles: the same for its last round.  The contraction is as long as the pass (16 panels are 1024 rows), so an
+// item's share beyond its panels counts in panels: about 6 for its prologue and its store, 12 for the launch that adds the slices.
+__host__ __device__ inline int dw_split(int tail_tiles, int panels, int max_items) {
+  int best = 1, end = panels + 6;
+  for (int s = 2; s <= 64 && s * 8 <= panels && s * tail_tiles <= max_items; ++s) {
+    const int e = (tail_tiles * s + kRound - 1) / kRound * ((panels + s - 1) / s + 6) + 12;
+    if (e < end) { end = e; best = s; }
+  }
+  return best;
+}
+struct DhSplit { __device__ int operator()(int tiles, int panels, int max_items) const { return dh_split(tiles, panels, max_items); } };
+struct DwSplit { __device__ int operator()(int tiles, int panels, int max_items) const { return dw_split(tiles, panels, max_items); } };
+// Workgroup -> tile or slice of one, for a launch whose last round may be cut.  Returns the item's number (its place in the
+// scratch area) for a slice, panels k_first .. k_first + nk - 1 of its tile; -1 for a whole tile; -2 for nothing.
+template <int BAND, class Split>
+__device__ inline int split_tile(int bid, int Mt, int Nt, int panels, int max_items, Split split_of, int& tm, int& tn, int& k_first, int& nk) {
+  const int tiles = Mt * Nt, whole = tiles / kRound * kRound, rest = tiles - whole;
+  if (bid >= whole && rest > 0) {
+    const int split = split_of(rest, panels, max_items);
+    if (split > 1) {
+      // an XCD takes consecutive items, i.e. mostly tiles of one slice
+      const int items = rest * split, per = (items + NXCD - 1) / NXCD;
+      const int e = bid - whole, item = e % NXCD * per + e / NXCD;
+      if (e / NXCD >= per || item >= items) return -2;
+      const int slice = item / rest, per_slice = slice_panels(panels, split);
+      tile_at<BAND>(whole + item - slice * rest, Mt, Nt, tm, tn);
+      k_first = slice * per_slice;
+      nk = panels - k_first < per_slice ? panels - k_first : per_slice;
+      return item;
+    }
+  }
+  return dealt_tile<BAND>(bid, Mt, Nt, tm, tn) ? -1 : -2;
 }
 // panels of the dW contraction: the pass's valid rows, rounded up to panel pairs
 __device__ inline int dw_panels(int nvalid, int chunk_rows) {
@@ -193,15 +206,14 @@ __host__ __device__ inline int num_blocks(int Mt, int Nt, int sup_m, int sup_n) 
   int s = ((Mt + sup_m - 1) / sup_m) * ((Nt + sup_n - 1) / sup_n);
   return (s + NXCD - 1) / NXCD * NXCD * (sup_m * sup_n);
 }
-__device__ inline bool tile_coords(int bid, int Mt, int Nt, int sup_m, int sup_n, int& tm, int& tn, int& sm, int& sn) {
+__device__ inline bool tile_coords(int bid, int Mt, int Nt, int sup_m, int sup_n, int& tm, int& tn) {
   const int sNt = (Nt + sup_n - 1) / sup_n, sMt = (Mt + sup_m - 1) / sup_m;
   const int xcd = bid % NXCD, local = bid / NXCD;
   const int q = local / (sup_m * sup_n), within = local % (sup_m * sup_n);
   const int s = q * NXCD + xcd;
   if (s >= sMt * sNt) return false;
-  sm = within % sup_m; sn = within / sup_m;
-  tm = (s / sNt) * sup_m + sm;
-  tn = (s % sNt) * sup_n + sn;
+  tm = (s / sNt) * sup_m + within % sup_m;
+  tn = (s % sNt) * sup_n + within / sup_m;
   return tm < Mt && tn < Nt;
 }
 
@@ -213,12 +225,12 @@ __device__ inline float exp2_fast(float x) { return __builtin_amdgcn_exp2f(x); }
 
 // The MFMA is issued through inline assembly with the accumulator tied in place in an
 // accumulation register: left to the register allocator, a few of the 64 accumulator tuples
-// (which fill the accumulation file completely) end up rotating through copies every iteration.
+// that fill the accumulation file completely end up rotating through copies every iteration.
 // The K loop issues the two 32-wide K steps of an accumulator back to back: the second MFMA reads
 // as SrcC the register tuple the first one writes as vDst.  That dependent pair with identical
 // SrcC / vDst is the case the hardware interlocks by itself (no software wait states required);
 // no other instruction touches an accumulator inside the loop.  The first ordinary reads after
-// the K loop are fenced by drain_mfma() below.
+// the K loop come behind wait states (the compiler's hazard checker does not look into inline assembly).
 __device__ __forceinline__ void mfma16(f32x4& c, const bf16x8& a, const bf16x8& b) {
   asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
 }
@@ -227,11 +239,16 @@ __device__ __forceinline__ void mfma16(f32x4& c, const bf16x8& a, const bf16x8& 
 __device__ __forceinline__ void mfma16_then_wait(f32x4& c, const bf16x8& a, const bf16x8& b) {
   asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0\n\ts_nop 15\n\ts_nop 3" : "+a"(c) : "v"(a), "v"(b));
 }
-// Wait states between the last MFMAs of the K loop and the first ordinary read of their
-// results (the hazard checker of the compiler does not look into inline assembly).
-__device__ __forceinline__ void drain_mfma(f32x4 (&r)[8]) {
-  asm volatile("s_nop 15\n\ts_nop 15"
-               : "+a"(r[0]), "+a"(r[1]), "+a"(r[2]), "+a"(r[3]), "+a"(r[4]), "+a"(r[5]), "+a"(r[6]), "+a"(r[7]));
+// The same with the accumulator in an ordinary register: the last third of a whole tile's, which do not fit the accumulation file.
+__device__ __forceinline__ void mfma16_v(f32x4& c, const bf16x8& a, const bf16x8& b) {
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
+}
+// An accumulation register, read where its value is used: left to the compiler, the copies out of the accumulation
+// registers are hoisted to the top of the epilogue and fill the register file.
+__device__ __forceinline__ float acc_now(const float& x) {
+  float z;
+  asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(z) : "a"(x));
+  return z;
 }
 
 // Lane number as the code after the K loops takes it: recomputed there from the execution mask, so
@@ -245,24 +262,23 @@ __device__ __forceinline__ int lane_now() {
   return l;
 }
 
-// Forward epilogue of a wave's 128 x (16 NJ) sub-tile: vocabulary ids from m0 + 128 wm, token columns from
-// n0 + 16 NJ wn, partial sums with index pidx; target_logit(j): that of the lane's token in column block j; accumulator element (i, j, e) of a lane is vocabulary
-// id vrow(i, e), token column ncol_base + 16 j.
-template <int NJ, class Zt>
-__device__ __forceinline__ void forward_epilogue(const Params& p, f32x4 (&acc)[8][NJ], Zt target_logit, int m0,
-                                                 int n0, int pidx, int wm, int wn, int N) {
+// Forward epilogue of a wave's 128 x (16 NJ) sub-tile: vocabulary ids from v0, token columns from n0, partial sums with
+// index pidx; target_logit(j): that of the lane's token in column block j; accumulator element (i, j, e) of a lane is
+// vocabulary id vrow(i, e), token column ncol_base + 16 j.
+template <int NJ, class Acc, class Zt>
+__device__ __forceinline__ void forward_epilogue(const Params& p, Acc read_acc, Zt target_logit, int v0, int n0, int pidx, int N) {
   const int lane = lane_now(), frow = lane & 15, fq = lane >> 4;
-  const int ncol_base = n0 + wn * (16 * NJ) + frow;
+  const int ncol_base = n0 + frow;
       // rows = vocabulary ids, cols = token rows of the chunk.  Exponentials are taken relative to
       // the row's offset c2 = z_target * log2(e) + margin (log2 domain), one offset for all
       // vocabulary tiles of a row: e = 2^(z log2(e) - c2), clamped so that neither e nor any sum of
       // it can overflow.  The sums over the wave's 128 vocabulary ids are this tile's partials; e
       // itself, as bf16, is the backward pass's operand (dz = (-g / S)(e - S onehot)).
       constexpr float LOG2E = 1.4426950408889634f;
-      const bool full = (m0 + wm * 128 + 128 <= p.V);
+      const bool full = (v0 + 128 <= p.V);
           // vocabulary id of accumulator (i, e) of this lane
       auto vrow = [&](int i, int e) {
-        return m0 + wm * 128 + 32 * (i >> 1) + 8 * fq + 4 * (i & 1) + e;
+        return v0 + 32 * (i >> 1) + 8 * fq + 4 * (i & 1) + e;
       };
       // The body is instantiated for full / ragged vocabulary tiles and with / without the entropy
       // sums: both conditions are uniform, and left as run-time selects they cost four more
@@ -276,7 +292,7 @@ __device__ __forceinline__ void forward_epilogue(const Params& p, f32x4 (&acc)[8
           const bool live = n < N;
           const float zt = target_logit(j);
           const float c2 = live ? fmaf(zt, LOG2E, kStashMargin2) : 0.f;
-          uint16_t* erow = p.estash + (int64_t)n * p.lde + m0 + wm * 128 + 8 * fq;
+          uint16_t* erow = p.estash + (int64_t)n * p.lde + v0 + 8 * fq;
           float s = 0.f, t = 0.f;
   #pragma unroll
           for (int q = 0; q < 4; ++q) {
@@ -286,10 +302,7 @@ __device__ __forceinline__ void forward_epilogue(const Params& p, f32x4 (&acc)[8
             for (int u = 0; u < 2; ++u)
   #pragma unroll
               for (int e = 0; e < 4; ++e) {
-                // (read where it is used: left to the compiler, the copies out of the accumulation
-                // registers are hoisted to the top of the epilogue and fill the register file)
-                float z;
-                asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(z) : "a"(acc[2 * q + u][j][e]));
+                const float z = read_acc(2 * q + u, j, e);
                 float w = exp2_fast(fminf(fmaf(z, LOG2E, -c2), kStashClamp2));
                 if (!kFull) w = vrow(2 * q + u, e) < p.V ? w : 0.f;
                 s += w;
@@ -328,6 +341,540 @@ __device__ __forceinline__ void forward_epilogue(const Params& p, f32x4 (&acc)[8
 }
 
 // ---------------------------------------------------------------------------------------------
+// The tile.  Per wave 8 blocks of 16 on the resident side (256 of the tile), NJ on the ring side (32 NJ: 384, 256 or 128).  The forward has
+// the vocabulary on the resident side and the tokens in the ring, dH the hidden columns and the tokens, dW the hidden columns and
+// the vocabulary: the ring side is the one that is cut into tiles of other sizes.
+// ---------------------------------------------------------------------------------------------
+constexpr int RES = 256;                              // resident side of a tile
+constexpr int kWide = 12;                             // ring blocks per wave of a whole tile
+constexpr int RING = 32 * kWide;                      // ring side of a whole tile: 384
+template <int NJ> constexpr int wave_bytes() { return (8 + NJ) * 1024; }     // of a slot: what one wave loads
+template <int NJ> constexpr int tile_slots() { return NJ == 4 ? 3 : 2; }
+template <int NJ> constexpr int tile_lds() { return tile_slots<NJ>() * 4 * wave_bytes<NJ>(); }
+constexpr int DHSTAGE_LD = 128 + 8;                   // bf16 elements per row of the dH epilogue's staging area
+static_assert(tile_lds<12>() == 160 * 1024 && tile_lds<8>() <= tile_lds<12>() && tile_lds<4>() <= tile_lds<12>(), "all of a compute unit's LDS");
+static_assert(4 * 96 * DHSTAGE_LD * 2 <= tile_lds<12>(), "half a wave's rows, four waves");
+
+// The kernel's arguments, read again where they are used: kept alive across the K loop they cost scalar spills.
+__device__ __forceinline__ const Params& args_now() {
+  typedef const __attribute__((address_space(4))) Params* KernArg;
+  KernArg arg = (KernArg)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(arg));
+  return *(const Params*)arg;
+}
+
+// Ring block i of half wr of a K-major ring panel (dW): its first row within the tile.  The first eight of a half are one 256-byte group
+// of a panel row, and the swizzle stays within such groups.
+__device__ __forceinline__ int ring_kmajor_row(int i, int wr) { return i < 8 ? wr * 128 + i * 16 : 256 + wr * 64 + (i - 8) * 16; }
+
+// dH epilogue of a wave's (16 NJ) x 128 sub-tile: token rows from m0, hidden columns from n0 (from tm0, tn0 within the tile), M valid rows.
+// Rows of the stash times W are the rows' dz W up to their scale -g / S, applied here.
+template <int NJ, class Acc>
+__device__ __forceinline__ void dh_epilogue(const Params& p, unsigned char* smem, Acc read_acc, int wave, int m0, int tm0, int n0, int tn0,
+                                            int M, float* tail_out) {
+  const int lane = lane_now(), frow = lane & 15, fq = lane >> 4;
+  if (tail_out != nullptr) {
+    // a slice of the contraction: the accumulators as they are, rows of 256
+#pragma unroll
+    for (int i = 0; i < NJ; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        float* row = tail_out + (tm0 + i * 16 + 4 * fq + e) * RES + tn0 + frow;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) row[j * 16] = read_acc(i, j, e);
+      }
+    return;
+  }
+  if (p.dh_f32) {
+#pragma unroll
+    for (int i = 0; i < NJ; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int m = m0 + i * 16 + 4 * fq + e;
+        if (m < M) {
+          const float sc = p.row_scale[m];
+          float* row = reinterpret_cast<float*>(p.dH) + (int64_t)p.row_index[m] * p.d;
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            const int n = n0 + j * 16 + frow;
+            const float x = read_acc(i, j, e);
+            if (n < p.d) row[n] = sc * x;
+          }
+        }
+      }
+    return;
+  }
+  // The wave's rows as bf16 through its own part of LDS, half of them at a time, then 16 lanes store 256 bytes of a row.
+  __syncthreads();                                    // (the panels are not read any more, and no wave's loads are outstanding)
+  __bf16* const st = reinterpret_cast<__bf16*>(smem) + wave * (8 * NJ * DHSTAGE_LD);
+#pragma unroll
+  for (int half = 0; half < 2; ++half) {
+#pragma unroll
+    for (int i = 0; i < NJ / 2; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int r = i * 16 + 4 * fq + e, m = m0 + half * (8 * NJ) + r;
+        const float sc = p.row_scale[m < M ? m : M - 1];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) st[r * DHSTAGE_LD + j * 16 + frow] = (__bf16)(sc * read_acc(half * (NJ / 2) + i, j, e));
+      }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll 4
+    for (int k = 0; k < 2 * NJ; ++k) {
+      const int r = k * 4 + fq, m = m0 + half * (8 * NJ) + r, n = n0 + frow * 8;
+      if (m < M && n < p.d) {
+        const u32x4 v = *reinterpret_cast<const u32x4*>(&st[r * DHSTAGE_LD + frow * 8]);
+        *reinterpret_cast<u32x4*>(reinterpret_cast<uint16_t*>(p.dH) + (int64_t)p.row_index[m] * p.d + n) = v;
+      }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  }
+}
+
+// dW epilogue: vocabulary rows from m0 up to v_end on the ring side, hidden columns from n0; fp32 accumulate into dW.  With the MFMA's operands
+// swapped a lane holds four consecutive columns of a row, so that dW is read and written 16 bytes at a time (d is a multiple
+// of 8; with 4-byte accesses the launch took 1128 instead of 1023 us for 512 rows, V = 151936, d = 4096, and 127 instead
+// of 109 for V = 32000, d = 2048).  The old values of a 16-row band are fetched as a batch before any store, so
+// that their latencies overlap.  A K slice of a tail tile stores its partial tile as it is, rows of 256, to the scratch
+// area instead (dw_tail_reduce adds the slices in their order): the same code with the tile's own origin, row stride and bounds.
+template <int NJ>
+__device__ __forceinline__ void dw_epilogue(const Params& p, f32x4 (&acc)[NJ][8], int wr, int m0, int n0, int res0, int v_last, float* tail_out) {
+  const int lane = lane_now(), frow = lane & 15, fq = lane >> 4;
+  const bool tail = tail_out != nullptr;
+  float* const dst = tail ? tail_out : p.dW;
+  const int64_t ld = tail ? RES : p.d;
+  const int v_org = tail ? m0 : 0, n_org = tail ? res0 : 0;
+  const int v_end = tail ? m0 + 32 * NJ : v_last, n_end = tail ? res0 + RES : p.d;
+  const bool overwrite = tail || p.overwrite;
+  const int nbase = n0 + 4 * fq;
+#pragma unroll
+  for (int i = 0; i < NJ; ++i) {
+    const int v = m0 + ring_kmajor_row(i, wr) + frow;
+    float* const row = dst + (int64_t)((v < v_end ? v : v_end - 1) - v_org) * ld - n_org;
+    f32x4 old[8];
+    if (!overwrite) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int n = nbase + j * 16;
+        old[j] = *reinterpret_cast<const f32x4_any*>(row + (n < n_end ? n : n_end - 4));
+      }
+    }
+    if (v < v_end) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int n = nbase + j * 16;
+        f32x4 x = acc[i][j];
+        if (!overwrite) x = old[j] + x;
+        if (n < n_end) *reinterpret_cast<f32x4_any*>(row + n) = x;
+      }
+    }
+  }
+}
+
+// one direct load of 1 KB to LDS address slot + lds, from byte voff + soff behind the descriptor's base
+__device__ __forceinline__ void load_lds16(uint32_t voff, uint32_t soff, const u32x4& desc, uint32_t slot, uint32_t lds) {
+  uint32_t off;
+  asm volatile("s_add_u32 m0, %4, %5\n\tv_add_u32 %0, %3, %1\n\tbuffer_load_dwordx4 %0, %2, 0 offen lds"
+               : "=&v"(off) : "v"(voff), "s"(desc), "s"(soff), "s"(slot), "s"(lds) : "memory", "scc");
+}
+
+// One tile's product and epilogue: ring rows ring0 .. ring_end - 1 (at most 32 NJ) times resident block res_tile, panels
+// k_first .. k_first + nk - 1.
+// A panel is 16 NJ products in duos: two ring blocks times the eight resident ones, the two 32-wide K steps of an accumulator back to
+// back (keeping an accumulator for two products costs about 5 % less energy than touching another one each time).  Registers:
+// the resident fragments of a panel in one set, each pair read again for the next panel behind its last product in the
+// panel's last duo and needed 32 products later; the ring's in two sets, a duo ahead.  384 + 64 + 32 of 512 registers.
+// Side work stands between products, one piece behind each: a wave issues in order and the matrix pipe takes a product
+// every 16 cycles, so what fits the 12 cycles left over is free, and a block of it idles the pipe (the advance to the next panel as
+// one block behind the barrier cost 1.5 - 2 %).
+//   barrier (fourth product of the last duo): the next panel has landed, and every wave's reads of this one are done
+//   behind it, in the last duo: ring blocks 0 and 1 and the resident blocks of the next panel
+//   from there on, every sixth product: the 8 + NJ loads of the panel behind the next, into the slot just released (15360 rows,
+//   d = 4096: every third 1 % slower, every eighth 0.5 %: four waves issue together and a load takes the load path 23 cycles)
+//   other duos: the next duo's ring blocks; then, in four pieces, the loads' advance by a panel
+// Loads go through buffer descriptors that end with the operand's last row and are emptied behind the last panel: edges need
+// no clamped addresses, and nothing is fetched twice at a tile's end.
+template <int MODE, int NJ>
+__device__ __forceinline__ void tile_product(unsigned char* smem, int ring_tile, int res_tile, int ring0, int ring_end,
+                                             int k_first, int nk, float* tail_out) {
+  constexpr bool RES_KMAJOR = MODE == MODE_DH, RING_KMAJOR = MODE == MODE_DW;
+  constexpr int ND = NJ / 2, kLoads = 8 + NJ, kSlots = tile_slots<NJ>(), kWave = wave_bytes<NJ>(), kSlot = 4 * kWave;
+  // Places in a panel's sequence of 16 NJ products: the barrier behind which the next panel may be read and this one's slot
+  // filled again, and from there the slot's loads.
+  constexpr int kPanel = 16 * NJ, kBarrier = kPanel - 32 + 3, kFirst = 2, kGap = NJ == 4 ? 3 : 6;
+  constexpr int kEarlyLoads = (kPanel - 1 - kBarrier - kFirst) / kGap + 1;     // those of the next slot that come before the panel's end
+  static_assert(kFirst + kGap * (kLoads - 1) < kPanel - 14, "a slot's loads are issued before the next barrier");
+  const Params& p = args_now();
+  // (wave-uniform all of them; some come out of integer divisions, which run on the vector unit)
+  ring_tile = __builtin_amdgcn_readfirstlane(ring_tile); res_tile = __builtin_amdgcn_readfirstlane(res_tile);
+  ring0 = __builtin_amdgcn_readfirstlane(ring0); ring_end = __builtin_amdgcn_readfirstlane(ring_end);
+  k_first = __builtin_amdgcn_readfirstlane(k_first); nk = __builtin_amdgcn_readfirstlane(nk);
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wr = wave >> 1, ws = wave & 1, frow = lane & 15, fq = lane >> 4;
+  const int res0 = res_tile * RES;
+  const uint32_t lds_wave = __builtin_amdgcn_readfirstlane(
+      (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem + wave * kWave);
+
+  // ---- direct loads
+  const uint16_t* const res_ptr = MODE == MODE_FWD ? p.A : p.B;
+  const uint16_t* const ring_ptr = MODE == MODE_FWD ? p.B : p.A;
+  const int64_t res_ld = MODE == MODE_FWD ? p.lda : p.ldb, ring_ld = MODE == MODE_FWD ? p.ldb : p.lda;
+  const uint32_t res_ld2 = (uint32_t)(res_ld * 2), ring_ld2 = (uint32_t)(ring_ld * 2);
+  const int rot_res = 4 * (ring_tile & 1);
+  const int rot_ring = !RING_KMAJOR ? 2 * (res_tile & 7) % NJ : (NJ == 12 ? 6 : 4) * (res_tile & 1);
+  constexpr int kResKinds = MODE == MODE_DW ? 2 : 4, kRingKinds = !RING_KMAJOR ? 2 : (NJ == 12 ? 6 : 4);
+  uint32_t vres[kResKinds], vring[kRingKinds];
+  auto chunk16 = [&](int row) { return (uint32_t)(((lane & 7) ^ ((row >> 1) & 7)) << 4); };
+#pragma unroll
+  for (int q = 0; q < kResKinds; ++q) {
+    const int b = ((RES_KMAJOR ? (q & 1) + 4 * (q >> 1) : q) + rot_res) & 7;
+    if (RES_KMAJOR) {
+      vres[q] = (uint32_t)(lane >> 5) * res_ld2 + (((lane & 31) ^ (kswz(16 * wave + 2 * b + (lane >> 5)) << 1)) << 4);
+    } else {
+      const int r = b * 8 + (lane >> 3);
+      vres[q] = (uint32_t)(lane >> 3) * res_ld2 + (MODE == MODE_FWD ? (uint32_t)(((lane & 7) ^ (((r >> 1) & 1) | (((r >> 3) & 3) << 1))) << 4) : chunk16(r));
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < kRingKinds; ++q) {
+    if (!RING_KMAJOR) {
+      vring[q] = (uint32_t)(lane >> 3) * ring_ld2 + chunk16((q + rot_ring) * 8 + (lane >> 3));
+    } else {
+      const int b = ((NJ == 12 ? q % 3 + 6 * (q / 3) : (q & 1) + 4 * (q >> 1)) + rot_ring) % NJ;
+      const int c = NJ == 12 ? 64 * (b % 3) + lane : lane, r = c / (4 * NJ);
+      const int k = (NJ == 12 ? 4 * (b / 3) : 2 * b) + r;
+      const int col = (c % (4 * NJ)) ^ (kswz(16 * wave + k) << 1);
+      // (columns from V on are not fetched: their products are not stored)
+      vring[q] = ring0 + col * 8 < p.V ? (uint32_t)r * ring_ld2 + (col << 4) : 0x80000000u;
+    }
+  }
+  uint32_t from[kLoads], to[kLoads];
+#pragma unroll
+  for (int l = 0; l < kLoads; ++l) {
+    const int b = l < 8 ? (l + rot_res) & 7 : (l - 8 + rot_ring) % NJ;
+    const uint32_t rows = l < 8 ? (RES_KMAJOR ? 2 * b : 8 * b) : (!RING_KMAJOR ? 8 * b : (NJ == 12 ? 4 * (b / 3) : 2 * b));
+    from[l] = __builtin_amdgcn_readfirstlane(rows * (l < 8 ? res_ld2 : ring_ld2));
+    to[l] = __builtin_amdgcn_readfirstlane((l < 8 ? b : b + 8) * 1024);
+  }
+  auto kind = [](int l) {
+    if (l < 8) return MODE == MODE_FWD ? l & 3 : MODE == MODE_DW ? l & 1 : (l & 1) | ((l >> 2) << 1);
+    l -= 8;
+    return !RING_KMAJOR ? l & 1 : NJ == 12 ? l % 3 + 3 * (l / 6) : (l & 1) | ((l >> 2) << 1);
+  };
+  u32x4 dres, dring;
+  auto set = [](u32x4& d, const uint16_t* at, uint32_t bytes) {
+    const uint64_t a = (uint64_t)at;
+    d[0] = __builtin_amdgcn_readfirstlane((uint32_t)a); d[1] = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
+    d[2] = __builtin_amdgcn_readfirstlane(bytes); d[3] = 0x00020000u;
+  };
+  auto move = [](u32x4& d, int64_t by) {
+    const uint64_t a = (((uint64_t)d[1] << 32) | d[0]) + (uint64_t)by;
+    d[0] = (uint32_t)a; d[1] = (uint32_t)(a >> 32);
+  };
+  auto rows_of = [&](u32x4& d, const uint16_t* base, int64_t ld, int first, int rows, int end) {
+    const int n = end - first < 0 ? 0 : (end - first < rows ? end - first : rows);
+    set(d, base + (int64_t)(n > 0 ? first : 0) * ld + (int64_t)k_first * BK, (uint32_t)n * (uint32_t)(ld * 2));
+  };
+  int w_left = 0;                                     // DH: rows of W from the wave's first one on
+  auto w_bytes = [&]() {
+    const int b = (w_left < 16 ? w_left : 16) * (int)res_ld2 - res0 * 2;
+    return (uint32_t)(b > 0 ? b : 0);
+  };
+  if (RES_KMAJOR) {
+    const int first = k_first * BK + wave * 16;
+    w_left = p.V - first;
+    set(dres, res_ptr + (int64_t)first * res_ld + res0, w_bytes());
+  } else {
+    rows_of(dres, res_ptr, res_ld, res0 + wave * 64, 64, MODE == MODE_FWD ? p.M : p.N);
+  }
+  if (RING_KMAJOR) set(dring, ring_ptr + ((int64_t)k_first * BK + wave * 16) * ring_ld + ring0, 16 * ring_ld2);
+  else rows_of(dring, ring_ptr, ring_ld, ring0 + wave * (NJ * 8), NJ * 8, ring_end);
+  uint32_t slot = lds_wave;                           // of the panel being loaded
+  int loading = 0;
+  auto load = [&](int l) {
+    if (l < 8) load_lds16(vres[kind(l)], from[l], dres, slot, to[l]); else load_lds16(vring[kind(l)], from[l], dring, slot, to[l]);
+  };
+  // to the next panel: the loads' slot and operands, in four pieces
+  auto next_load_panel = [&](int piece) {
+    if (piece == 0) { ++loading; slot = slot == lds_wave + (kSlots - 1) * kSlot ? lds_wave : slot + kSlot; }
+    if (piece == 1) {
+      if (RES_KMAJOR) { move(dres, (int64_t)res_ld2 * BK); w_left -= BK; }
+      else move(dres, BK * 2 + (MODE == MODE_FWD && loading == p.a_tail_panel ? p.a_tail_delta : 0));
+    }
+    if (piece == 2) move(dring, RING_KMAJOR ? (int64_t)ring_ld2 * BK : BK * 2);
+    if (piece == 3) {
+      if (RES_KMAJOR) dres[2] = w_bytes();
+      if (loading >= nk) { dres[2] = 0; dring[2] = 0; }   // behind the end nothing is fetched
+    }
+  };
+
+  // ---- fragment reads
+  int res_off[2], ring_off[2];                        // row-major: by K step; K-major: [0], and for ring blocks from 8 on [1]
+  const int kr = 8 * fq + (frow >> 2);
+  const int tr_col = ((frow & 2) << 3) + ((frow & 1) << 3);
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks) {
+    const int chunk = (ks << 2) | fq;
+    if (RES_KMAJOR) res_off[ks] = (kr >> 4) * kWave + (kr & 15) * 512 + (kswz(kr) << 5) + tr_col + ws * 256;
+    else if (MODE == MODE_FWD) res_off[ks] = ws * 2 * kWave + (8 * (frow >> 2) + (frow & 3)) * 128 + ((chunk ^ (((frow >> 1) & 1) | ((frow >> 2) << 1))) << 4);
+    else res_off[ks] = ws * 2 * kWave + frow * 128 + ((chunk ^ ((frow >> 1) & 7)) << 4);
+    if (RING_KMAJOR) ring_off[ks] = (kr >> 4) * kWave + 8192 + (kr & 15) * (NJ * 64) + tr_col + (ks == 0 ? wr * 256 + (kswz(kr) << 5) : 512 + ((kswz(kr) ^ (wr * 4)) << 5));
+    else ring_off[ks] = wr * 2 * kWave + 8192 + frow * 128 + ((chunk ^ ((frow >> 1) & 7)) << 4);
+  }
+  auto read_tr = [&](int off, int four_rows) -> bf16x8 {
+    typedef short v4i16 __attribute__((ext_vector_type(4)));
+    typedef __attribute__((address_space(3))) v4i16* lds_v4i16;
+    unsigned char* q = smem + off;
+    const v4i16 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16)q);
+    const v4i16 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16)(q + four_rows));
+    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+  };
+  auto read_res = [&](int i, int ks) -> bf16x8 {
+    if (RES_KMAJOR) return read_tr((res_off[0] ^ (i << 5)) + ks * 2 * kWave, 2048);
+    const int at = (i >> 2) * kWave + (MODE == MODE_FWD ? ((i >> 1) & 1) * 4096 + (i & 1) * 512 : (i & 3) * 2048);
+    return *reinterpret_cast<const bf16x8*>(smem + res_off[ks] + at);
+  };
+  auto read_ring = [&](int j, int ks) -> bf16x8 {
+    if (RING_KMAJOR) return read_tr((j < 8 ? ring_off[0] ^ (j << 5) : ring_off[1] ^ ((j - 8) << 5)) + ks * 2 * kWave, NJ * 256);
+    return *reinterpret_cast<const bf16x8*>(smem + ring_off[ks] + j / ND * kWave + j % ND * 2048);
+  };
+  int read_slot = 0;                                  // the reads' slot: the ring's, and behind it the resident side's
+  auto slot_step = [&]() { return read_slot == kSlots - 1 ? -(kSlots - 1) * kSlot : kSlot; };
+  auto next_ring_panel = [&]() { ring_off[0] += slot_step(); if (!RING_KMAJOR || NJ > 8) ring_off[1] += slot_step(); };
+  auto next_res_panel = [&]() {
+    res_off[0] += slot_step();
+    if (!RES_KMAJOR) res_off[1] += slot_step();
+    read_slot = read_slot == kSlots - 1 ? 0 : read_slot + 1;
+  };
+
+  // ---- K loop
+  f32x4 acc[NJ][8];
+#pragma unroll
+  for (int j = 0; j < NJ; ++j)
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[j][i][e] = 0.f;
+  bf16x8 res[8][2], ring[2][2][2];
+#pragma unroll
+  for (int s = 0; s < kSlots - 1; ++s) {
+#pragma unroll
+    for (int l = 0; l < kLoads; ++l) load(l);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) next_load_panel(q);
+  }
+#pragma unroll
+  for (int l = 0; l < kEarlyLoads; ++l) load(l);
+  __builtin_amdgcn_s_waitcnt(waitcnt_vm((kSlots - 2) * kLoads + kEarlyLoads));
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < 20; ++q) {                      // (in the order of the loop, which is what its waits go by)
+    if (q < 4) ring[0][q >> 1][q & 1] = read_ring(q >> 1, q & 1); else res[(q - 4) >> 1][q & 1] = read_res((q - 4) >> 1, q & 1);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  int kt = 0;
+  do {                                                // (at least one panel, as every caller has)
+#pragma unroll
+    for (int D = 0; D < ND; ++D) {
+#pragma unroll
+      for (int m = 0; m < 32; ++m) {
+        const int i = m >> 2, jj = (m >> 1) & 1, ks = m & 1, j = 2 * D + jj, at = 32 * D + m;
+        const bf16x8 &a = MODE == MODE_DH ? ring[D & 1][jj][ks] : res[i][ks], &b = MODE == MODE_DH ? res[i][ks] : ring[D & 1][jj][ks];
+        if (j < 8) mfma16(acc[j][i], a, b); else mfma16_v(acc[j][i], a, b);
+        const int since = at >= kBarrier ? at - kBarrier : at + kPanel - kBarrier;    // products since the last barrier
+        if (since == 0) {
+          __builtin_amdgcn_s_waitcnt(waitcnt_vm((kSlots - 2) * kLoads));
+          __syncthreads();
+        }
+        if (D < ND - 1) {
+          if (m < 4) ring[(D + 1) & 1][m >> 1][m & 1] = read_ring(2 * (D + 1) + (m >> 1), m & 1);
+        } else {
+          if (m >= 4 && m < 8) ring[0][(m - 4) >> 1][m & 1] = read_ring((m - 4) >> 1, m & 1);
+          // a resident block is read again behind its last product
+          if (m >= 8 && m < 12) res[(m - 8) >> 1][m & 1] = read_res((m - 8) >> 1, m & 1);
+          if (m >= 12 && m < 30 && (m & 2) == 0) res[(m - 4) >> 2][m & 1] = read_res((m - 4) >> 2, m & 1);
+          if (m == 31) { res[7][0] = read_res(7, 0); res[7][1] = read_res(7, 1); }
+        }
+        if (since >= kFirst && (since - kFirst) % kGap == 0 && (since - kFirst) / kGap < kLoads) load((since - kFirst) / kGap);
+        if (since >= kPanel - 14 && since < kPanel - 2 && (since - kPanel + 14) % 3 == 0) next_load_panel((since - kPanel + 14) / 3);
+        if (at == kPanel - 64 + 6) next_ring_panel();   // (behind the panel's last ring read)
+        if (since == kPanel - 1) next_res_panel();
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  } while (++kt < nk);
+  __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));          // no direct load may outlive the wave
+  // (the wait states between the last products and the first ordinary read of them)
+  asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+#pragma unroll
+  for (int j = 8; j < NJ; ++j)
+#pragma unroll
+    for (int i = 0; i < 8; ++i) asm volatile("" : "+v"(acc[j][i]));
+  auto read_acc = [&](int j, int i, int e) { if (j < 8) return acc_now(acc[j][i][e]); return acc[j][i][e]; };
+
+  if (MODE == MODE_FWD) {
+    const Params& q = args_now();
+    const int n0 = ring0 + wr * (NJ * 16), f = lane_now() & 15;
+    float zt[NJ];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) { const int n = n0 + j * 16 + f; zt[j] = q.zt[n < ring_end ? n : ring_end - 1]; }
+    forward_epilogue<NJ>(q, [&](int i, int j, int e) { return read_acc(j, i, e); }, [&](int j) { return zt[j]; }, res0 + ws * 128, n0, res_tile * 2 + ws, ring_end);
+  }
+  if (MODE == MODE_DH) dh_epilogue<NJ>(args_now(), smem, read_acc, wave, ring0 + wr * (NJ * 16), wr * (NJ * 16), res0 + ws * 128, ws * 128, ring_end, tail_out);
+  if (MODE == MODE_DW) dw_epilogue<NJ>(args_now(), acc, wr, ring0, res0 + ws * 128, res0, ring_end, tail_out);
+}
+
+// ---------------------------------------------------------------------------------------------
+// Forward, 256 x 256 tiles: where whole rounds of them end earlier than tiles of 384 columns (see cut_forward).  Waves 2 x 2, each
+// 128 x 128; the token side's fragments of a panel stay in registers, in two sets, and those of W go through a ring of four pairs; two
+// panels of LDS.  (tile_product with 8 ring blocks takes 2 - 3 % longer here: its resident fragments are all read again
+// within the last 28 products of a panel.)
+//   group 0      : W fragments of row block 3 (this panel); the last loads of the next panel's slot
+//   groups 1 - 4 : W fragments of row blocks 4 - 7
+//   group 5      : wait for this thread's part of panel kt+1, barrier; next panel's W block 0, token blocks 0 - 2; the first
+//                  loads of panel kt+2 into this panel's slot
+//   group 6      : next W block 1, token blocks 3 - 5, loads
+//   group 7      : next W block 2, token blocks 6 - 7, loads
+// ---------------------------------------------------------------------------------------------
+constexpr int TILE_BYTES = RES * BK * 2;               // one panel of 256 rows
+constexpr int STAGE_BYTES = 2 * TILE_BYTES, PIPE_BYTES = 2 * STAGE_BYTES;
+static_assert(PIPE_BYTES + RES * 4 <= tile_lds<kWide>(), "two panels and the tile's target logits");
+constexpr int kLoadsInGroup[8] = {4, 0, 0, 0, 0, 4, 4, 4};
+constexpr int load_index_base(int g) {      // loads issued before group g, in the order 5, 6, 7, 0, 1, ...
+  int n = 0;
+  for (int h = 5; h != g; h = (h + 1) & 7) n += kLoadsInGroup[h];
+  return n;
+}
+constexpr int kLoadsCarriedOver = kLoadsInGroup[0] + kLoadsInGroup[1] + kLoadsInGroup[2] + kLoadsInGroup[3] + kLoadsInGroup[4];
+static_assert(kLoadsCarriedOver + kLoadsInGroup[5] + kLoadsInGroup[6] + kLoadsInGroup[7] == 16, "a slot takes 16 loads per wave");
+
+__device__ __forceinline__ void square_tile(unsigned char* smem, int tm, int tn, int n0, int N) {
+  const Params& p = args_now();
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave >> 1, wn = wave & 1, frow = lane & 15, fq = lane >> 4;
+  const int m0 = tm * RES, M = p.M, nk = p.K / BK;
+  const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
+  // (opaque: else they are read again inside the loop, and the wait for that is one for every LDS read)
+  int tail_panel = p.a_tail_panel;
+  int64_t tail_delta = p.a_tail_delta;
+  asm volatile("" : "+s"(tail_panel), "+s"(tail_delta));
+  const uint32_t wave_lds = __builtin_amdgcn_readfirstlane(lds_base + wave * 8192);
+  // Workgroups that share a panel walk its row blocks in a different cyclic order (rot_a, rot_b), so that they do not all ask
+  // the L2 for the same lines at the same moment.
+  const uint16_t* a_ptr[8];
+  const uint16_t* b_ptr[8];
+  uint32_t lds_a[8], lds_b[8];
+  const int rot_a = 2 * tn & 7, rot_b = tm & 7;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const int ia = (i + rot_a) & 7, ib = (i + rot_b) & 7;
+    lds_a[i] = __builtin_amdgcn_readfirstlane(ia * 1024);
+    lds_b[i] = __builtin_amdgcn_readfirstlane(ib * 1024);
+    const int r = (wave * 8 + ia) * 8 + (lane >> 3), rB = (wave * 8 + ib) * 8 + (lane >> 3);
+    const int ra = m0 + r < M ? m0 + r : M - 1, rb = n0 + rB < N ? n0 + rB : N - 1;
+    a_ptr[i] = p.A + (int64_t)ra * p.lda + ((lane & 7) ^ (((r >> 1) & 1) | (((r >> 3) & 3) << 1))) * 8;
+    b_ptr[i] = p.B + (int64_t)rb * p.ldb + ((lane & 7) ^ ((rB >> 1) & 7)) * 8;
+  }
+  auto load_at = [](const uint16_t* base, int64_t byte_off, uint32_t lds) {
+    uint64_t addr;
+    asm volatile("s_mov_b32 m0, %3\n\tv_lshl_add_u64 %0, %1, 0, %2\n\tglobal_load_lds_dwordx4 %0, off"
+                 : "=&v"(addr) : "v"(base), "s"(byte_off), "s"(lds) : "memory");
+  };
+  auto issue_range = [&](int kt, int slot, int j0, int j1) {
+    const int64_t off = (int64_t)kt * (BK * 2);
+    const int64_t a_off = off + (kt >= tail_panel ? tail_delta : 0);
+#pragma unroll
+    for (int j = j0; j < j1; ++j) {
+      const uint32_t st = slot * STAGE_BYTES + wave_lds;
+      if (j & 1) load_at(b_ptr[j >> 1], off, st + TILE_BYTES + lds_b[j >> 1]); else load_at(a_ptr[j >> 1], a_off, st + lds_a[j >> 1]);
+    }
+  };
+  int a_off[2], b_off[2];
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks) {
+    const int chunk = (ks << 2) | fq;
+    a_off[ks] = (wm * 128 + 8 * (frow >> 2) + (frow & 3)) * 128 + ((chunk ^ (((frow >> 1) & 1) | ((frow >> 2) << 1))) << 4);
+    b_off[ks] = TILE_BYTES + (wn * 128 + frow) * 128 + ((chunk ^ ((frow >> 1) & 7)) << 4);
+  }
+  auto read_a = [&](int st, int ks, int i) { return *reinterpret_cast<const bf16x8*>(smem + st + a_off[ks] + (i >> 1) * 4096 + (i & 1) * 512); };
+  auto read_b = [&](int st, int ks, int j) { return *reinterpret_cast<const bf16x8*>(smem + st + b_off[ks] + j * 2048); };
+  f32x4 acc[8][8];
+  bf16x8 fbx[2][2][8];   // [set][K step][16-column block]
+  bf16x8 fax[4][2];      // [ring slot][K step]
+  auto side = [&](int g, int m, int set, int st_cur, int st_nxt, int kt_nxt, int slot_nxt, int kt_load, int slot_cur) {
+    int nr = 2;
+    if (g == 0) {
+      if (m < 2) fax[3][m] = read_a(st_cur, m, 3);
+    } else if (g <= 4) {
+      if (m < 2) fax[(g - 1) & 3][m] = read_a(st_cur, m, g + 3);
+    } else {
+      const int q = g - 5, nb = q == 2 ? 2 : 3;       // token blocks read in this group
+      if (g == 5 && m == 0) {
+        __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
+        __syncthreads();
+      }
+      if (m >= 1 && m < 3) fax[q][m - 1] = read_a(st_nxt, m - 1, q);
+      if (m >= 3 && m < 3 + 2 * nb) { const int j = 3 * q + (m - 3) / 2, ks = (m - 3) & 1; fbx[set ^ 1][ks][j] = read_b(st_nxt, ks, j); }
+      nr = 3 + 2 * nb;
+    }
+    const int nl = kLoadsInGroup[g];
+    if (nl > 0 && m >= nr) {
+#pragma unroll
+      for (int i = 0; i < nl; ++i)
+        if (m == nr + i * (16 - nr) / nl) {
+          const int l = load_index_base(g) + i;
+          if (g >= 5) issue_range(kt_load, slot_cur, l, l + 1); else issue_range(kt_nxt, slot_nxt, l, l + 1);
+        }
+    }
+  };
+  auto panel = [&](int set, int st_cur, int st_nxt, int kt_nxt, int slot_nxt, int kt_load, int slot_cur) {
+#pragma unroll
+    for (int g = 0; g < 8; ++g)
+#pragma unroll
+      for (int m = 0; m < 16; ++m) {
+        mfma16(acc[g][m >> 1], fax[g & 3][m & 1], fbx[set][m & 1][m >> 1]);
+        side(g, m, set, st_cur, st_nxt, kt_nxt, slot_nxt, kt_load, slot_cur);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+  };
+  auto last_k = [&](int k) { return k < nk ? k : nk - 1; };
+#pragma unroll
+  for (int i = 0; i < 8; ++i)
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[i][j][e] = 0.f;
+  issue_range(0, 0, 0, 16);
+  {
+    const int n = n0 + wave * 64 + lane;              // the tile's target logits, published with its first panel
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off"
+                 :: "v"(p.zt + (n < N ? n : N - 1)), "s"(__builtin_amdgcn_readfirstlane(lds_base + PIPE_BYTES + wave * 256)) : "memory");
+  }
+  __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
+  __syncthreads();
+  issue_range(last_k(1), 1, 0, 16 - kLoadsCarriedOver);   // the rest comes with the first groups of the first panel
+#pragma unroll
+  for (int j = 0; j < 8; ++j) { fbx[0][0][j] = read_b(0, 0, j); fbx[0][1][j] = read_b(0, 1, j); }
+#pragma unroll
+  for (int i = 0; i < 3; ++i) { fax[i][0] = read_a(0, 0, i); fax[i][1] = read_a(0, 1, i); }
+  int kt = 0;
+  do {                                                // (an even number of panels, at least two)
+    panel(0, 0, STAGE_BYTES, last_k(kt + 1), 1, last_k(kt + 2), 0);
+    panel(1, STAGE_BYTES, 0, last_k(kt + 2), 0, last_k(kt + 3), 1);
+    kt += 2;
+  } while (kt < nk);
+  __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));          // no direct load may outlive the wave
+  asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+  const unsigned char* const zt_lds = smem + PIPE_BYTES + ((wn * 128 + (lane_now() & 15)) << 2);
+  forward_epilogue<8>(args_now(), [&](int i, int j, int e) { return acc_now(acc[i][j][e]); },
+                      [&](int j) { return *reinterpret_cast<const float*>(zt_lds + j * 64); }, m0 + wm * 128, n0 + wn * 128, tm * 2 + wm, N);
+}
+
+// ---------------------------------------------------------------------------------------------
 // Forward, last column of tiles with at most 128 tokens: 256 x 128 tiles, waves 2 x 2, each 128 x 64.  A panel takes half
 // the MFMAs, so the fragments of two panels fit into registers and three panels into LDS: a panel's MFMAs run
 // on fragments read during the panel before, while the loads of the third next one go into the slot those left.
@@ -344,13 +891,10 @@ constexpr int HALF_STAGE = TILE_BYTES + TILE_BYTES / 2, HALF_PIPE = 3 * HALF_STA
 constexpr int HALF_LOADS = 12;                                      // direct loads per wave and panel: 8 of A, 4 of B
 
 __device__ __forceinline__ void half_column_tile(unsigned char* smem, int tm, int n0, int N) {
-  typedef const __attribute__((address_space(4))) Params* KernArg;
-  KernArg arg = (KernArg)__builtin_amdgcn_kernarg_segment_ptr();
-  asm volatile("" : "+s"(arg));
-  const Params& p = *(const Params*)arg;
+  const Params& p = args_now();
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave >> 1, wn = wave & 1, frow = lane & 15, fq = lane >> 4;
-  const int m0 = tm * BM, M = p.M, nk = p.K / BK;
+  const int m0 = tm * RES, M = p.M, nk = p.K / BK;
   const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
   // panels, swizzles and fragment rows as in the full tile
   const uint16_t* src[HALF_LOADS];
@@ -364,10 +908,14 @@ __device__ __forceinline__ void half_column_tile(unsigned char* smem, int tm, in
   }
   const uint32_t lds_a = __builtin_amdgcn_readfirstlane(lds_base + wave * 8192);
   const uint32_t lds_b = __builtin_amdgcn_readfirstlane(lds_base + TILE_BYTES + wave * 4096);
+  // (opaque: else they are read again inside the loop, and the wait for that is one for every LDS read)
+  int tail_panel = p.a_tail_panel;
+  int64_t tail_delta = p.a_tail_delta;
+  asm volatile("" : "+s"(tail_panel), "+s"(tail_delta));
   // load l of panel kt (behind the end: the last one again, into a slot nobody reads)
   auto load = [&](int l, int kt, uint32_t stage) {
     kt = kt < nk ? kt : nk - 1;
-    const int64_t off = (int64_t)kt * (BK * 2) + (l < 8 && kt >= p.a_tail_panel ? p.a_tail_delta : 0);
+    const int64_t off = (int64_t)kt * (BK * 2) + (l < 8 && kt >= tail_panel ? tail_delta : 0);
     const uint32_t lds = (l < 8 ? lds_a + l * 1024 : lds_b + (l - 8) * 1024) + stage;
     uint64_t addr;
     asm volatile("s_mov_b32 m0, %3\n\tv_lshl_add_u64 %0, %1, 0, %2\n\tglobal_load_lds_dwordx4 %0, off"
@@ -442,491 +990,142 @@ __device__ __forceinline__ void half_column_tile(unsigned char* smem, int tm, in
   } while (kt < nk);
   __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));          // no direct load may outlive the wave
   const unsigned char* const zt_lds = smem + HALF_PIPE + ((wn * 64 + (lane_now() & 15)) << 2);
-  forward_epilogue<4>(p, acc, [&](int j) { return *reinterpret_cast<const float*>(zt_lds + j * 64); }, m0, n0, tm * 2 + wm, wm, wn, N);
+  forward_epilogue<4>(p, [&](int i, int j, int e) { return acc_now(acc[i][j][e]); },
+                      [&](int j) { return *reinterpret_cast<const float*>(zt_lds + j * 64); }, m0 + wm * 128, n0 + wn * 64, tm * 2 + wm, N);
+}
+
+// No panels at all: a slice of the contraction that the plan did not need, or dW without a scored row.
+__device__ inline void zero_rows(float* at, int64_t ld, int rows, int cols) {
+  for (int r = threadIdx.x >> 6; r < rows; r += NTHREADS / 64)
+    for (int c = (threadIdx.x & 63) * 4; c < cols; c += 256) *reinterpret_cast<f32x4_any*>(at + (int64_t)r * ld + c) = f32x4{0.f, 0.f, 0.f, 0.f};
+}
+
+__device__ __forceinline__ int tiles_of(int n, int size) { return (n + size - 1) / size; }
+
+// How n token rows (columns of forward tiles, rows of dH tiles) are cut into tiles of 384, 256 and 128.
+struct Cut {
+  int wide, narrow, half;
+  __device__ int count() const { return wide + narrow + half; }
+  __device__ int start(int t) const { return t < wide ? t * RING : wide * RING + (t - wide) * 256; }
+  __device__ int blocks(int t) const { return t < wide ? kWide : t < wide + narrow ? 8 : 4; }   // of 16 rows per wave
+};
+// Tiles of 384 and what is left; two of 256 instead of one of 384 and one of 128, which waits for its panels more than it computes.
+__device__ inline Cut cut_wide(int n) {
+  const int w = n / RING, r = n - w * RING;
+  if (r == 0) return {w, 0, 0};
+  if (r <= 128) return w ? Cut{w - 1, 2, 0} : Cut{0, 0, 1};
+  return r <= 256 ? Cut{w, 1, 0} : Cut{w + 1, 0, 0};
+}
+__device__ inline Cut cut_narrow(int n) {
+  const int w = n / 256, r = n - w * 256;
+  return r == 0 ? Cut{0, w, 0} : r <= 128 ? Cut{0, w, 1} : Cut{0, w + 1, 0};
+}
+// dH: tiles of 384, but where all are cut into slices that fill the chip about once (a tile of 384 takes 1.43 of the time of one of
+// 256) those whose
+// slices are shorter.  2000 rows, V = 128256, d = 1024: 24 tiles of 10 slices 396 us, 32 of 8 386; 1100 rows, V = 5000, d = 136 (at most
+// 5 slices of 16 panels) 44 and 38; 327 rows, V = 151936, d = 4096: 16 tiles of 16 slices 356, 32 of 8 (256 x 256 tiles before) 459.
+__device__ inline Cut cut_dh(int n, int cols, int panels) {
+  const Cut a = cut_wide(n), b = cut_narrow(n);
+  const int ta = a.count() * cols, tb = b.count() * cols, most = panels < 2 * kMinSlicePanels ? 1 : panels / kMinSlicePanels;
+  if (a.wide == 0 || tb > kRound) return a;
+  const int sa = kRound / ta < most ? kRound / ta : most, sb = kRound / tb < most ? kRound / tb : most;
+  return 105 * sa < 143 * sb ? b : a;
+}
+// When a forward launch of rows x c tiles ends, in hundredths of a 256 x 256 tile's time: whole rounds of one kind of tile; of
+// several kinds, the mean and a part of a tile.  With a single column every tile streams its own rows of W from memory, and the wide
+// one waits for them.  Scoring call, us, 256 x 256 (and half) tiles and tiles of 384: V = 151936, d = 4096, 384 rows 451 and 466,
+// 600 rows 725 and 683, 1920 rows 1900 and 1763; d = 1536, 384 rows 188 and 204; V = 50257, d = 712, 384 rows 63 and 54, 1280 rows 115
+// and 132, 1920 rows 178 and 159; V = 32000, d = 2048, 300 rows 57 and 70, 600 rows 101 and 84, 1000 rows 108 and 138, 1920 rows 199 and 212.
+__device__ inline int forward_end(const Cut& c, int rows) {
+  constexpr int kWideTile = 143, kNarrowTile = 100, kHalfTile = 58;
+  const int w = c.wide * rows, n = c.narrow * rows, h = c.half * rows, tiles = w + n + h;
+  if (tiles <= kRound) return w ? kWideTile : n ? kNarrowTile : kHalfTile;
+  if (n + h == 0) return (w + kRound - 1) / kRound * (c.wide == 1 ? kWideTile + 14 : kWideTile);
+  if (w + h == 0) return (n + kRound - 1) / kRound * kNarrowTile;
+  return (int)(((int64_t)w * kWideTile + (int64_t)n * kNarrowTile + h * kHalfTile) / kRound) + (w ? (h ? 80 : 60) : 30);
+}
+__device__ inline Cut cut_forward(int n, int rows) {
+  const Cut a = cut_wide(n), b = cut_narrow(n);
+  const Cut c = a.narrow + a.half == 0 ? Cut{a.wide - 1, 1, 1} : a;
+  const int ea = forward_end(a, rows), eb = forward_end(b, rows), ec = forward_end(c, rows);
+  return eb < ea && eb <= ec ? b : ec < ea ? c : a;
 }
 
 template <int MODE>
 __global__ __launch_bounds__(NTHREADS) void gemm_nt_bf16(Params p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1;
-  const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-
   // valid rows of this chunk (device-side, no host sync)
-  int64_t nv64 = *p.n_scored - p.chunk_start;
-  const int nvalid = nv64 < 0 ? 0 : (nv64 > p.chunk_rows ? p.chunk_rows : (int)nv64);
-
-  int M = p.M, N = p.N, K = p.K;
-  if (MODE == MODE_FWD) N = nvalid;
-  if (MODE == MODE_DH) M = nvalid;
-  if (MODE == MODE_DW) K = dw_panels(nvalid, K) * BK;
-  if (MODE == MODE_FWD && nvalid == 0) return;
-  if (MODE == MODE_DH && nvalid == 0) return;
-  if (MODE == MODE_DW && nvalid == 0 && !p.overwrite) return;
-
-  const int Mt = (M + BM - 1) / BM, Nt = (N + BN - 1) / BN;
+  const int64_t nv64 = *p.n_scored - p.chunk_start;
+  const int nvalid = __builtin_amdgcn_readfirstlane(nv64 < 0 ? 0 : (nv64 > p.chunk_rows ? p.chunk_rows : (int)nv64));
+  if (nvalid == 0 && (MODE != MODE_DW || !p.overwrite)) return;
   int tm, tn;
-  int sm, sn, sup_m, sup_n;        // position of the tile among those that share its panels
-  int k_first = 0;                 // first K panel of this workgroup (tail slices start later)
-  float* tail_out = nullptr;       // DH / DW tail slice: where the accumulators go instead
-  if (MODE != MODE_DW) {
-    int bid = blockIdx.x, split = 1, slice = 0;
-    const int tiles = Mt * Nt, whole = tiles / kRound * kRound;
-    if (MODE == MODE_DH && bid >= whole) {
-      const int rest = tiles - whole;
-      split = dh_split(rest, K / BK, p.max_items);
-      if (split > 1) {
-        // an XCD takes consecutive items, i.e. mostly tiles of one slice
-        const int items = rest * split, per = (items + NXCD - 1) / NXCD;
-        const int e = bid - whole, item = e % NXCD * per + e / NXCD;
-        if (e / NXCD >= per || item >= items) return;
-        slice = item / rest;
-        tile_at(whole + item - slice * rest, Mt, Nt, tm, tn);
-        const int nk_all = K / BK, per_slice = slice_panels(nk_all, split);
-        k_first = slice * per_slice;
-        const int k_end = k_first + per_slice < nk_all ? k_first + per_slice : nk_all;
-        K = k_end > k_first ? (k_end - k_first) * BK : 0;
-        tail_out = p.tail_part + (int64_t)item * (BM * BN);
-      }
+  if (MODE == MODE_FWD) {
+    const int Mt = tiles_of(p.M, RES);
+    const Cut cut = cut_forward(nvalid, Mt);
+    const int Nt = cut.count();
+    if (!dealt_tile<8>(blockIdx.x, Mt, Nt, tm, tn)) return;
+    if (cut.half > 0 && Nt > 1) {
+      // half tiles are dealt like the others, to every XCD its share: the columns of a band start at another one in every
+      // band (with 8 columns, XCDs would else have all of them or none)
+      tn += tm / 8 % Nt;
+      tn = tn < Nt ? tn : tn - Nt;
     }
-    if (split == 1 && !dealt_tile(bid, Mt, Nt, tm, tn)) return;
-    sm = tm % kBand; sn = tn % 4; sup_m = kBand; sup_n = 4;
-  } else if (p.tail_split > 0) {
-    sup_m = p.sup_m; sup_n = p.sup_n;
-    if ((int)blockIdx.x < p.main_blocks) {
-      if (!tile_coords(blockIdx.x, p.tail_m0, Nt, p.sup_m, p.sup_n, tm, tn, sm, sn)) return;
+    const int n0 = cut.start(tn), blocks = cut.blocks(tn);
+    if (blocks == 4) half_column_tile(smem, tm, n0, nvalid);
+    else if (blocks == 8) square_tile(smem, tm, tn, n0, nvalid < n0 + 256 ? nvalid : n0 + 256);
+    else tile_product<MODE, kWide>(smem, tn, tm, n0, nvalid, 0, p.K / BK, nullptr);
+  } else if (MODE == MODE_DH) {
+    const int Nt = tiles_of(p.N, RES);
+    const Cut cut = cut_dh(nvalid, Nt, p.K / BK);
+    const int Mt = cut.count(), panels = p.K / BK;
+    int k_first = 0, nk = panels;
+    float* tail_out = nullptr;
+    const int item = split_tile<4>(blockIdx.x, Mt, Nt, panels, p.max_items, DhSplit{}, tm, tn, k_first, nk);
+    if (item < -1) return;
+    if (item >= 0) {
+      tail_out = p.tail_part + (int64_t)item * (RING * RES);
+      if (nk <= 0) { zero_rows(tail_out, RES, RING, RES); return; }
+    }
+    const int m0 = cut.start(tm), blocks = cut.blocks(tm);
+    if (blocks == 4) tile_product<MODE, 4>(smem, tm, tn, m0, nvalid, k_first, nk, tail_out);
+    else if (blocks == 8) tile_product<MODE, 8>(smem, tm, tn, m0, nvalid < m0 + 256 ? nvalid : m0 + 256, k_first, nk, tail_out);
+    else tile_product<MODE, kWide>(smem, tm, tn, m0, nvalid, k_first, nk, tail_out);
+  } else if (p.wide) {
+    const int panels = dw_panels(nvalid, p.K), Mt = tiles_of(p.V, RING), Nt = tiles_of(p.d, RES);
+    int k_first = 0, nk = panels;
+    const int item = split_tile<4>(blockIdx.x, Mt, Nt, panels, p.max_items, DwSplit{}, tm, tn, k_first, nk);
+    if (item < -1 || (item >= 0 && nk <= 0)) return;  // (an empty slice: nothing to store, and nobody reads it)
+    const int rows = p.V - tm * RING < RING ? p.V - tm * RING : RING, cols = p.d - tn * RES < RES ? p.d - tn * RES : RES;
+    if (panels == 0) zero_rows(p.dW + (int64_t)tm * RING * p.d + tn * RES, p.d, rows, cols);
+    else tile_product<MODE, kWide>(smem, tm, tn, tm * RING, p.V, k_first, nk, item >= 0 ? p.tail_part + (int64_t)item * (RING * RES) : nullptr);
+  } else {
+    // 256 x 256 tiles: the rows of tiles up to the tail's first one, and the tail's slices (see dw_tail_plan)
+    const int panels = dw_panels(nvalid, p.K), Nt = tiles_of(p.d, RES);
+    const int Mt = p.tail_split > 0 ? p.tail_m0 : tiles_of(p.V, RES);
+    int k_first = 0, nk = panels;
+    float* tail_out = nullptr;
+    if (p.tail_split == 0 || (int)blockIdx.x < p.main_blocks) {
+      if (!tile_coords(blockIdx.x, Mt, Nt, p.sup_m, p.sup_n, tm, tn)) return;
+      if (panels == 0) {
+        zero_rows(p.dW + (int64_t)tm * RES * p.d + tn * RES, p.d, p.V - tm * RES < RES ? p.V - tm * RES : RES, p.d - tn * RES < RES ? p.d - tn * RES : RES);
+        return;
+      }
     } else {
       // one XCD takes consecutive items (the host says how many: the XCDs that the whole tiles
       // leave idle earlier take more), i.e. mostly tiles of one slice: they walk the same K range
       // and share its operand panels in that L2
-      const int e = blockIdx.x - p.main_blocks;
-      const int tiles = p.tail_rows * Nt;
+      const int e = blockIdx.x - p.main_blocks, tiles = p.tail_rows * Nt;
       const int item = p.tail_first[e % NXCD] + e / NXCD;
       if (item >= p.tail_first[e % NXCD + 1]) return;
-      const int slice = item / tiles, t = item % tiles;
-      sm = t / Nt; sn = t % Nt;
-      tm = p.tail_m0 + sm; tn = sn;
-      const int nk_all = K / BK, per = slice_panels(nk_all, p.tail_split);
+      const int slice = item / tiles, t = item % tiles, per = slice_panels(panels, p.tail_split);
+      if (slice >= slices_in_use(panels, p.tail_split)) return;   // empty: nothing to store, and nobody reads it
+      tm = p.tail_m0 + t / Nt; tn = t % Nt;
       k_first = slice * per;
-      if (slice >= slices_in_use(nk_all, p.tail_split)) return;   // empty: nothing to store, and nobody reads it
-      const int k_end = k_first + per < nk_all ? k_first + per : nk_all;
-      K = k_end > k_first ? (k_end - k_first) * BK : 0;
-      tail_out = p.tail_part + (int64_t)item * (BM * BN);
+      nk = panels - k_first < per ? panels - k_first : per;
+      tail_out = p.tail_part + (int64_t)item * (RES * RES);
+      if (nk <= 0) { zero_rows(tail_out, RES, RES, RES); return; }
     }
-  } else {
-    sup_m = p.sup_m; sup_n = p.sup_n;
-    if (!tile_coords(blockIdx.x, Mt, Nt, sup_m, sup_n, tm, tn, sm, sn)) return;
-  }
-  if (MODE == MODE_FWD && __builtin_expect(N - (Nt - 1) * BN <= HALF_COLS, 0)) {
-    // A last column of at most 128 tokens takes half tiles.  They are dealt like the others, to every XCD its share: the
-    // columns of a band start at another one in every band (with 8 columns, XCDs would else have all of them or none).
-    int columns = Nt;
-    asm volatile("" : "+s"(columns));                 // (the division stays in this branch)
-    tn += tm / kBand % columns;
-    tn = tn < Nt ? tn : tn - Nt;
-    if (tn == Nt - 1) { half_column_tile(smem, tm, tn * BN, N); return; }
-  }
-  const int m0 = tm * BM, n0 = tn * BN;
-
-  // ---- global -> LDS: one direct load moves 1 KB, contiguous in LDS.
-  // Row-major operands ([row][k], k contiguous): 8 rows x 128 B per load.  Wave w owns row
-  // blocks 8w .. 8w+7 of each operand panel; lane l fills LDS chunk (row l/8, slot l%8) and
-  // therefore fetches logical chunk slot ^ ((row >> 1) & 7).
-  // K-major operands (DW: A[m][k] = dz[k][m], stored as token rows with the vocabulary contiguous;
-  // DH: B[n][k] = W[k][n], the rows of W): the panel is 64 k rows x 512 B and a load moves 2 of them; lane l fills chunk
-  // slot l%32 of row l/32 and fetches logical chunk slot ^ (h(k) << 1), the swizzle that makes
-  // the transposing fragment reads below conflict-free.
-  constexpr bool A_KMAJOR = (MODE == MODE_DW);
-  constexpr bool B_KMAJOR = (MODE == MODE_DH);
-  // FWD: the 16 rows of A fragment i are not 16 consecutive panel rows but
-  //   rho(i, r) = 32*(i/2) + 8*(r/4) + 4*(i%2) + r%4      (within the wave's 128 rows),
-  // so that a lane's accumulators (i = 2t, 2t+1; e = 0..3) are 8 consecutive vocabulary ids
-  // and the bf16 stash of exponentials can be stored from registers, 16 bytes per lane, without an LDS round
-  // trip.  The chunk swizzle of the A panel then takes row bits 1, 3, 4 (the ones that vary
-  // inside a fragment) instead of bits 1-3.
-  constexpr bool A_PERM = (MODE == MODE_FWD);
-  const int64_t a_kstep = A_KMAJOR ? (int64_t)BK * p.lda : BK;   // elements per K panel
-  const int lrow = lane >> 3;
-  const uint16_t* a_ptr[8];
-  const uint16_t* b_ptr[8];
-  uint32_t b_voff[8];                                 // DH: byte offset of the lane's chunk from the wave's 16 rows of W
-  // Workgroups that share a panel (same sm for A, same sn for B) walk its row blocks in a
-  // different cyclic order (rot_a, rot_b), so that they do not all ask the L2 for the same lines
-  // at the same moment (1-2 % on the forward and dH launches).
-  uint32_t lds_a[8], lds_b[8];                        // LDS offset of load i within the wave's 8 KB
-  const float* zt_ptr = nullptr;                      // forward: this lane's entry of the tile's target logits
-  {
-    const int rot_a = (sn * 8 / sup_n) & 7, rot_b = (sm * 8 / sup_m) & 7;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int ia = (i + rot_a) & 7, ib = (i + rot_b) & 7;
-      lds_a[i] = __builtin_amdgcn_readfirstlane(ia * 1024);
-      lds_b[i] = __builtin_amdgcn_readfirstlane(ib * 1024);
-      const int r = (wave * 8 + ia) * 8 + lrow;         // row within the 256-row panel
-      const int rB = (wave * 8 + ib) * 8 + lrow;
-      const int lchunk = (lane & 7) ^ ((rB >> 1) & 7);
-      const int lchunk_a = A_PERM ? ((lane & 7) ^ (((r >> 1) & 1) | (((r >> 3) & 3) << 1))) : ((lane & 7) ^ ((r >> 1) & 7));
-      int ra = m0 + r; ra = ra < M ? ra : M - 1;
-      int rb = n0 + rB; rb = rb < N ? rb : N - 1;
-      int64_t rowa = ra, rowb = rb;
-      if (A_KMAJOR) {
-        const int k = 2 * (wave * 8 + ia) + (lane >> 5);  // k row within the panel
-        // (columns from V on, whose products are not stored, come from the tile's first chunk again: the pad
-        // columns of the stash are written past the caches and no other launch reads them, and with few tiles
-        // this one lasts as long as the tile that fetches them: 41444 rows, V = 329, d = 240 924 us, now 671)
-        const int col = m0 + (((lane & 31) ^ (kswz(k) << 1)) << 3);
-        a_ptr[i] = p.A + ((int64_t)k_first * BK + k) * p.lda + (col < p.V ? col : m0);
-      } else {
-        a_ptr[i] = p.A + rowa * p.lda + lchunk_a * 8 + (MODE == MODE_DH ? k_first * BK : 0);
-      }
-      if (B_KMAJOR) {
-        const int k = 2 * ib + (lane >> 5);
-        b_voff[i] = (uint32_t)k * (uint32_t)(p.ldb * 2) + (((lane & 31) ^ (kswz(wave * 16 + k) << 1)) << 4);
-      } else b_ptr[i] = p.B + rowb * p.ldb + lchunk * 8 + (MODE == MODE_DW ? k_first * BK : 0);
-    }
-    if (MODE == MODE_FWD) {
-      int n = n0 + wave * 64 + lane; n = n < N ? n : N - 1;
-      zt_ptr = p.zt + n;
-    }
-  }
-  // The direct load is issued through inline assembly on purpose: the compiler's wait-count
-  // pass treats a global load that writes LDS as touching both address spaces and then
-  // drains every counter to zero before each LDS read, which serialises the pipeline.
-  // Issued this way the loads are invisible to that pass; their completion is awaited
-  // explicitly below with s_waitcnt vmcnt(0) before the barrier that publishes a panel.
-  const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
-  const uint32_t wave_lds = __builtin_amdgcn_readfirstlane(lds_base + wave * 8192);
-
-  // forward: the tile's 256 target logits travel to LDS with the tile's first panel (4 bytes per
-  // lane, one direct load per wave) and are published by the same barrier, so that the epilogue
-  // starts without a round trip to global memory
-  auto issue_zt = [&]() {
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off"
-                 :: "v"(zt_ptr), "s"(__builtin_amdgcn_readfirstlane(lds_base + PIPE_BYTES + wave * 256))
-                 : "memory");
-  };
-
-  // ---- fragment read offsets.  A 16x16x32 operand fragment: lane -> row (lane & 15),
-  // 16-byte K chunk (lane >> 4) of a 32-wide K step.  A 128-bit LDS read is served 16 lanes
-  // per cycle over 64 banks; rows 2 apart share a bank window (128-byte rows), the swizzle
-  // (row / 2) % 8 spreads the 16 rows of a fragment over distinct banks.
-  const int frow = lane & 15, fq = lane >> 4;
-  int a_off[2], b_off[2];
-#pragma unroll
-  for (int ks = 0; ks < 2; ++ks) {
-    const int chunk = ((ks << 2) | fq) ^ ((frow >> 1) & 7);
-    if (A_PERM) {
-      const int chunk_a = ((ks << 2) | fq) ^ (((frow >> 1) & 1) | ((frow >> 2) << 1));
-      a_off[ks] = (wm * 128 + 8 * (frow >> 2) + (frow & 3)) * 128 + (chunk_a << 4);
-    } else {
-      a_off[ks] = (wm * 128 + frow) * 128 + (chunk << 4);
-    }
-    b_off[ks] = TILE_BYTES + (wn * 128 + frow) * 128 + (chunk << 4);
-  }
-
-  // K-major panel: the transposing LDS read hands lane (g = lane / 16, s = lane % 16) the four
-  // k values kb .. kb+3 of column m = mb + s when lane s points at row kb + s/4, columns
-  // mb + 4*(s%4) .. +3.  Two of them (kb = 8g and 8g + 4 within the K step) make the lane's
-  // 8-element fragment.  A 64-bit read is served 32 lanes per cycle: 8 rows x 32 bytes, and the
-  // swizzle h(k) moves the 32-byte column groups of those rows to distinct bank windows.
-  int a_tr_base = 0, b_tr_base = 0;
-  {
-    const int k = 8 * fq + (frow >> 2);
-    const int base = k * 512 + (kswz(k) << 5) + ((frow & 2) << 3) + ((frow & 1) << 3);
-    if (A_KMAJOR) a_tr_base = base + wm * 256;
-    if (B_KMAJOR) b_tr_base = base + wn * 256;
-  }
-  auto read_kmajor = [&](int off) -> bf16x8 {
-    typedef short v4i16 __attribute__((ext_vector_type(4)));
-    typedef __attribute__((address_space(3))) v4i16* lds_v4i16;
-    unsigned char* q = smem + off;
-    const v4i16 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16)q);
-    const v4i16 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16)(q + 2048));
-    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-  };
-  auto read_a = [&](int st, int ks, int ib) -> bf16x8 {
-    if (A_KMAJOR) return read_kmajor(st + (a_tr_base ^ (ib << 5)) + ks * 16384);
-    return *reinterpret_cast<const bf16x8*>(smem + st + a_off[ks] +
-                                            (A_PERM ? (ib >> 1) * 4096 + (ib & 1) * 512 : ib * 2048));
-  };
-
-  f32x4 acc[8][8];
-  const int nk = K / BK;
-  // Software pipeline.  Panel kt+1 is loaded during the MFMAs of panel kt (double buffer).
-  // A panel is 8 groups; group g multiplies the A fragments of 16-row block g (both 32-wide
-  // K steps) with the panel's 16 B fragments: 16 MFMAs, the two K steps of an accumulator back
-  // to back.  Keeping an accumulator for two consecutive MFMAs costs measurably less energy than
-  // touching 64 different ones in turn (about 5 % more FLOP/s from an MFMA-only loop at the
-  // power limit), which is what bounds these kernels on real data.
-  // Registers: the B fragments of a whole panel stay resident, in two sets (this panel / the
-  // next one); A fragments sit in a ring of four pairs.  The schedule of reads, barrier and
-  // direct loads around the MFMAs is described at `side` below.
-  // The loop body (two panels, so that the B sets have fixed registers) is branch-free; loads
-  // that would run past the end re-fetch the last panel into a slot nobody reads.
-  bf16x8 fbx[2][2][8];   // [set][K step][16-column block]
-  bf16x8 fax[4][2];      // [ring slot][K step]
-  auto read_b = [&](int st, int ks, int j) -> bf16x8 {
-    if (B_KMAJOR) return read_kmajor(st + TILE_BYTES + (b_tr_base ^ (j << 5)) + ks * 16384);
-    return *reinterpret_cast<const bf16x8*>(smem + st + b_off[ks] + j * 2048);
-  };
-  // One load of the K loop: three instructions, what one MFMA leaves room for.  The address
-  // arithmetic (panel offset, uniform) is part of the piece, and it separates the write of M0
-  // from the load that reads it (one wait state).
-  auto load_lds16_at = [](const uint16_t* base, int64_t byte_off, uint32_t lds_addr) {
-    uint64_t addr;
-    asm volatile("s_mov_b32 m0, %3\n\tv_lshl_add_u64 %0, %1, 0, %2\n\tglobal_load_lds_dwordx4 %0, off"
-                 : "=&v"(addr) : "v"(base), "s"(byte_off), "s"(lds_addr) : "memory");
-  };
-  // DH: the wave's 16 rows of W in the panel being loaded, as a buffer descriptor that ends with row
-  // V - 1: the contraction runs over the vocabulary rounded up to whole panel pairs, and loads
-  // beyond the descriptor's end return zeros (the stash columns there are zeros as well).  w_advance
-  // moves it on by a panel.
-  uint64_t w_addr = 0;
-  int w_left = 0;                                     // rows of W from the wave's first one on
-  u32x4 w_desc = {0, 0, 0, 0x00020000u};
-  auto w_set = [&]() {
-    const int rows = min_int(w_left, 16);             // (below 2^25 bytes: ldb is at most 2^20)
-    const int bytes = rows * (int)(p.ldb * 2) - n0 * 2;
-    w_desc[0] = (uint32_t)w_addr; w_desc[1] = (uint32_t)(w_addr >> 32);
-    w_desc[2] = (uint32_t)(bytes > 0 ? bytes : 0);
-  };
-  auto w_advance = [&]() { w_addr += (uint64_t)p.ldb * (BK * 2); w_left -= BK; w_set(); };
-  if (B_KMAJOR) {
-    const int64_t first = (int64_t)k_first * BK + wave_u * 16;
-    w_addr = (uint64_t)(p.B + first * p.ldb + n0);
-    w_left = p.V - (int)first;
-    w_set();
-  }
-  auto load_lds16_w = [](uint32_t voff, const u32x4& desc, uint32_t lds_addr) {
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds"
-                 :: "v"(voff), "s"(desc), "s"(lds_addr) : "memory");
-  };
-  auto issue_range = [&](int kt, int slot, int j0, int j1) {
-    const int64_t a_off = (int64_t)kt * a_kstep * 2 + (MODE == MODE_FWD && kt >= p.a_tail_panel ? p.a_tail_delta : 0);
-#pragma unroll
-    for (int j = j0; j < j1; ++j) {
-      const uint32_t st = slot * STAGE_BYTES + wave_lds;
-      if (B_KMAJOR && (j & 1)) load_lds16_w(b_voff[j >> 1], w_desc, st + TILE_BYTES + lds_b[j >> 1]);
-      else if (j & 1) load_lds16_at(b_ptr[j >> 1], (int64_t)kt * (BK * 2), st + TILE_BYTES + lds_b[j >> 1]);
-      else load_lds16_at(a_ptr[j >> 1], a_off, st + lds_a[j >> 1]);
-    }
-  };
-  // One panel = 8 groups of 16 MFMAs.  A wave issues in order and the matrix pipe takes a new MFMA
-  // only every 16 cycles, so whatever stands between two MFMAs in the instruction stream is free
-  // as long as it fits the 12 issue cycles the pipe leaves over - and costs pipe time when it
-  // comes as a block after the sixteenth.  The side work of a panel (fragment reads, the barrier,
-  // direct loads with their address arithmetic) is therefore cut into pieces of one to four
-  // instructions, one piece after an MFMA, in source order (both are volatile assembly or fenced):
-  //   group 0      : A fragments of row block 3 (this panel); the last loads of the NEXT panel's slot
-  //   groups 1 - 4 : A fragments of row blocks 4 - 7
-  //   group 5      : wait for this thread's part of panel kt+1, barrier (every wave has issued its
-  //                  last read of this panel's slot by then, so the slot can be refilled; panel
-  //                  kt+1 becomes visible); next panel's A block 0, B column blocks 0 - 2; the first
-  //                  loads of panel kt+2 into this panel's slot
-  //   group 6      : next A block 1, B blocks 3 - 5, loads
-  //   group 7      : next A block 2, B blocks 6 - 7, loads   (the rest follows in group 0 of the
-  //                  next panel; kLoadsInGroup says how many where)
-  // A fragments sit in a ring of four pairs: group g multiplies ring slot g % 4, and the slot a
-  // group has just finished with is refilled during the next group.  Four loads per group over
-  // four groups measured best: packing them into groups 5 - 7 costs 2 - 4 % (the load path of a
-  // compute unit takes about 23 cycles per 1 KB load, four waves issuing one every 16 cycles run
-  // its queue full and stall their MFMAs with it), spreading them further leaves the late ones
-  // too little time to land.
-  auto side = [&](int g, int m, int set, int st_cur, int st_nxt, int kt_nxt, int slot_nxt, int kt_load, int slot_cur) {
-    // pieces before the loads: the barrier (group 5) and the fragment reads
-    int nr = 2;
-    if (g == 0) {
-      if (m < 2) fax[3][m] = read_a(st_cur, m, 3);
-    } else if (g <= 4) {
-      if (m < 2) fax[(g - 1) & 3][m] = read_a(st_cur, m, g + 3);
-      if (B_KMAJOR && g == 4 && m == 6) w_advance();
-    } else {
-      const int q = g - 5;                          // 0, 1, 2
-      if (g == 5 && m == 0) {
-        __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
-        __syncthreads();
-      }
-      if (m >= 1 && m < 3) fax[q][m - 1] = read_a(st_nxt, m - 1, q);
-      const int nb = q == 2 ? 2 : 3;                // B column blocks read in this group
-      if (m >= 3 && m < 3 + 2 * nb) { const int j = 3 * q + (m - 3) / 2, ks = (m - 3) & 1; fbx[set ^ 1][ks][j] = read_b(st_nxt, ks, j); }
-      nr = 3 + 2 * nb;
-    }
-    // this group's share of the 16 loads that fill a slot, spread over the remaining gaps
-    const int nl = kLoadsInGroup[g];
-    if (nl > 0 && m >= nr) {
-      const int room = 16 - nr;
-#pragma unroll
-      for (int i = 0; i < nl; ++i)
-        if (m == nr + i * room / nl) {
-          const int l = load_index_base(g) + i;
-          if (g >= 5) issue_range(kt_load, slot_cur, l, l + 1);
-          else issue_range(kt_nxt, slot_nxt, l, l + 1);
-        }
-    }
-  };
-  auto panel = [&](int set, int st_cur, int st_nxt, int kt_nxt, int slot_nxt, int kt_load, int slot_cur) {
-#pragma unroll
-    for (int g = 0; g < 8; ++g) {
-#pragma unroll
-      for (int m = 0; m < 16; ++m) {
-        // (DW: operands swapped, the accumulator holds the transposed 16 x 16 block)
-        if (MODE == MODE_DW) mfma16(acc[g][m >> 1], fbx[set][m & 1][m >> 1], fax[g & 3][m & 1]);
-        else mfma16(acc[g][m >> 1], fax[g & 3][m & 1], fbx[set][m & 1][m >> 1]);
-        side(g, m, set, st_cur, st_nxt, kt_nxt, slot_nxt, kt_load, slot_cur);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
-  };
-  auto last_k = [&](int k) { return k < nk ? k : nk - 1; };
-  // The number of panels is even (the launchers see to it), so that the two-panel body is the
-  // only code that touches the accumulators: there is no peeled tail whose different register
-  // assignment would make the compiler move accumulators around next to MFMAs it cannot see
-  // into.  The last two panels read ahead and load like any other (the panel after the last is
-  // a re-fetch of the last one, read into registers nobody uses).
-#pragma unroll
-  for (int i = 0; i < 8; ++i)
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) acc[i][j][e] = 0.f;
-  if (nk > 0) {
-    issue_range(0, 0, 0, 16);
-    if (B_KMAJOR) w_advance();
-    if (MODE == MODE_FWD) issue_zt();
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
-    __syncthreads();
-    issue_range(last_k(1), 1, 0, 16 - kLoadsCarriedOver);   // the rest comes with the first groups of the first panel
-#pragma unroll
-    for (int j = 0; j < 8; ++j) { fbx[0][0][j] = read_b(0, 0, j); fbx[0][1][j] = read_b(0, 1, j); }
-#pragma unroll
-    for (int i = 0; i < 3; ++i) { fax[i][0] = read_a(0, 0, i); fax[i][1] = read_a(0, 1, i); }
-    for (int kt = 0; kt < nk; kt += 2) {
-      panel(0, 0, STAGE_BYTES, last_k(kt + 1), 1, last_k(kt + 2), 0);
-      panel(1, STAGE_BYTES, 0, last_k(kt + 2), 0, last_k(kt + 3), 1);
-    }
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));   // no direct load may outlive the wave
-    drain_mfma(acc[7]);
-  }
-
-  // ---- epilogues.  Accumulator element (i, j, e) of this lane is
-  //   row m = m0 + wm*128 + i*16 + 4*(lane>>4) + e      (FWD: the permuted row, see vrow below)
-  //   col n = n0 + wn*128 + j*16 + (lane & 15)
-  // (DW: row m = m0 + wm*128 + i*16 + (lane & 15), col n = n0 + wn*128 + j*16 + 4*(lane>>4) + e)
-  if (MODE == MODE_DH) __syncthreads();   // its staged epilogue reuses the panels' LDS
-
-  if (MODE == MODE_FWD) {
-    const unsigned char* const zt_lds = smem + PIPE_BYTES + (((wave_u & 1) * 128 + (lane_now() & 15)) << 2);
-    forward_epilogue<8>(p, acc, [&](int j) { return *reinterpret_cast<const float*>(zt_lds + j * 64); }, m0, n0,
-                        tm * 2 + (wave_u >> 1), wave_u >> 1, wave_u & 1, N);
-  } else if (MODE == MODE_DH) {
-    const int lane = lane_now(), wave = wave_u, tid = wave * 64 + lane;
-    const int wm = wave >> 1, wn = wave & 1, frow = lane & 15, fq = lane >> 4;
-    const int mrow_base = m0 + wm * 128 + 4 * fq;
-    const int ncol_base = n0 + wn * 128 + frow;
-    // rows = token rows of the chunk (scattered to their slots), cols = hidden index; a row
-    // of the stash times W is the row's dz W up to its scale -g / S, applied here
-    // an accumulator, read where it is used on all three paths: left to the compiler, the copies out of the
-    // accumulation registers are hoisted above the branches and 13 of them spilled to scratch memory behind
-    // every tile's K loop (16384 rows, d = 1024, V = 512, no dW: float output 188.4 us a call, now 182.9;
-    // bf16 output 165.2 and 163.6)
-    auto read_acc = [&](int i, int j, int e) {
-      float x;
-      asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(x) : "a"(acc[i][j][e]));
-      return x;
-    };
-    if (tail_out != nullptr) {
-      // a slice of the contraction: the accumulators as they are, [256][256] fp32
-#pragma unroll
-      for (int i = 0; i < 8; ++i)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          float* row = tail_out + (wm * 128 + i * 16 + 4 * fq + e) * BN + wn * 128 + frow;
-#pragma unroll
-          for (int j = 0; j < 8; ++j) row[j * 16] = read_acc(i, j, e);
-        }
-    } else if (p.dh_f32) {
-#pragma unroll
-      for (int i = 0; i < 8; ++i)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int m = mrow_base + i * 16 + e;
-          if (m < M) {
-            const float sc = p.row_scale[m];
-            float* row = reinterpret_cast<float*>(p.dH) + (int64_t)p.row_index[m] * p.d;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-              const int n = ncol_base + j * 16;
-              const float x = read_acc(i, j, e);
-              if (n < p.d) row[n] = sc * x;
-            }
-          }
-        }
-    } else {
-      // stage the tile as bf16 in LDS, [token][hidden], then 32 lanes store one 512-byte row segment
-      __bf16* st = reinterpret_cast<__bf16*>(smem);
-#pragma unroll
-      for (int i = 0; i < 8; ++i)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int m = mrow_base + i * 16 + e;
-          const float sc = p.row_scale[m < M ? m : M - 1];
-#pragma unroll
-          for (int j = 0; j < 8; ++j)
-            st[(wm * 128 + i * 16 + 4 * fq + e) * DHSTAGE_LD + wn * 128 + j * 16 + frow] = (__bf16)(sc * read_acc(i, j, e));
-        }
-      __syncthreads();
-#pragma unroll 4
-      for (int k = 0; k < 32; ++k) {
-        const int c = tid + NTHREADS * k;
-        const int row = c >> 5, col = c & 31;
-        if (m0 + row < M && n0 + col * 8 < p.d) {
-          const u32x4 v = *reinterpret_cast<const u32x4*>(smem + row * (DHSTAGE_LD * 2) + col * 16);
-          *reinterpret_cast<u32x4*>(reinterpret_cast<uint16_t*>(p.dH) + (int64_t)p.row_index[m0 + row] * p.d + n0 + col * 8) = v;
-        }
-      }
-    }
-  } else {
-    const int lane = lane_now(), wave = wave_u;
-    const int wm = wave >> 1, wn = wave & 1, frow = lane & 15, fq = lane >> 4;
-    // rows = vocabulary ids, cols = hidden index; fp32 accumulate into dW.  With the operands swapped a
-    // lane holds four consecutive columns of a row, so that dW is read and written 16 bytes at a
-    // time (d is a multiple of 8; with 4-byte accesses the launch took 1128 instead of 1023 us for 512 rows,
-    // V = 151936, d = 4096, and 127 instead of 109 for V = 32000, d = 2048).  The old values of one 16-row band
-    // are fetched as a batch before any store, so their latencies overlap.
-    // A K slice of a tail tile stores its partial tile as it is, [256][256] fp32, to the scratch
-    // area instead (dw_tail_reduce adds the slices in their order): the same code with the
-    // tile's own origin, row stride and bounds.
-    const bool tail = tail_out != nullptr;
-    float* const dst = tail ? tail_out : p.dW;
-    const int64_t ld = tail ? BN : p.d;
-    const int v_org = tail ? m0 : 0, n_org = tail ? n0 : 0;
-    const int v_end = tail ? m0 + BM : p.V, n_end = tail ? n0 + BN : p.d;
-    const bool overwrite = tail || p.overwrite;
-    const int vbase = m0 + wm * 128 + frow, nbase = n0 + wn * 128 + 4 * fq;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int v = vbase + i * 16;
-      float* const row = dst + (int64_t)((v < v_end ? v : v_end - 1) - v_org) * ld - n_org;
-      f32x4 old[8];
-      if (!overwrite) {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const int n = nbase + j * 16;
-          old[j] = *reinterpret_cast<const f32x4_any*>(row + (n < n_end ? n : n_end - 4));
-        }
-      }
-      if (v < v_end) {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const int n = nbase + j * 16;
-          f32x4 x = acc[i][j];
-          if (!overwrite) x = old[j] + x;
-          if (n < n_end) *reinterpret_cast<f32x4_any*>(row + n) = x;
-        }
-      }
-    }
+    tile_product<MODE, 8>(smem, tm, tn, tm * RES, p.V, k_first, nk, tail_out);
   }
 }
 
@@ -1085,7 +1284,7 @@ __global__ __launch_bounds__(NTHREADS, 2) void forward_few_bf16(Params p) {
     kt += 2;
   } while (kt < nk);
   __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
-  forward_epilogue<4>(p, acc, [&](int j) { return zt[j]; }, m0, 0, tm, 0, wave, N);
+  forward_epilogue<4>(p, [&](int i, int j, int e) { return acc_now(acc[i][j][e]); }, [&](int j) { return zt[j]; }, m0, wave * 64, tm, N);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1124,7 +1323,7 @@ __global__ __launch_bounds__(NTHREADS, 2) void dw_few_bf16(Params p) {
   if (nvalid == 0 && !p.overwrite) return;
   const int Mt = (p.V + DM - 1) / DM, Nt = (p.d + DN - 1) / DN;
   int tm, tn;
-  if (!dealt_tile(blockIdx.x, Mt, Nt, tm, tn)) return;
+  if (!dealt_tile<8>(blockIdx.x, Mt, Nt, tm, tn)) return;
   const int m0 = tm * DM, n0 = tn * DN;
   const int nk = dw_panels(nvalid, p.K) * (BK / DK);
 
@@ -1248,12 +1447,11 @@ __global__ __launch_bounds__(NTHREADS, 2) void dw_few_bf16(Params p) {
 // more), so the model keeps two groups of them per XCD and fills a group at a time.  With every compute unit
 // on its own, and compiled without optimisation, the plan took 680 us of host time at V = 151936, d = 4096
 // and 490 at V = 32000, d = 2048 (where the launch takes 110 us); now 3 and 1.
-struct DwTailPlan { int m0, rows, split, first[NXCD + 1]; };
+struct DwTailPlan { int m0, rows, split, first[NXCD + 1]; double end; };   // end: of the launch, in tile times
 DwTailPlan dw_tail_plan(int Mt, int Nt, int sup_m, int sup_n) {
   constexpr double kItemOverhead = 0.02;         // prologue, partial-tile store, reduce: in tile times
-  DwTailPlan best = {Mt / sup_m * sup_m, Mt % sup_m, 0, {}};
+  DwTailPlan best = {Mt / sup_m * sup_m, Mt % sup_m, 0, {}, 0};
   const int tiles = best.rows * Nt;
-  if (tiles == 0 || best.m0 == 0) return best;
   const int sNt = (Nt + sup_n - 1) / sup_n;
   // tiles per XCD of the first `rows_m` tile rows under the super-tile mapping
   auto tiles_per_xcd = [&](int rows_m, int (&t)[NXCD]) {
@@ -1273,6 +1471,8 @@ DwTailPlan dw_tail_plan(int Mt, int Nt, int sup_m, int sup_n) {
     unsplit = all > unsplit ? all : unsplit;
     whole_end = main > whole_end ? main : whole_end;
   }
+  best.end = unsplit;
+  if (tiles == 0 || best.m0 == 0) return best;
   double best_end = unsplit - kItemOverhead;     // a split has to beat the plain mapping by a margin
   for (int split = 2; split <= 8 && tiles * split <= kDwTailMaxItems; ++split) {
     struct Group { double free_at; int units, left; };   // `left` of the units have not taken an item at this time yet
@@ -1298,7 +1498,7 @@ DwTailPlan dw_tail_plan(int Mt, int Nt, int sup_m, int sup_n) {
       if (group[f].left == 0) { group[f].free_at = ends; group[f].left = group[f].units; }
     }
     if (end < best_end - 1e-9) {
-      best_end = end; best.split = split; best.first[0] = 0;
+      best_end = best.end = end; best.split = split; best.first[0] = 0;
       for (int x = 0; x < NXCD; ++x) best.first[x + 1] = best.first[x] + count[x];
     }
   }
@@ -1313,41 +1513,47 @@ __global__ __launch_bounds__(256) void dw_tail_reduce(const float* __restrict__ 
   const int nvalid = nv64 < 0 ? 0 : (nv64 > chunk_rows ? chunk_rows : (int)nv64);
   if (!overwrite && nvalid == 0) return;              // the GEMM launch left dW (and part) alone
   const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int t = (int)(q / (BM * BN)), within = (int)(q % (BM * BN));
+  const int t = (int)(q / (RES * RES)), within = (int)(q % (RES * RES));
   if (t >= tiles) return;
-  const int v = (tail_m0 + t / Nt) * BM + within / BN, n = (t % Nt) * BN + within % BN;
+  const int v = (tail_m0 + t / Nt) * RES + within / RES, n = (t % Nt) * RES + within % RES;
   if (v >= V || n >= d) return;
   float s = 0.f;
   const int slices = slices_in_use(dw_panels(nvalid, chunk_rows), split);
-  for (int k = 0; k < slices; ++k) s += part[((int64_t)k * tiles + t) * (BM * BN) + within];
+  for (int k = 0; k < slices; ++k) s += part[((int64_t)k * tiles + t) * (RES * RES) + within];
   float* out = dW + (int64_t)v * d + n;
   *out = overwrite ? s : *out + s;
 }
 
-// Adds the slices of the dH launch's tail tiles (slice 0 first), applies the row scale and scatters
-// the rows to their slots: 8 columns per thread.  Blocks beyond the tiles that the device finds cut
-// return at once.
+// Adds the slices of the tiles that the dH launch cut (slice 0 first), applies the row scale and scatters the rows to their
+// slots: 8 columns per thread.  Blocks beyond the tiles that the device finds cut return at once.
+constexpr int kReduceBlocks = RING * RES / 2048;      // per tile
+__device__ inline void add_slices(const float* part, int slices, int rest, int t, int within, f32x4& lo, f32x4& hi) {
+  lo = hi = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+  for (int s = 0; s < slices; ++s) {
+    const f32x4* q = reinterpret_cast<const f32x4*>(part + ((int64_t)s * rest + t) * (RING * RES) + within);
+    lo += q[0];
+    hi += q[1];
+  }
+}
 __global__ __launch_bounds__(256) void dh_tail_reduce(Params p) {
   int64_t nv64 = *p.n_scored - p.chunk_start;
   const int M = nv64 < 0 ? 0 : (nv64 > p.chunk_rows ? p.chunk_rows : (int)nv64);
-  const int Mt = (M + BM - 1) / BM, Nt = (p.N + BN - 1) / BN;
+  const int Nt = tiles_of(p.N, RES);
+  const Cut cut = cut_dh(M, Nt, p.K / BK);
+  const int Mt = cut.count();
   const int tiles = Mt * Nt, whole = tiles / kRound * kRound, rest = tiles - whole;
-  const int t = blockIdx.x / (BM * BN / 2048);
+  const int t = blockIdx.x / kReduceBlocks;
   if (t >= rest) return;
   const int split = dh_split(rest, p.K / BK, p.max_items);
   if (split == 1) return;
   int tm, tn;
-  tile_at(whole + t, Mt, Nt, tm, tn);
-  const int within = (blockIdx.x % (BM * BN / 2048)) * 2048 + threadIdx.x * 8;
-  const int m = tm * BM + within / BN, n = tn * BN + within % BN;
-  if (m >= M || n >= p.d) return;
-  f32x4 lo = {0.f, 0.f, 0.f, 0.f}, hi = lo;
-#pragma unroll 4
-  for (int s = 0; s < split; ++s) {
-    const f32x4* q = reinterpret_cast<const f32x4*>(p.tail_part + ((int64_t)s * rest + t) * (BM * BN) + within);
-    lo += q[0];
-    hi += q[1];
-  }
+  tile_at<4>(whole + t, Mt, Nt, tm, tn);
+  const int within = (blockIdx.x % kReduceBlocks) * 2048 + threadIdx.x * 8;
+  const int m = cut.start(tm) + within / RES, n = tn * RES + within % RES;
+  if (within / RES >= 32 * cut.blocks(tm) || m >= M || n >= p.d) return;
+  f32x4 lo, hi;
+  add_slices(p.tail_part, split, rest, t, within, lo, hi);
   const float sc = p.row_scale[m];
   const int64_t at = (int64_t)p.row_index[m] * p.d + n;
   if (p.dh_f32) {
@@ -1361,41 +1567,35 @@ __global__ __launch_bounds__(256) void dh_tail_reduce(Params p) {
     *reinterpret_cast<bf16x8*>(static_cast<uint16_t*>(p.dH) + at) = h;
   }
 }
+// The same for the dW launch on 384 x 256 tiles.
+__global__ __launch_bounds__(256) void dw_wide_reduce(Params p) {
+  int64_t nv64 = *p.n_scored - p.chunk_start;
+  const int nvalid = nv64 < 0 ? 0 : (nv64 > p.chunk_rows ? p.chunk_rows : (int)nv64);
+  const int panels = dw_panels(nvalid, p.K);
+  const int Mt = tiles_of(p.V, RING), Nt = tiles_of(p.d, RES), tiles = Mt * Nt, whole = tiles / kRound * kRound, rest = tiles - whole;
+  const int split = dw_split(rest, panels, p.max_items);
+  if (split == 1) return;
+  int tm, tn;
+  const int t = blockIdx.x / kReduceBlocks;
+  tile_at<4>(whole + t, Mt, Nt, tm, tn);
+  const int within = (blockIdx.x % kReduceBlocks) * 2048 + threadIdx.x * 8;
+  const int v = tm * RING + within / RES, n = tn * RES + within % RES;
+  if (v >= p.V || n >= p.d) return;
+  f32x4 lo, hi;
+  add_slices(p.tail_part, slices_in_use(panels, split), rest, t, within, lo, hi);
+  f32x4_any* const out = reinterpret_cast<f32x4_any*>(p.dW + (int64_t)v * p.d + n);
+  if (!p.overwrite) { lo = out[0] + lo; hi = out[1] + hi; }
+  out[0] = lo;
+  out[1] = hi;
+}
 
 template <int MODE>
-void launch(Params& p, hipStream_t stream) {
+void launch(Params& p, int blocks, hipStream_t stream) {
   static LdsLimit lds_limit;
-  lds_limit.ensure(reinterpret_cast<const void*>(&gemm_nt_bf16<MODE>), lds_bytes<MODE>());
-  const int Mt = (p.M + BM - 1) / BM, Nt = (p.N + BN - 1) / BN;
-  const SuperTile st = pick_super_tile(Nt);
-  p.sup_m = st.m; p.sup_n = st.n;
-  int blocks = MODE == MODE_DW ? num_blocks(Mt, Nt, st.m, st.n) : (Mt * Nt + NXCD - 1) / NXCD * NXCD;
-  DwTailPlan tail = {0, 0, 0, {}};
-  if (MODE == MODE_DW && p.tail_part != nullptr) tail = dw_tail_plan(Mt, Nt, st.m, st.n);
-  if (tail.split > 0) {
-    p.main_blocks = num_blocks(tail.m0, Nt, st.m, st.n);
-    p.tail_m0 = tail.m0; p.tail_rows = tail.rows; p.tail_split = tail.split;
-    int most = 0;
-    for (int x = 0; x < NXCD; ++x) {
-      p.tail_first[x] = tail.first[x];
-      most = tail.first[x + 1] - tail.first[x] > most ? tail.first[x + 1] - tail.first[x] : most;
-    }
-    p.tail_first[NXCD] = tail.first[NXCD];
-    blocks = p.main_blocks + most * NXCD;
-  }
-  if (MODE == MODE_DH) blocks = (Mt * Nt) / kRound * kRound + (int)round_up(dh_most_items(Mt * Nt, p.K / BK, p.max_items), NXCD);
-  hipLaunchKernelGGL(gemm_nt_bf16<MODE>, dim3(blocks), dim3(NTHREADS), lds_bytes<MODE>(), stream, p);
-  if (tail.split > 0) {
-    const int tiles = tail.rows * Nt;
-    hipLaunchKernelGGL(dw_tail_reduce, dim3(tiles * (BM * BN / 256)), dim3(256), 0, stream, p.tail_part, tiles,
-                       tail.split, Nt, tail.m0, p.V, p.d, p.dW, p.overwrite, p.n_scored, p.chunk_start,
-                       p.chunk_rows);
-  }
-  if (MODE == MODE_DH && dh_most_split(p.K / BK) > 1) {
-    const int most = Mt * Nt < kRound ? Mt * Nt : kRound - 1;
-    hipLaunchKernelGGL(dh_tail_reduce, dim3(most * (BM * BN / 2048)), dim3(256), 0, stream, p);
-  }
+  lds_limit.ensure(reinterpret_cast<const void*>(&gemm_nt_bf16<MODE>), tile_lds<kWide>());
+  hipLaunchKernelGGL(gemm_nt_bf16<MODE>, dim3(blocks), dim3(NTHREADS), tile_lds<kWide>(), stream, p);
 }
+int tiles(int64_t n, int size) { return (int)((n + size - 1) / size); }
 
 }  // namespace
 
@@ -1419,11 +1619,11 @@ void launch_gemm_fwd_bf16(const void* W, int64_t ldw, const void* W_tail, const 
   if (in_blocks) {
     static LdsLimit lds_limit;
     lds_limit.ensure(reinterpret_cast<const void*>(&forward_few_bf16), F_LDS);
-    const int Mt = 2 * ((p.M + BM - 1) / BM);
+    const int Mt = 2 * tiles(p.M, RES);
     hipLaunchKernelGGL(forward_few_bf16, dim3(Mt), dim3(NTHREADS), F_LDS, stream, p);
     return;
   }
-  launch<MODE_FWD>(p, stream);
+  launch<MODE_FWD>(p, (int)round_up((int64_t)tiles(p.M, RES) * tiles(chunk_rows, 256), NXCD), stream);
 }
 
 void launch_gemm_dh_bf16(const void* E, int64_t lde, const void* W, int64_t ldw, int V,
@@ -1439,16 +1639,29 @@ void launch_gemm_dh_bf16(const void* E, int64_t lde, const void* W, int64_t ldw,
   p.n_scored = n_scored; p.chunk_start = chunk_start; p.chunk_rows = chunk_rows;
   p.dH = dH; p.dh_f32 = dh_f32; p.d = d; p.V = V;
   p.tail_part = tail_part; p.max_items = tail_items;
-  launch<MODE_DH>(p, stream);
+  // (as many tiles as any count of scored rows can make: of 384, or one round of 256)
+  const int Nt = tiles(d, RES), wide = tiles(chunk_rows, RING) * Nt, narrow = tiles(chunk_rows, 256) * Nt, panels = p.K / BK;
+  const int most = wide >= kRound ? wide : narrow < kRound ? narrow : kRound;
+  launch<MODE_DH>(p, most / kRound * kRound + (int)round_up(dh_most_items(most, panels, p.max_items), NXCD), stream);
+  if (dh_most_split(panels) > 1)
+    hipLaunchKernelGGL(dh_tail_reduce, dim3((most < kRound ? most : kRound - 1) * kReduceBlocks), dim3(256), 0, stream, p);
 }
 
-size_t gemm_tail_tile_bytes() { return (size_t)BM * BN * sizeof(float); }
-int gemm_dw_tail_items() { return kDwTailMaxItems; }
+size_t gemm_tail_tile_bytes() { return (size_t)RING * RES * sizeof(float); }
+// One partial tile per compute unit for the dW launch; the dH launch's last round of up to 255 tiles can use up to four; a
+// quarter of the size of the head, which has the longer tiles the larger it is, bounds the extra ones.
+int gemm_tail_items(size_t head_bytes) {
+  const size_t extra = head_bytes / 4 / ((size_t)RES * RES * sizeof(float));
+  return kDwTailMaxItems + (int)(extra < 768 ? extra : 768);
+}
+// (as many of 256 x 256: what a workspace had before the tiles grew; their last round is then cut into fewer slices)
+size_t gemm_tail_bytes_least(size_t head_bytes) { return (size_t)gemm_tail_items(head_bytes) * RES * RES * sizeof(float); }
 bool dw_rows_in_blocks(int rows) { return rows <= kFewDwRows; }
 
 void launch_gemm_dw_bf16(const void* E, int64_t lde, const void* Ht, int64_t ldht,
                          const int64_t* n_scored, int64_t chunk_start, int chunk_rows,
-                         int V, int d, float* dW, int overwrite, float* tail_part, bool in_blocks, hipStream_t stream) {
+                         int V, int d, float* dW, int overwrite, float* tail_part, int tail_items, int rows, bool in_blocks,
+                         hipStream_t stream) {
   Params p = {};
   p.A = static_cast<const uint16_t*>(E); p.lda = lde; p.M = (int)round_up(V, kTile);
   p.B = static_cast<const uint16_t*>(Ht); p.ldb = ldht; p.N = d;
@@ -1465,7 +1678,49 @@ void launch_gemm_dw_bf16(const void* E, int64_t lde, const void* Ht, int64_t ldh
     hipLaunchKernelGGL(dw_few_bf16, dim3((unsigned)round_up(tiles, NXCD)), dim3(NTHREADS), D_LDS, stream, p);
     return;
   }
-  launch<MODE_DW>(p, stream);
+  // 384 x 256 tiles, or 256 x 256 ones where those end earlier (short contractions over few rounds of tiles, whose last round the
+  // cut does not pay for): 1.43 of the other tile's time, and about 8 panels' time per tile for its epilogue in either.
+  // Launch, us, 256 x 256 and 384 x 256: V = 151936, 65536 rows, d = 4096 53800 and 50960, 47360 rows, d = 3584 34074 and 30363, 5120 rows,
+  // d = 1536 1797 and 1675; V = 128256, 2000 rows, d = 1024 457 and 438.
+  const int Nt = tiles(d, RES), wide_tiles = tiles(V, RING) * Nt, rest = wide_tiles % kRound;
+  const int expected = tiles(rows, BK), most_panels = chunk_rows / BK;
+  p.max_items = tail_items;
+  const SuperTile st = pick_super_tile(Nt);
+  const DwTailPlan tail = dw_tail_plan(tiles(V, RES), Nt, st.m, st.n);
+  const int split = rest > 0 ? dw_split(rest, expected, tail_items) : 1;
+  const double last = rest == 0 ? 0 : split == 1 ? expected + 6 : tiles(rest * split, kRound) * ((expected + split - 1) / split + 6) + 12;
+  p.wide = 1.43 * (wide_tiles / kRound * (expected + 6) + last) <= tail.end * (expected + 8);
+  if (p.wide) {
+    int blocks = wide_tiles;
+    int most_split = 1;
+    if (rest > 0 && most_panels >= 16) {              // (as many slices as any count of scored rows can make)
+      most_split = most_panels / 8 < 64 ? most_panels / 8 : 64;
+      const int items = rest * most_split < tail_items ? rest * most_split : tail_items;
+      blocks = wide_tiles - rest + (items > rest ? items : rest);
+    }
+    launch<MODE_DW>(p, (int)round_up(blocks, NXCD), stream);
+    if (most_split > 1) hipLaunchKernelGGL(dw_wide_reduce, dim3(rest * kReduceBlocks), dim3(256), 0, stream, p);
+    return;
+  }
+  p.sup_m = st.m; p.sup_n = st.n;
+  p.main_blocks = num_blocks(tail.split > 0 ? tail.m0 : tiles(V, RES), Nt, st.m, st.n);
+  int blocks = p.main_blocks;
+  if (tail.split > 0) {
+    p.tail_m0 = tail.m0; p.tail_rows = tail.rows; p.tail_split = tail.split;
+    int most = 0;
+    for (int x = 0; x < NXCD; ++x) {
+      p.tail_first[x] = tail.first[x];
+      most = tail.first[x + 1] - tail.first[x] > most ? tail.first[x + 1] - tail.first[x] : most;
+    }
+    p.tail_first[NXCD] = tail.first[NXCD];
+    blocks += most * NXCD;
+  }
+  launch<MODE_DW>(p, blocks, stream);
+  if (tail.split > 0) {
+    const int n = tail.rows * Nt;
+    hipLaunchKernelGGL(dw_tail_reduce, dim3(n * (RES * RES / 256)), dim3(256), 0, stream, tail_part, n, tail.split, Nt, tail.m0, V, d, dW,
+                       overwrite, n_scored, chunk_start, chunk_rows);
+  }
 }
 
 }  // namespace mrl
@@ -1482,7 +1737,7 @@ extern "C" int mrl_diag_dw_tail_plan(int32_t V, int32_t d, int32_t* out12) {
   using namespace mrl;
   if (out12 == nullptr) return MRL_ERR_NULL;
   if (V <= 0 || d <= 0) return MRL_ERR_SHAPE;
-  const int Mt = (int)(round_up(V, kTile) / BM), Nt = (d + BN - 1) / BN;
+  const int Mt = tiles(V, RES), Nt = tiles(d, RES);
   const SuperTile st = pick_super_tile(Nt);
   const DwTailPlan t = dw_tail_plan(Mt, Nt, st.m, st.n);
   out12[0] = t.m0; out12[1] = t.rows; out12[2] = t.split;

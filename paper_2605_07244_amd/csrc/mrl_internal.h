@@ -84,16 +84,18 @@ void launch_gemm_dh_bf16(const void* E, int64_t lde, const void* W, int64_t ldw,
 // columns >= V must be zero), B = Ht [d, chunk_rows] (the pass's hidden rows, each already
 // multiplied by its row scale); dW[v, :] = (or +=) sum over the chunk's valid rows.
 // overwrite = 1 stores, 0 adds into the existing values.
-// tail_part: scratch of gemm_dw_tail_items() * gemm_tail_tile_bytes() bytes for the K-split tail tiles (nullptr: the
-// ragged last rows of tiles run as whole tiles).
+// tail_part: scratch of tail_items * gemm_tail_tile_bytes() bytes (gemm_tail_bytes_least() or more) for the K slices of the last
+// tiles; rows: the scored rows expected (which tiles the launch takes; right for any number).
 // in_blocks: the launch for few rows, with Ht in blocks of kRowBlock token rows, [chunk_rows / 32][ldht][32], ldht = d
 // rounded up to 128; dw_rows_in_blocks says where it is the faster one (rows: the scored rows expected; right for any number).
 size_t gemm_tail_tile_bytes();
-int gemm_dw_tail_items();
+int gemm_tail_items(size_t head_bytes);               // of a workspace, for a head of so many bytes
+size_t gemm_tail_bytes_least(size_t head_bytes);      // ... in one that has no room for them all
 bool dw_rows_in_blocks(int rows);
 void launch_gemm_dw_bf16(const void* P, int64_t ldp, const void* Ht, int64_t ldht,
                          const int64_t* n_scored, int64_t chunk_start, int chunk_rows,
-                         int V, int d, float* dW, int overwrite, float* tail_part, bool in_blocks, hipStream_t stream);
+                         int V, int d, float* dW, int overwrite, float* tail_part, int tail_items, int rows, bool in_blocks,
+                         hipStream_t stream);
 
 // ---- fp32 GEMM (small-shape path): C[m][n] = sum_k A[m][k] * B[n][k] --------
 // An operand is k-contiguous (element (row, k) at row * ld + k) or, with its kmajor flag, stored with

@@ -514,3 +514,49 @@ def test_prep_inside_the_row_preparation(mrl, B, T, extra):
     assert torch.equal(a["dW"], b["dW"])
     assert all(torch.equal(p, q[:N]) and torch.all(q[N:] == 0) for p, q in zip(ca, cb))
     assert torch.all(a["logp"][mask[:N] == 0] == 0) and torch.all(a["dH"][mask[:N] == 0] == 0)
+
+
+@pytest.mark.parametrize("scored,d,V,chunk_rows", [
+    (600, 128, 32005, 1280),      # forward: a column of 384 and one of 256, a ragged last row of W; dH: two rows of tiles of 256 and a half one
+    (700, 136, 32000, 0),         # two columns of 384, the second with 316 tokens; a padded width
+    (1152, 256, 30001, 2048),     # three whole columns; dW on 79 rows of 384, the last with 49
+    (2000, 256, 40003, 0),        # dW: 105 tiles of two slices
+    (2000, 264, 40003, 1280),     # ... and a second pass that adds into the first's result
+    (4200, 1032, 9999, 0),        # dW: 135 tiles whole; dH: 55 tiles of four slices
+    (3500, 2056, 21000, 0),       # dW: 495 tiles, 239 behind a whole round; dH rows of 384 and a short one
+])
+def test_tiles_of_384(mrl, scored, d, V, chunk_rows):
+    """The large tiles of the three products: whole, ragged and in slices; the log-probs have the bits that a pass of few rows gives."""
+    N = scored + 21
+    H, W, y, mask = _head(N, d, V, scored, scored + d)
+    out, dH, dW = _step(mrl, H, W, y, mask, mrl.BF16, d, chunk_rows=chunk_rows, poison=True)
+    util.check_gradient("dH", util.to_f64(out["dH"]), dH)
+    util.check_gradient("dW", util.to_f64(out["dW"]), dW)
+    assert torch.all(out["dH"][mask == 0] == 0) and torch.all(out["logp"][mask == 0] == 0)
+    again, _, _ = _step(mrl, H, W, y, mask, mrl.BF16, d, chunk_rows=chunk_rows, poison=True)
+    assert all(torch.equal(out[k], again[k]) for k in ("logp", "dH", "dW"))
+    for first in (0, N - 200):
+        few, _ = mrl.token_logprobs(H[first:first + 200], W, y[first:first + 200], mask[first:first + 200])
+        assert torch.equal(few, out["logp"][first:first + 200])
+
+
+def test_workspace_without_room_for_all_partial_tiles(mrl):
+    """A loss call takes a workspace whose end holds two thirds of the partial tiles (what it held when they were 256 x 256), and none
+    smaller: the tiles of the last rounds are cut into fewer slices."""
+    scored, d, V = 900, 1024, 30000
+    H, W, y, mask = _head(scored, d, V, scored, 3)
+    cfg = mrl.LossConfig(kl_beta=0.0, chunk_rows=1024)
+    full = mrl.grpo_loss_workspace(1, scored, d, V, mrl.BF16, cfg)
+    items = 256 + min(768, d * (-(-V // 256) * 256 + 64) * 2 // 4 // (256 * 256 * 4))
+    least = full - items * 128 * 256 * 4
+    one = lambda v, t: torch.tensor([v], dtype=t, device="cuda")
+    call = lambda n: mrl.grpo_loss_fwd_bwd(H, W, y, mask, torch.full((scored,), -10.0, device="cuda"), None, one(0.7, torch.float32),
+                                           one(0, torch.int32), None, 1, scored, 1, cfg, workspace=torch.full((n,), 255, dtype=torch.uint8, device="cuda"))
+    want, got = call(full), call(least)
+    torch.cuda.synchronize()
+    assert torch.equal(got["logp"], want["logp"])
+    # dH is a bf16 result of fp32 sums in another order: neighbours at most; dW's order does not change
+    assert float((got["dH"].float() - want["dH"].float()).abs().max()) <= 2 ** -7 * float(want["dH"].float().abs().max())
+    util.check_gradient("dW", util.to_f64(got["dW"]), util.to_f64(want["dW"]))
+    with pytest.raises(RuntimeError):
+        call(least - 256)
