@@ -752,8 +752,7 @@ constexpr int load_index_base(int g) {      // loads issued before group g, in t
 constexpr int kLoadsCarriedOver = kLoadsInGroup[0] + kLoadsInGroup[1] + kLoadsInGroup[2] + kLoadsInGroup[3] + kLoadsInGroup[4];
 static_assert(kLoadsCarriedOver + kLoadsInGroup[5] + kLoadsInGroup[6] + kLoadsInGroup[7] == 16, "a slot takes 16 loads per wave");
 
-__device__ __forceinline__ void square_tile(unsigned char* smem, int tm, int tn, int n0, int N) {
-  const Params& p = args_now();
+__device__ __forceinline__ void square_tile(const Params& p, unsigned char* smem, int tm, int tn, int n0, int N) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave >> 1, wn = wave & 1, frow = lane & 15, fq = lane >> 4;
   const int m0 = tm * RES, M = p.M, nk = p.K / BK;
@@ -870,7 +869,7 @@ __device__ __forceinline__ void square_tile(unsigned char* smem, int tm, int tn,
   __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));          // no direct load may outlive the wave
   asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
   const unsigned char* const zt_lds = smem + PIPE_BYTES + ((wn * 128 + (lane_now() & 15)) << 2);
-  forward_epilogue<8>(args_now(), [&](int i, int j, int e) { return acc_now(acc[i][j][e]); },
+  forward_epilogue<8>(p, [&](int i, int j, int e) { return acc_now(acc[i][j][e]); },
                       [&](int j) { return *reinterpret_cast<const float*>(zt_lds + j * 64); }, m0 + wm * 128, n0 + wn * 128, tm * 2 + wm, N);
 }
 
@@ -1036,18 +1035,18 @@ __device__ inline Cut cut_dh(int n, int cols, int panels) {
 // one waits for them.  Scoring call, us, 256 x 256 (and half) tiles and tiles of 384: V = 151936, d = 4096, 384 rows 451 and 466,
 // 600 rows 725 and 683, 1920 rows 1900 and 1763; d = 1536, 384 rows 188 and 204; V = 50257, d = 712, 384 rows 63 and 54, 1280 rows 115
 // and 132, 1920 rows 178 and 159; V = 32000, d = 2048, 300 rows 57 and 70, 600 rows 101 and 84, 1000 rows 108 and 138, 1920 rows 199 and 212.
-__device__ inline int forward_end(const Cut& c, int rows) {
-  constexpr int kWideTile = 143, kNarrowTile = 100, kHalfTile = 58;
-  const int w = c.wide * rows, n = c.narrow * rows, h = c.half * rows, tiles = w + n + h;
+__device__ inline uint32_t forward_end(const Cut& c, int rows) {     // (below 2^32: 61440 rows are 160 columns, 2^24 ids 65536 rows)
+  constexpr uint32_t kWideTile = 143, kNarrowTile = 100, kHalfTile = 58;
+  const uint32_t w = c.wide * rows, n = c.narrow * rows, h = c.half * rows, tiles = w + n + h;
   if (tiles <= kRound) return w ? kWideTile : n ? kNarrowTile : kHalfTile;
   if (n + h == 0) return (w + kRound - 1) / kRound * (c.wide == 1 ? kWideTile + 14 : kWideTile);
   if (w + h == 0) return (n + kRound - 1) / kRound * kNarrowTile;
-  return (int)(((int64_t)w * kWideTile + (int64_t)n * kNarrowTile + h * kHalfTile) / kRound) + (w ? (h ? 80 : 60) : 30);
+  return (w * kWideTile + n * kNarrowTile + h * kHalfTile) / kRound + (w ? (h ? 80 : 60) : 30);
 }
 __device__ inline Cut cut_forward(int n, int rows) {
   const Cut a = cut_wide(n), b = cut_narrow(n);
   const Cut c = a.narrow + a.half == 0 ? Cut{a.wide - 1, 1, 1} : a;
-  const int ea = forward_end(a, rows), eb = forward_end(b, rows), ec = forward_end(c, rows);
+  const uint32_t ea = forward_end(a, rows), eb = forward_end(b, rows), ec = forward_end(c, rows);
   return eb < ea && eb <= ec ? b : ec < ea ? c : a;
 }
 
@@ -1071,8 +1070,9 @@ __global__ __launch_bounds__(NTHREADS) void gemm_nt_bf16(Params p) {
       tn = tn < Nt ? tn : tn - Nt;
     }
     const int n0 = cut.start(tn), blocks = cut.blocks(tn);
+    // (the arguments as they are in the short one's: read again they are two scalar latencies a tile, 1 % at 8 panels)
     if (blocks == 4) half_column_tile(smem, tm, n0, nvalid);
-    else if (blocks == 8) square_tile(smem, tm, tn, n0, nvalid < n0 + 256 ? nvalid : n0 + 256);
+    else if (__builtin_expect(blocks == 8, 1)) square_tile(p, smem, tm, tn, n0, nvalid < n0 + 256 ? nvalid : n0 + 256);
     else tile_product<MODE, kWide>(smem, tn, tm, n0, nvalid, 0, p.K / BK, nullptr);
   } else if (MODE == MODE_DH) {
     const int Nt = tiles_of(p.N, RES);
