@@ -264,23 +264,20 @@ void prepare_chunk(const void* H, const void* W, const int32_t* targets, int d, 
 // 1022 and 991, 8000 rows 1888 and 1904; V = 50257, d = 712, 2000 rows 190 and 183, 4000 rows 323 and 324;
 // with rows of whole lines, d = 1984, 8000 rows 3277 and 3123.
 bool head_tail_only(int d, int chunk_rows) { return d > 128 && (d % 64 == 0 || chunk_rows <= kTailOnlyRows); }
-void pad_head(const void* W, int d, int V, const Layout& L, void* ws, hipStream_t s) {
-  if (L.Wp == 0) return;
-  if (head_tail_only(d, L.chunk_rows)) {
-    const int first = L.dp - 128;
-    launch_pad_rows_b16(static_cast<const uint16_t*>(W) + first, d, at<void>(ws, L.Wp), d, V, d - first, 128, s);
-  } else {
-    launch_pad_rows_b16(W, d, at<void>(ws, L.Wp), L.ldh, V, d, L.dp, s);
-  }
+PadRows pad_head(const void* W, int d, int V, const Layout& L, void* ws) {
+  if (L.Wp == 0) return PadRows{nullptr, 0, nullptr, 0, 0, 0, 8};
+  if (!head_tail_only(d, L.chunk_rows)) return PadRows{W, d, at<void>(ws, L.Wp), L.ldh, V, d, L.dp};
+  const int first = L.dp - 128;
+  return PadRows{static_cast<const uint16_t*>(W) + first, d, at<void>(ws, L.Wp), d, V, d - first, 128};
 }
 
 // What comes before the first pass's row preparation: the compaction, unless that does it itself, and the padded columns of W.
 void prepare_call(const uint8_t* mask, const int32_t* targets, const void* W, int64_t N, int d, int V, const PrepOut& po,
                   const Layout& L, void* ws, hipStream_t s) {
-  if (prep_inline(N) && L.Wp == 0) return;
+  const PadRows pad = pad_head(W, d, V, L, ws);
+  if (prep_inline(N) && pad.rows == 0) return;
   Scope sc(MRL_PROF_PREP, s);
-  if (!prep_inline(N)) launch_prep(mask, targets, N, V, po, s);
-  pad_head(W, d, V, L, ws, s);
+  if (prep_inline(N)) launch_pad_rows_b16(pad, s); else launch_prep(mask, targets, N, V, po, pad, s);
 }
 
 // forward of one chunk: logits tile GEMM with fused (or, in fp32, separate) log-sum-exp

@@ -103,11 +103,36 @@ template <int WAVES> __device__ inline void count_sequences(const uint8_t* mask,
 // blocks the above takes
 inline int64_t sequence_blocks(int64_t B, int T, int waves) { return T > kLongSequence ? B : (B + waves - 1) / waves; }
 
-// Block 0: N <= kPrepOneBlock slots, a contiguous run of them per wave.  Blocks 1 ..: the sequences.
+// Row copy with zero padding: out[r][0:dp] = in[r][0:d] | 0, for a W whose width is no multiple of the forward
+// kernel's 128-wide panel pairs: its last 128 columns, or all of it where it is narrower than that or its
+// rows are no whole lines and the pass is long (head_tail_only in mrl_api.hip).
+constexpr int PAD_VECTORS = 4;                          // 16-byte vectors per thread
+template <int THREADS> __device__ inline void pad_rows(const PadRows& p, int64_t block) {
+  const int per_row = p.dp / 8;
+#pragma unroll
+  for (int k = 0; k < PAD_VECTORS; ++k) {
+    const int64_t i = (block * PAD_VECTORS + k) * THREADS + threadIdx.x;
+    const int64_t r = i / per_row;
+    if (r >= p.rows) return;
+    const int c = (int)(i - r * per_row) * 8;
+    uint4 v = make_uint4(0, 0, 0, 0);
+    if (c < p.d) v = *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(p.in) + r * p.ld_in + c);
+    *reinterpret_cast<uint4*>(static_cast<uint16_t*>(p.out) + r * p.ld_out + c) = v;
+  }
+}
+inline int64_t pad_blocks(const PadRows& p, int threads) {
+  const int64_t per_block = PAD_VECTORS * threads;
+  return (p.rows * (p.dp / 8) + per_block - 1) / per_block;
+}
+__global__ __launch_bounds__(256) void k_pad_rows_b16(PadRows p) { pad_rows<256>(p, blockIdx.x); }
+
+// Block 0: N <= kPrepOneBlock slots, a contiguous run of them per wave.  The blocks behind it: the sequences, up to first_pad, and the padded
+// columns of W, if there are any (a launch of their own: scoring call of 3003 slots, V = 50257, d = 712 158 us, now 153).
 __global__ __launch_bounds__(kPrepThreads) void k_prep_one(const uint8_t* mask, const int32_t* targets, int N, int V,
                                                            int64_t* n_scored, int64_t* n_bad, int32_t* row_index,
-                                                           SlotOutputs zero, int64_t B, int T, int32_t* seq_len) {
+                                                           SlotOutputs zero, int64_t B, int T, int32_t* seq_len, PadRows pad, int first_pad) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  if ((int)blockIdx.x >= first_pad) { pad_rows<kPrepThreads>(pad, (int64_t)blockIdx.x - first_pad); return; }
   if (blockIdx.x > 0) {
     count_sequences<kPrepWaves>(mask, targets, (int64_t)blockIdx.x - 1, B, T, V, seq_len);
     return;
@@ -599,23 +624,31 @@ __global__ __launch_bounds__(256) void k_row_lse_f32(const float* Z, int64_t ldz
 // Row epilogue: merge partials -> lse, log-prob; Eq. (1) token terms; loss partials; for the
 // bf16 backward the row scale -g / S and the patch of the stash's target column.
 // Block = 64 rows x 64 partial lanes: a thread adds every 64th partial of 4 neighbouring rows (16-byte
-// loads, 8 in flight), so that a pass of few rows is not a chain of hundreds of dependent-latency
+// loads, EPI_FLIGHT in flight, the last batch filled up: V = 50257 has 394 partials, seven per thread, which the remainder of a loop
+// unrolled by eight took one latency after the other: 6.0 us for 1877 rows, now 4.9), so that a pass of few rows is not a chain of hundreds of dependent-latency
 // loads (with 4 lanes per row: 112 us for 1188 partials and 201 rows; now 9 us, and 72 us instead of 150
 // for 65536 rows, whose partials are 311 MB).
 // ----------------------------------------------------------------------------
 constexpr int EPI_ROWS = 64;
 constexpr int EPI_THREADS = 1024;
 constexpr int EPI_LANES = EPI_THREADS / (EPI_ROWS / 4);
+constexpr int EPI_FLIGHT = 10;
 // Sum over all partials of this block's 64 rows; the result is valid in threads 0 .. 63 (one row
 // each).  Fixed order.  src points at the block's first row; rows beyond the valid ones hold
 // whatever the buffer held.  All threads must call it.
 __device__ inline float merge_partials(const float* src, int64_t stride, int n_partials, float4 (&sh)[EPI_LANES][EPI_ROWS / 4]) {
   const int quad = threadIdx.x & 15, part = threadIdx.x >> 4;
   float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll 8
-  for (int p = part; p < n_partials; p += EPI_LANES) {
-    const float4 v = *reinterpret_cast<const float4*>(src + (int64_t)p * stride + quad * 4);
-    s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+  for (int p0 = part; p0 < n_partials; p0 += EPI_LANES * EPI_FLIGHT) {
+    float4 v[EPI_FLIGHT];
+#pragma unroll
+    for (int k = 0; k < EPI_FLIGHT; ++k) {
+      const int p = p0 + k * EPI_LANES;
+      v[k] = *reinterpret_cast<const float4*>(src + (int64_t)(p < n_partials ? p : n_partials - 1) * stride + quad * 4);
+    }
+#pragma unroll
+    for (int k = 0; k < EPI_FLIGHT; ++k)
+      if (p0 + k * EPI_LANES < n_partials) { s.x += v[k].x; s.y += v[k].y; s.z += v[k].z; s.w += v[k].w; }
   }
   __syncthreads();                                  // an earlier merge has been read
   sh[part][quad] = s;
@@ -841,27 +874,6 @@ __global__ __launch_bounds__(256) void k_convert_f32(float* ZP, int64_t ldz, con
   }
 }
 
-// ----------------------------------------------------------------------------
-// Row copy with zero padding: Out[r][0:dp] = In[r][0:d] | 0, for a W whose width is no multiple of the forward
-// kernel's 128-wide panel pairs: its last 128 columns, or all of it where it is narrower than that or its
-// rows are no whole lines and the pass is long (head_tail_only in mrl_api.hip).
-// ----------------------------------------------------------------------------
-constexpr int PAD_VECTORS = 4;                          // 16-byte vectors per thread
-__global__ __launch_bounds__(256) void k_pad_rows_b16(const uint16_t* in, int64_t ld_in, uint16_t* out, int64_t ld_out,
-                                                      int64_t n_rows, int d, int dp) {
-  const int per_row = dp / 8;
-#pragma unroll
-  for (int k = 0; k < PAD_VECTORS; ++k) {
-    const int64_t i = ((int64_t)blockIdx.x * PAD_VECTORS + k) * 256 + threadIdx.x;
-    const int64_t r = i / per_row;
-    if (r >= n_rows) return;
-    const int c = (int)(i - r * per_row) * 8;
-    uint4 v = make_uint4(0, 0, 0, 0);
-    if (c < d) v = *reinterpret_cast<const uint4*>(in + r * ld_in + c);
-    *reinterpret_cast<uint4*>(out + r * ld_out + c) = v;
-  }
-}
-
 // Backward operand of the dW launch, bf16: Ht[c][r] (or, in blocks of 32 rows, Ht[r / 32][c][r % 32]) = scale[r] * Hc[r][c] for the pass's valid
 // rows, zeros up to the multiple of 128 the contraction runs over.  Tile 64 rows x 64 cols; n_cols a
 // multiple of 64, 16-byte aligned rows on both sides.  The blocks behind the tiles clear the stash
@@ -930,14 +942,20 @@ __global__ __launch_bounds__(256) void k_backward_rows_b16(const uint16_t* in, i
 }  // namespace
 
 // ------------------------------------------------------------------ launchers
-void launch_prep(const uint8_t* mask, const int32_t* targets, int64_t N, int V, const PrepOut& o, hipStream_t stream) {
+void launch_pad_rows_b16(const PadRows& p, hipStream_t stream) {
+  hipLaunchKernelGGL(k_pad_rows_b16, dim3((unsigned)pad_blocks(p, 256)), dim3(256), 0, stream, p);
+}
+
+void launch_prep(const uint8_t* mask, const int32_t* targets, int64_t N, int V, const PrepOut& o, const PadRows& pad, hipStream_t stream) {
   const SlotOutputs zero = {{o.zero[0], o.zero[1], o.zero[2]}};
   const int64_t B = o.seq_len != nullptr ? o.B : 0;
   if (N <= kPrepOneBlock) {
-    hipLaunchKernelGGL(k_prep_one, dim3((unsigned)(1 + sequence_blocks(B, o.T, kPrepWaves))), dim3(kPrepThreads), 0, stream,
-                       mask, targets, (int)N, V, o.n_scored, o.n_bad, o.row_index, zero, B, o.T, o.seq_len);
+    const int first_pad = (int)(1 + sequence_blocks(B, o.T, kPrepWaves));
+    hipLaunchKernelGGL(k_prep_one, dim3((unsigned)(first_pad + pad_blocks(pad, kPrepThreads))), dim3(kPrepThreads), 0, stream,
+                       mask, targets, (int)N, V, o.n_scored, o.n_bad, o.row_index, zero, B, o.T, o.seq_len, pad, first_pad);
     return;
   }
+  if (pad.rows > 0) launch_pad_rows_b16(pad, stream);
   const int64_t nblocks = (N + PREP_PER_BLOCK - 1) / PREP_PER_BLOCK, seq_blocks = sequence_blocks(B, o.T, PREP_BLOCK / 64);
   // block_counts: [2 * nblocks] int32 counts followed (8-byte aligned) by [nblocks] int64 offsets
   int64_t* block_offsets = reinterpret_cast<int64_t*>(o.block_counts + round_up(2 * nblocks, 2));
@@ -995,13 +1013,6 @@ void launch_convert_f32(float* ZP, int64_t ldz, const float* lse_c,
   dim3 grid(gx, chunk_rows);
   hipLaunchKernelGGL(k_convert_f32, grid, dim3(256), 0, stream, ZP, ldz, lse_c, g_c, targets,
                      row_index, n_scored, chunk_start, chunk_rows, V);
-}
-
-void launch_pad_rows_b16(const void* in, int64_t ld_in, void* out, int64_t ld_out, int64_t n_rows, int d, int dp,
-                         hipStream_t stream) {
-  const int64_t per_block = PAD_VECTORS * 256;
-  hipLaunchKernelGGL(k_pad_rows_b16, dim3((unsigned)((n_rows * (dp / 8) + per_block - 1) / per_block)), dim3(256), 0, stream,
-                     static_cast<const uint16_t*>(in), ld_in, static_cast<uint16_t*>(out), ld_out, n_rows, d, dp);
 }
 
 void launch_backward_rows_b16(const void* Hc, int64_t ldh, const float* scale, void* Ht, int64_t ldht,

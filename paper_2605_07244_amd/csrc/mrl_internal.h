@@ -130,7 +130,12 @@ struct PrepOut {
   float* zero[3];       // per-slot outputs that unscored slots set to 0 (or nullptr)
   int64_t B; int T; int32_t* seq_len;   // scored slots (valid targets only) per sequence of T slots, if not nullptr
 };
-void launch_prep(const uint8_t* mask, const int32_t* targets, int64_t N, int V, const PrepOut& o,
+// out[r][0:dp] = in[r][0:d], zero in [d, dp), r < rows (0: nothing to do).  16-byte vectors: d, dp, both row strides
+// multiples of 8 elements, both pointers 16-byte aligned.
+struct PadRows { const void* in; int64_t ld_in; void* out; int64_t ld_out; int64_t rows; int d, dp; };
+void launch_pad_rows_b16(const PadRows& p, hipStream_t stream);
+// The compaction, and what of W is to be padded.
+void launch_prep(const uint8_t* mask, const int32_t* targets, int64_t N, int V, const PrepOut& o, const PadRows& pad,
                  hipStream_t stream);
 // Calls of at most kPrepInline slots take no launch_prep: the first launch_row_prep of the call is given its outputs.
 // (Every block scans all slots, in a loop unrolled to this length.  Scoring calls, d = 64, V = 1000, us, with a launch and inline: 201
@@ -204,11 +209,6 @@ void launch_convert_f32(float* ZP, int64_t ldz, const float* lse_c,
                         const float* g_c, const int32_t* targets, const int32_t* row_index,
                         const int64_t* n_scored, int64_t chunk_start, int chunk_rows, int V,
                         hipStream_t stream);
-
-// Out[r][0:dp] = In[r][0:d], zero in [d, dp), r < n_rows.  16-byte vectors: d, dp, both row strides
-// multiples of 8 elements, both pointers 16-byte aligned.
-void launch_pad_rows_b16(const void* in, int64_t ld_in, void* out, int64_t ld_out, int64_t n_rows, int d, int dp,
-                         hipStream_t stream);
 
 // bf16 path, operands of the dW launch (Hc as the row preparation wrote it): Ht[c][r] = scale[r] * Hc[r][c] (c < dp, a multiple of 64) for the
 // pass's valid rows, zeros up to their multiple of 128; the stash rows in between are cleared (the
