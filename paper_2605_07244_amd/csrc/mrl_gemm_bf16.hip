@@ -355,7 +355,8 @@ constexpr int DHSTAGE_LD = 128 + 8;                   // bf16 elements per row o
 static_assert(tile_lds<12>() == 160 * 1024 && tile_lds<8>() <= tile_lds<12>() && tile_lds<4>() <= tile_lds<12>(), "all of a compute unit's LDS");
 static_assert(4 * 96 * DHSTAGE_LD * 2 <= tile_lds<12>(), "half a wave's rows, four waves");
 
-// The kernel's arguments, read again where they are used: kept alive across the K loop they cost scalar spills.
+// The kernel's arguments, read again where they are used: kept alive across the forward's K loop they cost scalar registers (15360 rows,
+// d = 2048 5556 us a scoring call, 5673 without); dH and dW have enough (5120 rows, d = 1536 dH 1553 and 1535 us, dW 1688 and 1667).
 __device__ __forceinline__ const Params& args_now() {
   typedef const __attribute__((address_space(4))) Params* KernArg;
   KernArg arg = (KernArg)__builtin_amdgcn_kernarg_segment_ptr();
@@ -499,7 +500,7 @@ __device__ __forceinline__ void load_lds16(uint32_t voff, uint32_t soff, const u
 // Loads go through buffer descriptors that end with the operand's last row and are emptied behind the last panel: edges need
 // no clamped addresses, and nothing is fetched twice at a tile's end.
 template <int MODE, int NJ>
-__device__ __forceinline__ void tile_product(unsigned char* smem, int ring_tile, int res_tile, int ring0, int ring_end,
+__device__ __forceinline__ void tile_product(const Params& args, unsigned char* smem, int ring_tile, int res_tile, int ring0, int ring_end,
                                              int k_first, int nk, float* tail_out) {
   constexpr bool RES_KMAJOR = MODE == MODE_DH, RING_KMAJOR = MODE == MODE_DW;
   constexpr int ND = NJ / 2, kLoads = 8 + NJ, kSlots = tile_slots<NJ>(), kWave = wave_bytes<NJ>(), kSlot = 4 * kWave;
@@ -508,7 +509,7 @@ __device__ __forceinline__ void tile_product(unsigned char* smem, int ring_tile,
   constexpr int kPanel = 16 * NJ, kBarrier = kPanel - 32 + 3, kFirst = 2, kGap = NJ == 4 ? 3 : 6;
   constexpr int kEarlyLoads = (kPanel - 1 - kBarrier - kFirst) / kGap + 1;     // those of the next slot that come before the panel's end
   static_assert(kFirst + kGap * (kLoads - 1) < kPanel - 14, "a slot's loads are issued before the next barrier");
-  const Params& p = args_now();
+  const Params& p = MODE == MODE_FWD ? args_now() : args;     // (see there)
   // (wave-uniform all of them; some come out of integer divisions, which run on the vector unit)
   ring_tile = __builtin_amdgcn_readfirstlane(ring_tile); res_tile = __builtin_amdgcn_readfirstlane(res_tile);
   ring0 = __builtin_amdgcn_readfirstlane(ring0); ring_end = __builtin_amdgcn_readfirstlane(ring_end);
@@ -724,8 +725,8 @@ __device__ __forceinline__ void tile_product(unsigned char* smem, int ring_tile,
     for (int j = 0; j < NJ; ++j) { const int n = n0 + j * 16 + f; zt[j] = q.zt[n < ring_end ? n : ring_end - 1]; }
     forward_epilogue<NJ>(q, [&](int i, int j, int e) { return read_acc(j, i, e); }, [&](int j) { return zt[j]; }, res0 + ws * 128, n0, res_tile * 2 + ws, ring_end);
   }
-  if (MODE == MODE_DH) dh_epilogue<NJ>(args_now(), smem, read_acc, wave, ring0 + wr * (NJ * 16), wr * (NJ * 16), res0 + ws * 128, ws * 128, ring_end, tail_out);
-  if (MODE == MODE_DW) dw_epilogue<NJ>(args_now(), acc, wr, ring0, res0 + ws * 128, res0, ring_end, tail_out);
+  if (MODE == MODE_DH) dh_epilogue<NJ>(p, smem, read_acc, wave, ring0 + wr * (NJ * 16), wr * (NJ * 16), res0 + ws * 128, ws * 128, ring_end, tail_out);
+  if (MODE == MODE_DW) dw_epilogue<NJ>(p, acc, wr, ring0, res0 + ws * 128, res0, ring_end, tail_out);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1073,7 +1074,7 @@ __global__ __launch_bounds__(NTHREADS) void gemm_nt_bf16(Params p) {
     // (the arguments as they are in the short one's: read again they are two scalar latencies a tile, 1 % at 8 panels)
     if (blocks == 4) half_column_tile(smem, tm, n0, nvalid);
     else if (__builtin_expect(blocks == 8, 1)) square_tile(p, smem, tm, tn, n0, nvalid < n0 + 256 ? nvalid : n0 + 256);
-    else tile_product<MODE, kWide>(smem, tn, tm, n0, nvalid, 0, p.K / BK, nullptr);
+    else tile_product<MODE, kWide>(p, smem, tn, tm, n0, nvalid, 0, p.K / BK, nullptr);
   } else if (MODE == MODE_DH) {
     const int Nt = tiles_of(p.N, RES);
     const Cut cut = cut_dh(nvalid, Nt, p.K / BK);
@@ -1087,9 +1088,9 @@ __global__ __launch_bounds__(NTHREADS) void gemm_nt_bf16(Params p) {
       if (nk <= 0) { zero_rows(tail_out, RES, RING, RES); return; }
     }
     const int m0 = cut.start(tm), blocks = cut.blocks(tm);
-    if (blocks == 4) tile_product<MODE, 4>(smem, tm, tn, m0, nvalid, k_first, nk, tail_out);
-    else if (blocks == 8) tile_product<MODE, 8>(smem, tm, tn, m0, nvalid < m0 + 256 ? nvalid : m0 + 256, k_first, nk, tail_out);
-    else tile_product<MODE, kWide>(smem, tm, tn, m0, nvalid, k_first, nk, tail_out);
+    if (blocks == 4) tile_product<MODE, 4>(p, smem, tm, tn, m0, nvalid, k_first, nk, tail_out);
+    else if (blocks == 8) tile_product<MODE, 8>(p, smem, tm, tn, m0, nvalid < m0 + 256 ? nvalid : m0 + 256, k_first, nk, tail_out);
+    else tile_product<MODE, kWide>(p, smem, tm, tn, m0, nvalid, k_first, nk, tail_out);
   } else if (p.wide) {
     const int panels = dw_panels(nvalid, p.K), Mt = tiles_of(p.V, RING), Nt = tiles_of(p.d, RES);
     int k_first = 0, nk = panels;
@@ -1097,7 +1098,7 @@ __global__ __launch_bounds__(NTHREADS) void gemm_nt_bf16(Params p) {
     if (item < -1 || (item >= 0 && nk <= 0)) return;  // (an empty slice: nothing to store, and nobody reads it)
     const int rows = p.V - tm * RING < RING ? p.V - tm * RING : RING, cols = p.d - tn * RES < RES ? p.d - tn * RES : RES;
     if (panels == 0) zero_rows(p.dW + (int64_t)tm * RING * p.d + tn * RES, p.d, rows, cols);
-    else tile_product<MODE, kWide>(smem, tm, tn, tm * RING, p.V, k_first, nk, item >= 0 ? p.tail_part + (int64_t)item * (RING * RES) : nullptr);
+    else tile_product<MODE, kWide>(p, smem, tm, tn, tm * RING, p.V, k_first, nk, item >= 0 ? p.tail_part + (int64_t)item * (RING * RES) : nullptr);
   } else {
     // 256 x 256 tiles: the rows of tiles up to the tail's first one, and the tail's slices (see dw_tail_plan)
     const int panels = dw_panels(nvalid, p.K), Nt = tiles_of(p.d, RES);
@@ -1125,7 +1126,7 @@ __global__ __launch_bounds__(NTHREADS) void gemm_nt_bf16(Params p) {
       tail_out = p.tail_part + (int64_t)item * (RES * RES);
       if (nk <= 0) { zero_rows(tail_out, RES, RES, RES); return; }
     }
-    tile_product<MODE, 8>(smem, tm, tn, tm * RES, p.V, k_first, nk, tail_out);
+    tile_product<MODE, 8>(p, smem, tm, tn, tm * RES, p.V, k_first, nk, tail_out);
   }
 }
 
