@@ -594,6 +594,9 @@ __device__ __forceinline__ void tile_product(const Params& args, unsigned char* 
   }
   if (RING_KMAJOR) set(dring, ring_ptr + ((int64_t)k_first * BK + wave * 16) * ring_ld + ring0, 16 * ring_ld2);
   else rows_of(dring, ring_ptr, ring_ld, ring0 + wave * (NJ * 8), NJ * 8, ring_end);
+  // Five wait states between a vector instruction that writes a scalar register (readfirstlane in `set`) and a load that reads it:
+  // the compiler keeps them for its own loads only.  (In the loop the descriptors are moved by scalar instructions.)
+  asm volatile("s_nop 4" : "+s"(dres), "+s"(dring));
   uint32_t slot = lds_wave;                           // of the panel being loaded
   int loading = 0;
   auto load = [&](int l) {
