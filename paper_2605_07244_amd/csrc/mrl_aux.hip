@@ -624,32 +624,38 @@ __global__ __launch_bounds__(256) void k_row_lse_f32(const float* Z, int64_t ldz
 // Row epilogue: merge partials -> lse, log-prob; Eq. (1) token terms; loss partials; for the
 // bf16 backward the row scale -g / S and the patch of the stash's target column.
 // Block = 64 rows x 64 partial lanes: a thread adds every 64th partial of 4 neighbouring rows (16-byte
-// loads, EPI_FLIGHT in flight, the last batch filled up: V = 50257 has 394 partials, seven per thread, which the remainder of a loop
-// unrolled by eight took one latency after the other: 6.0 us for 1877 rows, now 4.9), so that a pass of few rows is not a chain of hundreds of dependent-latency
+// loads, eight in flight, the last batch as long as the power of two that takes what is left: V = 50257 has 394 partials, seven per thread, which
+// the remainder of a loop unrolled by eight took one latency after the other), so that a pass of few rows is not a chain of hundreds of dependent-latency
 // loads (with 4 lanes per row: 112 us for 1188 partials and 201 rows; now 9 us, and 72 us instead of 150
 // for 65536 rows, whose partials are 311 MB).
 // ----------------------------------------------------------------------------
 constexpr int EPI_ROWS = 64;
 constexpr int EPI_THREADS = 1024;
 constexpr int EPI_LANES = EPI_THREADS / (EPI_ROWS / 4);
-constexpr int EPI_FLIGHT = 10;
+// K loads of a thread's partials, in flight together: every EPI_LANES-th from q on, of which `left` (of the block's numbering) remain.
+template <int K, bool ALL> __device__ __forceinline__ void add_partials(const float* q, int64_t step, int left, float4& s) {
+  float4 v[K];
+#pragma unroll
+  for (int k = 0; k < K; ++k) v[k] = *reinterpret_cast<const float4*>(ALL || k * EPI_LANES < left ? q + k * step : q);
+#pragma unroll
+  for (int k = 0; k < K; ++k)
+    if (ALL || k * EPI_LANES < left) { s.x += v[k].x; s.y += v[k].y; s.z += v[k].z; s.w += v[k].w; }
+}
 // Sum over all partials of this block's 64 rows; the result is valid in threads 0 .. 63 (one row
 // each).  Fixed order.  src points at the block's first row; rows beyond the valid ones hold
 // whatever the buffer held.  All threads must call it.
 __device__ inline float merge_partials(const float* src, int64_t stride, int n_partials, float4 (&sh)[EPI_LANES][EPI_ROWS / 4]) {
   const int quad = threadIdx.x & 15, part = threadIdx.x >> 4;
+  const int64_t step = stride * EPI_LANES;
+  const float* q = src + (part < n_partials ? part : 0) * stride + quad * 4;
   float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int p0 = part; p0 < n_partials; p0 += EPI_LANES * EPI_FLIGHT) {
-    float4 v[EPI_FLIGHT];
-#pragma unroll
-    for (int k = 0; k < EPI_FLIGHT; ++k) {
-      const int p = p0 + k * EPI_LANES;
-      v[k] = *reinterpret_cast<const float4*>(src + (int64_t)(p < n_partials ? p : n_partials - 1) * stride + quad * 4);
-    }
-#pragma unroll
-    for (int k = 0; k < EPI_FLIGHT; ++k)
-      if (p0 + k * EPI_LANES < n_partials) { s.x += v[k].x; s.y += v[k].y; s.z += v[k].z; s.w += v[k].w; }
-  }
+  int rest = n_partials;                              // from the block's first on
+  for (; rest >= EPI_LANES * 8; rest -= EPI_LANES * 8, q += 8 * step) add_partials<8, true>(q, step, 0, s);
+  const int left = rest - part;                       // the thread's first is `part` of them
+  if (rest > EPI_LANES * 4) add_partials<8, false>(q, step, left, s);
+  else if (rest > EPI_LANES * 2) add_partials<4, false>(q, step, left, s);
+  else if (rest > EPI_LANES) add_partials<2, false>(q, step, left, s);
+  else if (left > 0) add_partials<1, true>(q, step, 0, s);
   __syncthreads();                                  // an earlier merge has been read
   sh[part][quad] = s;
   __syncthreads();

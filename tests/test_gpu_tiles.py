@@ -46,6 +46,20 @@ def test_forward_tiles_cover_scored_rows(mrl, N, scored, d, V):
     assert torch.all(logp[mask == 0] == 0) and torch.all(lse[mask == 0] == 0)
 
 
+@pytest.mark.parametrize("V", [120, 8192, 8200, 16400, 32800, 65536, 65600, 98400])
+def test_partial_sums_in_batches(mrl, V):
+    """A thread of the row epilogue adds every 64th of 2 ceil(V / 256) partial sums: 1, 1 and the next, 2 - 3, 4 - 5, a full batch of
+    8, and 1 and 5 behind one."""
+    H, W, y, mask = _head(130, 64, V, 129, V)
+    logp, lse, ent = mrl.token_scores(H, W, y, mask)
+    rows = torch.nonzero(mask)[:, 0]
+    Hs, Ws = util.to_f64(H[rows]), util.to_f64(W)
+    want, want_lse = orc.token_logprobs(Hs, Ws, y[rows].cpu().numpy())
+    want_ent = orc.token_entropy(Hs, Ws)
+    for got, exact in ((logp, want), (lse, want_lse), (ent, want_ent)):
+        assert np.max(np.abs(got[rows].cpu().numpy() - exact)) <= 1e-4
+
+
 def _step(mrl, H, W, y, mask, dh_dtype, seed, chunk_rows=0, poison=False, hint=0):
     """One loss step of a single sequence (its tokens' advantages and traces random) and the same in float64.
     poison: the workspace holds NaN before the call."""
