@@ -1,6 +1,7 @@
-"""Wait states the compiler does not see: its hazard pass leaves inline assembly alone, and the direct loads of the GEMM kernels
-are written that way.  On gfx950 five wait states have to lie between a vector instruction that writes a scalar
-register (v_readfirstlane of a buffer descriptor) and a vector-memory instruction that reads it; with fewer it may see the old value."""
+"""Wait states the compiler does not see: its hazard pass leaves inline assembly alone, and the direct loads and the matrix products of the
+GEMM kernels are written that way.  On gfx950 five wait states have to lie between a vector instruction that writes a scalar
+register (v_readfirstlane of a buffer descriptor) and a vector-memory instruction that reads it; with fewer it may see the old value.
+And a 16x16x32 product (four passes) has to be eight wait states old before anything but another product reads what it writes."""
 import os
 import re
 import subprocess
@@ -11,6 +12,7 @@ from paper_2605_07244_amd import build
 
 LLVM = "/opt/rocm/llvm/bin"
 NEEDED = 5
+PRODUCT_NEEDED = 8
 VMEM = ("buffer_", "global_", "flat_", "scratch_")
 
 
@@ -29,8 +31,8 @@ def _written(op, operands):
     return _scalars(",".join(operands[:2 if two else 1]))
 
 
-def hazards(listing):
-    """(instruction, its predecessor) for every scalar register that is read too early, along every path of up to five instructions."""
+def _parse(listing):
+    """[(operation, operands)] and, for each, the instructions that may come before it."""
     code, at = [], {}
     for line in listing.splitlines():
         m = re.match(r"\s+([a-z][a-z0-9_]*)\s*(.*?)\s*// ([0-9A-F]+):", line)
@@ -46,22 +48,51 @@ def hazards(listing):
             target = at.get(addr + 4 + 4 * (offset - 65536 if offset >= 32768 else offset))
             if target is not None:
                 before[target].append(i)
-    found = []
-    for i, (op, operands, _) in enumerate(code):
-        if not op.startswith(VMEM):
+    return [(op, operands) for op, operands, _ in code], before
+
+
+def _early(code, before, i, wanted, needed, written):
+    """Predecessors of instruction i, along every path of fewer than `needed` wait states, that write one of the wanted registers."""
+    found, seen, todo = [], {}, [(b, 0) for b in before[i]]
+    while todo:
+        b, states = todo.pop()
+        if seen.get(b, needed) <= states:
             continue
-        todo = [(b, 0, frozenset(_scalars(",".join(operands)))) for b in before[i]]
-        while todo:
-            b, states, wanted = todo.pop()
-            bop, bops, _ = code[b]
-            late = wanted & _written(bop, bops)
-            if late:
-                found.append((" ".join([op, *operands]), " ".join([bop, *bops])))
-                continue
-            states += int(bops[0]) + 1 if bop == "s_nop" else 1
-            if states < NEEDED:
-                todo += [(c, states, wanted) for c in before[b]]
+        seen[b] = states
+        op, operands = code[b]
+        if wanted & written(op, operands):
+            found.append(" ".join([op, *operands]))
+            continue
+        states += int(operands[0]) + 1 if op == "s_nop" else 1
+        if states < needed:
+            todo += [(c, states) for c in before[b]]
     return found
+
+
+def hazards(listing):
+    """(instruction, predecessor) for every scalar register that a vector-memory instruction reads too early."""
+    code, before = _parse(listing)
+    return [(" ".join([op, *operands]), early) for i, (op, operands) in enumerate(code) if op.startswith(VMEM)
+            for early in _early(code, before, i, _scalars(",".join(operands)), NEEDED, _written)]
+
+
+def _vectors(text):
+    out = set()
+    for f, a, b in re.findall(r"\b([av])\[(\d+):(\d+)\]", text):
+        out |= {(f, r) for r in range(int(a), int(b) + 1)}
+    return out | {(f, int(r)) for f, r in re.findall(r"\b([av])(\d+)\b", text)}
+
+
+def product_hazards(listing):
+    """The same for registers that a matrix product writes and another kind of instruction names too early."""
+    code, before = _parse(listing)
+    products = [i for i, (op, _) in enumerate(code) if op.startswith("v_mfma")]
+    near = {j for i in products for j in range(i + 1, min(i + 1 + PRODUCT_NEEDED, len(code)))}
+    near |= {j for j, b in enumerate(before) if any(k != j - 1 for k in b)}          # (and where branches meet)
+    near |= {j + n for j in list(near) for n in range(PRODUCT_NEEDED) if j + n < len(code)}
+    written = lambda op, operands: _vectors(operands[0]) if op.startswith("v_mfma") else set()
+    return [(" ".join([op, *operands]), early) for i in sorted(near) for op, operands in [code[i]]
+            if not op.startswith(("v_mfma", "s_")) for early in _early(code, before, i, _vectors(",".join(operands)), PRODUCT_NEEDED, written)]
 
 
 def test_the_search_finds_what_it_is_for():
@@ -70,9 +101,12 @@ def test_the_search_finds_what_it_is_for():
          "buffer_load_dwordx4 v6, s[4:7], 0 offen lds", "s_endpgm"]))
     assert len(hazards(early)) == 1
     assert hazards(early.replace("s_add_u32 m0, s75, s36", "s_nop 3")) == []
+    soon = early.replace("s_add_u32 m0, s75, s36", "v_mfma_f32_16x16x32_bf16 a[4:7], v[0:3], v[4:7], a[4:7]").replace(
+        "v_add_u32_e32 v6, s35, v1", "v_accvgpr_read_b32 v6, a5")
+    assert len(product_hazards(soon)) == 1 and product_hazards(soon.replace("a5", "a8")) == []
 
 
-def test_scalar_registers_are_not_read_early_by_vector_memory_instructions(tmp_path):
+def test_registers_are_not_read_early(tmp_path):
     """Every kernel of the library, as it was built."""
     if not os.path.exists(f"{LLVM}/llvm-objdump"):
         pytest.skip("no llvm-objdump")
@@ -85,5 +119,6 @@ def test_scalar_registers_are_not_read_early_by_vector_memory_instructions(tmp_p
     for p in objects:
         listing = subprocess.run([f"{LLVM}/llvm-objdump", "-d", str(p)], check=True, capture_output=True, text=True).stdout
         assert hazards(listing) == [], p.name
+        assert product_hazards(listing) == [], p.name
         loads += listing.count(" lds ")
     assert loads > 100                                  # (the direct loads of the GEMM kernels were among them)
