@@ -220,7 +220,6 @@ __device__ inline bool tile_coords(int bid, int Mt, int Nt, int sup_m, int sup_n
 // swizzle of the K-major A panel: rows k, k+1, k+2, k+3 and k+8 (or k+16) get distinct values
 __device__ inline int kswz(int k) { return (k & 3) | ((((k >> 3) ^ (k >> 4)) & 1) << 2); }
 
-__device__ inline int min_int(int a, int b) { return a < b ? a : b; }
 __device__ inline float exp2_fast(float x) { return __builtin_amdgcn_exp2f(x); }
 
 // The MFMA is issued through inline assembly with the accumulator tied in place in an
@@ -341,7 +340,7 @@ __device__ __forceinline__ void forward_epilogue(const Params& p, Acc read_acc, 
 }
 
 // ---------------------------------------------------------------------------------------------
-// The tile.  Per wave 8 blocks of 16 on the resident side (256 of the tile), NJ on the ring side (32 NJ: 384, 256 or 128).  The forward has
+// The tile.  Per wave 8 blocks of 16 on the resident side (256 of the tile), NJ on the ring side (32 NJ: 384, or 128 in dH).  The forward has
 // the vocabulary on the resident side and the tokens in the ring, dH the hidden columns and the tokens, dW the hidden columns and
 // the vocabulary: the ring side is the one that is cut into tiles of other sizes.
 // ---------------------------------------------------------------------------------------------
@@ -352,7 +351,7 @@ template <int NJ> constexpr int wave_bytes() { return (8 + NJ) * 1024; }     // 
 template <int NJ> constexpr int tile_slots() { return NJ == 4 ? 3 : 2; }
 template <int NJ> constexpr int tile_lds() { return tile_slots<NJ>() * 4 * wave_bytes<NJ>(); }
 constexpr int DHSTAGE_LD = 128 + 8;                   // bf16 elements per row of the dH epilogue's staging area
-static_assert(tile_lds<12>() == 160 * 1024 && tile_lds<8>() <= tile_lds<12>() && tile_lds<4>() <= tile_lds<12>(), "all of a compute unit's LDS");
+static_assert(tile_lds<12>() == 160 * 1024 && tile_lds<4>() <= tile_lds<12>(), "all of a compute unit's LDS");
 static_assert(4 * 96 * DHSTAGE_LD * 2 <= tile_lds<12>(), "half a wave's rows, four waves");
 
 // The kernel's arguments, read again where they are used: kept alive across the forward's K loop they cost scalar registers (15360 rows,
@@ -526,8 +525,9 @@ __device__ __forceinline__ void tile_product(const Params& args, unsigned char* 
   const int64_t res_ld = MODE == MODE_FWD ? p.lda : p.ldb, ring_ld = MODE == MODE_FWD ? p.ldb : p.lda;
   const uint32_t res_ld2 = (uint32_t)(res_ld * 2), ring_ld2 = (uint32_t)(ring_ld * 2);
   const int rot_res = 4 * (ring_tile & 1);
-  const int rot_ring = !RING_KMAJOR ? 2 * (res_tile & 7) % NJ : (NJ == 12 ? 6 : 4) * (res_tile & 1);
-  constexpr int kResKinds = MODE == MODE_DW ? 2 : 4, kRingKinds = !RING_KMAJOR ? 2 : (NJ == 12 ? 6 : 4);
+  const int rot_ring = !RING_KMAJOR ? 2 * (res_tile & 7) % NJ : 6 * (res_tile & 1);
+  constexpr int kResKinds = MODE == MODE_DW ? 2 : 4, kRingKinds = !RING_KMAJOR ? 2 : 6;
+  static_assert(!RING_KMAJOR || NJ == kWide, "places of a K-major ring's loads");
   uint32_t vres[kResKinds], vring[kRingKinds];
   auto chunk16 = [&](int row) { return (uint32_t)(((lane & 7) ^ ((row >> 1) & 7)) << 4); };
 #pragma unroll
@@ -545,9 +545,8 @@ __device__ __forceinline__ void tile_product(const Params& args, unsigned char* 
     if (!RING_KMAJOR) {
       vring[q] = (uint32_t)(lane >> 3) * ring_ld2 + chunk16((q + rot_ring) * 8 + (lane >> 3));
     } else {
-      const int b = ((NJ == 12 ? q % 3 + 6 * (q / 3) : (q & 1) + 4 * (q >> 1)) + rot_ring) % NJ;
-      const int c = NJ == 12 ? 64 * (b % 3) + lane : lane, r = c / (4 * NJ);
-      const int k = (NJ == 12 ? 4 * (b / 3) : 2 * b) + r;
+      const int b = (q % 3 + 6 * (q / 3) + rot_ring) % NJ;
+      const int c = 64 * (b % 3) + lane, r = c / (4 * NJ), k = 4 * (b / 3) + r;
       const int col = (c % (4 * NJ)) ^ (kswz(16 * wave + k) << 1);
       // (columns from V on are not fetched: their products are not stored)
       vring[q] = ring0 + col * 8 < p.V ? (uint32_t)r * ring_ld2 + (col << 4) : 0x80000000u;
@@ -557,14 +556,14 @@ __device__ __forceinline__ void tile_product(const Params& args, unsigned char* 
 #pragma unroll
   for (int l = 0; l < kLoads; ++l) {
     const int b = l < 8 ? (l + rot_res) & 7 : (l - 8 + rot_ring) % NJ;
-    const uint32_t rows = l < 8 ? (RES_KMAJOR ? 2 * b : 8 * b) : (!RING_KMAJOR ? 8 * b : (NJ == 12 ? 4 * (b / 3) : 2 * b));
+    const uint32_t rows = l < 8 ? (RES_KMAJOR ? 2 * b : 8 * b) : (!RING_KMAJOR ? 8 * b : 4 * (b / 3));
     from[l] = __builtin_amdgcn_readfirstlane(rows * (l < 8 ? res_ld2 : ring_ld2));
     to[l] = __builtin_amdgcn_readfirstlane((l < 8 ? b : b + 8) * 1024);
   }
   auto kind = [](int l) {
     if (l < 8) return MODE == MODE_FWD ? l & 3 : MODE == MODE_DW ? l & 1 : (l & 1) | ((l >> 2) << 1);
     l -= 8;
-    return !RING_KMAJOR ? l & 1 : NJ == 12 ? l % 3 + 3 * (l / 6) : (l & 1) | ((l >> 2) << 1);
+    return !RING_KMAJOR ? l & 1 : l % 3 + 3 * (l / 6);
   };
   u32x4 dres, dring;
   auto set = [](u32x4& d, const uint16_t* at, uint32_t bytes) {
@@ -648,7 +647,7 @@ __device__ __forceinline__ void tile_product(const Params& args, unsigned char* 
   };
   int read_slot = 0;                                  // the reads' slot: the ring's, and behind it the resident side's
   auto slot_step = [&]() { return read_slot == kSlots - 1 ? -(kSlots - 1) * kSlot : kSlot; };
-  auto next_ring_panel = [&]() { ring_off[0] += slot_step(); if (!RING_KMAJOR || NJ > 8) ring_off[1] += slot_step(); };
+  auto next_ring_panel = [&]() { ring_off[0] += slot_step(); ring_off[1] += slot_step(); };
   auto next_res_panel = [&]() {
     res_off[0] += slot_step();
     if (!RES_KMAJOR) res_off[1] += slot_step();
@@ -736,16 +735,19 @@ __device__ __forceinline__ void tile_product(const Params& args, unsigned char* 
 }
 
 // ---------------------------------------------------------------------------------------------
-// Forward, 256 x 256 tiles: where whole rounds of them end earlier than tiles of 384 columns (see cut_forward).  Waves 2 x 2, each
-// 128 x 128; the token side's fragments of a panel stay in registers, in two sets, and those of W go through a ring of four pairs; two
-// panels of LDS.  (tile_product with 8 ring blocks takes 2 - 3 % longer here: its resident fragments are all read again
-// within the last 28 products of a panel.)
-//   group 0      : W fragments of row block 3 (this panel); the last loads of the next panel's slot
-//   groups 1 - 4 : W fragments of row blocks 4 - 7
-//   group 5      : wait for this thread's part of panel kt+1, barrier; next panel's W block 0, token blocks 0 - 2; the first
+// 256 x 256 tiles: where they end earlier than tiles of 384 (see Cut and launch_gemm_dw_bf16).  Waves 2 x 2, each
+// 128 x 128; the fragments of a panel's B side stay in registers, in two sets, and those of A go through a ring of four pairs; two
+// panels of LDS.  (tile_product with 8 ring blocks takes 1 - 3 % longer: its resident fragments are all read again
+// within the last 28 products of a panel.  dH of 2000 rows, d = 4096, V = 151936 1750 us with it and 1703, V = 32000 380 and 371.)
+//   group 0      : A fragments of row block 3 (this panel); the last loads of the next panel's slot
+//   groups 1 - 4 : A fragments of row blocks 4 - 7
+//   group 5      : wait for this thread's part of panel kt+1, barrier; next panel's A block 0, B blocks 0 - 2; the first
 //                  loads of panel kt+2 into this panel's slot
-//   group 6      : next W block 1, token blocks 3 - 5, loads
-//   group 7      : next W block 2, token blocks 6 - 7, loads
+//   group 6      : next A block 1, B blocks 3 - 5, loads
+//   group 7      : next A block 2, B blocks 6 - 7, loads
+// FWD: A = W, rows permuted within fragments, B = token rows.  DH: A = rows of the stash, B = W^T from the rows of W (K-major, through a
+// descriptor that ends with row V - 1: beyond it zeros are fetched).  DW: A = stash^T from its rows (K-major), B = rows of Ht; the
+// MFMA's operands are swapped.  Panels k_first .. k_first + nk - 1, an even number, at least two.
 // ---------------------------------------------------------------------------------------------
 constexpr int TILE_BYTES = RES * BK * 2;               // one panel of 256 rows
 constexpr int STAGE_BYTES = 2 * TILE_BYTES, PIPE_BYTES = 2 * STAGE_BYTES;
@@ -759,55 +761,117 @@ constexpr int load_index_base(int g) {      // loads issued before group g, in t
 constexpr int kLoadsCarriedOver = kLoadsInGroup[0] + kLoadsInGroup[1] + kLoadsInGroup[2] + kLoadsInGroup[3] + kLoadsInGroup[4];
 static_assert(kLoadsCarriedOver + kLoadsInGroup[5] + kLoadsInGroup[6] + kLoadsInGroup[7] == 16, "a slot takes 16 loads per wave");
 
-__device__ __forceinline__ void square_tile(const Params& p, unsigned char* smem, int tm, int tn, int n0, int N) {
+// A rows m0 .. M - 1 (at most 256), B rows n0 .. N - 1.  Workgroups that share a panel walk its row blocks in a different cyclic order
+// (rot_a, rot_b), so that they do not all ask the L2 for the same lines at the same moment.
+template <int MODE>
+__device__ __forceinline__ void square_tile(const Params& p, unsigned char* smem, int m0, int M, int n0, int N, int rot_a, int rot_b, int part,
+                                            int k_first, int nk, float* tail_out) {
+  constexpr bool A_KMAJOR = MODE == MODE_DW, B_KMAJOR = MODE == MODE_DH;
+  // (wave-uniform all of them; some come out of integer divisions, which run on the vector unit)
+  m0 = __builtin_amdgcn_readfirstlane(m0); n0 = __builtin_amdgcn_readfirstlane(n0);
+  k_first = __builtin_amdgcn_readfirstlane(k_first); nk = __builtin_amdgcn_readfirstlane(nk);
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave >> 1, wn = wave & 1, frow = lane & 15, fq = lane >> 4;
-  const int m0 = tm * RES, M = p.M, nk = p.K / BK;
   const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
   // (opaque: else they are read again inside the loop, and the wait for that is one for every LDS read)
-  int tail_panel = p.a_tail_panel;
-  int64_t tail_delta = p.a_tail_delta;
-  asm volatile("" : "+s"(tail_panel), "+s"(tail_delta));
+  int tail_panel = MODE == MODE_FWD ? p.a_tail_panel : 0;
+  int64_t tail_delta = MODE == MODE_FWD ? p.a_tail_delta : 0;
+  if (MODE == MODE_FWD) asm volatile("" : "+s"(tail_panel), "+s"(tail_delta));
   const uint32_t wave_lds = __builtin_amdgcn_readfirstlane(lds_base + wave * 8192);
-  // Workgroups that share a panel walk its row blocks in a different cyclic order (rot_a, rot_b), so that they do not all ask
-  // the L2 for the same lines at the same moment.
   const uint16_t* a_ptr[8];
   const uint16_t* b_ptr[8];
+  uint32_t b_voff[8];                                 // DH: byte offset of the lane's chunk from the wave's 16 rows of W
   uint32_t lds_a[8], lds_b[8];
-  const int rot_a = 2 * tn & 7, rot_b = tm & 7;
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
     const int ia = (i + rot_a) & 7, ib = (i + rot_b) & 7;
     lds_a[i] = __builtin_amdgcn_readfirstlane(ia * 1024);
     lds_b[i] = __builtin_amdgcn_readfirstlane(ib * 1024);
     const int r = (wave * 8 + ia) * 8 + (lane >> 3), rB = (wave * 8 + ib) * 8 + (lane >> 3);
-    const int ra = m0 + r < M ? m0 + r : M - 1, rb = n0 + rB < N ? n0 + rB : N - 1;
-    a_ptr[i] = p.A + (int64_t)ra * p.lda + ((lane & 7) ^ (((r >> 1) & 1) | (((r >> 3) & 3) << 1))) * 8;
-    b_ptr[i] = p.B + (int64_t)rb * p.ldb + ((lane & 7) ^ ((rB >> 1) & 7)) * 8;
+    if (A_KMAJOR) {
+      const int k = 2 * (wave * 8 + ia) + (lane >> 5);
+      const int col = m0 + (((lane & 31) ^ (kswz(k) << 1)) << 3);     // (columns from V on: products that are not stored)
+      a_ptr[i] = p.A + ((int64_t)k_first * BK + k) * p.lda + (col < p.V ? col : m0);
+    } else {
+      const int ra = m0 + r < M ? m0 + r : M - 1;
+      const int chunk = MODE == MODE_FWD ? (lane & 7) ^ (((r >> 1) & 1) | (((r >> 3) & 3) << 1)) : (lane & 7) ^ ((r >> 1) & 7);
+      a_ptr[i] = p.A + (int64_t)ra * p.lda + chunk * 8 + (int64_t)k_first * BK;
+    }
+    if (B_KMAJOR) {
+      const int k = 2 * ib + (lane >> 5);
+      b_voff[i] = (uint32_t)k * (uint32_t)(p.ldb * 2) + (((lane & 31) ^ (kswz(wave * 16 + k) << 1)) << 4);
+    } else {
+      const int rb = n0 + rB < N ? n0 + rB : N - 1;
+      b_ptr[i] = p.B + (int64_t)rb * p.ldb + ((lane & 7) ^ ((rB >> 1) & 7)) * 8 + (int64_t)k_first * BK;
+    }
   }
+  const int64_t a_kstep = A_KMAJOR ? p.lda * (BK * 2) : BK * 2, w_kstep = p.ldb * (BK * 2);    // bytes per panel
   auto load_at = [](const uint16_t* base, int64_t byte_off, uint32_t lds) {
     uint64_t addr;
     asm volatile("s_mov_b32 m0, %3\n\tv_lshl_add_u64 %0, %1, 0, %2\n\tglobal_load_lds_dwordx4 %0, off"
                  : "=&v"(addr) : "v"(base), "s"(byte_off), "s"(lds) : "memory");
   };
+  // DH: the wave's 16 rows of W in the panel being loaded
+  uint64_t w_addr = 0;
+  int w_left = 0;
+  u32x4 w_desc = {0, 0, 0, 0x00020000u};
+  auto w_set = [&]() {
+    const int bytes = (w_left < 16 ? w_left : 16) * (int)(p.ldb * 2) - n0 * 2;    // (below 2^25: ldb is at most 2^20)
+    w_desc[0] = (uint32_t)w_addr; w_desc[1] = (uint32_t)(w_addr >> 32);
+    w_desc[2] = (uint32_t)(bytes > 0 ? bytes : 0);
+  };
+  auto w_advance = [&]() { w_addr += (uint64_t)w_kstep; w_left -= BK; w_set(); };
+  if (B_KMAJOR) {
+    const int first = k_first * BK + wave * 16;
+    w_addr = (uint64_t)(p.B + (int64_t)first * p.ldb + n0);     // (uniform: the wave's number and the tile's are)
+    w_left = p.V - first;
+    w_set();
+    asm volatile("s_nop 4" : "+s"(w_desc));           // (wait states in front of the first load, as in tile_product)
+  }
+  auto load_w = [](uint32_t voff, const u32x4& desc, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds" :: "v"(voff), "s"(desc), "s"(lds) : "memory");
+  };
   auto issue_range = [&](int kt, int slot, int j0, int j1) {
-    const int64_t off = (int64_t)kt * (BK * 2);
-    const int64_t a_off = off + (kt >= tail_panel ? tail_delta : 0);
+    const int64_t off = (int64_t)kt * (BK * 2), a_off = kt * a_kstep + (MODE == MODE_FWD && kt >= tail_panel ? tail_delta : 0);
 #pragma unroll
     for (int j = j0; j < j1; ++j) {
       const uint32_t st = slot * STAGE_BYTES + wave_lds;
-      if (j & 1) load_at(b_ptr[j >> 1], off, st + TILE_BYTES + lds_b[j >> 1]); else load_at(a_ptr[j >> 1], a_off, st + lds_a[j >> 1]);
+      if (B_KMAJOR && (j & 1)) load_w(b_voff[j >> 1], w_desc, st + TILE_BYTES + lds_b[j >> 1]);
+      else if (j & 1) load_at(b_ptr[j >> 1], off, st + TILE_BYTES + lds_b[j >> 1]);
+      else load_at(a_ptr[j >> 1], a_off, st + lds_a[j >> 1]);
     }
   };
   int a_off[2], b_off[2];
 #pragma unroll
   for (int ks = 0; ks < 2; ++ks) {
     const int chunk = (ks << 2) | fq;
-    a_off[ks] = (wm * 128 + 8 * (frow >> 2) + (frow & 3)) * 128 + ((chunk ^ (((frow >> 1) & 1) | ((frow >> 2) << 1))) << 4);
+    if (MODE == MODE_FWD) a_off[ks] = (wm * 128 + 8 * (frow >> 2) + (frow & 3)) * 128 + ((chunk ^ (((frow >> 1) & 1) | ((frow >> 2) << 1))) << 4);
+    else a_off[ks] = (wm * 128 + frow) * 128 + ((chunk ^ ((frow >> 1) & 7)) << 4);
     b_off[ks] = TILE_BYTES + (wn * 128 + frow) * 128 + ((chunk ^ ((frow >> 1) & 7)) << 4);
   }
-  auto read_a = [&](int st, int ks, int i) { return *reinterpret_cast<const bf16x8*>(smem + st + a_off[ks] + (i >> 1) * 4096 + (i & 1) * 512); };
-  auto read_b = [&](int st, int ks, int j) { return *reinterpret_cast<const bf16x8*>(smem + st + b_off[ks] + j * 2048); };
+  // K-major panel: the transposing LDS read hands lane (g = lane / 16, s = lane % 16) the four
+  // k values kb .. kb+3 of column m = mb + s when lane s points at row kb + s/4, columns
+  // mb + 4*(s%4) .. +3.  Two of them (kb = 8g and 8g + 4 within the K step) make the lane's
+  // 8-element fragment.
+  const int kr = 8 * fq + (frow >> 2);
+  const int tr = kr * 512 + (kswz(kr) << 5) + ((frow & 2) << 3) + ((frow & 1) << 3);
+  const int a_tr = tr + wm * 256, b_tr = tr + wn * 256;
+  auto read_tr = [&](int off) -> bf16x8 {
+    typedef short v4i16 __attribute__((ext_vector_type(4)));
+    typedef __attribute__((address_space(3))) v4i16* lds_v4i16;
+    unsigned char* q = smem + off;
+    const v4i16 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16)q);
+    const v4i16 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16)(q + 2048));
+    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+  };
+  auto read_a = [&](int st, int ks, int i) -> bf16x8 {
+    if (A_KMAJOR) return read_tr(st + (a_tr ^ (i << 5)) + ks * 16384);
+    return *reinterpret_cast<const bf16x8*>(smem + st + a_off[ks] + (MODE == MODE_FWD ? (i >> 1) * 4096 + (i & 1) * 512 : i * 2048));
+  };
+  auto read_b = [&](int st, int ks, int j) -> bf16x8 {
+    if (B_KMAJOR) return read_tr(st + TILE_BYTES + (b_tr ^ (j << 5)) + ks * 16384);
+    return *reinterpret_cast<const bf16x8*>(smem + st + b_off[ks] + j * 2048);
+  };
   f32x4 acc[8][8];
   bf16x8 fbx[2][2][8];   // [set][K step][16-column block]
   bf16x8 fax[4][2];      // [ring slot][K step]
@@ -817,8 +881,9 @@ __device__ __forceinline__ void square_tile(const Params& p, unsigned char* smem
       if (m < 2) fax[3][m] = read_a(st_cur, m, 3);
     } else if (g <= 4) {
       if (m < 2) fax[(g - 1) & 3][m] = read_a(st_cur, m, g + 3);
+      if (B_KMAJOR && g == 4 && m == 6) w_advance();
     } else {
-      const int q = g - 5, nb = q == 2 ? 2 : 3;       // token blocks read in this group
+      const int q = g - 5, nb = q == 2 ? 2 : 3;       // B blocks read in this group
       if (g == 5 && m == 0) {
         __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
         __syncthreads();
@@ -842,7 +907,8 @@ __device__ __forceinline__ void square_tile(const Params& p, unsigned char* smem
     for (int g = 0; g < 8; ++g)
 #pragma unroll
       for (int m = 0; m < 16; ++m) {
-        mfma16(acc[g][m >> 1], fax[g & 3][m & 1], fbx[set][m & 1][m >> 1]);
+        const bf16x8 &a = fax[g & 3][m & 1], &b = fbx[set][m & 1][m >> 1];
+        if (MODE == MODE_DW) mfma16(acc[g][m >> 1], b, a); else mfma16(acc[g][m >> 1], a, b);
         side(g, m, set, st_cur, st_nxt, kt_nxt, slot_nxt, kt_load, slot_cur);
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -855,7 +921,8 @@ __device__ __forceinline__ void square_tile(const Params& p, unsigned char* smem
 #pragma unroll
       for (int e = 0; e < 4; ++e) acc[i][j][e] = 0.f;
   issue_range(0, 0, 0, 16);
-  {
+  if (B_KMAJOR) w_advance();
+  if (MODE == MODE_FWD) {
     const int n = n0 + wave * 64 + lane;              // the tile's target logits, published with its first panel
     asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off"
                  :: "v"(p.zt + (n < N ? n : N - 1)), "s"(__builtin_amdgcn_readfirstlane(lds_base + PIPE_BYTES + wave * 256)) : "memory");
@@ -864,20 +931,29 @@ __device__ __forceinline__ void square_tile(const Params& p, unsigned char* smem
   __syncthreads();
   issue_range(last_k(1), 1, 0, 16 - kLoadsCarriedOver);   // the rest comes with the first groups of the first panel
 #pragma unroll
-  for (int j = 0; j < 8; ++j) { fbx[0][0][j] = read_b(0, 0, j); fbx[0][1][j] = read_b(0, 1, j); }
+  for (int q = 0; q < 3; ++q) {                       // (in the order of the loop, which is what its waits go by)
 #pragma unroll
-  for (int i = 0; i < 3; ++i) { fax[i][0] = read_a(0, 0, i); fax[i][1] = read_a(0, 1, i); }
+    for (int m = 0; m < (q == 2 ? 6 : 8); ++m) {
+      const int j = 3 * q + (m - 2) / 2;
+      if (m < 2) fax[q][m] = read_a(0, m, q); else fbx[0][m & 1][j] = read_b(0, m & 1, j);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
   int kt = 0;
-  do {                                                // (an even number of panels, at least two)
+  do {
     panel(0, 0, STAGE_BYTES, last_k(kt + 1), 1, last_k(kt + 2), 0);
     panel(1, STAGE_BYTES, 0, last_k(kt + 2), 0, last_k(kt + 3), 1);
     kt += 2;
   } while (kt < nk);
   __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));          // no direct load may outlive the wave
   asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
-  const unsigned char* const zt_lds = smem + PIPE_BYTES + ((wn * 128 + (lane_now() & 15)) << 2);
-  forward_epilogue<8>(p, [&](int i, int j, int e) { return acc_now(acc[i][j][e]); },
-                      [&](int j) { return *reinterpret_cast<const float*>(zt_lds + j * 64); }, m0 + wm * 128, n0 + wn * 128, tm * 2 + wm, N);
+  auto read_acc = [&](int i, int j, int e) { return acc_now(acc[i][j][e]); };
+  if (MODE == MODE_FWD) {
+    const unsigned char* const zt_lds = smem + PIPE_BYTES + ((wn * 128 + (lane_now() & 15)) << 2);
+    forward_epilogue<8>(p, read_acc, [&](int j) { return *reinterpret_cast<const float*>(zt_lds + j * 64); }, m0 + wm * 128, n0 + wn * 128, part * 2 + wm, N);
+  }
+  if (MODE == MODE_DH) dh_epilogue<8>(p, smem, read_acc, wave, m0 + wm * 128, wm * 128, n0 + wn * 128, wn * 128, M, tail_out);
+  if (MODE == MODE_DW) dw_epilogue<8>(p, acc, wm, m0, n0 + wn * 128, n0, M, tail_out);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1065,7 +1141,7 @@ __global__ __launch_bounds__(NTHREADS) void gemm_nt_bf16(Params p) {
   const int nvalid = __builtin_amdgcn_readfirstlane(nv64 < 0 ? 0 : (nv64 > p.chunk_rows ? p.chunk_rows : (int)nv64));
   if (nvalid == 0 && (MODE != MODE_DW || !p.overwrite)) return;
   int tm, tn;
-  if (MODE == MODE_FWD) {
+  if constexpr (MODE == MODE_FWD) {
     const int Mt = tiles_of(p.M, RES);
     const Cut cut = cut_forward(nvalid, Mt);
     const int Nt = cut.count();
@@ -1079,9 +1155,9 @@ __global__ __launch_bounds__(NTHREADS) void gemm_nt_bf16(Params p) {
     const int n0 = cut.start(tn), blocks = cut.blocks(tn);
     // (the arguments as they are in the short one's: read again they are two scalar latencies a tile, 1 % at 8 panels)
     if (blocks == 4) half_column_tile(smem, tm, n0, nvalid);
-    else if (__builtin_expect(blocks == 8, 1)) square_tile(p, smem, tm, tn, n0, nvalid < n0 + 256 ? nvalid : n0 + 256);
+    else if (__builtin_expect(blocks == 8, 1)) square_tile<MODE>(p, smem, tm * RES, p.M, n0, nvalid < n0 + 256 ? nvalid : n0 + 256, 2 * tn & 7, tm & 7, tm, 0, p.K / BK, nullptr);
     else tile_product<MODE, kWide>(p, smem, tn, tm, n0, nvalid, 0, p.K / BK, nullptr);
-  } else if (MODE == MODE_DH) {
+  } else if constexpr (MODE == MODE_DH) {
     const int Nt = tiles_of(p.N, RES);
     const Cut cut = cut_dh(nvalid, Nt, p.K / BK);
     const int Mt = cut.count(), panels = p.K / BK;
@@ -1095,7 +1171,7 @@ __global__ __launch_bounds__(NTHREADS) void gemm_nt_bf16(Params p) {
     }
     const int m0 = cut.start(tm), blocks = cut.blocks(tm);
     if (blocks == 4) tile_product<MODE, 4>(p, smem, tm, tn, m0, nvalid, k_first, nk, tail_out);
-    else if (blocks == 8) tile_product<MODE, 8>(p, smem, tm, tn, m0, nvalid < m0 + 256 ? nvalid : m0 + 256, k_first, nk, tail_out);
+    else if (blocks == 8) square_tile<MODE>(p, smem, m0, nvalid < m0 + 256 ? nvalid : m0 + 256, tn * RES, p.N, 2 * tn & 7, tm & 7, 0, k_first, nk, tail_out);
     else tile_product<MODE, kWide>(p, smem, tm, tn, m0, nvalid, k_first, nk, tail_out);
   } else if (p.wide) {
     const int panels = dw_panels(nvalid, p.K), Mt = tiles_of(p.V, RING), Nt = tiles_of(p.d, RES);
@@ -1132,7 +1208,7 @@ __global__ __launch_bounds__(NTHREADS) void gemm_nt_bf16(Params p) {
       tail_out = p.tail_part + (int64_t)item * (RES * RES);
       if (nk <= 0) { zero_rows(tail_out, RES, RES, RES); return; }
     }
-    tile_product<MODE, 8>(p, smem, tm, tn, tm * RES, p.V, k_first, nk, tail_out);
+    square_tile<MODE>(p, smem, tm * RES, p.V, tn * RES, p.N, tn * 8 / p.sup_n & 7, tm * 8 / p.sup_m & 7, 0, k_first, nk, tail_out);
   }
 }
 
@@ -1670,7 +1746,7 @@ void launch_gemm_dw_bf16(const void* E, int64_t lde, const void* Ht, int64_t ldh
                          int V, int d, float* dW, int overwrite, float* tail_part, int tail_items, int rows, bool in_blocks,
                          hipStream_t stream) {
   Params p = {};
-  p.A = static_cast<const uint16_t*>(E); p.lda = lde; p.M = (int)round_up(V, kTile);
+  p.A = static_cast<const uint16_t*>(E); p.lda = lde;
   p.B = static_cast<const uint16_t*>(Ht); p.ldb = ldht; p.N = d;
   p.K = chunk_rows;
   p.n_scored = n_scored; p.chunk_start = chunk_start; p.chunk_rows = chunk_rows;
