@@ -56,8 +56,7 @@ int mrl_probe_mfma_rate(int32_t random_operands, double seconds, void* scratch /
 
 /* ------------------------------------------------------------------------
  * The launch plan of the dW GEMM for an LM head of V rows and d columns where
- * it runs on 256 x 256 tiles (short contractions; else on 384 x 256 ones, whose
- * last round is cut on the device) (host code only, no GPU call): which rows of 256 x 256 tiles are cut into slices of
+ * it runs on 256 x 256 tiles (short contractions; mrl_diag_gemm_cut says which) (host code only, no GPU call): which rows of 256 x 256 tiles are cut into slices of
  * the contraction at the end of the launch, into how many, and how many of the
  * resulting work items each of the 8 XCDs takes.  For tests of the host logic
  * and for reading profiles.  out12 (host): [0] first tile row of the tail,
@@ -82,6 +81,19 @@ int mrl_diag_dw_few_rows(void);
  * code here, no GPU call).  Errors: MRL_ERR_SHAPE.
  * ---------------------------------------------------------------------- */
 int mrl_diag_dh_split(int32_t tail_tiles, int32_t panels, int32_t max_items);
+
+/* ------------------------------------------------------------------------
+ * The tiles of a large bf16 launch (host code only, no GPU call), for tests that mean to reach one
+ * path or the other.  launch: MRL_PROF_GEMM_FWD, _DH or _DW; rows: valid rows of the pass (FWD: of the launch's part of it);
+ * expected (DW): rows at most, as far as scored_rows_hint says, else chunk_rows; chunk_rows: length of the pass (or
+ * part), a multiple of 256; tail_items: partial tiles the workspace has room for (0: the full size's).
+ * out9 (host): [0] tiles of 384, [1] of 256, [2] of 128 along the token rows (DW: the vocabulary), [3] tiles of the launch, [4] those
+ * of its last round, which may be cut, [5] slices of the contraction that each of them is cut into (1: whole), [6] workgroups launched (DW on
+ * 256 x 256 tiles: for the whole tiles), [7] tail_items, [8] first row of the last tile along the token rows.  FWD of passes of at most 256
+ * rows and DW of at most mrl_diag_dw_few_rows() have launches of their own (DW: all zeros but [7]).  Errors: MRL_ERR_NULL, MRL_ERR_SHAPE.
+ * ---------------------------------------------------------------------- */
+int mrl_diag_gemm_cut(int32_t launch, int32_t rows, int32_t expected, int32_t chunk_rows, int32_t V, int32_t d, int32_t tail_items,
+                      int32_t* out9 /*host*/);
 
 #ifdef __cplusplus
 }

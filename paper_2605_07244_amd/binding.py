@@ -115,6 +115,8 @@ def lib() -> ctypes.CDLL:
                                                       c_void_p, c_void_p]
     L.mrl_diag_dw_tail_plan.restype = c_int
     L.mrl_diag_dw_tail_plan.argtypes = [c_int32, c_int32, POINTER(c_int32)]
+    L.mrl_diag_gemm_cut.restype = c_int
+    L.mrl_diag_gemm_cut.argtypes = [c_int32] * 7 + [POINTER(c_int32)]
     L.mrl_diag_dw_few_rows.restype = c_int
     L.mrl_diag_dw_few_rows.argtypes = []
     L.mrl_probe_mfma_rate.restype = c_int
@@ -360,6 +362,17 @@ def dw_tail_plan(V: int, d: int) -> dict:
     out = (c_int32 * 12)()
     _check(lib().mrl_diag_dw_tail_plan(int(V), int(d), out), "mrl_diag_dw_tail_plan")
     return dict(first_tile_row=out[0], tile_rows=out[1], split=out[2], items_before_xcd=list(out[3:12]))
+
+
+GEMM_FWD, GEMM_DH, GEMM_DW = 2, 5, 6      # MRL_PROF_GEMM_*
+
+
+def gemm_cut(launch: int, rows: int, V: int, d: int, chunk_rows: int = 0, expected: int = 0, tail_items: int = 0) -> dict:
+    """The tiles of a large bf16 launch (mrl_diag_gemm_cut); chunk_rows 0: rows rounded up to 256, expected 0: chunk_rows."""
+    chunk = int(chunk_rows) or -(-int(rows) // 256) * 256
+    out = (c_int32 * 9)()
+    _check(lib().mrl_diag_gemm_cut(int(launch), int(rows), int(expected) or chunk, chunk, int(V), int(d), int(tail_items), out), "mrl_diag_gemm_cut")
+    return dict(zip(("wide", "narrow", "half", "tiles", "rest", "split", "blocks", "tail_items", "last_start"), out))
 
 
 def dw_few_rows() -> int:

@@ -36,6 +36,8 @@
 #include "../../include/mrl_diag.h"
 #include "mrl_internal.h"
 
+#include <cstring>
+
 namespace mrl {
 namespace {
 
@@ -67,6 +69,7 @@ struct Params {
   // bytes behind where it would be
   int a_tail_panel; int64_t a_tail_delta;
   const float* zt; float* part_sum; float* part_ez; int64_t part_stride; uint16_t* estash; int64_t lde; int V;
+  uint64_t cuts[4];           // FWD, DH: how the token rows are cut into tiles, two bits per 128 of them (see Cut)
   // DH
   const float* row_scale; void* dH; int dh_f32; int d; int max_items;   // max_items: partial tiles tail_part holds
   // DW
@@ -80,22 +83,22 @@ struct Params {
 
 // Workgroup -> tile mapping of the launches.  Workgroups are dealt round-robin to the
 // 8 XCDs, each with its own L2 and 32 compute units; 32 consecutive workgroups of one XCD take 32
-// consecutive tiles, numbered down the columns of bands of BAND tile rows, so that they share operand panels in that L2 and all XCDs
-// walk the same A rows at the same time.  Bands of 8 rows of 256 in the forward (8 x 4 tiles, the tokens' side of 384), of 4 rows of 384 in dH
-// and dW (4 x 8): either takes 3584 rows of panels per group, the other shape 4096 (dH of 15360 rows, d = 4096 12920 and 12775 us).  The numbering runs over the VALID tiles (the scored rows are counted on the device) without
+// consecutive tiles, numbered down the columns of bands of tile rows, so that they share operand panels in that L2 and all XCDs
+// walk the same A rows at the same time.  Bands of 8 rows of 256 in the forward (8 x 4 tiles, the tokens' side of 384) and in dH without tiles of 384, of 4
+// rows of 384 in dH and dW (4 x 8): either takes 3584 rows of panels per group, the other shape 4096 (dH of 15360 rows, d = 4096 12920 and 12775 us).  The numbering runs over the VALID tiles (the scored rows are counted on the device) without
 // holes: numbering super-tiles over the launch's upper bound gave each XCD fixed tile columns, and
 // with 20 of 32 tile columns valid three XCDs had nothing to do (scoring 5120 of 8192 slots,
 // V = 128256, d = 2048: 3233 us a call against 2088 us now).  The tiles of the last, incomplete round
 // of 256 are dealt evenly.
 constexpr int kXcdCus = 32;
 constexpr int kRound = NXCD * kXcdCus;
-template <int BAND> __device__ inline void tile_at(int t, int Mt, int Nt, int& tm, int& tn) {
-  const int band = t / (BAND * Nt), in_band = t - band * BAND * Nt;
-  const int rows = Mt - band * BAND < BAND ? Mt - band * BAND : BAND;
+__device__ __forceinline__ void tile_at(int band, int t, int Mt, int Nt, int& tm, int& tn) {
+  const int first = t / (band * Nt) * band, in_band = t - first * Nt;
+  const int rows = Mt - first < band ? Mt - first : band;
   tn = in_band / rows;
-  tm = band * BAND + in_band - tn * rows;
+  tm = first + in_band - tn * rows;
 }
-template <int BAND> __device__ inline bool dealt_tile(int bid, int Mt, int Nt, int& tm, int& tn) {
+__device__ __forceinline__ bool dealt_tile(int band, int bid, int Mt, int Nt, int& tm, int& tn) {
   const int tiles = Mt * Nt, whole = tiles / kRound * kRound;
   const int xcd = bid % NXCD, local = bid / NXCD;
   int t;
@@ -106,7 +109,7 @@ template <int BAND> __device__ inline bool dealt_tile(int bid, int Mt, int Nt, i
     t = whole + xcd * per + k;
     if (k >= per || t >= tiles) return false;
   }
-  tile_at<BAND>(t, Mt, Nt, tm, tn);
+  tile_at(band, t, Mt, Nt, tm, tn);
   return true;
 }
 
@@ -162,8 +165,8 @@ struct DhSplit { __device__ int operator()(int tiles, int panels, int max_items)
 struct DwSplit { __device__ int operator()(int tiles, int panels, int max_items) const { return dw_split(tiles, panels, max_items); } };
 // Workgroup -> tile or slice of one, for a launch whose last round may be cut.  Returns the item's number (its place in the
 // scratch area) for a slice, panels k_first .. k_first + nk - 1 of its tile; -1 for a whole tile; -2 for nothing.
-template <int BAND, class Split>
-__device__ inline int split_tile(int bid, int Mt, int Nt, int panels, int max_items, Split split_of, int& tm, int& tn, int& k_first, int& nk) {
+template <class Split>
+__device__ __forceinline__ int split_tile(int band, int bid, int Mt, int Nt, int panels, int max_items, Split split_of, int& tm, int& tn, int& k_first, int& nk) {
   const int tiles = Mt * Nt, whole = tiles / kRound * kRound, rest = tiles - whole;
   if (bid >= whole && rest > 0) {
     const int split = split_of(rest, panels, max_items);
@@ -173,16 +176,16 @@ __device__ inline int split_tile(int bid, int Mt, int Nt, int panels, int max_it
       const int e = bid - whole, item = e % NXCD * per + e / NXCD;
       if (e / NXCD >= per || item >= items) return -2;
       const int slice = item / rest, per_slice = slice_panels(panels, split);
-      tile_at<BAND>(whole + item - slice * rest, Mt, Nt, tm, tn);
+      tile_at(band, whole + item - slice * rest, Mt, Nt, tm, tn);
       k_first = slice * per_slice;
       nk = panels - k_first < per_slice ? panels - k_first : per_slice;
       return item;
     }
   }
-  return dealt_tile<BAND>(bid, Mt, Nt, tm, tn) ? -1 : -2;
+  return dealt_tile(band, bid, Mt, Nt, tm, tn) ? -1 : -2;
 }
 // panels of the dW contraction: the pass's valid rows, rounded up to panel pairs
-__device__ inline int dw_panels(int nvalid, int chunk_rows) {
+__host__ __device__ inline int dw_panels(int nvalid, int chunk_rows) {
   const int k = (nvalid + 2 * BK - 1) / (2 * BK) * (2 * BK);
   return (k < chunk_rows ? k : chunk_rows) / BK;
 }
@@ -1082,56 +1085,46 @@ __device__ inline void zero_rows(float* at, int64_t ld, int rows, int cols) {
     for (int c = (threadIdx.x & 63) * 4; c < cols; c += 256) *reinterpret_cast<f32x4_any*>(at + (int64_t)r * ld + c) = f32x4{0.f, 0.f, 0.f, 0.f};
 }
 
-__device__ __forceinline__ int tiles_of(int n, int size) { return (n + size - 1) / size; }
+__host__ __device__ __forceinline__ int tiles_of(int n, int size) { return (n + size - 1) / size; }
 
-// How n token rows (columns of forward tiles, rows of dH tiles) are cut into tiles of 384, 256 and 128.
+// How n token rows (columns of forward tiles, rows of dH tiles) are cut into tiles of 384, 256 and 128.  The host says for every count of rows
+// up to 16384, in steps of 128, which of three ways it is (Params::cuts): the scored rows are known on the device only, and a choice
+// made there cost every tile of a short launch a microsecond and more.
 struct Cut {
   int wide, narrow, half;
-  __device__ int count() const { return wide + narrow + half; }
-  __device__ int start(int t) const { return t < wide ? t * RING : wide * RING + (t - wide) * 256; }
-  __device__ int blocks(int t) const { return t < wide ? kWide : t < wide + narrow ? 8 : 4; }   // of 16 rows per wave
+  __host__ __device__ __forceinline__ int count() const { return wide + narrow + half; }
+  __host__ __device__ __forceinline__ int start(int t) const {
+    return t < wide ? t * RING : t < wide + narrow ? wide * RING + (t - wide) * 256 : wide * RING + narrow * 256 + (t - wide - narrow) * 128;
+  }
+  __host__ __device__ __forceinline__ int blocks(int t) const { return t < wide ? kWide : t < wide + narrow ? 8 : 4; }   // of 16 rows per wave
 };
 // Tiles of 384 and what is left; two of 256 instead of one of 384 and one of 128, which waits for its panels more than it computes.
-__device__ inline Cut cut_wide(int n) {
+__host__ __device__ __forceinline__ Cut cut_wide(int n) {
   const int w = n / RING, r = n - w * RING;
   if (r == 0) return {w, 0, 0};
   if (r <= 128) return w ? Cut{w - 1, 2, 0} : Cut{0, 0, 1};
   return r <= 256 ? Cut{w, 1, 0} : Cut{w + 1, 0, 0};
 }
-__device__ inline Cut cut_narrow(int n) {
+__host__ __device__ __forceinline__ Cut cut_narrow(int n) {
   const int w = n / 256, r = n - w * 256;
   return r == 0 ? Cut{0, w, 0} : r <= 128 ? Cut{0, w, 1} : Cut{0, w + 1, 0};
 }
-// dH: tiles of 384, but where all are cut into slices that fill the chip about once (a tile of 384 takes 1.43 of the time of one of
-// 256) those whose
-// slices are shorter.  2000 rows, V = 128256, d = 1024: 24 tiles of 10 slices 396 us, 32 of 8 386; 1100 rows, V = 5000, d = 136 (at most
-// 5 slices of 16 panels) 44 and 38; 327 rows, V = 151936, d = 4096: 16 tiles of 16 slices 356, 32 of 8 (256 x 256 tiles before) 459.
-__device__ inline Cut cut_dh(int n, int cols, int panels) {
-  const Cut a = cut_wide(n), b = cut_narrow(n);
-  const int ta = a.count() * cols, tb = b.count() * cols, most = panels < 2 * kMinSlicePanels ? 1 : panels / kMinSlicePanels;
-  if (a.wide == 0 || tb > kRound) return a;
-  const int sa = kRound / ta < most ? kRound / ta : most, sb = kRound / tb < most ? kRound / tb : most;
-  return 105 * sa < 143 * sb ? b : a;
+constexpr int kCutStep = 128, kCutSteps = 128;
+enum { CUT_WIDE = 0, CUT_NARROW = 1, CUT_SHORT = 2, CUT_EVEN = 3 };
+// CUT_NARROW: of 256, and in the forward one of 128; CUT_SHORT: forward a last tile of 384 as one of 256 and one of 128, dH all of 128; CUT_EVEN: all of 256.
+template <int MODE> __host__ __device__ __forceinline__ Cut cut_rows(int n, int kind) {
+  if (kind == CUT_WIDE) return cut_wide(n);
+  if (kind == CUT_EVEN) return Cut{0, tiles_of(n, 256), 0};
+  if (MODE == MODE_FWD) return kind == CUT_NARROW ? cut_narrow(n) : Cut{tiles_of(n, RING) - 1, 1, 1};
+  return Cut{0, 0, tiles_of(n, 128)};
 }
-// When a forward launch of rows x c tiles ends, in hundredths of a 256 x 256 tile's time: whole rounds of one kind of tile; of
-// several kinds, the mean and a part of a tile.  With a single column every tile streams its own rows of W from memory, and the wide
-// one waits for them.  Scoring call, us, 256 x 256 (and half) tiles and tiles of 384: V = 151936, d = 4096, 384 rows 451 and 466,
-// 600 rows 725 and 683, 1920 rows 1900 and 1763; d = 1536, 384 rows 188 and 204; V = 50257, d = 712, 384 rows 63 and 54, 1280 rows 115
-// and 132, 1920 rows 178 and 159; V = 32000, d = 2048, 300 rows 57 and 70, 600 rows 101 and 84, 1000 rows 108 and 138, 1920 rows 199 and 212.
-__device__ inline uint32_t forward_end(const Cut& c, int rows) {     // (below 2^32: 61440 rows are 160 columns, 2^24 ids 65536 rows)
-  constexpr uint32_t kWideTile = 143, kNarrowTile = 100, kHalfTile = 58;
-  const uint32_t w = c.wide * rows, n = c.narrow * rows, h = c.half * rows, tiles = w + n + h;
-  if (tiles <= kRound) return w ? kWideTile : n ? kNarrowTile : kHalfTile;
-  if (n + h == 0) return (w + kRound - 1) / kRound * (c.wide == 1 ? kWideTile + 14 : kWideTile);
-  if (w + h == 0) return (n + kRound - 1) / kRound * kNarrowTile;
-  return (w * kWideTile + n * kNarrowTile + h * kHalfTile) / kRound + (w ? (h ? 80 : 60) : 30);
+__host__ __device__ __forceinline__ int cut_kind(const uint64_t (&cuts)[4], int n) {
+  const int i = (n - 1) / kCutStep;                   // (all four words read and selected from: every tile 0.3 us later)
+  return i < kCutSteps ? (int)(cuts[i >> 5] >> (2 * (i & 31))) & 3 : CUT_WIDE;
 }
-__device__ inline Cut cut_forward(int n, int rows) {
-  const Cut a = cut_wide(n), b = cut_narrow(n);
-  const Cut c = a.narrow + a.half == 0 ? Cut{a.wide - 1, 1, 1} : a;
-  const uint32_t ea = forward_end(a, rows), eb = forward_end(b, rows), ec = forward_end(c, rows);
-  return eb < ea && eb <= ec ? b : ec < ea ? c : a;
-}
+template <int MODE> __device__ __forceinline__ Cut cut_of(const Params& p, int n) { return cut_rows<MODE>(n, cut_kind(p.cuts, n)); }
+
+__device__ __forceinline__ int dh_band(const Cut& cut) { return cut.wide > 0 ? 4 : 8; }
 
 template <int MODE>
 __global__ __launch_bounds__(NTHREADS) void gemm_nt_bf16(Params p) {
@@ -1143,9 +1136,9 @@ __global__ __launch_bounds__(NTHREADS) void gemm_nt_bf16(Params p) {
   int tm, tn;
   if constexpr (MODE == MODE_FWD) {
     const int Mt = tiles_of(p.M, RES);
-    const Cut cut = cut_forward(nvalid, Mt);
+    const Cut cut = cut_of<MODE>(p, nvalid);
     const int Nt = cut.count();
-    if (!dealt_tile<8>(blockIdx.x, Mt, Nt, tm, tn)) return;
+    if (!dealt_tile(8, blockIdx.x, Mt, Nt, tm, tn)) return;
     if (cut.half > 0 && Nt > 1) {
       // half tiles are dealt like the others, to every XCD its share: the columns of a band start at another one in every
       // band (with 8 columns, XCDs would else have all of them or none)
@@ -1155,28 +1148,29 @@ __global__ __launch_bounds__(NTHREADS) void gemm_nt_bf16(Params p) {
     const int n0 = cut.start(tn), blocks = cut.blocks(tn);
     // (the arguments as they are in the short one's: read again they are two scalar latencies a tile, 1 % at 8 panels)
     if (blocks == 4) half_column_tile(smem, tm, n0, nvalid);
-    else if (__builtin_expect(blocks == 8, 1)) square_tile<MODE>(p, smem, tm * RES, p.M, n0, nvalid < n0 + 256 ? nvalid : n0 + 256, 2 * tn & 7, tm & 7, tm, 0, p.K / BK, nullptr);
+    else if (__builtin_expect(blocks == 8, 1))
+      square_tile<MODE>(p, smem, tm * RES, p.M, n0, nvalid < n0 + 256 ? nvalid : n0 + 256, 2 * tn & 7, tm & 7, tm, 0, p.K / BK, nullptr);
     else tile_product<MODE, kWide>(p, smem, tn, tm, n0, nvalid, 0, p.K / BK, nullptr);
   } else if constexpr (MODE == MODE_DH) {
     const int Nt = tiles_of(p.N, RES);
-    const Cut cut = cut_dh(nvalid, Nt, p.K / BK);
+    const Cut cut = cut_of<MODE>(p, nvalid);
     const int Mt = cut.count(), panels = p.K / BK;
     int k_first = 0, nk = panels;
     float* tail_out = nullptr;
-    const int item = split_tile<4>(blockIdx.x, Mt, Nt, panels, p.max_items, DhSplit{}, tm, tn, k_first, nk);
+    const int item = split_tile(dh_band(cut), blockIdx.x, Mt, Nt, panels, p.max_items, DhSplit{}, tm, tn, k_first, nk);
     if (item < -1) return;
     if (item >= 0) {
       tail_out = p.tail_part + (int64_t)item * (RING * RES);
       if (nk <= 0) { zero_rows(tail_out, RES, RING, RES); return; }
     }
     const int m0 = cut.start(tm), blocks = cut.blocks(tm);
-    if (blocks == 4) tile_product<MODE, 4>(p, smem, tm, tn, m0, nvalid, k_first, nk, tail_out);
+    if (blocks == 4) tile_product<MODE, 4>(p, smem, tm, tn, m0, nvalid < m0 + 128 ? nvalid : m0 + 128, k_first, nk, tail_out);
     else if (blocks == 8) square_tile<MODE>(p, smem, m0, nvalid < m0 + 256 ? nvalid : m0 + 256, tn * RES, p.N, 2 * tn & 7, tm & 7, 0, k_first, nk, tail_out);
     else tile_product<MODE, kWide>(p, smem, tm, tn, m0, nvalid, k_first, nk, tail_out);
   } else if (p.wide) {
     const int panels = dw_panels(nvalid, p.K), Mt = tiles_of(p.V, RING), Nt = tiles_of(p.d, RES);
     int k_first = 0, nk = panels;
-    const int item = split_tile<4>(blockIdx.x, Mt, Nt, panels, p.max_items, DwSplit{}, tm, tn, k_first, nk);
+    const int item = split_tile(4, blockIdx.x, Mt, Nt, panels, p.max_items, DwSplit{}, tm, tn, k_first, nk);
     if (item < -1 || (item >= 0 && nk <= 0)) return;  // (an empty slice: nothing to store, and nobody reads it)
     const int rows = p.V - tm * RING < RING ? p.V - tm * RING : RING, cols = p.d - tn * RES < RES ? p.d - tn * RES : RES;
     if (panels == 0) zero_rows(p.dW + (int64_t)tm * RING * p.d + tn * RES, p.d, rows, cols);
@@ -1406,7 +1400,7 @@ __global__ __launch_bounds__(NTHREADS, 2) void dw_few_bf16(Params p) {
   if (nvalid == 0 && !p.overwrite) return;
   const int Mt = (p.V + DM - 1) / DM, Nt = (p.d + DN - 1) / DN;
   int tm, tn;
-  if (!dealt_tile<8>(blockIdx.x, Mt, Nt, tm, tn)) return;
+  if (!dealt_tile(8, blockIdx.x, Mt, Nt, tm, tn)) return;
   const int m0 = tm * DM, n0 = tn * DN;
   const int nk = dw_panels(nvalid, p.K) * (BK / DK);
 
@@ -1623,7 +1617,8 @@ __global__ __launch_bounds__(256) void dh_tail_reduce(Params p) {
   int64_t nv64 = *p.n_scored - p.chunk_start;
   const int M = nv64 < 0 ? 0 : (nv64 > p.chunk_rows ? p.chunk_rows : (int)nv64);
   const int Nt = tiles_of(p.N, RES);
-  const Cut cut = cut_dh(M, Nt, p.K / BK);
+  if (M == 0) return;
+  const Cut cut = cut_of<MODE_DH>(p, M);
   const int Mt = cut.count();
   const int tiles = Mt * Nt, whole = tiles / kRound * kRound, rest = tiles - whole;
   const int t = blockIdx.x / kReduceBlocks;
@@ -1631,7 +1626,7 @@ __global__ __launch_bounds__(256) void dh_tail_reduce(Params p) {
   const int split = dh_split(rest, p.K / BK, p.max_items);
   if (split == 1) return;
   int tm, tn;
-  tile_at<4>(whole + t, Mt, Nt, tm, tn);
+  tile_at(dh_band(cut), whole + t, Mt, Nt, tm, tn);
   const int within = (blockIdx.x % kReduceBlocks) * 2048 + threadIdx.x * 8;
   const int m = cut.start(tm) + within / RES, n = tn * RES + within % RES;
   if (within / RES >= 32 * cut.blocks(tm) || m >= M || n >= p.d) return;
@@ -1660,7 +1655,7 @@ __global__ __launch_bounds__(256) void dw_wide_reduce(Params p) {
   if (split == 1) return;
   int tm, tn;
   const int t = blockIdx.x / kReduceBlocks;
-  tile_at<4>(whole + t, Mt, Nt, tm, tn);
+  tile_at(4, whole + t, Mt, Nt, tm, tn);
   const int within = (blockIdx.x % kReduceBlocks) * 2048 + threadIdx.x * 8;
   const int v = tm * RING + within / RES, n = tn * RES + within % RES;
   if (v >= p.V || n >= p.d) return;
@@ -1672,13 +1667,139 @@ __global__ __launch_bounds__(256) void dw_wide_reduce(Params p) {
   out[1] = hi;
 }
 
-template <int MODE>
-void launch(Params& p, int blocks, hipStream_t stream) {
+template <void (*KERNEL)(Params)> void launch(Params& p, int blocks, hipStream_t stream) {
   static LdsLimit lds_limit;
-  lds_limit.ensure(reinterpret_cast<const void*>(&gemm_nt_bf16<MODE>), tile_lds<kWide>());
-  hipLaunchKernelGGL(gemm_nt_bf16<MODE>, dim3(blocks), dim3(NTHREADS), tile_lds<kWide>(), stream, p);
+  lds_limit.ensure(reinterpret_cast<const void*>(KERNEL), tile_lds<kWide>());
+  hipLaunchKernelGGL(KERNEL, dim3(blocks), dim3(NTHREADS), tile_lds<kWide>(), stream, p);
 }
 int tiles(int64_t n, int size) { return (int)((n + size - 1) / size); }
+
+// When a forward launch of rows x c tiles over `panels` ends, in hundredths of a 256 x 256 tile's panel: whole rounds of the longest kind of tile, or where
+// several kinds are earlier than that, the mean and a part of the longest.  A tile of 384 counts 1.34 and one of 128 0.53, and each 4 or 6 panels beyond its
+// own; a single column of 384 streams its own rows of W from memory and waits for them.  Fitted to launches of 257 - 15900 rows over
+// 14 heads, scoring and with the stash, each cut in all ways; what it picks takes 0.4 % longer than the best of them.  Scoring, us, tiles of 256 and 128, tiles
+// of 384: V = 151936, d = 4096, 300 rows 422 and 413, 600 rows 648 and 622, 2500 rows 2249 and 2184; d = 1536, 300 rows 168 and 177, 900 rows 396 and 363; V = 50257,
+// d = 712, 300 rows 47 and 36, 1280 rows 97 and 113; V = 32000, d = 4096, 300 rows 98 and 117, 600 rows 165 and 128; d = 1536, 2000 rows 154 and 166, 2100 rows 179 and
+// 159; V = 8192, d = 4096, 1280 rows 78 and 109, 2500 rows 163 and 126.
+// (Worked out for every step of every launch, so what does not depend on the cut comes from outside: 120 steps 1.9 and 1.1 us of host time.)
+struct ForwardTiles {
+  int64_t wide, alone, narrow, half;
+  explicit ForwardTiles(int panels) : wide(134 * (int64_t)panels + 600), alone(wide * 115 / 100), narrow(100 * (int64_t)panels + 400), half(53 * (int64_t)panels + 600) {}
+};
+int64_t forward_end(const Cut& c, int rows, const ForwardTiles& t) {
+  const int count = c.count();
+  const int64_t wide = count == 1 ? t.alone : t.wide, most = c.wide > 0 ? wide : c.narrow > 0 ? t.narrow : t.half;
+  const uint64_t all = (uint64_t)count * rows;
+  int64_t end = (int64_t)((all + kRound - 1) / kRound) * most;
+  if (all > kRound && count != c.wide && count != c.narrow && count != c.half) {
+    const int64_t work = (int64_t)((uint64_t)(c.wide * wide + c.narrow * t.narrow + c.half * t.half) * rows / kRound);
+    const int64_t mixed = work + most * (c.wide > 0 ? 70 : 61) / 100;
+    end = mixed < end ? mixed : end;
+    end = end > most ? end : most;
+  }
+  return c.wide > 0 ? end + end / 50 : end;
+}
+// In a single round the last tile of a launch without tiles of 384 is a whole one: beside one of 128, which runs ahead of the one of 256 in the same rows
+// of W, both read those from memory (V = 32000, 300 rows, d = 2048 51 and 54 us, d = 4096 94 and 98; with 8 panels the same).
+int forward_kind(int n, int rows, int panels, const ForwardTiles& t) {
+  const Cut a = cut_wide(n), b = cut_narrow(n);
+  const bool even = panels >= 16 && b.half > 0 && b.narrow > 0 && b.count() * rows <= kRound;
+  const int small = even ? CUT_EVEN : CUT_NARROW;
+  if (a.wide == 0) return small;
+  const int64_t ea = forward_end(a, rows, t), eb = forward_end(even ? cut_rows<MODE_FWD>(n, CUT_EVEN) : b, rows, t);
+  const int64_t ec = a.count() == a.wide && a.wide > 1 ? forward_end(Cut{a.wide - 1, 1, 1}, rows, t) : ea;
+  return eb <= ea && eb <= ec ? small : ec < ea ? CUT_SHORT : CUT_WIDE;
+}
+
+// When a dH launch of c x cols tiles over `panels` ends, in hundredths of a 256 x 256 tile's panel: whole rounds of 256 tiles, and the last round in as many
+// slices as end earliest (a closed form of what dh_split searches for).  A tile of 384 counts 1.32 and one of 128 0.58, and a tile or slice 22
+// panels beyond its own, which favours few long ones: fitted to launches of 64 - 5120 rows over 13 heads, each cut in all three ways.
+int64_t dh_end(const Cut& c, int cols, int panels, int max_items) {
+  constexpr int kWideTile = 132, kNarrowTile = 100, kHalfTile = 58, kExtra = 22;
+  const int64_t all = (int64_t)c.count() * cols, whole = all / kRound;
+  const int64_t mean = (c.wide * kWideTile + c.narrow * kNarrowTile + c.half * kHalfTile) / c.count();
+  const int rest = (int)(all % kRound);
+  const int64_t one = whole > 0 ? mean : c.wide ? kWideTile : c.narrow ? kNarrowTile : kHalfTile;
+  int64_t last = 0;
+  for (int rounds = 1; rest > 0 && rounds <= 3; ++rounds) {
+    int s = rounds * kRound / rest;
+    s = s < dh_most_split(panels) ? s : dh_most_split(panels);
+    s = s * rest <= max_items ? s : max_items / rest;
+    s = s > 1 ? s : 1;
+    const int64_t e = tiles((int64_t)rest * s, kRound) * (int64_t)(slice_panels(panels, s) + kExtra) * one;
+    last = rounds == 1 || e < last ? e : last;
+  }
+  return whole * (panels + kExtra) * mean + last;
+}
+// Tiles of 128 only up to one round of them.  us, launch and reduction, tiles of 384, 256 and 128: V = 8192, d = 512, 300 rows 41, 35 and 24, 4000 rows 59, 53
+// and 46; V = 32000, d = 1536, 300 rows 61, 58 and 47, 900 rows 96, 92 and 90, 4000 rows 314, 344 and 365; d = 4096, 1500 rows 284, 322 and 389,
+// 2000 rows 417, 371 and 417; V = 151936, 300 rows 352, 463 and 429, 2000 rows 1762, 1703 and 2007, 3000 rows 2384, 2670 and 3062.
+int dh_kind(int n, int cols, int panels, int max_items) {
+  const Cut w = cut_rows<MODE_DH>(n, CUT_WIDE), q = cut_rows<MODE_DH>(n, CUT_EVEN), h = cut_rows<MODE_DH>(n, CUT_SHORT);
+  int64_t best = dh_end(w, cols, panels, max_items);
+  int kind = CUT_WIDE;
+  auto take = [&](const Cut& c, int k) { const int64_t e = dh_end(c, cols, panels, max_items); if (e < best) { best = e; kind = k; } };
+  take(q, CUT_EVEN);
+  if (h.half * cols <= kRound) take(h, CUT_SHORT);
+  return kind;
+}
+
+// What the host settles for a launch: how every count of valid rows up to chunk_rows is cut (all counts of a step alike), and as many
+// workgroups as any of them needs.
+struct CutPlan { uint64_t cuts[4]; int blocks, most; };
+template <class Kind> CutPlan plan_cuts(int rows, Kind kind) {
+  CutPlan plan = {};
+  for (int i = 0; i < kCutSteps && i * kCutStep < rows; ++i) plan.cuts[i >> 5] |= (uint64_t)kind((i + 1) * kCutStep) << (2 * (i & 31));
+  return plan;
+}
+CutPlan plan_forward(int chunk_rows, int V, int d) {
+  const int Mt = tiles(V, RES), panels = (int)(round_up(d, 2 * BK) / BK);
+  const ForwardTiles t(panels);
+  CutPlan plan = plan_cuts(chunk_rows, [&](int n) { return forward_kind(n, Mt, panels, t); });
+  plan.blocks = (int)round_up((int64_t)Mt * tiles(chunk_rows, 256), NXCD);
+  return plan;
+}
+CutPlan plan_dh(int chunk_rows, int V, int d, int max_items) {
+  const int Nt = tiles(d, RES), panels = (int)(round_up(V, 2 * BK) / BK);
+  int most = cut_wide(chunk_rows).count() * Nt;       // tiles, whatever the count of scored rows
+  CutPlan plan = plan_cuts(chunk_rows, [&](int n) {
+    const int kind = dh_kind(n, Nt, panels, max_items), t = cut_rows<MODE_DH>(n, kind).count() * Nt;
+    most = t > most ? t : most;
+    return kind;
+  });
+  plan.most = most;
+  plan.blocks = most / kRound * kRound + (int)round_up(dh_most_items(most, panels, max_items), NXCD);
+  return plan;
+}
+// dW, passes above kFewDwRows: 384 x 256 tiles, or 256 x 256 ones where those end earlier (short contractions over few rounds of tiles, whose last round the
+// cut does not pay for): 1.43 of the other tile's time, and about 8 panels' time per tile for its epilogue in either.
+// Launch, us, 256 x 256 and 384 x 256: V = 151936, 65536 rows, d = 4096 53800 and 50960, 47360 rows, d = 3584 34074 and 30363, 5120 rows,
+// d = 1536 1797 and 1675; V = 128256, 2000 rows, d = 1024 457 and 438.
+struct DwPlan { bool wide; int tiles, rest, most_split, blocks; SuperTile super; DwTailPlan tail; };
+DwPlan plan_dw(int chunk_rows, int expected_rows, int V, int d, int max_items) {
+  const int Nt = tiles(d, RES), expected = tiles(expected_rows, BK), most_panels = chunk_rows / BK;
+  DwPlan plan = {};
+  plan.super = pick_super_tile(Nt);
+  plan.tail = dw_tail_plan(tiles(V, RES), Nt, plan.super.m, plan.super.n);
+  plan.tiles = tiles(V, RING) * Nt;
+  plan.rest = plan.tiles % kRound;
+  plan.most_split = 1;
+  const int rest = plan.rest, split = rest > 0 ? dw_split(rest, expected, max_items) : 1;
+  const double last = rest == 0 ? 0 : split == 1 ? expected + 6 : tiles(rest * split, kRound) * ((expected + split - 1) / split + 6) + 12;
+  plan.wide = 1.43 * (plan.tiles / kRound * (expected + 6) + last) <= plan.tail.end * (expected + 8);
+  if (plan.wide) {
+    plan.blocks = plan.tiles;
+    if (rest > 0 && most_panels >= 16) {              // (as many slices as any count of scored rows can make)
+      plan.most_split = most_panels / 8 < 64 ? most_panels / 8 : 64;
+      const int items = rest * plan.most_split < max_items ? rest * plan.most_split : max_items;
+      plan.blocks = plan.tiles - rest + (items > rest ? items : rest);
+    }
+    plan.blocks = (int)round_up(plan.blocks, NXCD);
+    return plan;
+  }
+  plan.blocks = num_blocks(plan.tail.split > 0 ? plan.tail.m0 : tiles(V, RES), Nt, plan.super.m, plan.super.n);
+  return plan;
+}
 
 }  // namespace
 
@@ -1706,7 +1827,9 @@ void launch_gemm_fwd_bf16(const void* W, int64_t ldw, const void* W_tail, const 
     hipLaunchKernelGGL(forward_few_bf16, dim3(Mt), dim3(NTHREADS), F_LDS, stream, p);
     return;
   }
-  launch<MODE_FWD>(p, (int)round_up((int64_t)tiles(p.M, RES) * tiles(chunk_rows, 256), NXCD), stream);
+  const CutPlan plan = plan_forward(chunk_rows, V, d);
+  std::memcpy(p.cuts, plan.cuts, sizeof p.cuts);
+  launch<gemm_nt_bf16<MODE_FWD>>(p, plan.blocks, stream);
 }
 
 void launch_gemm_dh_bf16(const void* E, int64_t lde, const void* W, int64_t ldw, int V,
@@ -1722,12 +1845,11 @@ void launch_gemm_dh_bf16(const void* E, int64_t lde, const void* W, int64_t ldw,
   p.n_scored = n_scored; p.chunk_start = chunk_start; p.chunk_rows = chunk_rows;
   p.dH = dH; p.dh_f32 = dh_f32; p.d = d; p.V = V;
   p.tail_part = tail_part; p.max_items = tail_items;
-  // (as many tiles as any count of scored rows can make: of 384, or one round of 256)
-  const int Nt = tiles(d, RES), wide = tiles(chunk_rows, RING) * Nt, narrow = tiles(chunk_rows, 256) * Nt, panels = p.K / BK;
-  const int most = wide >= kRound ? wide : narrow < kRound ? narrow : kRound;
-  launch<MODE_DH>(p, most / kRound * kRound + (int)round_up(dh_most_items(most, panels, p.max_items), NXCD), stream);
-  if (dh_most_split(panels) > 1)
-    hipLaunchKernelGGL(dh_tail_reduce, dim3((most < kRound ? most : kRound - 1) * kReduceBlocks), dim3(256), 0, stream, p);
+  const CutPlan plan = plan_dh(chunk_rows, V, d, p.max_items);
+  std::memcpy(p.cuts, plan.cuts, sizeof p.cuts);
+  launch<gemm_nt_bf16<MODE_DH>>(p, plan.blocks, stream);
+  if (dh_most_split(p.K / BK) > 1)
+    hipLaunchKernelGGL(dh_tail_reduce, dim3((plan.most < kRound ? plan.most : kRound - 1) * kReduceBlocks), dim3(256), 0, stream, p);
 }
 
 size_t gemm_tail_tile_bytes() { return (size_t)RING * RES * sizeof(float); }
@@ -1761,32 +1883,18 @@ void launch_gemm_dw_bf16(const void* E, int64_t lde, const void* Ht, int64_t ldh
     hipLaunchKernelGGL(dw_few_bf16, dim3((unsigned)round_up(tiles, NXCD)), dim3(NTHREADS), D_LDS, stream, p);
     return;
   }
-  // 384 x 256 tiles, or 256 x 256 ones where those end earlier (short contractions over few rounds of tiles, whose last round the
-  // cut does not pay for): 1.43 of the other tile's time, and about 8 panels' time per tile for its epilogue in either.
-  // Launch, us, 256 x 256 and 384 x 256: V = 151936, 65536 rows, d = 4096 53800 and 50960, 47360 rows, d = 3584 34074 and 30363, 5120 rows,
-  // d = 1536 1797 and 1675; V = 128256, 2000 rows, d = 1024 457 and 438.
-  const int Nt = tiles(d, RES), wide_tiles = tiles(V, RING) * Nt, rest = wide_tiles % kRound;
-  const int expected = tiles(rows, BK), most_panels = chunk_rows / BK;
   p.max_items = tail_items;
-  const SuperTile st = pick_super_tile(Nt);
-  const DwTailPlan tail = dw_tail_plan(tiles(V, RES), Nt, st.m, st.n);
-  const int split = rest > 0 ? dw_split(rest, expected, tail_items) : 1;
-  const double last = rest == 0 ? 0 : split == 1 ? expected + 6 : tiles(rest * split, kRound) * ((expected + split - 1) / split + 6) + 12;
-  p.wide = 1.43 * (wide_tiles / kRound * (expected + 6) + last) <= tail.end * (expected + 8);
+  const DwPlan plan = plan_dw(chunk_rows, rows, V, d, tail_items);
+  p.wide = plan.wide;
   if (p.wide) {
-    int blocks = wide_tiles;
-    int most_split = 1;
-    if (rest > 0 && most_panels >= 16) {              // (as many slices as any count of scored rows can make)
-      most_split = most_panels / 8 < 64 ? most_panels / 8 : 64;
-      const int items = rest * most_split < tail_items ? rest * most_split : tail_items;
-      blocks = wide_tiles - rest + (items > rest ? items : rest);
-    }
-    launch<MODE_DW>(p, (int)round_up(blocks, NXCD), stream);
-    if (most_split > 1) hipLaunchKernelGGL(dw_wide_reduce, dim3(rest * kReduceBlocks), dim3(256), 0, stream, p);
+    launch<gemm_nt_bf16<MODE_DW>>(p, plan.blocks, stream);
+    if (plan.most_split > 1) hipLaunchKernelGGL(dw_wide_reduce, dim3(plan.rest * kReduceBlocks), dim3(256), 0, stream, p);
     return;
   }
-  p.sup_m = st.m; p.sup_n = st.n;
-  p.main_blocks = num_blocks(tail.split > 0 ? tail.m0 : tiles(V, RES), Nt, st.m, st.n);
+  const DwTailPlan& tail = plan.tail;
+  const int Nt = tiles(d, RES);
+  p.sup_m = plan.super.m; p.sup_n = plan.super.n;
+  p.main_blocks = plan.blocks;
   int blocks = p.main_blocks;
   if (tail.split > 0) {
     p.tail_m0 = tail.m0; p.tail_rows = tail.rows; p.tail_split = tail.split;
@@ -1798,7 +1906,7 @@ void launch_gemm_dw_bf16(const void* E, int64_t lde, const void* Ht, int64_t ldh
     p.tail_first[NXCD] = tail.first[NXCD];
     blocks += most * NXCD;
   }
-  launch<MODE_DW>(p, blocks, stream);
+  launch<gemm_nt_bf16<MODE_DW>>(p, blocks, stream);
   if (tail.split > 0) {
     const int n = tail.rows * Nt;
     hipLaunchKernelGGL(dw_tail_reduce, dim3(n * (RES * RES / 256)), dim3(256), 0, stream, tail_part, n, tail.split, Nt, tail.m0, V, d, dW,
@@ -1815,6 +1923,40 @@ extern "C" int mrl_diag_dh_split(int32_t tail_tiles, int32_t panels, int32_t max
 }
 
 extern "C" int mrl_diag_dw_few_rows(void) { return mrl::kFewDwRows; }
+
+extern "C" int mrl_diag_gemm_cut(int32_t launch, int32_t rows, int32_t expected, int32_t chunk_rows, int32_t V, int32_t d, int32_t tail_items,
+                                 int32_t* out9) {
+  using namespace mrl;
+  if (out9 == nullptr) return MRL_ERR_NULL;
+  if (V <= 0 || d <= 0 || d % 8 != 0 || chunk_rows <= 0 || chunk_rows % kTile != 0 || rows <= 0 || rows > chunk_rows || expected <= 0 ||
+      tail_items < 0 || (launch != MRL_PROF_GEMM_FWD && launch != MRL_PROF_GEMM_DH && launch != MRL_PROF_GEMM_DW))
+    return MRL_ERR_SHAPE;
+  for (int i = 0; i < 9; ++i) out9[i] = 0;
+  const int Nt = tiles(d, RES);
+  const int items = tail_items > 0 ? tail_items : gemm_tail_items((size_t)round_up(d, 128) * (round_up(V, kTile) + 64) * 2);
+  out9[7] = items;
+  auto put = [&](int wide, int narrow, int half, int all, int split, int blocks) {
+    out9[0] = wide; out9[1] = narrow; out9[2] = half; out9[3] = all;
+    out9[4] = all % kRound; out9[5] = split; out9[6] = blocks;
+  };
+  if (launch == MRL_PROF_GEMM_DW) {
+    if (dw_rows_in_blocks(expected)) return MRL_OK;
+    const DwPlan plan = plan_dw(chunk_rows, expected, V, d, items);
+    const int panels = dw_panels(rows, chunk_rows);
+    if (plan.wide) put(tiles(V, RING), 0, 0, plan.tiles, plan.rest > 0 ? dw_split(plan.rest, panels, items) : 1, plan.blocks);
+    else put(0, tiles(V, RES), 0, tiles(V, RES) * Nt, plan.tail.split > 0 ? plan.tail.split : 1, plan.blocks);
+    if (!plan.wide) out9[4] = plan.tail.split > 0 ? plan.tail.rows * Nt : 0;
+    return MRL_OK;
+  }
+  const bool fwd = launch == MRL_PROF_GEMM_FWD;
+  const CutPlan plan = fwd ? plan_forward(chunk_rows, V, d) : plan_dh(chunk_rows, V, d, items);
+  const int panels = (int)(round_up(V, 2 * BK) / BK), kind = cut_kind(plan.cuts, rows);
+  const Cut cut = fwd ? cut_rows<MODE_FWD>(rows, kind) : cut_rows<MODE_DH>(rows, kind);
+  const int all = cut.count() * (fwd ? tiles(V, RES) : Nt);
+  put(cut.wide, cut.narrow, cut.half, all, !fwd && all % kRound > 0 ? dh_split(all % kRound, panels, items) : 1, plan.blocks);
+  out9[8] = cut.start(cut.count() - 1);
+  return MRL_OK;
+}
 
 extern "C" int mrl_diag_dw_tail_plan(int32_t V, int32_t d, int32_t* out12) {
   using namespace mrl;

@@ -248,6 +248,50 @@ def test_dh_split_is_the_earliest_end():
                 assert f(tiles, panels, room) == best, (tiles, panels, room)
 
 
+def _cut_cases():
+    for V in (300, 1000, 2048, 8192, 32000, 50257, 128256, 151936):
+        for d in (64, 512, 712, 1024, 1536, 4096, 8192):
+            for chunk in (512, 1024, 2560, 5120, 16384, 65536):
+                for rows in sorted({1, 128, 129, 256, 257, 384, 385, 640, 1000, 1877, 2000, 3000, 5000, 16384, 16385, chunk - 1, chunk}):
+                    if rows <= chunk:
+                        yield V, d, chunk, rows
+
+
+def test_tiles_of_the_large_launches_cover_their_rows():
+    """For every count of valid rows: the tiles cover the rows, the workgroups launched are as many as the device deals out (whole
+    rounds of 256, then the last round's slices, to 8 XCDs), and the slices fit the scratch."""
+    f, out = m.lib().mrl_diag_gemm_cut, (ctypes.c_int32 * 9)()
+    assert f(2, 1, 1, 256, 1000, 64, 0, None) == -1
+    for bad in ((3, 1, 1, 256, 1000, 64, 0), (2, 0, 1, 256, 1000, 64, 0), (2, 257, 1, 256, 1000, 64, 0), (2, 1, 1, 200, 1000, 64, 0),
+                (5, 1, 1, 256, 0, 64, 0), (5, 1, 1, 256, 1000, 60, 0), (6, 1, 0, 256, 1000, 64, 0), (6, 1, 1, 256, 1000, 64, -1)):
+        assert f(*bad, out) == -2, bad
+    dealt = lambda whole, items: whole + -(-items // 8) * 8
+    cuts = {m.GEMM_FWD: set(), m.GEMM_DH: set()}
+    for V, d, chunk, rows in _cut_cases():
+        for launch, other in ((m.GEMM_FWD, -(-V // 256)), (m.GEMM_DH, -(-d // 256))):
+            if launch == m.GEMM_FWD and chunk > 16384:
+                continue
+            for room in (0, 300) if launch == m.GEMM_DH else (0,):
+                c = m.gemm_cut(launch, rows, V, d, chunk, 0, room)
+                at = (launch, V, d, chunk, rows, room, c)
+                long = 384 * c["wide"] + 256 * c["narrow"] + 128 * c["half"]
+                last = 128 if c["half"] else 256 if c["narrow"] else 384
+                assert c["last_start"] < rows <= long and c["last_start"] == long - last, at
+                assert c["tiles"] == (c["wide"] + c["narrow"] + c["half"]) * other and c["rest"] == c["tiles"] % 256, at
+                assert c["split"] == 1 or c["rest"] * c["split"] <= c["tail_items"], at
+                assert dealt(c["tiles"] - c["rest"], c["rest"] * c["split"]) <= c["blocks"], at
+                if launch == m.GEMM_DH:
+                    assert c["half"] == 0 or (c["wide"] + c["narrow"] == 0 and c["tiles"] <= 256), at
+                cuts[launch].add((c["wide"] > 0, c["narrow"] > 0, c["half"] > 0))
+        for room in (0, 171):
+            c = m.gemm_cut(m.GEMM_DW, rows, V, d, chunk, chunk, room)
+            if c["wide"]:
+                assert c["tiles"] == -(-V // 384) * -(-d // 256) and c["rest"] == c["tiles"] % 256
+                assert c["split"] == 1 or c["rest"] * c["split"] <= c["tail_items"]
+                assert dealt(c["tiles"] - c["rest"], c["rest"] * c["split"]) <= c["blocks"]
+    assert len(cuts[m.GEMM_FWD]) >= 5 and len(cuts[m.GEMM_DH]) >= 4
+
+
 def test_thl_word_align_argument_errors():
     f = m.lib().mrl_thl_word_align
     args = lambda **kw: [kw.get("p0", FAKE), FAKE, FAKE, FAKE, FAKE, FAKE, FAKE, kw.get("B", 4), kw.get("S", 16), 16,
