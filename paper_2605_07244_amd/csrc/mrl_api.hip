@@ -16,10 +16,12 @@ static __device__ __align__(256) unsigned char scratch[MRL_STATIC_SCRATCH_BYTES]
 namespace mrl {
 namespace {
 
-constexpr int kDefaultChunkBf16 = 61440;   // rows per pass: amortises the fp32 dW read-modify-write (19 GB of stash at V = 151936); four forward launches
-// forward launches cover this many rows: their H rows stay in the Infinity Cache, and 40 columns of tiles make whole groups of 8 x 4 in a
-// band (V = 151936, d = 4096: 15360 rows 314 us a column, 16384 rows - 42 and one of 256 - 321, 16512 rows 328)
-constexpr int kFwdSubChunk = 15360;
+constexpr int kDefaultChunkBf16 = 65536;   // rows per pass: amortises the fp32 dW read-modify-write (20 GB of stash at V = 151936)
+// Forward launches cover this many rows: their H rows stay in the Infinity Cache.  15360 of them are 40 columns of tiles, whole groups of 8 x 4 in a
+// band (V = 151936, d = 4096: 15360 rows 314 us a column, 16384 rows - 42 and one of 256 - 321, 16512 rows 328; 16384 rows in two launches
+// and in one 13007 and 13282 us), but what is left of a pass then takes a launch more, which weighs with small heads (65536 rows in five launches and in four: V = 1000,
+// d = 64 98 and 86 us, V = 32000, d = 512 2015 and 1970, d = 2048 5861 and 5780, d = 4096 11129 and 11256).
+int forward_part(int V, int d) { return (int64_t)V * d > 100000000 ? 15360 : 16384; }
 constexpr int kDefaultChunkF32 = 2048;
 constexpr int kTailOnlyRows = 4096;        // (see head_tail_only)
 constexpr int64_t kMaxSlots = (int64_t)1 << 30;
@@ -293,8 +295,9 @@ void forward_chunk(const void* H, const void* W, int d, int V, bool bf16, const 
     const void* W_tail = L.dp != d && !padded ? at<void>(ws, L.Wp) : nullptr;
     const int64_t ldw = padded ? L.ldh : d;
     const bool blocks = rows_in_blocks(L.chunk_rows);
-    for (int sub = 0; sub < L.chunk_rows; sub += kFwdSubChunk) {
-      const int rows = L.chunk_rows - sub < kFwdSubChunk ? L.chunk_rows - sub : kFwdSubChunk;
+    const int part = forward_part(V, d);
+    for (int sub = 0; sub < L.chunk_rows; sub += part) {
+      const int rows = L.chunk_rows - sub < part ? L.chunk_rows - sub : part;
       Scope sc(MRL_PROF_GEMM_FWD, s);   // one event pair per kernel launch
       launch_gemm_fwd_bf16(Wk, ldw, W_tail, at<uint16_t>(ws, L.Hc) + (size_t)sub * L.ldh, blocks ? L.chunk_rows : L.ldh,
                            L.dp, at<float>(ws, L.zt),

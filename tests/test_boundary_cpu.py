@@ -292,6 +292,16 @@ def test_tiles_of_the_large_launches_cover_their_rows():
     assert len(cuts[m.GEMM_FWD]) >= 5 and len(cuts[m.GEMM_DH]) >= 4
 
 
+def test_a_pass_holds_up_to_65536_rows():
+    """A call of up to 65536 slots is one pass: its stash grows with every 256 slots up to there, and not beyond."""
+    f = m.lib().mrl_grpo_loss_workspace
+    size = lambda N: f(1, N, 64, 1000, 1, None)
+    stash = 256 * (1024 + 64) * 2
+    for N in (61440, 65280):
+        assert size(N + 256) - size(N) >= stash, N
+    assert size(65536 + 256) - size(65536) < stash
+
+
 def test_thl_word_align_argument_errors():
     f = m.lib().mrl_thl_word_align
     args = lambda **kw: [kw.get("p0", FAKE), FAKE, FAKE, FAKE, FAKE, FAKE, FAKE, kw.get("B", 4), kw.get("S", 16), 16,
