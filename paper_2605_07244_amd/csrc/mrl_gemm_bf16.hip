@@ -1699,11 +1699,12 @@ int64_t forward_end(const Cut& c, int rows, const ForwardTiles& t) {
   }
   return c.wide > 0 ? end + end / 50 : end;
 }
-// In a single round the last tile of a launch without tiles of 384 is a whole one: beside one of 128, which runs ahead of the one of 256 in the same rows
-// of W, both read those from memory (V = 32000, 300 rows, d = 2048 51 and 54 us, d = 4096 94 and 98; with 8 panels the same).
+// In a single round that fills most of the chip the last tile of a launch without tiles of 384 is a whole one: beside one of 128, which runs ahead of the one
+// of 256 in the same rows of W, both read those from memory (300 rows, V = 32000, d = 2048 51 and 54 us, d = 4096 94 and 98, d = 8192 195 and 239; with 8 panels
+// the same; fewer tiles V = 20000, d = 6144 120 and 114, V = 8000, d = 16384 305 and 283).
 int forward_kind(int n, int rows, int panels, const ForwardTiles& t) {
   const Cut a = cut_wide(n), b = cut_narrow(n);
-  const bool even = panels >= 16 && b.half > 0 && b.narrow > 0 && b.count() * rows <= kRound;
+  const bool even = panels >= 16 && b.half > 0 && b.narrow > 0 && b.count() * rows <= kRound && b.count() * rows > kRound * 3 / 4;
   const int small = even ? CUT_EVEN : CUT_NARROW;
   if (a.wide == 0) return small;
   const int64_t ea = forward_end(a, rows, t), eb = forward_end(even ? cut_rows<MODE_FWD>(n, CUT_EVEN) : b, rows, t);
@@ -1752,6 +1753,16 @@ template <class Kind> CutPlan plan_cuts(int rows, Kind kind) {
   for (int i = 0; i < kCutSteps && i * kCutStep < rows; ++i) plan.cuts[i >> 5] |= (uint64_t)kind((i + 1) * kCutStep) << (2 * (i & 31));
   return plan;
 }
+// The plan of the launch before, per thread: a call's passes and the parts of a pass are alike (1000000 slots, 100 scored, V = 1000, d = 64: 64 forward
+// launches, 358 us a call without it and 349 with it).
+struct LastPlan {
+  int64_t key[4] = {-1, -1, -1, -1};
+  CutPlan plan;
+  template <class Make> const CutPlan& get(int64_t a, int64_t b, int64_t c, int64_t e, Make make) {
+    if (key[0] != a || key[1] != b || key[2] != c || key[3] != e) { plan = make(); key[0] = a; key[1] = b; key[2] = c; key[3] = e; }
+    return plan;
+  }
+};
 CutPlan plan_forward(int chunk_rows, int V, int d) {
   const int Mt = tiles(V, RES), panels = (int)(round_up(d, 2 * BK) / BK);
   const ForwardTiles t(panels);
@@ -1827,7 +1838,8 @@ void launch_gemm_fwd_bf16(const void* W, int64_t ldw, const void* W_tail, const 
     hipLaunchKernelGGL(forward_few_bf16, dim3(Mt), dim3(NTHREADS), F_LDS, stream, p);
     return;
   }
-  const CutPlan plan = plan_forward(chunk_rows, V, d);
+  thread_local LastPlan last;
+  const CutPlan& plan = last.get(chunk_rows, V, d, 0, [&] { return plan_forward(chunk_rows, V, d); });
   std::memcpy(p.cuts, plan.cuts, sizeof p.cuts);
   launch<gemm_nt_bf16<MODE_FWD>>(p, plan.blocks, stream);
 }
@@ -1845,7 +1857,8 @@ void launch_gemm_dh_bf16(const void* E, int64_t lde, const void* W, int64_t ldw,
   p.n_scored = n_scored; p.chunk_start = chunk_start; p.chunk_rows = chunk_rows;
   p.dH = dH; p.dh_f32 = dh_f32; p.d = d; p.V = V;
   p.tail_part = tail_part; p.max_items = tail_items;
-  const CutPlan plan = plan_dh(chunk_rows, V, d, p.max_items);
+  thread_local LastPlan last;
+  const CutPlan& plan = last.get(chunk_rows, V, d, tail_items, [&] { return plan_dh(chunk_rows, V, d, tail_items); });
   std::memcpy(p.cuts, plan.cuts, sizeof p.cuts);
   launch<gemm_nt_bf16<MODE_DH>>(p, plan.blocks, stream);
   if (dh_most_split(p.K / BK) > 1)
