@@ -149,19 +149,25 @@ def test_runs_are_bit_reproducible(mrl, synth):
     assert a["st"] == c["st"]
 
 
-def test_dw_with_k_split_tail_is_bit_reproducible_and_accumulates(mrl, synth):
-    # V = 151936, d = 1536: the ragged last rows of dW tiles are cut into K slices whose partial tiles a
-    # second kernel adds in slice order; two passes, longer than the launch for few rows takes, so that the
-    # second adds into the first's result
-    sp, b = _small(synth, n_prompts=5, T=64, V=151936, d=1536)
-    assert mrl.dw_few_rows() < 1280 < int(b["mask"].sum()) <= 2560 and mrl.dw_tail_plan(151936, 1536)["split"] > 1
+@pytest.mark.parametrize("V,wide", [(11000, False), (151936, True)])
+def test_dw_with_k_split_tail_is_bit_reproducible_and_accumulates(mrl, synth, V, wide):
+    # d = 1536.  V = 11000: the ragged last rows of dW tiles are cut into eight K slices whose partial tiles a second kernel adds in
+    # slice order.  V = 151936: tiles of 384, the last 72 of them left whole in passes of 1280 rows and cut into three slices in one of 2560.
+    # Two passes, longer than the launch for few rows takes, so that the second adds into the first's result
+    sp, b = _small(synth, n_prompts=5, T=64, V=V, d=1536)
+    n = int(b["mask"].sum())
+    assert mrl.dw_few_rows() < 1280 < n <= 2560
+    cuts = [mrl.gemm_cut(mrl.GEMM_DW, min(n, rows), V, 1536, rows) for rows in (1280, 2560)]
+    assert [c["wide"] > 0 for c in cuts] == [wide] * 2 and [c["split"] > 1 for c in cuts] == [not wide, True]
     a = _gpu_loss(mrl, sp, b, cfg=dict(chunk_rows=1280))
     c = _gpu_loss(mrl, sp, b, cfg=dict(chunk_rows=1280))
     assert torch.equal(a["dW"], c["dW"]) and torch.equal(a["dH"], c["dH"])
     one = _gpu_loss(mrl, sp, b, cfg=dict(chunk_rows=2560))         # one pass
+    again = _gpu_loss(mrl, sp, b, cfg=dict(chunk_rows=2560))
+    assert torch.equal(one["dW"], again["dW"])
     scale = float(one["dW"].abs().max())
     assert float((a["dW"] - one["dW"]).abs().max()) <= 1e-5 * scale   # fp32 sums in a different order
-    tail = a["dW"][151936 // 256 // 8 * 8 * 256:]                     # the rows of the split tiles
+    tail = a["dW"][V // 256 // 8 * 8 * 256:]                          # the rows of the split tiles
     assert float(tail.abs().max()) > 0
 
 

@@ -143,23 +143,24 @@ def test_mini_config5_full_vocab_and_width(mrl, synth):
 
 
 def test_mini_config2_full_vocab_uneven_dw_tail(mrl, synth):
-    # full V = 151936 at d = 1536: the last two rows of dW tiles (12 tiles) are cut into K slices that
-    # the launch plan deals to the XCDs unevenly (those that finish their whole tiles early take them); a pass that could
-    # hold more rows than the launch for few rows takes, with a part of the slices filled
+    # full V = 151936 at d = 1536: dW in nine whole rounds of tiles of 384 x 256 and 72 more, a last row of tiles with 256 of 384 rows; a pass that could
+    # hold more rows than the launch for few rows takes, with a part of its panels
     sp = synth.spec(2, n_prompts=1, T=40)
-    assert mrl.dw_few_rows() < 1280
+    cut = mrl.gemm_cut(mrl.GEMM_DW, 1280, 151936, 1536)
+    assert mrl.dw_few_rows() < 1280 and (cut["wide"], cut["rest"]) == (396, 72)
     _run_both(mrl, synth, sp, chunk_rows=1280)
 
 
-@pytest.mark.parametrize("V,d", [(8627, 2048), (20224, 2304), (7424, 2304), (11008, 1536), (16819, 640),
-                                 (13312, 2304), (17587, 1024)])
+@pytest.mark.parametrize("V,d", [(8627, 2048), (13444, 2304), (7766, 2304), (7424, 2304), (11008, 1536), (16819, 640),
+                                 (13312, 2304), (17587, 1024), (16448, 1024)])
 def test_dw_tail_plans(mrl, synth, V, d):
-    """Head shapes whose dW launch cuts its ragged last rows of tiles into K slices, with 1 to 7 such rows,
+    """Head shapes whose dW launch runs on 256 x 256 tiles and cuts its ragged last rows of tiles into K slices, with 1 to 7 such rows,
     2 to 8 slices, item counts that differ from XCD to XCD, and widths of a whole and of a ragged number of
     256-wide tiles; two passes of the length that takes this launch, so that the second adds the slices into the first's
     result."""
     plan = mrl.dw_tail_plan(V, d)
-    assert plan["split"] >= 2 and mrl.dw_few_rows() < 1280
+    cut = mrl.gemm_cut(mrl.GEMM_DW, 1280, V, d)
+    assert plan["split"] >= 2 and mrl.dw_few_rows() < 1280 and cut["wide"] == 0 and cut["split"] == plan["split"]
     sp = synth.spec(2, n_prompts=5, T=64, V=V, d=d)
     batch, _, _, _ = _run_both(mrl, synth, sp, chunk_rows=1280)
     assert int(batch["mask"].sum()) > 1280

@@ -27,12 +27,18 @@ def _head(N, d, V, scored, seed):
     return H, W, y, mask
 
 
+def _cut(mrl, launch, rows, d, V, chunk_rows=0, tail_items=0):
+    """(tiles of 384, 256, 128 along the tokens - dW: the vocabulary -, tiles of the last round, slices of each) of a launch."""
+    c = mrl.gemm_cut(launch, rows, V, d, chunk_rows, 0, tail_items)
+    return c["wide"], c["narrow"], c["half"], c["rest"], c["split"]
+
+
 @pytest.mark.parametrize("N,scored,d,V", [
     (4096, 1, 128, 300),          # one row, two vocabulary tiles
-    (4096, 257, 128, 2048),       # two tile columns of sixteen, one whole band
-    (2048, 700, 256, 8192),       # three of eight columns, 96 tiles: less than a round
-    (2048, 1281, 128, 11000),     # six columns, 43 vocabulary tiles (ragged last band), 258 tiles
-    (4096, 4096, 128, 8300),      # every slot scored: sixteen columns, 33 vocabulary tiles
+    (4096, 257, 128, 2048),       # a column of 256 and one of 128, one whole band
+    (2048, 700, 256, 8192),       # three columns of 256, 96 tiles: less than a round
+    (2048, 1281, 128, 11000),     # three columns of 384 and one of 256, 43 vocabulary tiles (ragged last band), 172 tiles
+    (4096, 4096, 128, 8300),      # every slot scored: ten columns of 384 and one of 256, 33 vocabulary tiles, 107 behind a whole round
 ])
 def test_forward_tiles_cover_scored_rows(mrl, N, scored, d, V):
     H, W, y, mask = _head(N, d, V, scored, N + scored)
@@ -90,15 +96,23 @@ def _step(mrl, H, W, y, mask, dh_dtype, seed, chunk_rows=0, poison=False, hint=0
     return out, dH.cpu().numpy(), (dz.t() @ H[rows].double()).cpu().numpy()
 
 
-@pytest.mark.parametrize("scored,d,V,dh_f32", [
-    (1, 256, 70, 0),              # one tile, a vocabulary shorter than a panel pair
-    (300, 136, 1000, 1),          # two tiles of a padded width, too few panels to slice
-    (255, 512, 9001, 0),          # two tiles of eight slices
-    (700, 1000, 16500, 1),        # twelve tiles of 16 slices, float output, a width that ends inside a tile
-    (2500, 4096, 4200, 0),        # 160 tiles: more than half a round, left whole
-    (4200, 4096, 5003, 0),        # 272 tiles: a whole round and 16 tiles of five slices
+@pytest.mark.parametrize("scored,d,V,dh_f32,cut", [
+    (1, 256, 70, 0, (0, 0, 1, 1, 1)),                # one tile, a vocabulary shorter than a panel pair
+    (300, 136, 1000, 1, (0, 0, 3, 3, 1)),            # three tiles of 128 over a padded width, too few panels to slice
+    (255, 512, 9001, 0, (0, 0, 2, 4, 8)),            # four tiles of 128, eight slices
+    (700, 1000, 16500, 1, (0, 0, 6, 24, 10)),        # float output from slices, a width that ends inside a tile
+    (2500, 4096, 4200, 0, (6, 1, 0, 112, 2)),        # tiles of 384 and a row of tiles of 256, two slices
+    (2500, 4096, 4200, 1, (6, 1, 0, 112, 2)),
+    (4200, 4096, 5003, 0, (11, 0, 0, 176, 1)),       # 176 tiles of 384: more than half a round, left whole
+    (4200, 4096, 5003, 1, (11, 0, 0, 176, 1)),
+    (8300, 4096, 2000, 0, (21, 1, 0, 96, 2)),        # 352 tiles: a whole round and 96 of two slices
+    (2500, 3080, 1000, 0, (0, 10, 0, 130, 1)),       # tiles of 256: whole
+    (2500, 3080, 1000, 1, (0, 10, 0, 130, 1)),
+    (8300, 264, 3001, 0, (0, 33, 0, 66, 3)),         # ... in slices, the last row of tiles with 108 tokens
+    (5200, 3080, 8000, 0, (0, 21, 0, 17, 7)),        # ... a whole round and 17 of seven slices
 ])
-def test_dh_tiles_and_slices(mrl, scored, d, V, dh_f32):
+def test_dh_tiles_and_slices(mrl, scored, d, V, dh_f32, cut):
+    assert _cut(mrl, mrl.GEMM_DH, scored, d, V, -(-(scored + 37) // 256) * 256) == cut
     H, W, y, mask = _head(scored + 37, d, V, scored, scored)
     out, dH, dW = _step(mrl, H, W, y, mask, mrl.F32 if dh_f32 else mrl.BF16, scored)
     # bf16 operands (e, the scaled hidden rows, the output): 2^-9 each, the bar of the parity tests
@@ -231,7 +245,7 @@ def test_dw_tail_slices_without_panels(mrl, scored):
     """The tail of this head is planned as 8 slices; 2, 4, 6, 12 and 18 panels fill 1, 2, 3, 6 and 5 of them.  The others store
     nothing and are not read: the scratch holds NaN before.  (A pass that can hold 1280 rows, which is what the launch goes by.)"""
     d, V = 1024, 16405
-    assert mrl.dw_tail_plan(V, d)["split"] == 8 and mrl.dw_few_rows() < 1280
+    assert mrl.dw_tail_plan(V, d)["split"] == 8 and mrl.dw_few_rows() < 1280 and _cut(mrl, mrl.GEMM_DW, scored, d, V, 1280) == (0, 65, 0, 4, 8)
     H, W, y, mask = _head(scored + 3, d, V, scored, scored)
     out, dH, dW = _step(mrl, H, W, y, mask, mrl.BF16, scored, chunk_rows=1280, poison=True)
     util.check_gradient("dW", util.to_f64(out["dW"]), dW)
@@ -292,10 +306,10 @@ def test_few_rows_behind_others(mrl, N, scored, chunk_rows):
     assert torch.all(out["dH"][~ok] == 0)
 
 
-def test_dh_slices_in_two_rounds(mrl):
-    """144 tiles of three slices: more items than compute units."""
-    scored, d, V = 2050, 4096, 24000
-    assert mrl.lib().mrl_diag_dh_split(144, 376, 444) == 3     # (444: partial tiles in this head's workspace)
+@pytest.mark.parametrize("scored,d,V,cut", [(1100, 8192, 21000, (3, 0, 0, 96, 5)), (1100, 8192, 40003, (3, 0, 0, 96, 8))])
+def test_dh_slices_in_two_rounds(mrl, scored, d, V, cut):
+    """96 tiles of five and of eight slices: more items than compute units, in two and in three rounds."""
+    assert _cut(mrl, mrl.GEMM_DH, scored, d, V, -(-(scored + 5) // 256) * 256) == cut and cut[3] * cut[4] > 256
     H, W, y, mask = _head(scored + 5, d, V, scored, 9)
     rows = torch.nonzero(mask)[:, 0]
     z = H[rows].double() @ W.double().t()
@@ -439,6 +453,7 @@ def test_dw_k_split_tail_above_the_few_rows(mrl, scored):
     adds into the first's result, poisoned scratch."""
     d, V = 1536, 11000
     assert mrl.dw_tail_plan(V, d)["split"] == 8 and mrl.dw_few_rows() == 1024
+    assert all(_cut(mrl, mrl.GEMM_DW, 1025, d, V, chunk) == (0, 43, 0, 18, 8) for chunk in (1280, 1536))
     H, W, y, mask = _head(1500, d, V, scored, scored)
     out, _, dW = _step(mrl, H, W, y, mask, mrl.BF16, V, poison=True)
     again, _, _ = _step(mrl, H, W, y, mask, mrl.BF16, V, poison=True)
@@ -530,18 +545,26 @@ def test_prep_inside_the_row_preparation(mrl, B, T, extra):
     assert torch.all(a["logp"][mask[:N] == 0] == 0) and torch.all(a["dH"][mask[:N] == 0] == 0)
 
 
-@pytest.mark.parametrize("scored,d,V,chunk_rows", [
-    (600, 128, 32005, 1280),      # forward: a column of 384 and one of 256, a ragged last row of W; dH: two rows of tiles of 256 and a half one
-    (700, 136, 32000, 0),         # two columns of 384, the second with 316 tokens; a padded width
-    (1152, 256, 30001, 2048),     # three whole columns; dW on 79 rows of 384, the last with 49
-    (2000, 256, 40003, 0),        # dW: 105 tiles of two slices
-    (2000, 264, 40003, 1280),     # ... and a second pass that adds into the first's result
-    (4200, 1032, 9999, 0),        # dW: 135 tiles whole; dH: 55 tiles of four slices
-    (3500, 2056, 21000, 0),       # dW: 495 tiles, 239 behind a whole round; dH rows of 384 and a short one
+@pytest.mark.parametrize("scored,d,V,chunk_rows,fwd,dh,dw", [
+    (600, 128, 32005, 1280, (1, 1, 0, 252, 1), (0, 0, 5, 5, 31), (0, 126, 0, 0, 1)),      # forward: a column of 384 and one of 256, a ragged last row of W
+    (700, 136, 32000, 0, (2, 0, 0, 250, 1), (0, 0, 6, 6, 31), None),                      # two columns of 384, the second with 316 tokens; a padded width
+    (1152, 256, 30001, 2048, (3, 0, 0, 98, 1), (0, 0, 9, 9, 28), (0, 118, 0, 0, 1)),      # three whole columns of 384
+    (300, 1032, 32005, 0, (0, 2, 0, 252, 1), (0, 0, 3, 15, 17), None),                    # 44 tokens in a last column of 256, a round nearly full
+    (4200, 1032, 24000, 0, (10, 1, 1, 104, 1), (0, 17, 0, 85, 3), (0, 94, 0, 30, 2)),     # a last column of 384 as one of 256 and one of 128
+    (2000, 256, 40003, 0, (0, 8, 0, 232, 1), (0, 0, 16, 16, 16), (0, 157, 0, 0, 1)),
+    (2000, 136, 1000, 0, (0, 8, 0, 32, 1), (0, 0, 16, 16, 1), (3, 0, 0, 3, 4)),           # dW: three tiles of four slices
+    (2000, 264, 40003, 1280, (0, 5, 0, 17, 1), (0, 0, 10, 20, 12), (105, 0, 0, 210, 1)),  # dW: tiles of 384 left whole, a second pass that adds into the first's result
+    (2000, 3080, 9999, 0, (4, 2, 0, 240, 1), (4, 2, 0, 78, 3), (27, 0, 0, 95, 2)),        # dW: a whole round, and 95 tiles of two slices
+    (3200, 3080, 9999, 1792, (4, 1, 0, 200, 1), (4, 1, 0, 65, 3), (27, 0, 0, 95, 2)),      # ... twice
+    (3500, 2056, 21000, 0, (0, 14, 0, 138, 1), (0, 14, 0, 126, 2), (55, 0, 0, 239, 1)),   # dW: 239 tiles behind a whole round
 ])
-def test_tiles_of_384(mrl, scored, d, V, chunk_rows):
-    """The large tiles of the three products: whole, ragged and in slices; the log-probs have the bits that a pass of few rows gives."""
+def test_tiles_of_384(mrl, scored, d, V, chunk_rows, fwd, dh, dw):
+    """The large tiles of the three products: whole, ragged and in slices; the log-probs have the bits that a pass of few rows gives.
+    The cuts are those of the first pass."""
     N = scored + 21
+    chunk = chunk_rows or -(-N // 256) * 256
+    for launch, cut in ((mrl.GEMM_FWD, fwd), (mrl.GEMM_DH, dh), (mrl.GEMM_DW, dw)):
+        assert _cut(mrl, launch, min(scored, chunk), d, V, chunk) == (cut or (0, 0, 0, 0, 0)), launch
     H, W, y, mask = _head(N, d, V, scored, scored + d)
     out, dH, dW = _step(mrl, H, W, y, mask, mrl.BF16, d, chunk_rows=chunk_rows, poison=True)
     util.check_gradient("dH", util.to_f64(out["dH"]), dH)
@@ -574,3 +597,28 @@ def test_workspace_without_room_for_all_partial_tiles(mrl):
     util.check_gradient("dW", util.to_f64(got["dW"]), util.to_f64(want["dW"]))
     with pytest.raises(RuntimeError):
         call(least - 256)
+
+
+@pytest.mark.parametrize("scored,d,V,full,least", [
+    (2500, 136, 14001, (37, 0, 0, 37, 5), (37, 0, 0, 37, 4)),          # tiles of 384: fewer slices
+    (1100, 2304, 7424, (0, 29, 0, 45, 5), (0, 29, 0, 45, 5)),          # tiles of 256: 225 items, smaller ones, as before
+])
+def test_dw_slices_in_the_least_workspace(mrl, scored, d, V, full, least):
+    """dW's partial tiles, above the rows that have a launch without any, in the smallest workspace that a pass takes: nothing
+    is written behind it, and dW is that of the full one to rounding."""
+    assert scored > mrl.dw_few_rows()
+    chunk = -(-scored // 256) * 256
+    items = mrl.gemm_cut(mrl.GEMM_DW, scored, V, d, chunk)["tail_items"]
+    H, W, y, mask = _head(scored, d, V, scored, 5)
+    cfg = mrl.LossConfig(kl_beta=0.0, chunk_rows=chunk)
+    size = mrl.grpo_loss_workspace(1, scored, d, V, mrl.BF16, cfg)
+    small = size - items * 128 * 256 * 4
+    assert _cut(mrl, mrl.GEMM_DW, scored, d, V, chunk) == full and _cut(mrl, mrl.GEMM_DW, scored, d, V, chunk, items * 2 // 3) == least
+    _, _, dW = _step(mrl, H, W, y, mask, mrl.BF16, 7, chunk_rows=chunk)
+    behav = _behaviour(H, W, y, mask, 7)
+    one = lambda v, t: torch.tensor([v], dtype=t, device="cuda")
+    buf = torch.full((small + 4096,), 255, dtype=torch.uint8, device="cuda")
+    out = mrl.grpo_loss_fwd_bwd(H, W, y, mask, behav, None, one(0.7, torch.float32), one(0, torch.int32), None, 1, scored, 1, cfg, workspace=buf[:small])
+    torch.cuda.synchronize()
+    util.check_gradient("dW", util.to_f64(out["dW"]), dW)
+    assert torch.all(buf[small:] == 255)
