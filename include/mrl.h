@@ -228,9 +228,10 @@ typedef struct {
                                hint, the excess rows are NOT processed: their out_logp is NaN and
                                n_unprocessed_rows reports how many.  (Rows that a pass holds beyond
                                the hint are processed.)  The bf16 path also goes by the hint where it
-                               chooses between two dW launches, one for passes of at most 1024
-                               expected rows: both are right for any number of rows, but where the
-                               other one splits the contraction they add in another order, so that
+                               chooses between its dW launches, one for passes of at most 1024
+                               expected rows and two, of larger and of smaller tiles, above: each is
+                               right for any number of rows, but they split the contraction in
+                               different places or not at all, so that
                                dW with a hint and without one agrees to fp32 rounding and not bit
                                for bit.  The other outputs have the same bits.                   */
   int32_t ratio_level;   /* which importance ratio enters Eq. (1):
@@ -266,6 +267,8 @@ typedef struct {
                                                     "Numerical range" above): dropped from the loss and the gradients */
 } mrl_loss_stats;
 
+/* (A smaller workspace than the query's may do as well: shorter passes, or on the bf16 path fewer slices of the
+ * contractions of dH and dW, where both then agree to rounding and not bit for bit.)                                */
 size_t mrl_grpo_loss_workspace(int64_t B, int32_t T, int32_t d, int32_t V, int32_t dtype,
                                const mrl_loss_config* cfg);
 int mrl_grpo_loss_fwd_bwd(const void* hidden /*[B*T,d] dev*/, const void* lm_head_w /*[V,d] dev*/,

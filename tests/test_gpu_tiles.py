@@ -478,8 +478,27 @@ def test_hint_and_dw_launch(mrl, scored, chunk_rows):
         got, _, _ = _step(mrl, H, W, y, mask, mrl.BF16, V, chunk_rows=chunk_rows, poison=True, hint=hint)
         assert torch.equal(got["logp"], out["logp"]) and torch.equal(got["dH"], out["dH"])
         assert mrl.read_stats(got["stats"]) == stats and stats["n_unprocessed_rows"] == 0
-        # fp32 sums of at most 1500 products in two orders: 2^-24 * sqrt(1500) of the largest sum of absolute terms
+        # fp32 sums of at most 2000 products in two orders: 2^-24 * sqrt(2000) of the largest sum of absolute terms
         assert float((got["dW"] - out["dW"]).abs().max()) <= 1e-5 * float(out["dW"].abs().max())
+
+
+@pytest.mark.parametrize("scored,chunk_rows,d,V,cuts", [
+    (1500, 4096, 136, 1000, ((3, 0, 0, 3, 3), (0, 4, 0, 0, 1))),         # tiles of 384 in three slices without the hint, whole ones of 256 with it
+    (2000, 4096, 520, 9999, ((27, 0, 0, 81, 3), (0, 40, 0, 0, 1))),
+])
+def test_hint_above_the_few_rows(mrl, scored, chunk_rows, d, V, cuts):
+    """The hint also chooses between the larger and the smaller tiles of dW: dW to rounding, everything else bit for bit."""
+    for expected, cut in zip((chunk_rows, scored), cuts):
+        c = mrl.gemm_cut(mrl.GEMM_DW, scored, V, d, chunk_rows, expected)
+        assert (c["wide"], c["narrow"], c["half"], c["rest"], c["split"]) == cut
+    H, W, y, mask = _head(chunk_rows, d, V, scored, scored)
+    out, _, dW = _step(mrl, H, W, y, mask, mrl.BF16, V, chunk_rows=chunk_rows, poison=True)
+    got, _, _ = _step(mrl, H, W, y, mask, mrl.BF16, V, chunk_rows=chunk_rows, poison=True, hint=scored)
+    util.check_gradient("dW", util.to_f64(out["dW"]), dW)
+    assert torch.equal(got["logp"], out["logp"]) and torch.equal(got["dH"], out["dH"])
+    assert mrl.read_stats(got["stats"]) == mrl.read_stats(out["stats"])
+    # fp32 sums of at most 2000 products in two orders: 2^-24 * sqrt(2000) of the largest sum of absolute terms
+    assert float((got["dW"] - out["dW"]).abs().max()) <= 1e-5 * float(out["dW"].abs().max())
 
 
 @pytest.mark.parametrize("N,scored,V,chunk_rows", [
