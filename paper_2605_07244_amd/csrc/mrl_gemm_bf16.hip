@@ -2,11 +2,13 @@
 //
 // One kernel body computes C[m][n] = sum_k A[m][k] * B[n][k] for a 384 x 256 tile per workgroup: four wave64 wavefronts in a
 // 2 x 2 grid, each owning a 192 x 128 sub-tile as 12 x 8 MFMA 16x16x32 accumulators (384 accumulator registers per lane, 256 of them
-// in the accumulation file).  What bounds these launches is the energy and the issue of moving operands: with random mantissas the
-// chip is at its power limit, and of two loops with the same products the one that moves fewer bytes runs at the higher clock.
+// in the accumulation file).  What bounds these launches is the power limit, which the chip is at with random mantissas, and the issue
+// of moving operands, which leaves the matrix cores idle: a tile that moves fewer bytes per product keeps them busier, and the limit
+// takes a part of that back through the clock.
 // 384 x 256 is the largest tile that fits registers and LDS (two panels of 80 KB); per product it takes 17 % less from the L2
 // and from LDS than 256 x 256.  Launches of 15360 rows, V = 151936, d = 4096, 256 x 256 and now, us: forward with the stash 12660 and
-// 12340, dH 12740 and 11750, dW 13010 and 12080 (clock 1.78 - 1.88 and 1.83 - 1.95 GHz, matrix cores 73 - 78 % busy in either);
+// 12340, dH 12740 and 11750, dW 13010 and 12080 (matrix cores busy 74 and 75, 77 and 83, 75 and 80 % of the cycles; clock 1.88 and 1.86,
+// 1.84 and 1.78, 1.86 and 1.79 GHz);
 // 28672 rows, V = 128256, d = 2048 11055 and 10680, 10080 and 9420, 9905 and 9000.
 // The 16x16x32 shape is chosen over 32x32x16 for energy: an MFMA-only loop sustains about 13 % more FLOP/s with it.  Operand
 // panels of 64 K-elements go from global memory straight into LDS (buffer_load ... lds, no staging registers)
@@ -116,13 +118,13 @@ __device__ __forceinline__ bool dealt_tile(int band, int bid, int Mt, int Nt, in
 // dH: the tiles of the last, incomplete round of 256 (all of them, when a pass has few rows) are cut
 // into slices of the contraction over the vocabulary, one work item each, which store their
 // accumulators to a scratch area; dh_tail_reduce adds them in slice order.  A dH tile is long (2374
-// panels at V = 151936, about 2.4 ms), so an idle compute unit in that round costs more than
-// writing and adding the partial tiles (256 KB per item): 327 rows at d = 4096 are 32 tiles.
+// panels at V = 151936, about 3.6 ms), so an idle compute unit in that round costs more than
+// writing and adding the partial tiles (384 KB per item): 327 rows at d = 4096 are 16 tiles.
 // The slice count is the one whose rounds of items end earliest, 1 / kItemCostInv of a tile covering an item's
 // prologue, partial store and share of the reduce.  In whole numbers: the launch and the reduction each work
-// it out on the device and have to come to the same answer.  Measured (launch and reduce, V = 151936; before:
-// whole tiles and a transposed copy of W in front): 327 rows, d = 4096, 32 tiles: 3480 -> 527 us;
-// 5120 rows, d = 1536, 120 tiles: 3251 -> 1720 us; 47360 rows, d = 3584, 2590 tiles: 39.1 -> 35.9 ms.
+// it out on the device and have to come to the same answer.  Measured when it was introduced, on tiles of 256 x 256 (launch and reduce,
+// V = 151936; before: whole tiles and a transposed copy of W in front): 327 rows, d = 4096, 32 tiles: 3480 -> 527 us (353 on tiles
+// of 384); 5120 rows, d = 1536, 120 tiles: 3251 -> 1720 us; 47360 rows, d = 3584, 2590 tiles: 39.1 -> 35.9 ms.
 constexpr int kMinSlicePanels = 16;
 __host__ __device__ inline int dh_split(int tail_tiles, int panels, int max_items) {
   constexpr int kItemCostInv = 50;
@@ -443,7 +445,7 @@ __device__ __forceinline__ void dh_epilogue(const Params& p, unsigned char* smem
 // of 8; with 4-byte accesses the launch took 1128 instead of 1023 us for 512 rows, V = 151936, d = 4096, and 127 instead
 // of 109 for V = 32000, d = 2048).  The old values of a 16-row band are fetched as a batch before any store, so
 // that their latencies overlap.  A K slice of a tail tile stores its partial tile as it is, rows of 256, to the scratch
-// area instead (dw_tail_reduce adds the slices in their order): the same code with the tile's own origin, row stride and bounds.
+// area instead (dw_wide_reduce or, of 256 x 256 tiles, dw_tail_reduce adds the slices in their order): the same code with the tile's own origin, row stride and bounds.
 template <int NJ>
 __device__ __forceinline__ void dw_epilogue(const Params& p, f32x4 (&acc)[NJ][8], int wr, int m0, int n0, int res0, int v_last, float* tail_out) {
   const int lane = lane_now(), frow = lane & 15, fq = lane >> 4;
