@@ -1683,6 +1683,10 @@ int tiles(int64_t n, int size) { return (int)((n + size - 1) / size); }
 // of 384: V = 151936, d = 4096, 300 rows 422 and 413, 600 rows 648 and 622, 2500 rows 2249 and 2184; d = 1536, 300 rows 168 and 177, 900 rows 396 and 363; V = 50257,
 // d = 712, 300 rows 47 and 36, 1280 rows 97 and 113; V = 32000, d = 4096, 300 rows 98 and 117, 600 rows 165 and 128; d = 1536, 2000 rows 154 and 166, 2100 rows 179 and
 // 159; V = 8192, d = 4096, 1280 rows 78 and 109, 2500 rows 163 and 126.
+// An even number of groups of four columns in a band puts the group with the shorter columns on the same XCDs in every band, and the others have whole rounds of
+// the longest kind: no mean there (`apart`; 5633 - 5888 and 8705 - 8960 rows, with the mean, tiles of 384 and two columns of 256, and without it, tiles of 256:
+// V = 20711, d = 2048 420 and 388, V = 45174 809 and 751, V = 30328, d = 1840 549 and 523, V = 5816, d = 1536 180 and 168, V = 74627, d = 496 468 and 461, V = 128256,
+// d = 128 449 and 457). With eight columns the mean holds all the same (2814 rows, V = 151936, d = 744 595 with the mean, 648 without).
 // (Worked out for every step of every launch, so what does not depend on the cut comes from outside: 120 steps 1.9 and 1.1 us of host time.)
 struct ForwardTiles {
   int64_t wide, alone, narrow, half;
@@ -1693,7 +1697,8 @@ int64_t forward_end(const Cut& c, int rows, const ForwardTiles& t) {
   const int64_t wide = count == 1 ? t.alone : t.wide, most = c.wide > 0 ? wide : c.narrow > 0 ? t.narrow : t.half;
   const uint64_t all = (uint64_t)count * rows;
   int64_t end = (int64_t)((all + kRound - 1) / kRound) * most;
-  if (all > kRound && count != c.wide && count != c.narrow && count != c.half) {
+  const bool apart = c.wide > 0 && c.half == 0 && count > 8 && count % 8 == 0;
+  if (!apart && all > kRound && count != c.wide && count != c.narrow && count != c.half) {
     const int64_t work = (int64_t)((uint64_t)(c.wide * wide + c.narrow * t.narrow + c.half * t.half) * rows / kRound);
     const int64_t mixed = work + most * (c.wide > 0 ? 70 : 61) / 100;
     end = mixed < end ? mixed : end;

@@ -292,6 +292,15 @@ def test_tiles_of_the_large_launches_cover_their_rows():
     assert len(cuts[m.GEMM_FWD]) >= 5 and len(cuts[m.GEMM_DH]) >= 4
 
 
+@pytest.mark.parametrize("rows,d,V,cut", [
+    (5814, 1536, 21132, (0, 23, 0)), (8874, 792, 5427, (0, 35, 0)),     # 16 or 24 columns of 384 and 256: the shorter ones would lie on the same XCDs in every band
+    (2814, 744, 151936, (6, 2, 0)), (3000, 1536, 151936, (8, 0, 0)),
+])
+def test_forward_columns_of_two_kinds(rows, d, V, cut):
+    c = m.gemm_cut(m.GEMM_FWD, rows, V, d, 15360)
+    assert (c["wide"], c["narrow"], c["half"]) == cut
+
+
 def test_a_pass_holds_up_to_65536_rows():
     """A call of up to 65536 slots is one pass: its stash grows with every 256 slots up to there, and not beyond."""
     f = m.lib().mrl_grpo_loss_workspace
